@@ -108,8 +108,6 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
     m.dtype = dst_dtype;
     return pa::launch_merge_n(m, hip_stream);
   };
-  auto launch_pass = (d.dtype == PA_BF16) ? pa::launch_pass_bf16 : pa::launch_pass_f32;
-
   hipStream_t hs = static_cast<hipStream_t>(hip_stream);
   if (ev && hipEventRecord(ev[0], hs) != hipSuccess) return PA_ERR_HIP;
   if (d.dtype == PA_BF16) {  // layout pre-pass: V^T tile images for the MFMA passes
@@ -130,7 +128,24 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
     if (pa::launch_vt_images(t, hip_stream) != 0) return PA_ERR_HIP;
   }
   if (ev && hipEventRecord(ev[1], hs) != hipSuccess) return PA_ERR_HIP;
-  // bf16, unsplit short prefix (the plan decides), own keys included: one sweep over [prefix | own keys] per
+  if (d.dtype == PA_F32) {  // every mode is one sweep over the keys it covers; nothing is left to merge
+    a.k = k_suffix;
+    a.v = v_suffix;
+    a.k_pre = has_prefix ? k_prefix : nullptr;
+    a.v_pre = v_prefix;
+    a.P = d.prefix_len;
+    a.num_cu = plan->num_cu;
+    a.causal = with_suffix;
+    a.o_part = static_cast<float*>(out);
+    a.lse_part = mode == FULL ? lse : lse_partial;
+    a.items = plan->d_items[1];
+    a.num_items = (int64_t)plan->items[1].size();
+    if (ev && hipEventRecord(ev[2], hs) != hipSuccess) return PA_ERR_HIP;
+    if (pa::launch_pass_f32(a, hip_stream) != 0) return PA_ERR_HIP;
+    if (ev && (hipEventRecord(ev[3], hs) != hipSuccess || hipEventRecord(ev[4], hs) != hipSuccess)) return PA_ERR_HIP;
+    return PA_OK;
+  }
+  // unsplit short prefix (the plan decides), own keys included: one sweep over [prefix | own keys] per
   // block of rows does the work of the prefix pass, the suffix pass and the merge (the sweep list carries both
   // extents); it leaves the result of the call, or the fp32 partial of a shard that also holds the own keys
   const bool sweep = with_suffix && !plan->sweep_items.empty();
@@ -146,7 +161,7 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
     a.items = plan->d_items[0];
     a.num_items = (int64_t)plan->items[0].size();
     a.causal = false;
-    if (launch_pass(a, hip_stream) != 0) return PA_ERR_HIP;
+    if (pa::launch_pass_bf16(a, hip_stream) != 0) return PA_ERR_HIP;
   }
   if (ev && hipEventRecord(ev[2], hs) != hipSuccess) return PA_ERR_HIP;
   if (!with_suffix) {
@@ -165,7 +180,7 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   a.causal = true;
   // bf16, whole call, unsplit prefix: the suffix pass combines its result with the prefix partial in its
   // epilogue and writes `out` and the merged LSE itself (no merge launch, no suffix partial in memory)
-  const bool fused = mode == FULL && d.dtype == PA_BF16 && ks == 1;
+  const bool fused = mode == FULL && ks == 1;
   if (fused) {
     a.epilogue = (has_prefix && !sweep) ? 2 : 1;
     a.o1 = o1;
@@ -185,7 +200,7 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
       a.lse_part = lse_partial;
     }
   }
-  if (launch_pass(a, hip_stream) != 0) return PA_ERR_HIP;
+  if (pa::launch_pass_bf16(a, hip_stream) != 0) return PA_ERR_HIP;
 
   if (ev && hipEventRecord(ev[3], hs) != hipSuccess) return PA_ERR_HIP;
   if (fused || sweep) {
@@ -203,11 +218,10 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   m.lse1 = lse1;
   m.o2 = o2;
   m.lse2 = lse2;
-  m.out = out;
-  m.lse = mode == FULL ? lse : lse_partial;
+  m.out = static_cast<float*>(out);  // a partial: whole calls ended above
+  m.lse = lse_partial;
   m.rows = plan->T * d.num_q_heads;
   m.D = d.head_dim;
-  m.dtype = mode == FULL ? d.dtype : (int32_t)PA_F32;
   m.has_prefix = has_prefix;
   if (pa::launch_merge(m, hip_stream) != 0) return PA_ERR_HIP;
   if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;

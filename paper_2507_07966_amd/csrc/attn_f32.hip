@@ -1,11 +1,23 @@
-// fp32 attention pass (prefix or causal suffix) for fp32 inputs: plain FMA arithmetic, one
-// wavefront per stacked query row, online softmax over chunks of 64 keys.  This path exists
-// for small fp32 problems where exactness matters and speed does not; the bf16 MFMA
-// kernels are the performance path.
+// fp32 attention for fp32 inputs (exact checks, gradient checks, small debugging runs): the whole call in one kernel,
+// a sweep over [prefix keys | the rollout's own keys] per block of rows with fp32 MFMAs (v_mfma_f32_16x16x4_f32: fp32
+// products and sums, nothing is rounded below fp32).
 //
-// Same contract as the bf16 pass: for each stacked row it writes a normalised partial output
-// and the natural-log LSE over the keys the pass covers (all P prefix keys, or the rollout's
-// own keys 0..i).
+// What bounds it: at its sizes (tens to a few thousand rows) the latency of one block's sweep, then the fp32 matrix
+// rate (157 TFLOP/s nominal, 153 reached by a large product).  Hence the split: a workgroup owns only 16 * NQ stacked
+// rows m = i * group + (h % group), and its 8 wavefronts take the keys between them, 32 (NQ = 1) or 16 (NQ = 2) at a
+// time, each with an online softmax of its own; at the end the 8 partial results are combined through LDS in a fixed
+// order.  A wavefront reads its K and V rows straight into MFMA operand registers: no two wavefronts of a workgroup
+// need the same ones, so staging them in LDS would only add barriers.
+//   - S^T = K Q^T: the A operand's lane (key l16, channel quarter g4) loads 16 consecutive bytes, four contraction
+//     steps of K; Q sits in registers in the same channel order.
+//   - The accumulator then holds, per lane, keys 4 g4 + i (i = 0..3) of query column l16, which is exactly the B
+//     operand of O^T += V^T P^T when step j contracts over keys 4 g4 + j: P needs no data movement at all.
+//   - V^T operands: a lane loads 4 consecutive channels of key 4 g4 + j, one for each of four MFMAs; row r of
+//     accumulator (B, e) is channel 64 B + 4 r + e.
+// NQ = 2 reads every key once for 32 rows (half the L2 traffic), NQ = 1 has twice the workgroups: see launch_pass_f32.
+// Measured against one wavefront per row with scalar products (what this replaced): one head of 64 channels, 192 rows,
+// 256 + 96 keys 2,223 -> 22 us for the call; 8 / 2 heads of 128 channels, 740 tokens over 1,000 + 70..300 keys 13.3 ms ->
+// 62 us (67 TFLOP/s); 28 / 4 heads, 9,600 tokens over 4,000 + 600 keys 102 TFLOP/s, two thirds of the fp32 matrix rate.
 #include <hip/hip_runtime.h>
 
 #include "common.h"
@@ -13,68 +25,194 @@
 namespace pa {
 namespace {
 
-__device__ inline float wave_max(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int F32_WAVES = 8;
+
+__device__ inline float quad_max(float x) {  // over the lanes l16, l16 + 16, l16 + 32, l16 + 48 of a query column
+  x = fmaxf(x, __shfl_xor(x, 16));
+  return fmaxf(x, __shfl_xor(x, 32));
 }
-__device__ inline float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+__device__ inline float quad_sum(float x) {
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void pass_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                       const float* __restrict__ v, float* __restrict__ o_part,
-                                                       float* __restrict__ lse_part, const WorkItem* __restrict__ items,
-                                                       const int32_t* __restrict__ cu, int Hq, int Hkv, int group,
-                                                       float scale, bool causal) {
-  __shared__ float qs[4][D];
-  const WorkItem it = items[blockIdx.x];
-  if (it.g < 0) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <int D, int NQ>
+__global__ __launch_bounds__(F32_WAVES * 64, 2) void pass_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k_pre, const float* __restrict__ v_pre,
+    const float* __restrict__ k_own, const float* __restrict__ v_own, float* __restrict__ out, float* __restrict__ lse,
+    const WorkItem* __restrict__ items, const int32_t* __restrict__ cu, int P, bool with_own, int Hq, int Hkv, int group,
+    float scale) {
+  constexpr int ROWS = 16 * NQ, SUB = ROWS_PER_ITEM / ROWS;  // rows of a workgroup; workgroups per work item
+  constexpr int KB = NQ == 1 ? 2 : 1;                        // 16-key blocks per step of a wavefront
+  constexpr int KS = D / 16, VB = D / 64;                    // 16-byte loads per key: along its row / per key of a step
+  constexpr int LD = D + 4;                                  // padded row of the combine buffer (bank spread)
+  __shared__ __attribute__((aligned(16))) float o_s[F32_WAVES][ROWS][LD];
+  __shared__ float m_s[F32_WAVES][ROWS], l_s[F32_WAVES][ROWS];
+
+  const WorkItem it = items[blockIdx.x / SUB];
+  const int row0 = it.row0 + (int)(blockIdx.x % SUB) * ROWS;
   const int off_g = cu[it.g];
-  const int S_g = cu[it.g + 1] - off_g;
-  const int nrows = S_g * group;
-  const int64_t kv_row0 = causal ? off_g : 0;
-  constexpr int ROWS_PER_WAVE = ROWS_PER_ITEM / 4;
-  for (int rr = 0; rr < ROWS_PER_WAVE; ++rr) {
-    const int m = it.row0 + wave * ROWS_PER_WAVE + rr;
-    if (m >= nrows) break;  // wave-uniform
-    const int i = m / group, hh = m - i * group;
-    const int64_t row = (int64_t)(off_g + i) * Hq + it.c * group + hh;
-    for (int d = lane; d < D; d += 64) qs[wave][d] = q[row * D + d];
-    __builtin_amdgcn_wave_barrier();
-    const int nk = causal ? i + 1 : it.nkeys;
-    float mrun = -INFINITY, lrun = 0.f, o0 = 0.f, o1 = 0.f;
-    for (int base = 0; base < nk; base += 64) {
-      const int j = base + lane;
-      float s = -INFINITY;
-      if (j < nk) {
-        const float* kr = k + ((kv_row0 + j) * Hkv + it.c) * D;
-        float acc = 0.f;
-        for (int d = 0; d < D; ++d) acc = fmaf(qs[wave][d], kr[d], acc);
-        s = scale * acc;
-      }
-      const float m_new = fmaxf(mrun, wave_max(s));
-      const float p = (j < nk) ? expf(s - m_new) : 0.f;
-      const float alpha = expf(mrun - m_new);  // first chunk: exp(-inf) = 0
-      lrun = lrun * alpha + wave_sum(p);
-      o0 *= alpha;
-      o1 *= alpha;
-      const int cnt = (nk - base < 64) ? nk - base : 64;
-      for (int jj = 0; jj < cnt; ++jj) {
-        const float pj = __shfl(p, jj);
-        const float* vr = v + ((kv_row0 + base + jj) * Hkv + it.c) * D;
-        o0 = fmaf(pj, vr[lane], o0);
-        if (D > 64) o1 = fmaf(pj, vr[lane + 64], o1);
-      }
-      mrun = m_new;
+  const int nrows = (cu[it.g + 1] - off_g) * group;
+  if (row0 >= nrows) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
+  auto packed_row = [&](int m) { return (int64_t)(off_g + m / group) * Hq + it.c * group + m % group; };
+
+  // ---- this lane's query columns; rows past the rollout's end repeat its last row and are not written
+  f32x4 Q[NQ][KS];
+  int pos[NQ];
+#pragma unroll
+  for (int nq = 0; nq < NQ; ++nq) {
+    const int m = min(row0 + nq * 16 + l16, nrows - 1);
+    pos[nq] = m / group;
+    const float* qp = q + packed_row(m) * D + 4 * g4;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) Q[nq][s] = *reinterpret_cast<const f32x4*>(qp + 16 * s);
+  }
+  const int nown = with_own ? (min(row0 + ROWS, nrows) - 1) / group + 1 : 0;  // own keys the last row sees
+  const int np = (P + 15) / 16, nb = np + (nown + 15) / 16;                   // 16-key blocks: prefix, then own
+
+  f32x4 O[NQ][4 * VB];
+  float m_run[NQ], l_run[NQ];
+#pragma unroll
+  for (int nq = 0; nq < NQ; ++nq) {
+    m_run[nq] = -INFINITY;
+    l_run[nq] = 0.f;
+#pragma unroll
+    for (int b = 0; b < 4 * VB; ++b) O[nq][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  // keys [key0, ..) of block b (a block past the last one: the last one again, masked away)
+  struct Block { const float *k, *v; int key0, last; };
+  auto block_of = [&](int b) {
+    b = min(b, nb - 1);
+    const bool pre = b < np;
+    const int64_t first = ((int64_t)(pre ? 0 : off_g) * Hkv + it.c) * D;
+    return Block{(pre ? k_pre : k_own) + first, (pre ? v_pre : v_own) + first, (pre ? b : b - np) * 16, (pre ? P : nown) - 1};
+  };
+  const int64_t stride = (int64_t)Hkv * D;
+  f32x4 K[KB][KS], V[KB][4][VB];
+  auto load_k = [&](int b0) {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const Block b = block_of(b0 + kb);
+      const float* p = b.k + min(b.key0 + l16, b.last) * stride + 4 * g4;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) K[kb][s] = *reinterpret_cast<const f32x4*>(p + 16 * s);
     }
-    const float inv = 1.0f / lrun;
-    o_part[row * D + lane] = o0 * inv;
-    if (D > 64) o_part[row * D + lane + 64] = o1 * inv;
-    if (lane == 0) lse_part[row] = mrun + logf(lrun);
-    __builtin_amdgcn_wave_barrier();
+  };
+  auto load_v = [&](int b0) {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const Block b = block_of(b0 + kb);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float* p = b.v + min(b.key0 + 4 * g4 + j, b.last) * stride + 4 * l16;
+#pragma unroll
+        for (int B = 0; B < VB; ++B) V[kb][j][B] = *reinterpret_cast<const f32x4*>(p + 64 * B);
+      }
+    }
+  };
+
+  if (wave * KB < nb) load_k(wave * KB);
+  for (int b0 = wave * KB; b0 < nb; b0 += F32_WAVES * KB) {
+    load_v(b0);
+    f32x4 S[KB][NQ];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int nq = 0; nq < NQ; ++nq) S[kb][nq] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int nq = 0; nq < NQ; ++nq)
+            S[kb][nq] = __builtin_amdgcn_mfma_f32_16x16x4f32(K[kb][s][j], Q[nq][s][j], S[kb][nq], 0, 0, 0);
+    if (b0 + F32_WAVES * KB < nb) load_k(b0 + F32_WAVES * KB);
+    // register i of S[kb][nq]: key 4 g4 + i of block b0 + kb, query column l16
+#pragma unroll
+    for (int nq = 0; nq < NQ; ++nq) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const bool pre = b0 + kb < np;
+        const int key0 = (pre ? b0 + kb : b0 + kb - np) * 16 + 4 * g4;
+        const int limit = b0 + kb >= nb ? -1 : pre ? P - 1 : pos[nq];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          S[kb][nq][i] = key0 + i <= limit ? S[kb][nq][i] * scale : -INFINITY;
+          mx = fmaxf(mx, S[kb][nq][i]);
+        }
+      }
+      const float m_new = fmaxf(m_run[nq], quad_max(mx));
+      const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // no visible key yet: every weight below is exp(-inf) = 0
+      if (__any(m_new > m_run[nq])) {
+        const float alpha = expf(m_run[nq] - m_ref);
+        l_run[nq] *= alpha;
+#pragma unroll
+        for (int b = 0; b < 4 * VB; ++b) O[nq][b] *= alpha;
+        m_run[nq] = m_new;
+      }
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          S[kb][nq][i] = expf(S[kb][nq][i] - m_ref);
+          l_run[nq] += S[kb][nq][i];
+        }
+    }
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int B = 0; B < VB; ++B)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int nq = 0; nq < NQ; ++nq)
+              O[nq][4 * B + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(V[kb][j][B][e], S[kb][nq][j], O[nq][4 * B + e], 0, 0, 0);
+  }
+
+  // ---- combine the wavefronts: register i of O[nq][4 B + e] is channel 64 B + 4 (4 g4 + i) + e of query column l16
+#pragma unroll
+  for (int nq = 0; nq < NQ; ++nq) {
+    const int r = nq * 16 + l16;
+#pragma unroll
+    for (int B = 0; B < VB; ++B)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<f32x4*>(&o_s[wave][r][64 * B + 16 * g4 + 4 * i]) =
+            f32x4{O[nq][4 * B][i], O[nq][4 * B + 1][i], O[nq][4 * B + 2][i], O[nq][4 * B + 3][i]};
+    const float l = quad_sum(l_run[nq]);
+    if (g4 == 0) {
+      m_s[wave][r] = m_run[nq];
+      l_s[wave][r] = l;
+    }
+  }
+  __syncthreads();
+  for (int n = threadIdx.x; n < ROWS * (D / 4); n += F32_WAVES * 64) {
+    const int r = n / (D / 4), ch = n % (D / 4) * 4;
+    if (row0 + r >= nrows) continue;
+    float m = m_s[0][r];
+#pragma unroll
+    for (int w = 1; w < F32_WAVES; ++w) m = fmaxf(m, m_s[w][r]);  // finite: every row sees a key
+    float l = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < F32_WAVES; ++w) {
+      const float a = expf(m_s[w][r] - m);  // a wavefront without a visible key: exp(-inf) = 0
+      l += a * l_s[w][r];
+      acc += a * *reinterpret_cast<const f32x4*>(&o_s[w][r][ch]);
+    }
+    const int64_t row = packed_row(row0 + r);
+    *reinterpret_cast<f32x4*>(out + row * D + ch) = acc * (1.0f / l);
+    if (ch == 0) lse[row] = m + logf(l);
   }
 }
 
@@ -83,15 +221,25 @@ __global__ __launch_bounds__(256) void pass_f32_kernel(const float* __restrict__
 int launch_pass_f32(const PassArgs& a, void* stream) {
   if (a.num_items == 0) return 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const float* q = static_cast<const float*>(a.q);
-  const float* k = static_cast<const float*>(a.k);
-  const float* v = static_cast<const float*>(a.v);
-  if (a.D == 64)
-    pass_f32_kernel<64><<<(unsigned)a.num_items, 256, 0, s>>>(q, k, v, a.o_part, a.lse_part, a.items, a.cu, a.Hq,
-                                                                 a.Hkv, a.group, a.scale, a.causal);
-  else
-    pass_f32_kernel<128><<<(unsigned)a.num_items, 256, 0, s>>>(q, k, v, a.o_part, a.lse_part, a.items, a.cu, a.Hq,
-                                                                  a.Hkv, a.group, a.scale, a.causal);
+  auto f = [](const void* p) { return static_cast<const float*>(p); };
+  const int P = a.k_pre ? (int)a.P : 0;
+#define PA_LAUNCH(DD, NQ)                                                                                          \
+  pass_f32_kernel<DD, NQ><<<(unsigned)(a.num_items * (ROWS_PER_ITEM / (16 * NQ))), F32_WAVES * 64, 0, s>>>(        \
+      f(a.q), f(a.k_pre), f(a.v_pre), f(a.k), f(a.v), a.o_part, a.lse_part, a.items, a.cu, P, a.causal, a.Hq,      \
+      a.Hkv, a.group, a.scale)
+  // One workgroup runs per CU at a time, so a launch takes ceil(workgroups / CUs) rounds, and a round of 32-row
+  // workgroups takes 1.5 to 1.65 times one of 16-row workgroups (measured, 8 / 2 heads of 128 channels, 1,000 prefix
+  // keys, us with 16 / 32 rows: 370 blocks of 16 rows 72 / 62, 600 blocks 106 / 104, 1,024 blocks 152 / 121, 2,400 blocks
+  // 352 / 273; up to 256 blocks 16 rows take one round and 32 rows leave half the CUs idle).
+  const int64_t blocks = (a.part_rows + 15) / 16;
+  const int64_t rounds16 = (blocks + a.num_cu - 1) / a.num_cu, rounds32 = ((blocks + 1) / 2 + a.num_cu - 1) / a.num_cu;
+  const bool wide = 3 * rounds32 <= 2 * rounds16;
+  if (a.D == 128) {
+    if (wide) PA_LAUNCH(128, 2); else PA_LAUNCH(128, 1);
+  } else {
+    if (wide) PA_LAUNCH(64, 2); else PA_LAUNCH(64, 1);
+  }
+#undef PA_LAUNCH
   return (int)hipGetLastError();
 }
 

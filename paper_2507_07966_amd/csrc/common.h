@@ -74,7 +74,8 @@ struct PassArgs {
   int64_t part_rows;    // T * Hq: rows of one partial (key split s writes slot s of o_part / lse_part)
   int32_t Hq, Hkv, D, group;
   float scale;          // softmax scale
-  bool causal;          // false: prefix pass (k/v indexed from 0, no mask); true: suffix pass
+  bool causal;          // bf16: false: prefix pass (k/v indexed from 0, no mask); true: suffix pass.  fp32 (one sweep over
+                        // prefix and own keys in every mode): whether the rollouts' own keys are covered
   // bf16 suffix pass only: finish the call in the epilogue instead of leaving a partial for the merge kernel.
   // 0: fp32 partial into o_part / lse_part; 1: no prefix, the result is final; 2: combine with the prefix
   // partial (o1, lse1).  1 and 2 write `out_final` (bf16 [T, Hq, D]) and `lse_final` ([T, Hq]).
@@ -86,7 +87,10 @@ struct PassArgs {
   // bf16 suffix pass with epilogue 1 only: sweep the prefix keys first (items carry pkeys), in the same
   // online softmax, so the call is one pass over [prefix | own keys] per block of rows.
   bool sweep_prefix;
-  const void* k_pre;           // [P, Hkv, D]
+  const void* k_pre;           // [P, Hkv, D]; fp32: null when the call covers no prefix keys
+  const void* v_pre;           // fp32 only: [P, Hkv, D]
+  int64_t P;                   // fp32 only: prefix keys
+  int32_t num_cu;              // fp32 only: compute units of the plan's device
   const void* vt_pre;          // prefix V tile images
   int64_t vt_pre_tiles_per_head;
   // bf16: one word per (work item, wavefront), written by the common kernel of a pass and read by its careful
@@ -99,11 +103,10 @@ struct MergeArgs {
   const float* lse1;
   const float* o2;      // suffix partial
   const float* lse2;
-  void* out;            // [T, Hq, D] in the plan's dtype
+  float* out;           // [T, Hq, D] fp32
   float* lse;           // [T, Hq] merged
   int64_t rows;         // T * Hq
   int32_t D;
-  int32_t dtype;
   bool has_prefix;
 };
 

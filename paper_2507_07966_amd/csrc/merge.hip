@@ -15,11 +15,11 @@ namespace {
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// One thread handles 4 consecutive channels of one row; rows are walked grid-stride.
-template <bool OUT_BF16>
+// One thread handles 4 consecutive channels of one row; rows are walked grid-stride.  The result is an fp32 partial (a
+// whole call combines the two in the suffix pass's epilogue instead, see attn_bf16.hip).
 __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ o1, const float* __restrict__ lse1,
                                                     const float* __restrict__ o2, const float* __restrict__ lse2,
-                                                    void* __restrict__ out, float* __restrict__ lse, int64_t rows,
+                                                    float* __restrict__ out, float* __restrict__ lse, int64_t rows,
                                                     int D, bool has_prefix) {
   const int per_row = D / 4;
   const int64_t total = rows * per_row;
@@ -41,12 +41,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ o1
     }
     f32x4 r = a2 * *reinterpret_cast<const f32x4*>(o2 + idx * 4);
     if (has_prefix) r += a1 * *reinterpret_cast<const f32x4*>(o1 + idx * 4);
-    if (OUT_BF16) {
-      bf16x4 b = __builtin_convertvector(r, bf16x4);
-      *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(out) + idx * 4) = b;
-    } else {
-      *reinterpret_cast<f32x4*>(static_cast<float*>(out) + idx * 4) = r;
-    }
+    *reinterpret_cast<f32x4*>(out + idx * 4) = r;
     if (ch == 0) lse[row] = l;
   }
 }
@@ -106,10 +101,7 @@ int launch_merge(const MergeArgs& a, void* stream) {
   const int64_t want = (total + 255) / 256;
   const int blocks = (int)(want < 256 * 32 ? want : 256 * 32);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (a.dtype == PA_BF16)
-    merge_kernel<true><<<blocks, 256, 0, s>>>(a.o1, a.lse1, a.o2, a.lse2, a.out, a.lse, a.rows, a.D, a.has_prefix);
-  else
-    merge_kernel<false><<<blocks, 256, 0, s>>>(a.o1, a.lse1, a.o2, a.lse2, a.out, a.lse, a.rows, a.D, a.has_prefix);
+  merge_kernel<<<blocks, 256, 0, s>>>(a.o1, a.lse1, a.o2, a.lse2, a.out, a.lse, a.rows, a.D, a.has_prefix);
   return (int)hipGetLastError();
 }
 

@@ -381,7 +381,7 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
            hipMemcpy(p->d_cu + n, p->vt_off.data(), n * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
       p->d_vt_off = p->d_cu + n;
       for (int s = 0; ok && s < 2; ++s) {
-        if (p->items[s].empty()) continue;
+        if (p->items[s].empty() || (s == 0 && desc->dtype == PA_F32)) continue;  // fp32: no separate prefix pass
         const size_t bytes = p->items[s].size() * sizeof(WorkItem);
         ok = hipMalloc((void**)&p->d_items[s], bytes) == hipSuccess &&
              hipMemcpy(p->d_items[s], p->items[s].data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
