@@ -81,7 +81,7 @@ struct BwdDkvArgs {
 };
 int launch_bwd_dkv_bf16(const BwdDkvArgs& a, void* stream);
 
-// fp32 path: plain kernels (one wavefront per query row / per key)
+// fp32 path (bwd_f32.hip)
 struct BwdF32Args {
   const void* q;
   const void* d_out;
@@ -96,6 +96,8 @@ struct BwdF32Args {
   void* dv_prefix;
   void* dk_suffix;
   void* dv_suffix;
+  const WorkItem* items;  // dQ: the plan's suffix list (every block of rows once)
+  int64_t num_items;
   const int32_t* cu;
   int64_t T, P;
   int32_t G, Hq, Hkv, D, group;
