@@ -5,7 +5,7 @@
 
 namespace pa {
 
-constexpr int LP_TILE = 256;  // vocabulary rows and tokens per workgroup tile
+constexpr int LP_TILE = 256;  // vocabulary rows per workgroup tile (and the most tokens)
 
 struct LogprobArgs {
   const void* hidden;      // [N, d] bf16

@@ -7,22 +7,27 @@
 // product per model, 1.8e13 FLOP for 16K response tokens, and the logits (10 GB in fp32) are only
 // ever reduced to two numbers per token.
 //
-// Kernel 1 (bf16 MFMA GEMM with a reducing epilogue).  A workgroup (8 wavefronts) computes one
-// 256-vocabulary x 256-token tile of Z^T = W H^T: wavefront (wv, wt) owns 64 vocabulary rows x 128
-// tokens (4 x 8 accumulator blocks of v_mfma_f32_16x16x32_bf16, 128 registers; that shape moves half
-// the accumulator data per FLOP of the 32 x 32 x 16 one and sustains about 10 % more under the board's
-// power limit).  W and H panels of
-// 64 channels go global -> LDS through range-checked buffer loads (rows past the end of either
-// matrix read as zero), double buffered, one barrier per 64 channels; 12 LDS operand reads feed 32
-// MFMAs.  In the epilogue every lane holds 16 logits of each of 8 tokens: it reduces them to a
-// maximum and a sum of exponentials, combines with the three lanes holding the token's other rows and, through
-// LDS, with the other three row blocks, so the tile writes one (m, l) pair per token; the lane that
-// holds the target's logit writes it out.  Workgroups are numbered so that the 32 tiles running together on one XCD form an
-// 8-token-tile x 4-vocabulary-tile block: 12 distinct panels per step share that XCD's L2
-// instead of 64.
+// Kernel 1 (bf16 MFMA GEMM with a reducing epilogue), bound by MFMA power for many tokens and by reading W for
+// few. A workgroup (8 wavefronts) computes one 256-vocabulary x 32 NB-token tile of Z^T = W H^T (NB = 8, 6, 4,
+// 2; launch_logprob chooses): wavefront (wv, wt) owns 64 vocabulary rows x 16 NB tokens (4 x NB accumulator
+// blocks of v_mfma_f32_16x16x32_bf16, 128 registers for NB = 8; that shape moves half the accumulator data per
+// FLOP of the 32 x 32 x 16 one and sustains about 10 % more under the board's power limit).  W and H panels of
+// 64 channels go global -> LDS through range-checked buffer loads (rows past the end of either matrix read as
+// zero), double buffered, one barrier per 64 channels (a third buffer gained nothing at 64 and 128 tokens);
+// for NB = 8, 12 LDS operand reads feed 32 MFMAs.  In the epilogue every lane holds 16 logits of each of NB
+// tokens: it reduces them to a maximum and a sum of exponentials, combines with the three lanes holding the
+// token's other rows and, through LDS, with the other three row blocks, so the tile writes one (m, l) pair per
+// token; the lane that holds the target's logit writes it out.  Every XCD gets an equal, contiguous share of
+// the tiles, walked in bands of four vocabulary tiles, so the 32 tiles running together on one XCD form an
+// 8-token-tile x 4-vocabulary-tile block: 12 distinct panels per step share that XCD's L2 instead of 64.
+// (Dealing whole token tiles to the XCDs instead left most of the chip idle when their number was not a
+// multiple of 8: 2,100 tokens x 152,064 words 6.04 ms, now 1.95; 8,200 tokens 12.97, now 7.20; 16,384 tokens,
+// where it was balanced, 13.84, now 13.48.)
 // Kernel 2 combines the (m, l) pairs of a token over all vocabulary blocks: LSE = m + ln l,
 // logp = z_target - LSE.
 #include <hip/hip_runtime.h>
+
+#include <utility>
 
 #include "logprob.h"
 #include "mfma_tiles.h"
@@ -34,8 +39,8 @@ using namespace mt;
 
 constexpr int LP_WAVES = 8, LP_THREADS = LP_WAVES * 64;
 constexpr int BK = 64;                      // channels per stage
-constexpr int PANEL_BYTES = LP_TILE * BK * 2;  // one 256-row x 64-channel panel
-constexpr int LP_STAGE = 2 * PANEL_BYTES;      // W panel, H panel
+constexpr int BAND = 4;                     // vocabulary tiles that are walked together
+constexpr int PANEL_BYTES = LP_TILE * BK * 2;  // the 256-row x 64-channel panel of W
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -61,40 +66,39 @@ __device__ inline float column_sum(float x) {
   return u + w;
 }
 
-__global__ __launch_bounds__(LP_THREADS, 1) void logprob_tile_kernel(
+template <int NB>
+__global__ __launch_bounds__(LP_THREADS, NB == 2 ? 4 : 2) void logprob_tile_kernel(
     const __bf16* __restrict__ hidden, const __bf16* __restrict__ lm_head, const int32_t* __restrict__ targets,
     float2* __restrict__ partials, float* __restrict__ target_logit, int64_t N, int d, int V, int TM, int TV,
-    int by_tm, float logit_scale) {
+    float logit_scale) {
+  constexpr int TT = 32 * NB;                           // tokens per tile
+  constexpr int LP_STAGE = PANEL_BYTES + TT * BK * 2;   // W panel, H panel
+  constexpr int HB = NB / 2;                            // 1 KiB blocks of the H panel per wavefront
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * LP_STAGE];
 
-  // ---- which tile: XCD x = blockIdx % 8 owns a slice of the token tiles (or, with fewer than 8
-  //      token tiles, of the vocabulary tiles) and walks it in 8 x 4 blocks of tiles
+  // ---- which tile: XCD x = blockIdx % 8 computes a contiguous eighth of the tiles, numbered band by band (a band:
+  //      four vocabulary tiles x all token tiles, vocabulary fastest; the last band may be narrower)
   int tm, tv;
   {
-    const int n = blockIdx.x, x = n & 7, j = n >> 3;
-    if (by_tm) {
-      const int mine = (TM - x + 7) / 8;          // token tiles tm = x + 8 k, k < mine
-      const int ngm = ((TM + 7) / 8 + 7) / 8;     // groups of 8 owned token tiles (same for every XCD)
-      const int g = j / 32, i = j % 32;
-      const int k = (g % ngm) * 8 + (i & 7);
-      tv = (g / ngm) * 4 + (i >> 3);
-      tm = x + 8 * k;
-      if (k >= mine || tv >= TV) return;
-    } else {
-      tm = j % TM;
-      tv = x + 8 * (j / TM);
-      if (tv >= TV) return;
-    }
+    const int per_xcd = gridDim.x >> 3;
+    const int idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (idx >= TM * TV) return;
+    const int whole = TV / BAND * BAND * TM;  // tiles in bands of full width
+    const int width = idx < whole ? BAND : TV % BAND;
+    const int r = idx < whole ? idx % (BAND * TM) : idx - whole;
+    tm = r / width;
+    tv = (idx < whole ? idx / (BAND * TM) * BAND : TV / BAND * BAND) + r % width;
   }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
   const int wv = wave & 3, wt = wave >> 2;
-  const int64_t v0 = (int64_t)tv * LP_TILE, t0 = (int64_t)tm * LP_TILE;
+  const int64_t v0 = (int64_t)tv * LP_TILE, t0 = (int64_t)tm * TT;
 
-  // ---- loads: a panel is 256 rows x 128 bytes = 32 blocks of 1 KiB (8 rows each), 4 per wavefront
+  // ---- loads: the W panel is 256 rows x 128 bytes = 32 blocks of 1 KiB (8 rows each), 4 per wavefront, the H
+  //      panel TT / 8 blocks, NB / 2 per wavefront
   const int64_t rowb = (int64_t)d * 2;
-  const int64_t w_rows = V - v0 < LP_TILE ? V - v0 : LP_TILE, h_rows = N - t0 < LP_TILE ? N - t0 : LP_TILE;
+  const int64_t w_rows = V - v0 < LP_TILE ? V - v0 : LP_TILE, h_rows = N - t0 < TT ? N - t0 : TT;
   const rsrc_t r_w = make_rsrc(lm_head + v0 * d, w_rows * rowb);
   const rsrc_t r_h = make_rsrc(hidden + t0 * d, h_rows * rowb);
   unsigned loff[4];
@@ -104,18 +108,24 @@ __global__ __launch_bounds__(LP_THREADS, 1) void logprob_tile_kernel(
     const int chunk = (lane % 8) ^ swizzle_term(row, 128);  // logical chunk stored at this position
     loff[n] = (unsigned)(row * rowb + chunk * 16);
   }
+  unsigned hoff[HB];
+#pragma unroll
+  for (int n = 0; n < HB; ++n) {
+    const int row = (wave * HB + n) * 8 + lane / 8;
+    const int chunk = (lane % 8) ^ swizzle_term(row, 128);
+    hoff[n] = (unsigned)(row * rowb + chunk * 16);
+  }
   auto issue = [&](int stage, int buf) {
     unsigned char* dst = smem + buf * LP_STAGE;
     const unsigned k_off = (unsigned)stage * (BK * 2);
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r_w, (PA_LDS_PTR(void))(dst + (wave * 4 + n) * 1024), 16, loff[n], k_off, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r_h, (PA_LDS_PTR(void))(dst + PANEL_BYTES + (wave * 4 + n) * 1024), 16,
-                                               loff[n], k_off, 0, 0);
+      load_chunk_to_lds(r_w, dst + (wave * 4 + n) * 1024, loff[n], k_off);
+      if (n < HB) load_chunk_to_lds(r_h, dst + PANEL_BYTES + (wave * HB + n) * 1024, hoff[n < HB ? n : 0], k_off);
     }
   };
 
-  constexpr int NA = 4, NB = 8;   // 16-row blocks of the wavefront's 64 vocabulary rows / 128 tokens
+  constexpr int NA = 4;   // 16-row blocks of the wavefront's 64 vocabulary rows; NB: of its 16 NB tokens
   f32x4 C[NA][NB];
 #pragma unroll
   for (int a = 0; a < NA; ++a)
@@ -133,7 +143,7 @@ __global__ __launch_bounds__(LP_THREADS, 1) void logprob_tile_kernel(
     for (int ks = 0; ks < BK / 32; ++ks) {
       const int off = l16 * 128 + (((4 * ks + g4) ^ swizzle_term(l16, 128)) << 4);
       wop[bufi][ks] = smem + bufi * LP_STAGE + (wv * 64) * 128 + off;
-      hop[bufi][ks] = smem + bufi * LP_STAGE + PANEL_BYTES + (wt * 128) * 128 + off;
+      hop[bufi][ks] = smem + bufi * LP_STAGE + PANEL_BYTES + (wt * 16 * NB) * 128 + off;
     }
 
   const int nstages = (d + BK - 1) / BK;  // channels past d read as zero (range-checked loads)
@@ -171,14 +181,14 @@ __global__ __launch_bounds__(LP_THREADS, 1) void logprob_tile_kernel(
   }
 
   // ---- epilogue.  Register i of C[a][b]: vocabulary row v0 + wv*64 + a*16 + 4*g4 + i,
-  //      token t0 + wt*128 + b*16 + l16.
+  //      token t0 + wt*16*NB + b*16 + l16.
   const float c2 = logit_scale * LOG2E;  // work in base 2
   __syncthreads();                        // every wavefront is done with the panels: reuse the LDS
-  float2* stage_ml = reinterpret_cast<float2*>(smem);  // [4 row blocks][256 tokens] (m in base-2 units, l)
+  float2* stage_ml = reinterpret_cast<float2*>(smem);  // [4 row blocks][TT tokens] (m in base-2 units, l)
   const int64_t vlane = v0 + wv * 64 + 4 * g4;         // this lane's first vocabulary row
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const int64_t tok = t0 + wt * 128 + b * 16 + l16;
+    const int64_t tok = t0 + wt * 16 * NB + b * 16 + l16;
     float m = -INFINITY;
 #pragma unroll
     for (int a = 0; a < NA; ++a)
@@ -193,7 +203,7 @@ __global__ __launch_bounds__(LP_THREADS, 1) void logprob_tile_kernel(
       for (int i = 0; i < 4; ++i)
         if (vlane + a * 16 + i < V) l += __builtin_amdgcn_exp2f(__builtin_fmaf(C[a][b][i], c2, -m));
     l = column_sum(l);
-    if (g4 == 0) stage_ml[wv * LP_TILE + wt * 128 + b * 16 + l16] = float2{m, l};  // m = -inf, l = 0 for a block past V
+    if (g4 == 0) stage_ml[wv * TT + wt * 16 * NB + b * 16 + l16] = float2{m, l};  // m = -inf, l = 0 for a block past V
     if (tok < N) {
       // the target's logit, if it lies in this wavefront's 64 rows and this lane's four of every 16
       const int64_t rel = (int64_t)targets[tok] - (v0 + wv * 64);
@@ -214,36 +224,46 @@ __global__ __launch_bounds__(LP_THREADS, 1) void logprob_tile_kernel(
   }
   // one (m, l) pair per token for the tile's 256 vocabulary rows (block 0 always exists)
   __syncthreads();
-  if (tid < LP_TILE && t0 + tid < N) {
+  if (tid < TT && t0 + tid < N) {
     float m = stage_ml[tid].x;
 #pragma unroll
-    for (int k = 1; k < 4; ++k) m = fmaxf(m, stage_ml[k * LP_TILE + tid].x);
+    for (int k = 1; k < 4; ++k) m = fmaxf(m, stage_ml[k * TT + tid].x);
     float l = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const float2 v = stage_ml[k * LP_TILE + tid];
+      const float2 v = stage_ml[k * TT + tid];
       l += v.y * __builtin_amdgcn_exp2f(v.x - m);
     }
     partials[(int64_t)tv * N + t0 + tid] = float2{m * LN2, l};
   }
 }
 
-// (m, l) pairs of a token over all vocabulary tiles -> LSE and log-probability.  A block handles
-// 64 tokens; its 4 thread groups each walk every fourth tile with an online combine, then merge.
-__global__ __launch_bounds__(256) void logprob_finalize_kernel(const float2* __restrict__ partials,
-                                                               const float* __restrict__ target_logit,
-                                                               const int32_t* __restrict__ targets,
-                                                               float* __restrict__ logprob, float* __restrict__ lse_out,
-                                                               int64_t N, int nparts, int V) {
-  __shared__ float2 sm[4][64];
-  const int tl = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int64_t tok = (int64_t)blockIdx.x * 64 + tl;
+// (m, l) pairs of a token over all vocabulary tiles -> LSE and log-probability.  A block handles 16 tokens (one
+// 128-byte line of each row of pairs); each of its 16 thread groups takes every 16th row, eight loads in flight and
+// one rescaling per eight, and the groups are merged through LDS.  (64 tokens per block and one load at a time took
+// 69 us for 333 tokens x 594 rows on 6 CUs; now 9 us.)
+constexpr int FIN_TOKENS = 16, FIN_GROUPS = 16, FIN_DEPTH = 8;
+__global__ __launch_bounds__(FIN_TOKENS * FIN_GROUPS) void logprob_finalize_kernel(
+    const float2* __restrict__ partials, const float* __restrict__ target_logit, const int32_t* __restrict__ targets,
+    float* __restrict__ logprob, float* __restrict__ lse_out, int64_t N, int nparts, int V) {
+  __shared__ float2 sm[FIN_GROUPS][FIN_TOKENS];
+  const int tl = threadIdx.x % FIN_TOKENS, grp = threadIdx.x / FIN_TOKENS;
+  const int64_t tok = (int64_t)blockIdx.x * FIN_TOKENS + tl;
   float m = -INFINITY, l = 0.f;
   if (tok < N)
-    for (int p = grp; p < nparts; p += 4) {
-      const float2 v = partials[(int64_t)p * N + tok];
-      const float mn = fmaxf(m, v.x);
-      l = l * expf(m - mn) + v.y * expf(v.x - mn);  // first term: 0 * exp(-inf) = 0
+    for (int p0 = grp; p0 < nparts; p0 += FIN_GROUPS * FIN_DEPTH) {
+      float2 v[FIN_DEPTH];
+#pragma unroll
+      for (int i = 0; i < FIN_DEPTH; ++i) {
+        const int p = p0 + i * FIN_GROUPS;
+        v[i] = p < nparts ? partials[(int64_t)p * N + tok] : float2{-INFINITY, 0.f};
+      }
+      float mn = fmaxf(m, v[0].x);  // row p0 exists: finite
+#pragma unroll
+      for (int i = 1; i < FIN_DEPTH; ++i) mn = fmaxf(mn, v[i].x);
+      l *= expf(m - mn);            // first time: 0 * exp(-inf) = 0
+#pragma unroll
+      for (int i = 0; i < FIN_DEPTH; ++i) l += v[i].y * expf(v[i].x - mn);
       m = mn;
     }
   sm[grp][tl] = float2{m, l};
@@ -251,10 +271,10 @@ __global__ __launch_bounds__(256) void logprob_finalize_kernel(const float2* __r
   if (grp == 0 && tok < N) {
     float mm = m;
 #pragma unroll
-    for (int k = 1; k < 4; ++k) mm = fmaxf(mm, sm[k][tl].x);
+    for (int k = 1; k < FIN_GROUPS; ++k) mm = fmaxf(mm, sm[k][tl].x);
     float ll = 0.f;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < FIN_GROUPS; ++k) {
       const float2 v = sm[k][tl];
       ll += v.y > 0.f ? v.y * expf(v.x - mm) : 0.f;  // a group that saw no tile holds (-inf, 0)
     }
@@ -283,22 +303,46 @@ __global__ __launch_bounds__(64) void group_advantages_kernel(const float* __res
 
 }  // namespace
 
+namespace {
+
+constexpr int64_t CUS = 256;
+
+int64_t tile_rounds(int nb, int64_t N, int TV) { return ((N + 32 * nb - 1) / (32 * nb) * TV + CUS - 1) / CUS; }
+
+template <int NB>
+int launch_tiles(const LogprobArgs& a, int TV, hipStream_t s) {
+  const int TM = (int)((a.N + 32 * NB - 1) / (32 * NB));
+  const int64_t grid = ((int64_t)TM * TV + 7) / 8 * 8;
+  logprob_tile_kernel<NB><<<(unsigned)grid, LP_THREADS, 0, s>>>(
+      static_cast<const __bf16*>(a.hidden), static_cast<const __bf16*>(a.lm_head), a.targets,
+      reinterpret_cast<float2*>(a.partials), a.target_logit, a.N, a.d, a.V, TM, TV, a.logit_scale);
+  return (int)hipGetLastError();
+}
+
+}  // namespace
+
 int launch_logprob(const LogprobArgs& a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int TM = (int)((a.N + LP_TILE - 1) / LP_TILE), TV = (a.V + LP_TILE - 1) / LP_TILE;
-  const int by_tm = TM >= 8;
-  int64_t grid;
-  if (by_tm) {
-    const int ngm = ((TM + 7) / 8 + 7) / 8;
-    grid = (int64_t)8 * 32 * ngm * ((TV + 3) / 4);
-  } else {
-    grid = (int64_t)8 * TM * ((TV + 7) / 8);
-  }
-  logprob_tile_kernel<<<(unsigned)grid, LP_THREADS, 0, s>>>(
-      static_cast<const __bf16*>(a.hidden), static_cast<const __bf16*>(a.lm_head), a.targets,
-      reinterpret_cast<float2*>(a.partials), a.target_logit, a.N, a.d, a.V, TM, TV, by_tm, a.logit_scale);
-  if (hipGetLastError() != hipSuccess) return 1;
-  logprob_finalize_kernel<<<(unsigned)((a.N + 63) / 64), 256, 0, s>>>(
+  const int TV = (a.V + LP_TILE - 1) / LP_TILE;
+  // Tokens per tile, 64 ... 256: the launch runs in rounds of one tile per CU (two for 64 tokens), so the tile with
+  // the least rounds x time per round is taken.  Time of a round relative to 256 tokens, measured on launches of
+  // whole rounds (d = 3584): 192 tokens 0.78, 128 tokens 0.62 (smaller tiles read more LDS operands per MFMA).
+  // Against 256-token tiles, V = 152,064: 333 tokens 489 -> 447 us, 128 tokens 297 -> 276; V = 50,000, d = 1536:
+  // 640 tokens 121 -> 101, 4100 tokens 568 -> 544.  A smaller tile has to promise 2 %.  Up to 64 tokens the call is
+  // bound by reading W: two 64-token workgroups per CU keep more loads in flight (314 -> 229 us, 4.8 TB/s).
+  int nb = 8;
+  double best = 0.98 * tile_rounds(8, a.N, TV);
+  for (const auto& [smaller, t] : {std::pair{6, 0.78}, {4, 0.62}})
+    if (const double cost = tile_rounds(smaller, a.N, TV) * t; cost < best) {
+      best = cost;
+      nb = smaller;
+    }
+  if (a.N <= 64) nb = 2;
+  const int st = nb == 8 ? launch_tiles<8>(a, TV, s)
+               : nb == 6 ? launch_tiles<6>(a, TV, s)
+               : nb == 4 ? launch_tiles<4>(a, TV, s) : launch_tiles<2>(a, TV, s);
+  if (st != 0) return 1;
+  logprob_finalize_kernel<<<(unsigned)((a.N + FIN_TOKENS - 1) / FIN_TOKENS), FIN_TOKENS * FIN_GROUPS, 0, s>>>(
       reinterpret_cast<const float2*>(a.partials), a.target_logit, a.targets, a.logprob, a.lse, a.N, TV, a.V);
   return (int)hipGetLastError();
 }

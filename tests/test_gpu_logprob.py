@@ -55,6 +55,20 @@ def test_logprob_small_shapes_full(N, d, V, scale):
     assert np.abs(lp - rp).max() <= TOL and np.abs(lse - rl).max() <= TOL
 
 
+@pytest.mark.parametrize("N,d,V", [
+    (64, 128, 1281), (65, 128, 1281), (129, 64, 1281),   # 64- and 128-token tiles, a last band of two vocabulary tiles
+    (150, 64, 40000), (192, 192, 33000), (385, 64, 17000),   # 192-token tiles
+    (256, 64, 40000), (193, 128, 33000),                 # 256-token tiles
+    (1100, 64, 2100), (3000, 64, 513),                   # token tiles not a multiple of the XCD count
+])
+def test_logprob_every_tile_width_at_its_edges(N, d, V):
+    x = custom(N, d, V, seed=N * 3 + V)
+    print(f"logprob tile edges N={N} d={d} V={V}", flush=True)
+    lp, lse = run_hip(x.bits["hidden"], x.bits["lm_head"], x.targets, 1.0, junk_workspace=True)
+    rp, rl = ref.token_logprobs(x.hidden, x.lm_head, x.targets, 1.0)
+    assert np.abs(lp - rp).max() <= TOL and np.abs(lse - rl).max() <= TOL
+
+
 def test_logprob_peaked_and_wide_logits():
     """Logits with a wide range (std about 8): the running maximum matters."""
     x = custom(300, 256, 3000, seed=5, head_std=0.5)
