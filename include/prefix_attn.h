@@ -200,7 +200,8 @@ int prefix_attn_backward(const prefix_attn_plan_t* plan, const void* q, const vo
 /* Measurement variant: same arguments and result, but the stages are bracketed by HIP events
  * and the call WAITS for them.  kernel_ms (HOST [4]) receives the durations in milliseconds of
  * {pre-pass (delta, layouts), dQ pass, dK/dV pass over the prefix keys, dK/dV pass over the
- * rollouts' own keys}; for fp32 plans entry 2 is the whole dK/dV kernel and entry 3 is ~0. */
+ * rollouts' own keys and sums of partial gradients}; own keys whose items share the launch of the
+ * prefix keys (calls with few key blocks) count in entry 2; for fp32 plans entry 2 is the whole dK/dV kernel and entry 3 is ~0. */
 int prefix_attn_backward_timed(const prefix_attn_plan_t* plan, const void* q, const void* k_prefix,
                                const void* v_prefix, const void* k_suffix, const void* v_suffix,
                                const void* out, const void* d_out, const float* lse,
@@ -278,7 +279,7 @@ int prefix_attn_plan_items(const prefix_attn_plan_t* plan, int32_t pass, int32_t
  * masked item streams the tiles that hold rows needing the causal mask (its diagonal) plus, via
  * prefix_attn_plan_key_item_extra_tiles, the rollout's last tile when rows of the next rollout share it; its
  * mask-free item streams the tiles between; together they cover every tile from the block's first key to the
- * rollout's end exactly once. */
+ * rollout's end exactly once.  A launch of few items may cut a masked item's tiles into several workgroups. */
 int64_t prefix_attn_plan_num_key_items(const prefix_attn_plan_t* plan, int32_t pass);
 int prefix_attn_plan_key_items(const prefix_attn_plan_t* plan, int32_t pass, int32_t* items_out);
 /* tiles_out [num_items] (HOST): for pass 1 the one row tile an item streams after [tile0, tile1), or -1. */

@@ -57,27 +57,28 @@ struct BwdDqArgs {
 int launch_bwd_dq_bf16(const BwdDqArgs& a, void* stream);
 
 struct BwdDkvArgs {
-  const void* k;        // prefix: [P, Hkv, D]; suffix: [T, Hkv, D]
-  const void* v;
-  const void* qs;       // stacked-row copies / images / statistics from the pre-pass
+  const void* k_prefix;  // [P, Hkv, D]
+  const void* v_prefix;
+  const void* k_suffix;  // [T, Hkv, D]
+  const void* v_suffix;
+  const void* qs;        // stacked-row copies / statistics from the pre-pass
   const void* dos;
   const float* lse2s;
   const float* deltas;
   const int32_t* toks;
-  void* dk;             // same shape as k
-  void* dv;
-  float* partial;       // partials == true: unscaled fp32 partial gradients [2][splits][P][Hkv][D]
-  const KeyItem* items;
+  void* dk_prefix;       // same shapes as k / v
+  void* dv_prefix;
+  void* dk_suffix;
+  void* dv_suffix;
+  float* partial;        // unscaled fp32 partial gradients [slots][2][KEYS_PER_KEY_ITEM][D]
+  const KeyItem* items;  // the plan's launch list
+  const KeySum* sums;    // key blocks whose slots have to be added
   const int32_t* cu;
-  int64_t num_items, T, Mpad;
-  int64_t P;            // keys (rows) of k / v / dk / dv: the prefix length, or T for the rollouts' own keys
-  int32_t splits;       // partial-gradient slots (an item writes slot KeyItem::split)
-  int32_t Hkv, D, group;
+  int64_t num_items, num_sums, Mpad;
+  int32_t Hkv, D;
   float scale;
-  bool causal;          // true: the masked kernel (keys indexed inside their rollout, rows from the key on);
-                        // false: the mask-free kernel (keys indexed over the whole array, every streamed row sees them)
-  bool partials;        // items leave fp32 partials instead of writing dk / dv
-  bool reduce;          // after the launch, add the slots of `partial` into dk / dv (scaled, in the tensors' dtype)
+  enum { BOTH, MASK_FREE, MASKED } kinds;  // of the items of this launch
+  bool sum_partials;     // false: the pass over the items; true (afterwards): the sums of its partial gradients
 };
 int launch_bwd_dkv_bf16(const BwdDkvArgs& a, void* stream);
 

@@ -1,5 +1,5 @@
 // prefix_attn_backward: argument checks on the host, then the launches (pre-pass, dQ pass,
-// dK/dV pass over the prefix keys, dK/dV pass over the rollouts' own keys) on the caller's
+// dK/dV pass over prefix and own keys in one launch or two, sums of its partial gradients) on the caller's
 // stream.  Nothing here allocates or synchronises (the timed variant waits for its events).
 #include <hip/hip_runtime_api.h>
 
@@ -158,56 +158,45 @@ int enqueue_backward(const prefix_attn_plan_t* plan, const BackwardArgs& x, void
   if (pa::launch_bwd_dq_bf16(a, hip_stream) != 0) return PA_ERR_HIP;
   if (ev && hipEventRecord(ev[2], hs) != hipSuccess) return PA_ERR_HIP;
 
-  // ---- stages 2, 3: dK/dV of the prefix keys, then of the rollouts' own keys
+  // ---- stage 2: dK/dV of the prefix keys and of the own keys that share their launch; stage 3: the other own keys,
+  //      and the sums of partial gradients
   pa::BwdDkvArgs kv{};
+  kv.k_prefix = x.k_prefix;
+  kv.v_prefix = x.v_prefix;
+  kv.k_suffix = x.k_suffix;
+  kv.v_suffix = x.v_suffix;
   kv.qs = ws + plan->boff_qs;
   kv.dos = ws + plan->boff_dos;
   kv.lse2s = reinterpret_cast<const float*>(ws + plan->boff_lse2s);
   kv.deltas = reinterpret_cast<const float*>(ws + plan->boff_deltas);
   kv.toks = reinterpret_cast<const int32_t*>(ws + plan->boff_toks);
+  kv.dk_prefix = x.dk_prefix;
+  kv.dv_prefix = x.dv_prefix;
+  kv.dk_suffix = x.dk_suffix;
+  kv.dv_suffix = x.dv_suffix;
+  kv.partial = reinterpret_cast<float*>(ws + plan->boff_part);
+  kv.sums = plan->d_key_sums;
+  kv.num_sums = (int64_t)plan->key_sums.size();
   kv.cu = plan->d_cu;
-  kv.T = plan->T;
   kv.Mpad = plan->Mpad;
   kv.Hkv = d.num_kv_heads;
   kv.D = d.head_dim;
-  kv.group = plan->group;
   kv.scale = d.softmax_scale;
-  kv.partial = reinterpret_cast<float*>(ws + plan->boff_part);
-  if (has_prefix) {
-    kv.k = x.k_prefix;
-    kv.v = x.v_prefix;
-    kv.dk = x.dk_prefix;
-    kv.dv = x.dv_prefix;
-    kv.P = d.prefix_len;
-    kv.items = plan->d_key_items[0];
-    kv.num_items = (int64_t)plan->key_items[0].size();
-    kv.causal = false;
-    kv.partials = kv.reduce = plan->row_splits > 1;
-    kv.splits = plan->row_splits;
-    if (pa::launch_bwd_dkv_bf16(kv, hip_stream) != 0) return PA_ERR_HIP;
-  }
-  if (ev && hipEventRecord(ev[3], hs) != hipSuccess) return PA_ERR_HIP;
-  // the rollouts' own keys: the masked kernel (on the tiles that need the mask only, when the plan splits the
-  // pass), then the mask-free kernel on the other tiles and the sum of the two partial gradients
-  kv.k = x.k_suffix;
-  kv.v = x.v_suffix;
-  kv.dk = x.dk_suffix;
-  kv.dv = x.dv_suffix;
-  kv.P = plan->T;
-  kv.items = plan->d_key_items[1];
-  kv.num_items = (int64_t)plan->key_items[1].size();
-  kv.causal = true;
-  kv.partials = plan->suffix_split;
-  kv.reduce = false;
-  kv.splits = 2;
+  auto launch = [&](int64_t first, int64_t end, decltype(kv.kinds) kinds) {
+    kv.items = plan->d_key_launch + first;
+    kv.num_items = end - first;
+    kv.kinds = kinds;
+    return pa::launch_bwd_dkv_bf16(kv, hip_stream) == 0;
+  };
+  // without a prefix all of it is stage 3
+  if (ev && !has_prefix && hipEventRecord(ev[3], hs) != hipSuccess) return PA_ERR_HIP;
+  const int64_t items = (int64_t)plan->key_launch.size(), mask_free = plan->key_mask_free;
+  if (mask_free < 0 ? !launch(0, items, pa::BwdDkvArgs::BOTH) : !launch(0, mask_free, pa::BwdDkvArgs::MASK_FREE))
+    return PA_ERR_HIP;
+  if (ev && has_prefix && hipEventRecord(ev[3], hs) != hipSuccess) return PA_ERR_HIP;
+  if (mask_free >= 0 && !launch(mask_free, items, pa::BwdDkvArgs::MASKED)) return PA_ERR_HIP;
+  kv.sum_partials = true;
   if (pa::launch_bwd_dkv_bf16(kv, hip_stream) != 0) return PA_ERR_HIP;
-  if (plan->suffix_split) {
-    kv.items = plan->d_key_items_full;
-    kv.num_items = (int64_t)plan->key_items_full.size();
-    kv.causal = false;
-    kv.reduce = true;
-    if (pa::launch_bwd_dkv_bf16(kv, hip_stream) != 0) return PA_ERR_HIP;
-  }
   if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;
   return PA_OK;
 }

@@ -36,29 +36,28 @@ using namespace mt;
 constexpr int KV_THREADS = KEY_WAVES * 64;
 constexpr float LOG2E = 1.4426950408889634f;
 
-// PARTIAL: the item leaves unscaled fp32 partial gradients in slot `it.split` of `partial`
-// ([2][splits][P][Hkv][D], P = number of keys of the array k / v) and a reduction kernel adds the slots.  Used for
-// the prefix keys of a short prefix (each item streams one range of row tiles) and for a rollout's own keys
-// when their pass is split: the CAUSAL instantiation then streams only the tiles that need the mask (the
-// block's diagonal, and the rollout's last tile if rows of the next rollout share it), the mask-free
-// instantiation the tiles between, with the keys indexed over all packed tokens (P = T).
-template <int D, bool CAUSAL, bool PARTIAL>
-__global__ __launch_bounds__(KV_THREADS, 1) void bwd_dkv_kernel(
-    const __bf16* __restrict__ k, const __bf16* __restrict__ v, const __bf16* __restrict__ qs,
-    const __bf16* __restrict__ dos,
-    const float* __restrict__ lse2s, const float* __restrict__ deltas, const int32_t* __restrict__ toks,
-    __bf16* __restrict__ dk,
-    __bf16* __restrict__ dv, float* __restrict__ partial, int64_t P, int splits,
-    const KeyItem* __restrict__ items, const int32_t* __restrict__ cu, int64_t T, int64_t Mpad, int Hkv, int group,
+template <int D>
+struct DkvStage {  // one LDS buffer: Q tile, dO tile, statistics (LSE * log2 e, delta, packed token index: 3 x 64 words)
+  static constexpr int BYTES = 2 * Geo<D>::ROW_TILE_BYTES + 1024;
+};
+
+// One work item.  CAUSAL: a block of a rollout's own keys and row tiles that need the mask (key0 is a position inside
+// the rollout); otherwise every streamed row sees every key, and key0 indexes the whole array (the prefix, or all
+// packed tokens).  An item that streams only some of its block's row tiles leaves unscaled fp32 partial gradients in
+// slot `it.slot` of `partial` ([slots][2][128 keys][D]: dK, dV) and bwd_dkv_reduce_kernel adds the block's slots:
+// blocks of a short prefix, long rollouts (whose masked items stream the tiles on the block's diagonal, and the
+// rollout's last tile if rows of the next rollout share it, and whose mask-free items stream the tiles between), and
+// own key blocks that the plan cuts because the launch has few items.
+template <int D, bool CAUSAL>
+__device__ __forceinline__ void dkv_item(
+    unsigned char* smem, const KeyItem& it, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+    const __bf16* __restrict__ qs, const __bf16* __restrict__ dos, const float* __restrict__ lse2s,
+    const float* __restrict__ deltas, const int32_t* __restrict__ toks, __bf16* __restrict__ dk,
+    __bf16* __restrict__ dv, float* __restrict__ partial, const int32_t* __restrict__ cu, int64_t Mpad, int Hkv,
     float scale) {
   using G = Geo<D>;
   constexpr int KK = G::KK, DB = G::DB;
-  constexpr int STATS = 1024;  // per row: LSE*log2e, delta, packed token index (3 x 64 words)
-  constexpr int STAGE = 2 * G::ROW_TILE_BYTES + STATS;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
-
-  const KeyItem it = items[blockIdx.x];
-  if (it.c < 0) return;
+  constexpr int STAGE = DkvStage<D>::BYTES;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
@@ -301,21 +300,20 @@ __global__ __launch_bounds__(KV_THREADS, 1) void bwd_dkv_kernel(
   }
 
   // ---- epilogue: register i of block db is channel db*32 + 8*(i/4) + 4*hf + i%4 of this lane's key
-  if (PARTIAL) {
-    if (key_ok) {
-      float* pk = partial + (((int64_t)it.split * P + off_g + key) * Hkv + it.c) * D + 4 * hf;
-      float* pv = pk + (int64_t)splits * P * Hkv * D;
+  if (!key_ok) return;
+  if (it.slot >= 0) {
+    float* pk = partial + ((int64_t)it.slot * 2 * KEYS_PER_KEY_ITEM + kloc) * D + 4 * hf;
+    float* pv = pk + KEYS_PER_KEY_ITEM * D;
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const f32x4 wk = {dK[db][4 * a], dK[db][4 * a + 1], dK[db][4 * a + 2], dK[db][4 * a + 3]};
-          const f32x4 wv = {dV[db][4 * a], dV[db][4 * a + 1], dV[db][4 * a + 2], dV[db][4 * a + 3]};
-          *reinterpret_cast<f32x4*>(pk + db * 32 + 8 * a) = wk;
-          *reinterpret_cast<f32x4*>(pv + db * 32 + 8 * a) = wv;
-        }
-    }
-  } else if (key_ok) {
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 wk = {dK[db][4 * a], dK[db][4 * a + 1], dK[db][4 * a + 2], dK[db][4 * a + 3]};
+        const f32x4 wv = {dV[db][4 * a], dV[db][4 * a + 1], dV[db][4 * a + 2], dV[db][4 * a + 3]};
+        *reinterpret_cast<f32x4*>(pk + db * 32 + 8 * a) = wk;
+        *reinterpret_cast<f32x4*>(pv + db * 32 + 8 * a) = wv;
+      }
+  } else {
     __bf16* kp = dk + krow * D + 4 * hf;
     __bf16* vp = dv + krow * D + 4 * hf;
 #pragma unroll
@@ -331,20 +329,49 @@ __global__ __launch_bounds__(KV_THREADS, 1) void bwd_dkv_kernel(
   }
 }
 
-// Adds the row splits' fp32 partials of the prefix gradients and converts: 4 channels per thread.
-__global__ __launch_bounds__(256) void bwd_dkv_reduce_kernel(const float* __restrict__ partial, __bf16* __restrict__ dk,
-                                                             __bf16* __restrict__ dv, int64_t n4, int splits,
-                                                             float scale) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
+// MASK_FREE, MASKED: the kinds of items in the launch.  A launch of few items holds both, so that those of one kind fill
+// the CUs that the other leaves idle in its last round; the plan decides (build_key_launch).
+template <int D, bool MASK_FREE, bool MASKED>
+__global__ __launch_bounds__(KV_THREADS, D == 64 ? 2 : 1) void bwd_dkv_kernel(
+    const __bf16* __restrict__ k_pre, const __bf16* __restrict__ v_pre, const __bf16* __restrict__ k_own,
+    const __bf16* __restrict__ v_own, const __bf16* __restrict__ qs, const __bf16* __restrict__ dos,
+    const float* __restrict__ lse2s, const float* __restrict__ deltas, const int32_t* __restrict__ toks,
+    __bf16* __restrict__ dk_pre, __bf16* __restrict__ dv_pre, __bf16* __restrict__ dk_own, __bf16* __restrict__ dv_own,
+    float* __restrict__ partial, const KeyItem* __restrict__ items, const int32_t* __restrict__ cu, int64_t Mpad,
+    int Hkv, float scale) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * DkvStage<D>::BYTES];
+  const KeyItem it = items[blockIdx.x];
+  if (it.c < 0) return;
+  if (MASKED && (!MASK_FREE || it.g >= 0)) {
+    dkv_item<D, true>(smem, it, k_own, v_own, qs, dos, lse2s, deltas, toks, dk_own, dv_own, partial, cu, Mpad, Hkv, scale);
+  } else if (MASK_FREE) {
+    const bool own = it.g == -2;
+    dkv_item<D, false>(smem, it, own ? k_own : k_pre, own ? v_own : v_pre, qs, dos, lse2s, deltas, toks,
+                       own ? dk_own : dk_pre, own ? dv_own : dv_pre, partial, cu, Mpad, Hkv, scale);
+  }
+}
+
+// Adds the partial gradients of a key block and converts; a workgroup handles a quarter of a block's keys.
+__global__ __launch_bounds__(256) void bwd_dkv_reduce_kernel(
+    const float* __restrict__ partial, __bf16* __restrict__ dk_pre, __bf16* __restrict__ dv_pre,
+    __bf16* __restrict__ dk_own, __bf16* __restrict__ dv_own, const KeySum* __restrict__ sums, int Hkv, int D,
+    float scale) {
+  const KeySum s = sums[blockIdx.x];
+  __bf16* dk = s.own ? dk_own : dk_pre;
+  __bf16* dv = s.own ? dv_own : dv_pre;
+  const int per_key = D / 4;  // 4 channels per thread and step
+  const int n = s.nkeys * per_key, n_slot = KEYS_PER_KEY_ITEM * per_key;
+  const f32x4* p = reinterpret_cast<const f32x4*>(partial) + (int64_t)s.slot0 * 2 * n_slot;
+  for (int i = blockIdx.y * 256 + threadIdx.x; i < n; i += gridDim.y * 256) {
     f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < splits; ++s) {
-      sk += *reinterpret_cast<const f32x4*>(partial + ((int64_t)s * n4 + i) * 4);
-      sv += *reinterpret_cast<const f32x4*>(partial + (((int64_t)splits + s) * n4 + i) * 4);
+    for (int t = 0; t < s.nslots; ++t) {
+      sk += p[(int64_t)t * 2 * n_slot + i];
+      sv += p[(int64_t)t * 2 * n_slot + n_slot + i];
     }
     sk *= scale;
-    *reinterpret_cast<bf16x4*>(dk + i * 4) = __builtin_convertvector(sk, bf16x4);
-    *reinterpret_cast<bf16x4*>(dv + i * 4) = __builtin_convertvector(sv, bf16x4);
+    const int64_t at = ((int64_t)(s.key0 + i / per_key) * Hkv + s.c) * D + i % per_key * 4;
+    *reinterpret_cast<bf16x4*>(dk + at) = __builtin_convertvector(sk, bf16x4);
+    *reinterpret_cast<bf16x4*>(dv + at) = __builtin_convertvector(sv, bf16x4);
   }
 }
 
@@ -353,32 +380,33 @@ __global__ __launch_bounds__(256) void bwd_dkv_reduce_kernel(const float* __rest
 int launch_bwd_dkv_bf16(const BwdDkvArgs& a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   auto b = [](const void* p) { return static_cast<const __bf16*>(p); };
-  if (a.num_items > 0) {
-    const unsigned grid = (unsigned)a.num_items;
-#define PA_LAUNCH(DD, CC, PP)                                                                                      \
-  bwd_dkv_kernel<DD, CC, PP><<<grid, KV_THREADS, 0, s>>>(                                                          \
-      b(a.k), b(a.v), b(a.qs), b(a.dos), a.lse2s, a.deltas, a.toks, static_cast<__bf16*>(a.dk),                    \
-      static_cast<__bf16*>(a.dv), a.partial, a.P, a.splits, a.items, a.cu, a.T, a.Mpad, a.Hkv, a.group, a.scale)
+  auto w = [](void* p) { return static_cast<__bf16*>(p); };
+  if (a.sum_partials) {
+    if (a.num_sums == 0) return 0;
+    bwd_dkv_reduce_kernel<<<dim3((unsigned)a.num_sums, 4), 256, 0, s>>>(
+        a.partial, w(a.dk_prefix), w(a.dv_prefix), w(a.dk_suffix), w(a.dv_suffix), a.sums, a.Hkv, a.D, a.scale);
+    return (int)hipGetLastError();
+  }
+#define PA_LAUNCH(DD, FF, MM, ITEMS, N)                                                                            \
+  bwd_dkv_kernel<DD, FF, MM><<<(unsigned)(N), KV_THREADS, 0, s>>>(                                                 \
+      b(a.k_prefix), b(a.v_prefix), b(a.k_suffix), b(a.v_suffix), b(a.qs), b(a.dos), a.lse2s, a.deltas, a.toks,    \
+      w(a.dk_prefix), w(a.dv_prefix), w(a.dk_suffix), w(a.dv_suffix), a.partial, ITEMS, a.cu, a.Mpad, a.Hkv, a.scale)
 #define PA_LAUNCH_D(DD)                                                                                            \
-  if (a.causal && a.partials) PA_LAUNCH(DD, true, true);                                                           \
-  else if (a.causal) PA_LAUNCH(DD, true, false);                                                                   \
-  else if (a.partials) PA_LAUNCH(DD, false, true);                                                                 \
-  else PA_LAUNCH(DD, false, false)
-    if (a.D == 128) {
-      PA_LAUNCH_D(128);
-    } else {
-      PA_LAUNCH_D(64);
-    }
+  if (a.kinds == BwdDkvArgs::BOTH) {                                                                               \
+    PA_LAUNCH(DD, true, true, a.items, a.num_items);                                                               \
+  } else if (a.kinds == BwdDkvArgs::MASK_FREE) {                                                                   \
+    PA_LAUNCH(DD, true, false, a.items, a.num_items);                                                              \
+  } else {                                                                                                         \
+    PA_LAUNCH(DD, false, true, a.items, a.num_items);                                                              \
+  }
+  if (a.num_items == 0) return 0;
+  if (a.D == 128) {
+    PA_LAUNCH_D(128)
+  } else {
+    PA_LAUNCH_D(64)
+  }
 #undef PA_LAUNCH_D
 #undef PA_LAUNCH
-    if (hipGetLastError() != hipSuccess) return 1;
-  }
-  if (a.partials && a.reduce) {
-    const int64_t n4 = a.P * a.Hkv * a.D / 4;
-    const int64_t want = (n4 + 255) / 256;
-    bwd_dkv_reduce_kernel<<<(unsigned)(want < 8192 ? want : 8192), 256, 0, s>>>(
-        a.partial, static_cast<__bf16*>(a.dk), static_cast<__bf16*>(a.dv), n4, a.splits, a.scale);
-  }
   return (int)hipGetLastError();
 }
 

@@ -54,8 +54,18 @@ struct KeyItem {
   int32_t nkeys;  // keys in the block (<= KEYS_PER_KEY_ITEM)
   int32_t tile0;  // the row tiles [tile0, tile1) of the kv head this item streams (a short prefix is split over
   int32_t tile1;  //   `row_splits` items per key block to fill the chip; a rollout's own keys: see suffix_split)
-  int32_t split;  // which partial-gradient slot the item writes when its pass leaves partials
+  int32_t slot;   // launch list: partial-gradient slot the item writes, or -1: it writes dk / dv itself; in
+                  //   key_items[0] the number of the item's row range
   int32_t extra_tile;  // masked suffix items: one more row tile after [tile0, tile1), or -1
+};
+
+// A key block whose gradients are the sum of the partial slots [slot0, slot0 + nslots).
+struct KeySum {
+  int32_t own;    // 0: prefix keys, 1: the rollouts' own keys
+  int32_t key0;   // first key of the block: prefix index or packed token index
+  int32_t c;      // kv head
+  int32_t nkeys;
+  int32_t slot0, nslots;
 };
 
 // Arguments of one attention pass (prefix or suffix).  All pointers are device pointers.
@@ -174,7 +184,6 @@ struct prefix_attn_plan {
          ws_bytes = 0;
   // backward: dK/dV work lists (0 = prefix key blocks, 1 = suffix key blocks) and workspace layout
   std::vector<pa::KeyItem> key_items[2];
-  pa::KeyItem* d_key_items[2] = {nullptr, nullptr};
   int64_t Mpad = 0;                    // stacked rows per kv head, rounded up to ROWS_PER_ROW_TILE
   int32_t row_splits = 1;              // items per prefix key block (> 1: fp32 partial gradients are reduced)
   // A rollout's own key block sees masked rows only near its diagonal and in the rollout's last, partly filled
@@ -182,7 +191,14 @@ struct prefix_attn_plan {
   // kernel the rest (key_items_full); both leave fp32 partials that a reduction adds.
   bool suffix_split = false;
   std::vector<pa::KeyItem> key_items_full;
-  pa::KeyItem* d_key_items_full = nullptr;
+  // What the dK/dV launch runs (bf16): the items of the three lists, own key blocks cut further where the launch has
+  // few items, in launch order; and the key blocks whose partial gradients have to be added.
+  std::vector<pa::KeyItem> key_launch;
+  pa::KeyItem* d_key_launch = nullptr;
+  int64_t key_mask_free = -1;          // -1: one launch; else two, the first of this many (mask-free) items
+  std::vector<pa::KeySum> key_sums;
+  pa::KeySum* d_key_sums = nullptr;
+  int32_t key_slots = 0;               // partial-gradient slots in use, 2 x KEYS_PER_KEY_ITEM x D fp32 each
   size_t boff_delta = 0, boff_lse_th = 0, boff_qs = 0, boff_dos = 0, boff_lse2s = 0, boff_deltas = 0,
          boff_toks = 0, boff_ktp = 0, boff_kts = 0, boff_part = 0, boff_dqpart = 0, bws_bytes = 0;
 };

@@ -8,7 +8,11 @@
 
 #include <algorithm>
 #include <cmath>
+#include <functional>
+#include <map>
 #include <new>
+#include <queue>
+#include <utility>
 
 #include "common.h"
 
@@ -253,7 +257,7 @@ void build_key_items(prefix_attn_plan_t& p) {
           full.push_back({-2, p.cu[g] + key0, c, n, r.tile_full, r.tile_e_full, 1, -1});
         } else {
           suf.push_back({g, key0, c, n, r.tile_b, r.tile_e, 0, -1});
-          if (p.suffix_split) full.push_back({-1, p.cu[g] + key0, c, n, 0, 0, 1, -1});  // no tiles: writes zeros
+          if (p.suffix_split) full.push_back({-1, p.cu[g] + key0, c, n, 0, 0, 1, -1});  // no tiles
         }
       }
   auto tiles_of = [](const pa::KeyItem& a) { return a.tile1 - a.tile0 + (a.extra_tile >= 0 ? 1 : 0); };
@@ -264,6 +268,145 @@ void build_key_items(prefix_attn_plan_t& p) {
     for (const pa::KeyItem& it : full) per_head[it.c].push_back(it);
     interleave_over_xcds(per_head, p.num_xcd, pa::KeyItem{-1, 0, -1, 0, 0, 0, 0, -1}, full);
   }
+}
+
+// The launch list of the bf16 dK/dV pass.  With fewer than four items per CU, prefix blocks, mask-free and masked own
+// blocks run in one launch, longest items first, so that the last round of one kind is filled with items of another:
+// 5,377 prefix keys, 5 rollouts of 37 ... 1,901 tokens, 14 / 2 heads of 64: 131 + 199 us in two launches, 155 in one
+// (own blocks cut, see below); 4,096 prefix keys, 8 rollouts of 1,152, 28 / 4 heads of 128: 1,196 -> 1,128.  Larger
+// launches lose nothing to their last round, and the kernel that holds both kinds runs the mask-free items 1 % slower
+// (32,768 own keys: 13.44 ms in two launches, 13.52 in one), so they stay two launches.
+//
+// A launch with fewer than two items per CU is as long as its longest item, and that is often an own block (the first
+// keys of a rollout are seen by all of its rows).  Those blocks are then cut into ranges of at most `limit` row
+// tiles, each leaving a partial; the limit is the one for which list scheduling over the CUs ends first.  Launches
+// with more items keep whole blocks: their partials would be re-read for a tail that is short anyway.
+void build_key_launch(prefix_attn_plan_t& p) {
+  p.key_launch.clear();
+  p.key_sums.clear();
+  p.key_slots = 0;
+  if (p.desc.dtype != PA_BF16) return;
+  const pa::KeyItem pad{-1, 0, -1, 0, 0, 0, -1, -1};
+  const bool cut_prefix = p.row_splits > 1;
+  auto tiles_of = [](const pa::KeyItem& a) { return a.tile1 - a.tile0 + (a.extra_tile >= 0 ? 1 : 0); };
+
+  std::vector<int> others;  // tiles of the items that are not cut here
+  for (const pa::KeyItem& it : p.key_items[0])
+    if (it.c >= 0) others.push_back(it.tile1 - it.tile0);
+  int limit = 0;  // most row tiles of an own item; 0: no limit
+  if (!p.suffix_split && !p.key_items[1].empty() && others.size() + p.key_items[1].size() < 2 * (size_t)p.num_cu) {
+    const int longest = tiles_of(p.key_items[1].front());
+    auto makespan = [&](int lim) {
+      std::vector<double> cost;
+      for (int t : others) cost.push_back(t + 3.0);
+      for (const pa::KeyItem& it : p.key_items[1]) {
+        const int t = tiles_of(it), n = lim ? (t + lim - 1) / lim : 1;
+        for (int i = 0; i < n; ++i) cost.push_back((double)t / n + (n > 1 ? 3.5 : 3.0));
+      }
+      std::sort(cost.begin(), cost.end(), std::greater<double>());
+      std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
+      for (int i = 0; i < p.num_cu; ++i) cu.push(0.0);
+      double end = 0.0;
+      for (double c : cost) {
+        const double t = cu.top() + c;
+        cu.pop();
+        cu.push(t);
+        end = std::max(end, t);
+      }
+      return end;
+    };
+    double best = 0.95 * makespan(0) - 4.0;  // the sum of partials is one more launch (about 4 tiles' time)
+    for (int n = 2; n <= 16 && longest / n >= 16; ++n) {
+      const int lim = (longest + n - 1) / n;
+      const double m = makespan(lim);
+      if (m < best) {
+        best = m;
+        limit = lim;
+      }
+    }
+  }
+
+  // slots: those of a block are adjacent, in the order in which the reduction adds them
+  std::vector<pa::KeyItem> prefix, own;
+  if (cut_prefix) {
+    std::vector<std::vector<int>> first(p.desc.num_kv_heads, std::vector<int>((p.desc.prefix_len + pa::KEYS_PER_KEY_ITEM - 1) / pa::KEYS_PER_KEY_ITEM, -1));
+    for (pa::KeyItem it : p.key_items[0]) {
+      if (it.c >= 0) {
+        int& slot0 = first[it.c][it.key0 / pa::KEYS_PER_KEY_ITEM];
+        if (slot0 < 0) {
+          slot0 = p.key_slots;
+          p.key_slots += p.row_splits;
+          p.key_sums.push_back({0, it.key0, it.c, it.nkeys, slot0, p.row_splits});
+        }
+        it.slot = slot0 + it.slot;  // the prefix list's items carry their range's number
+      }
+      prefix.push_back(it);
+    }
+  } else {
+    for (pa::KeyItem it : p.key_items[0]) {
+      it.slot = -1;
+      prefix.push_back(it);
+    }
+  }
+  std::map<std::pair<int, int>, int> masked_slot;  // split pass: (kv head, packed first key) -> slot of the masked item
+  for (pa::KeyItem it : p.key_items[1]) {
+    const int t = tiles_of(it), n = limit ? (t + limit - 1) / limit : 1;
+    const int packed = p.cu[it.g] + it.key0;
+    it.slot = -1;
+    if (it.extra_tile >= 0 || n == 1) {
+      own.push_back(it);
+      masked_slot[{it.c, packed}] = (int)own.size() - 1;
+      continue;
+    }
+    p.key_sums.push_back({1, packed, it.c, it.nkeys, p.key_slots, n});
+    for (int i = 0; i < n; ++i) {
+      pa::KeyItem part = it;
+      part.tile0 = it.tile0 + (int)((int64_t)t * i / n);
+      part.tile1 = it.tile0 + (int)((int64_t)t * (i + 1) / n);
+      part.slot = p.key_slots++;
+      own.push_back(part);
+    }
+  }
+  std::vector<pa::KeyItem> full;
+  for (pa::KeyItem it : p.key_items_full) {
+    if (it.c >= 0 && it.tile1 > it.tile0) {  // masked item and mask-free item: one partial each
+      pa::KeyItem& m = own[masked_slot[{it.c, it.key0}]];
+      p.key_sums.push_back({1, it.key0, it.c, it.nkeys, p.key_slots, 2});
+      m.slot = p.key_slots++;
+      it.slot = p.key_slots++;
+      full.push_back(it);
+    } else {
+      full.push_back(pad);  // keeps the list's layout over the XCDs
+    }
+  }
+  std::stable_sort(own.begin(), own.end(), [&](const pa::KeyItem& a, const pa::KeyItem& b) { return tiles_of(a) > tiles_of(b); });
+
+  // launch order; the lists laid out over the XCDs start at a multiple of the XCD count
+  auto append = [&](const pa::KeyItem* b, const pa::KeyItem* e) {
+    while ( p.key_launch.size() % p.num_xcd != 0) p.key_launch.push_back(pad);
+    p.key_launch.insert(p.key_launch.end(), b, e);
+  };
+  int prefix_tiles = 0;
+  for (const pa::KeyItem& it : prefix)
+    if (it.c >= 0) prefix_tiles = std::max(prefix_tiles, it.tile1 - it.tile0);
+  size_t real = own.size();
+  for (const auto* v : {&prefix, &full})
+    for (const pa::KeyItem& it : *v) real += it.c >= 0;
+  p.key_mask_free = -1;
+  if (real >= 4 * (size_t)p.num_cu) {
+    append(full.data(), full.data() + full.size());
+    append(prefix.data(), prefix.data() + prefix.size());
+    append(nullptr, nullptr);  // pads, so that the count below is where the masked items begin
+    p.key_mask_free = (int64_t)p.key_launch.size();
+    append(own.data(), own.data() + own.size());
+    return;
+  }
+  size_t long_own = 0;
+  while (long_own < own.size() && full.empty() && tiles_of(own[long_own]) > prefix_tiles) ++long_own;
+  append(full.data(), full.data() + full.size());
+  append(own.data(), own.data() + long_own);
+  append(prefix.data(), prefix.data() + prefix.size());
+  append(own.data() + long_own, own.data() + own.size());
 }
 
 // Backward workspace: delta and the re-ordered LSE (used by the fp32 path); for bf16 also the stacked Q/dO copies, the
@@ -287,14 +430,8 @@ void layout_backward_workspace(prefix_attn_plan_t& p) {
     p.boff_ktp = p.boff_toks + stats;
     p.boff_kts = p.boff_ktp + align_up((size_t)d.num_kv_heads * p.tiles_prefix * image, 256);
     end = p.boff_kts + align_up((size_t)d.num_kv_heads * p.tiles_suffix * image, 256);
-    // fp32 partial dK, dV: of the prefix per row split [2][row_splits][P][Hkv][D]; of the rollouts' own keys, when
-    // their pass is split into a masked and a mask-free item per block, [2][2][T][Hkv][D].  The two stages run
-    // one after the other and share the region.
-    p.boff_part = end;
-    size_t part = 0;
-    if (p.row_splits > 1) part = (size_t)2 * p.row_splits * d.prefix_len * d.num_kv_heads * d.head_dim * sizeof(float);
-    if (p.suffix_split) part = std::max(part, (size_t)2 * 2 * p.T * d.num_kv_heads * d.head_dim * sizeof(float));
-    end += align_up(part, 256);
+    p.boff_part = end;  // fp32 partial dK, dV: [key_slots][2][KEYS_PER_KEY_ITEM][D]
+    end += align_up((size_t)p.key_slots * 2 * pa::KEYS_PER_KEY_ITEM * d.head_dim * sizeof(float), 256);
     p.boff_dqpart = end;  // fp32 partial dQ per key split: [key_splits][T][Hq][D]
     if (p.key_splits > 1) end += align_up((size_t)p.key_splits * rows * d.head_dim * sizeof(float), 256);
   }
@@ -343,6 +480,7 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
     build_sweep_items(*p);
     p->Mpad = ((int64_t)p->T * p->group + pa::ROWS_PER_ROW_TILE - 1) / pa::ROWS_PER_ROW_TILE * pa::ROWS_PER_ROW_TILE;
     build_key_items(*p);
+    build_key_launch(*p);
   } catch (const std::bad_alloc&) {
     delete p;
     return PA_ERR_ALLOC;
@@ -396,21 +534,20 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
         ok = hipMalloc((void**)&p->d_dq_items, bytes) == hipSuccess &&
              hipMemcpy(p->d_dq_items, p->dq_items.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
       }
-      for (int s = 0; ok && s < 2; ++s) {
-        if (p->key_items[s].empty()) continue;
-        const size_t bytes = p->key_items[s].size() * sizeof(pa::KeyItem);
-        ok = hipMalloc((void**)&p->d_key_items[s], bytes) == hipSuccess &&
-             hipMemcpy(p->d_key_items[s], p->key_items[s].data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
+      if (ok && !p->key_launch.empty()) {
+        const size_t bytes = p->key_launch.size() * sizeof(pa::KeyItem);
+        ok = hipMalloc((void**)&p->d_key_launch, bytes) == hipSuccess &&
+             hipMemcpy(p->d_key_launch, p->key_launch.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
+      }
+      if (ok && !p->key_sums.empty()) {
+        const size_t bytes = p->key_sums.size() * sizeof(pa::KeySum);
+        ok = hipMalloc((void**)&p->d_key_sums, bytes) == hipSuccess &&
+             hipMemcpy(p->d_key_sums, p->key_sums.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
       }
       // set-up for prefix_attn_forward_static: look its workspace up now, with the plan's device current,
       // so that the call itself only reads a table
       void* unused = nullptr;
       ok = ok && pa::static_scratch(desc->device, &unused) == PA_OK;
-      if (ok && !p->key_items_full.empty()) {
-        const size_t bytes = p->key_items_full.size() * sizeof(pa::KeyItem);
-        ok = hipMalloc((void**)&p->d_key_items_full, bytes) == hipSuccess &&
-             hipMemcpy(p->d_key_items_full, p->key_items_full.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
-      }
       (void)hipSetDevice(prev);
     }
     if (!ok) {
@@ -429,9 +566,8 @@ void prefix_attn_destroy(prefix_attn_plan_t* plan) {
   if (plan->d_cu) (void)hipFree(plan->d_cu);
   for (int s = 0; s < 2; ++s)
     if (plan->d_items[s]) (void)hipFree(plan->d_items[s]);
-  for (int s = 0; s < 2; ++s)
-    if (plan->d_key_items[s]) (void)hipFree(plan->d_key_items[s]);
-  if (plan->d_key_items_full) (void)hipFree(plan->d_key_items_full);
+  if (plan->d_key_launch) (void)hipFree(plan->d_key_launch);
+  if (plan->d_key_sums) (void)hipFree(plan->d_key_sums);
   if (plan->d_dq_items) (void)hipFree(plan->d_dq_items);
   if (plan->d_sweep_items) (void)hipFree(plan->d_sweep_items);
   delete plan;

@@ -179,3 +179,31 @@ def test_backward_and_logprob_on_side_stream_and_graph_replay():
             assert np.array_equal(grads[n].float().cpu().numpy().astype(np.float64), eager[n]), f"replay {rep} {n}"
         assert np.array_equal(lp.cpu().numpy(), lp_eager), f"replay {rep} logprob"
     plan.destroy()
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens", [
+    (14, 2, 64, 700, (1900, 37, 640)), (7, 1, 128, 0, (1111, 5)), (12, 2, 128, 129, (1025, 400)), (16, 2, 64, 0, (513,)),
+])
+def test_backward_own_key_blocks_cut_into_row_ranges_full_tensor(Hq, Hkv, D, P, lens):
+    """Few key blocks: the rows of a rollout's first key blocks are cut into ranges, each a work item with a partial
+    gradient (the workspace then holds slots of 2 x 128 x D fp32), in the same launch as the prefix blocks.  Ragged
+    last blocks, row tiles that two rollouts share."""
+    import paper_2507_07966_amd as pa
+    plan = pa.prefix_attn_plan(Hq, Hkv, D, P, list(lens), D ** -0.5, dtype="bf16", device=-1)
+    T, group = sum(lens), Hq // Hkv
+    mpad = -(-T * group // 64) * 64
+    tiles = -(-P // 64) + sum(-(-n // 64) for n in lens)
+    fixed = 2 * T * Hq * 4 + 2 * Hkv * mpad * D * 2 + 3 * Hkv * mpad * 4 + Hkv * tiles * D * 64 * 2 + 12 * 256
+    longest = max(plan.key_items(1)[:, 5] - plan.key_items(1)[:, 4])
+    pre = plan.key_items(0)
+    prefix_slots = len(pre[pre[:, 2] >= 0]) if len(pre) and pre[0, 5] - pre[0, 4] < mpad // 64 else 0
+    dq_splits = len({int(k) for k in plan.items(2)[:, 4]})
+    fixed += prefix_slots * 2 * 128 * D * 4 + (dq_splits if dq_splits > 1 else 0) * T * Hq * D * 4
+    assert longest >= 32 and plan.backward_workspace_bytes >= fixed + 2 * 2 * 128 * D * 4
+    plan.destroy()
+    x = wl.make_custom("bf16", Hq, Hkv, D, P, lens, seed=31)
+    do, bits = wl.make_d_out(x)
+    # without a prefix the first rows see one or two keys, so their dQ is a difference of rounded terms: the absolute
+    # few-keys term of few_keys_floor bounds it, as for the one-key prefix above
+    check_grads(run_hip_backward(x, do, bits), oracle_backward(x, do), "bf16", f"own blocks cut {Hq}/{Hkv}/{D} P={P} {lens}",
+                few_keys_floor(x, do))
