@@ -266,7 +266,9 @@ int64_t prefix_attn_plan_num_items(const prefix_attn_plan_t* plan, int32_t pass)
  * padding items.
  * Single sweep (whole bf16 calls whose prefix is at most 1,024 tiles and not cut into key
  * ranges run as one pass per block of rows instead of prefix pass + suffix pass): like the
- * dQ pass with key0 = 0 and pkeys = P, laid out over the XCDs like the prefix pass. */
+ * dQ pass with key0 = 0 and pkeys = P, laid out over the XCDs like the prefix pass.  Whole calls with
+ * few rows cut [prefix | own keys] of every block into ranges of tiles instead and merge their partials;
+ * the prefix pass's ranges then serve partials over the prefix keys only. */
 int prefix_attn_plan_items(const prefix_attn_plan_t* plan, int32_t pass, int32_t* items_out);
 
 /* Work lists of the backward dK/dV pass, padding entries included.  pass 0 = prefix key blocks, 1 = the

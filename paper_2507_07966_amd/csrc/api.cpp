@@ -49,10 +49,12 @@ enum Mode {
 
 // Checks, then the launches (layout pre-pass, prefix pass, suffix pass, merge).  When `ev` is
 // non-null it holds 5 events recorded before, between and after them.  In the partial modes
-// `out` is the fp32 partial output and `lse_partial` its [T, Hq] LSE.
+// `out` is the fp32 partial output and `lse_partial` its [T, Hq] LSE.  `lse_out` (whole calls, may be null) receives the
+// [Hq, T] LSE; the workspace's copy is then not written where the merge can write the caller's directly.
 int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k_prefix, const void* v_prefix,
                     const void* k_suffix, const void* v_suffix, void* out, void* workspace, size_t workspace_bytes,
-                    void* hip_stream, hipEvent_t* ev, Mode mode = FULL, float* lse_partial = nullptr) {
+                    void* hip_stream, hipEvent_t* ev, Mode mode = FULL, float* lse_partial = nullptr,
+                    float* lse_out = nullptr) {
   if (!plan || !q || !out || !workspace) return PA_ERR_NULL;
   const bool with_suffix = mode != PARTIAL_PREFIX;
   if (with_suffix && (!k_suffix || !v_suffix)) return PA_ERR_NULL;
@@ -86,23 +88,19 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   a.scale = d.softmax_scale;
   a.part_rows = plan->T * d.num_q_heads;
   a.flags = reinterpret_cast<int32_t*>(ws + plan->off_flags);  // bf16 passes only
-  // With key splits the prefix pass leaves `ks` partials in the workspace and an n-way merge
-  // combines them (and the suffix partial) instead of the two-way merge.
+  // Few rows: the passes leave one partial per key range in the workspace, and an n-way merge combines them.
   const int ks = plan->key_splits;
-  auto merge_splits = [&](bool suffix_too, void* dst, int32_t dst_dtype, float* lse_th) {
+  auto merge_ranges = [&](int n, void* dst, int32_t dst_dtype, float* lse_th, float* lse_ht) {
     pa::MergeNArgs m{};
-    for (int i = 0; i < ks; ++i) {
+    for (int i = 0; i < n; ++i) {
       m.o[i] = o1 + (size_t)i * a.part_rows * d.head_dim;
       m.lse[i] = lse1 + (size_t)i * a.part_rows;
     }
-    if (suffix_too) {
-      m.o[ks] = o2;
-      m.lse[ks] = lse2;
-    }
     m.out = dst;
     m.lse_th_out = lse_th;
+    m.lse_out = lse_ht;
     m.T = plan->T;
-    m.n = ks + (suffix_too ? 1 : 0);
+    m.n = n;
     m.Hq = d.num_q_heads;
     m.D = d.head_dim;
     m.dtype = dst_dtype;
@@ -143,12 +141,13 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
     if (ev && hipEventRecord(ev[2], hs) != hipSuccess) return PA_ERR_HIP;
     if (pa::launch_pass_f32(a, hip_stream) != 0) return PA_ERR_HIP;
     if (ev && (hipEventRecord(ev[3], hs) != hipSuccess || hipEventRecord(ev[4], hs) != hipSuccess)) return PA_ERR_HIP;
-    return PA_OK;
+    return lse_out ? prefix_attn_lse(plan, workspace, lse_out, hip_stream) : PA_OK;
   }
-  // unsplit short prefix (the plan decides), own keys included: one sweep over [prefix | own keys] per
+  // few rows or a short prefix (the plan decides), own keys included: one sweep over [prefix | own keys] per
   // block of rows does the work of the prefix pass, the suffix pass and the merge (the sweep list carries both
   // extents); it leaves the result of the call, or the fp32 partial of a shard that also holds the own keys
-  const bool sweep = with_suffix && !plan->sweep_items.empty();
+  const bool ranges = with_suffix && !plan->range_items.empty();  // few rows: the same sweep, cut into key ranges
+  const bool sweep = with_suffix && (ranges || !plan->sweep_items.empty());
   if (has_prefix && !sweep) {
     a.k = k_prefix;
     a.v = v_prefix;
@@ -165,7 +164,7 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   }
   if (ev && hipEventRecord(ev[2], hs) != hipSuccess) return PA_ERR_HIP;
   if (!with_suffix) {
-    if (ks > 1 && merge_splits(false, out, PA_F32, lse_partial) != 0) return PA_ERR_HIP;
+    if (ks > 1 && merge_ranges(ks, out, PA_F32, lse_partial, nullptr) != 0) return PA_ERR_HIP;
     return PA_OK;
   }
   a.k = k_suffix;
@@ -178,9 +177,9 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   a.items = plan->d_items[1];
   a.num_items = (int64_t)plan->items[1].size();
   a.causal = true;
-  // bf16, whole call, unsplit prefix: the suffix pass combines its result with the prefix partial in its
+  // bf16, whole call, keys not cut into ranges: the suffix pass combines its result with the prefix partial in its
   // epilogue and writes `out` and the merged LSE itself (no merge launch, no suffix partial in memory)
-  const bool fused = mode == FULL && ks == 1;
+  const bool fused = mode == FULL && !ranges;
   if (fused) {
     a.epilogue = (has_prefix && !sweep) ? 2 : 1;
     a.o1 = o1;
@@ -193,9 +192,12 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
     a.k_pre = k_prefix;
     a.vt_pre = ws + plan->off_vtp;
     a.vt_pre_tiles_per_head = plan->tiles_prefix;
-    a.items = plan->d_sweep_items;
-    a.num_items = (int64_t)plan->sweep_items.size();
-    if (!fused) {  // a shard's partial: straight into the caller's buffers
+    a.items = ranges ? plan->d_range_items : plan->d_sweep_items;
+    a.num_items = (int64_t)(ranges ? plan->range_items : plan->sweep_items).size();
+    if (ranges) {
+      a.o_part = o1;
+      a.lse_part = lse1;
+    } else if (!fused) {  // a shard's partial: straight into the caller's buffers
       a.o_part = static_cast<float*>(out);
       a.lse_part = lse_partial;
     }
@@ -203,12 +205,13 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   if (pa::launch_pass_bf16(a, hip_stream) != 0) return PA_ERR_HIP;
 
   if (ev && hipEventRecord(ev[3], hs) != hipSuccess) return PA_ERR_HIP;
-  if (fused || sweep) {
+  if (fused || (sweep && !ranges)) {
     if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;
-    return PA_OK;
+    return lse_out ? prefix_attn_lse(plan, workspace, lse_out, hip_stream) : PA_OK;
   }
-  if (ks > 1) {
-    if (merge_splits(true, out, mode == FULL ? d.dtype : (int32_t)PA_F32, mode == FULL ? lse : lse_partial) != 0)
+  if (ranges) {
+    float* lse_th = mode == FULL ? (lse_out ? nullptr : lse) : lse_partial;
+    if (merge_ranges(plan->key_ranges, out, mode == FULL ? d.dtype : (int32_t)PA_F32, lse_th, lse_out) != 0)
       return PA_ERR_HIP;
     if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;
     return PA_OK;
@@ -251,10 +254,8 @@ int prefix_attn_forward_static(const prefix_attn_plan_t* plan, const void* q, co
   void* ws = nullptr;
   int st = pa::static_scratch(cur, &ws);  // already resolved when the plan was made; a table look-up here
   if (st != PA_OK) return st;
-  st = enqueue_forward(plan, q, k_prefix, v_prefix, k_suffix, v_suffix, out, ws, PA_STATIC_SCRATCH_BYTES, hip_stream,
-                       nullptr);
-  if (st != PA_OK || !lse_out) return st;
-  return prefix_attn_lse(plan, ws, lse_out, hip_stream);
+  return enqueue_forward(plan, q, k_prefix, v_prefix, k_suffix, v_suffix, out, ws, PA_STATIC_SCRATCH_BYTES, hip_stream,
+                         nullptr, FULL, nullptr, lse_out);
 }
 
 int prefix_attn_forward_timed(const prefix_attn_plan_t* plan, const void* q, const void* k_prefix,

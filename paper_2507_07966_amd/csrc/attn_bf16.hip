@@ -115,7 +115,9 @@ __device__ inline float quad_sum(float x) { return pair_sum(x + __shfl_xor(x, 16
 // in bf16 with its LSE; 2 = combine with the prefix partial (o1, lse1) by log-sum-exp and write the result.
 // SWEEP (suffix pass with EPI 0 or 1): the item first sweeps the prefix keys [0, it.pkeys) (no mask) and then
 // the rollout's own keys, all in one online softmax, so its result is the result of the call (EPI 1) or the
-// fp32 partial over a prefix shard and the own keys together (EPI 0).
+// fp32 partial over a prefix shard and the own keys together (EPI 0).  With EPI 0 an item may cover one range of that
+// key sequence only: prefix keys [it.key0, it.key0 + it.pkeys), then own keys [it.okey0, it.okey0 + it.nkeys), either of
+// them possibly none; the plan starts a range inside the own keys only where every row of the block sees its first key.
 template <int D, bool CAUSAL, int EPI, bool SWEEP, bool CAREFUL>
 __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ vt,
@@ -152,8 +154,10 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
   const int nkeys = it.nkeys;
   const int64_t row_stride = (int64_t)Hkv * D;
   // prefix pass: the item sweeps prefix keys [key0, key0 + nkeys), key0 a multiple of the tile
-  const __bf16* kown = k + ((int64_t)(CAUSAL ? off_g : it.key0) * Hkv + it.c) * D;
-  const __bf16* vtbase = vt + ((int64_t)it.c * vt_tiles_per_head + (CAUSAL ? vt_off[it.g] : it.key0 / BN)) * (D * BN);
+  constexpr bool RANGE = SWEEP && EPI == 0;
+  const int okey0 = RANGE ? it.okey0 : 0;  // own keys and positions count from here
+  const __bf16* kown = k + ((int64_t)(CAUSAL ? off_g + okey0 : it.key0) * Hkv + it.c) * D;
+  const __bf16* vtbase = vt + ((int64_t)it.c * vt_tiles_per_head + (CAUSAL ? vt_off[it.g] + okey0 / BN : it.key0 / BN)) * (D * BN);
 
   // ---- this lane's two query columns: query block nq (16 rows) of the wavefront's 32 rows, column l16; the
   //      lane holds channels 32*ks + 8*g4 .. +7 of each contraction step ks
@@ -171,7 +175,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
   for (int nq = 0; nq < NQ; ++nq) {
     const int64_t row = out_row(nq);
     if (row >= 0) {
-      pos[nq] = (it.row0 + wave * ROWS_PER_WAVE + nq * 16 + l16) / group;
+      pos[nq] = (it.row0 + wave * ROWS_PER_WAVE + nq * 16 + l16) / group - okey0;
       const __bf16* qp = q + row * D + 8 * g4;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) Q[nq][ks] = *reinterpret_cast<const bf16x8*>(qp + 32 * ks);
@@ -182,7 +186,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     }
   }
   // first suffix position among the wavefront's rows: tiles reaching past it need the mask
-  const int wave_first_pos = (it.row0 + wave * ROWS_PER_WAVE) / group;
+  const int wave_first_pos = (it.row0 + wave * ROWS_PER_WAVE) / group - okey0;
 
   // ---- LDS: two K buffers then two V^T buffers.  Per-lane byte offsets of the operand reads
   //      inside a buffer (the buffer base is an immediate).
@@ -210,8 +214,9 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
   const int P = SWEEP ? it.pkeys : 0;
   const int tp = SWEEP ? (P + BN - 1) / BN : 0;
   const int ntiles = tp + (nkeys + BN - 1) / BN;
-  const __bf16* kpre = SWEEP ? k_pre + (int64_t)it.c * D : nullptr;
-  const __bf16* vtpre = SWEEP ? vt_pre + (int64_t)it.c * vt_pre_tiles_per_head * (D * BN) : nullptr;
+  const int pkey0 = RANGE ? it.key0 : 0;
+  const __bf16* kpre = SWEEP ? k_pre + ((int64_t)pkey0 * Hkv + it.c) * D : nullptr;
+  const __bf16* vtpre = SWEEP ? vt_pre + ((int64_t)it.c * vt_pre_tiles_per_head + pkey0 / BN) * (D * BN) : nullptr;
   // Whole tiles are fetched with buffer loads: uniform tile offset in a scalar register plus the lane's
   // constant 32-bit offset.  Every such access lies inside the arrays (a ragged last K tile takes the
   // clamped path below), so the descriptors' range (2 GiB) never comes into play.
@@ -532,7 +537,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
       }
     } else if (row >= 0) {
       const float inv = 1.0f / l;
-      const int64_t prow = (CAUSAL ? 0 : (int64_t)it.split * part_rows) + row;  // key split s fills partial s
+      const int64_t prow = (CAUSAL && !RANGE ? 0 : (int64_t)it.split * part_rows) + row;  // key range s fills partial s
       float* op = o_part + prow * D + 4 * g4;
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f32x4*>(op + cb * 16) = O[cb][nq] * inv;

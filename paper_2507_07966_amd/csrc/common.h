@@ -35,8 +35,8 @@ struct WorkItem {
   int32_t nkeys;  // keys swept: the item's share of P in the prefix pass, causal extent in the suffix pass
   int32_t key0;   // prefix pass: first prefix key swept (a multiple of KEYS_PER_TILE); suffix pass: 0
   int32_t split;  // prefix pass: which key split this is (its partial lands in slot `split`); else 0
-  int32_t pkeys;  // backward dQ list only: prefix keys [key0, key0 + pkeys) swept before the nkeys own keys
-  int32_t pad_;
+  int32_t pkeys;  // backward dQ list, sweep and range lists: prefix keys [key0, key0 + pkeys) swept before the nkeys own keys
+  int32_t okey0;  // range list only: the own keys swept are [okey0, okey0 + nkeys), okey0 a multiple of KEYS_PER_TILE
 };
 
 // Backward tile geometry.  The key-stationary pass (dK/dV) gives a workgroup KEYS_PER_KEY_ITEM
@@ -179,6 +179,11 @@ struct prefix_attn_plan {
   // interleaved over the XCDs by kv head like the prefix pass, longest first inside a kv head
   std::vector<pa::WorkItem> sweep_items;
   pa::WorkItem* d_sweep_items = nullptr;
+  // Few rows: the keys [prefix | own keys] of every block of rows cut into `key_ranges` ranges, one sweep item each;
+  // range i leaves its fp32 partial in slot i and the n-way merge adds them.  Empty unless the plan uses it.
+  std::vector<pa::WorkItem> range_items;
+  pa::WorkItem* d_range_items = nullptr;
+  int32_t key_ranges = 1;
   // workspace layout, byte offsets
   size_t off_o1 = 0, off_o2 = 0, off_lse1 = 0, off_lse2 = 0, off_lse = 0, off_vtp = 0, off_vts = 0, off_flags = 0,
          ws_bytes = 0;

@@ -170,6 +170,57 @@ void build_sweep_items(prefix_attn_plan_t& p) {
   interleave_over_xcds(per_head, p.num_xcd, PAD_ITEM, p.sweep_items);
 }
 
+// Forward, few rows (bf16, with a prefix): the keys [prefix | own keys] of every block of rows are cut into n ranges, so
+// one launch of n x blocks sweep items fills the chip and one merge finishes the call (prefix pass, suffix pass, their
+// careful kernels and the merge are five launches).  n minimises the time of one round plus the partials, from measured
+// rates: 1.56 us per key tile at D = 128, 5 tiles' time for an item's start and end, fp32 partials written and read at
+// 4 TB/s, 5 us for the merge launch.  128 tokens, 28 / 4 heads of 128, 1,024 prefix keys (6 ranges):
+// passes 37 -> 18 us, the whole call with its LSE 45.3 -> 29.3 us.
+// Cuts inside the own keys stay at or before the position of the block's first row: every row then sees the first key
+// of every range, so no partial is empty.
+void build_range_items(prefix_attn_plan_t& p, size_t fixed_bytes, size_t slot_bytes) {
+  p.range_items.clear();
+  p.key_ranges = 1;
+  const std::vector<WorkItem>& blocks = p.items[1];
+  const int P = (int)p.desc.prefix_len, tp = p.tiles_prefix, BN = pa::KEYS_PER_TILE;
+  if (p.desc.dtype != PA_BF16 || P == 0 || blocks.size() * 2 > (size_t)p.num_cu) return;
+  auto cut = [&](const WorkItem& it, int n, int i) {  // first tile of range i of the block's tile sequence
+    const int total = tp + (it.nkeys + BN - 1) / BN, legal = tp + it.row0 / p.group / BN;
+    return i == n ? total : std::max(i, std::min((int)((int64_t)total * i / n), legal - (n - 1 - i)));
+  };
+  const double tile_us = p.desc.head_dim == 128 ? 1.56 : 0.9;
+  const double slot_us = (double)p.T * p.desc.num_q_heads * p.desc.head_dim * 4 * 2 / 4e6;
+  auto cost = [&](int n) {
+    int longest = 0;
+    for (const WorkItem& it : blocks)
+      for (int i = 0; i < n; ++i) longest = std::max(longest, cut(it, n, i + 1) - cut(it, n, i));
+    return tile_us * (longest + 5) + (n > 1 ? n * slot_us + 5.0 : 0.0);
+  };
+  // what fitted the library's own workspace keeps fitting
+  const size_t had = fixed_bytes + (size_t)(p.key_splits + 1) * slot_bytes;
+  int best = 1;
+  double best_us = p.key_splits > 1 ? 1e30 : 0.95 * cost(1);
+  for (int n = 2; n <= PA_MAX_PARTIALS && n * blocks.size() <= (size_t)p.num_cu && n - 1 <= tp; ++n) {
+    const size_t flags = align_up((n * blocks.size() + 64) * pa::WAVES_PER_ITEM * sizeof(int32_t), 256);
+    if (n > p.key_splits + 1 && had <= PA_STATIC_SCRATCH_BYTES && fixed_bytes + n * slot_bytes + flags > PA_STATIC_SCRATCH_BYTES) break;
+    if (const double us = cost(n); us < best_us) {
+      best_us = us;
+      best = n;
+    }
+  }
+  if (best == 1) return;
+  p.key_ranges = best;
+  std::vector<std::vector<WorkItem>> per_head(p.desc.num_kv_heads);
+  for (int i = 0; i < best; ++i)
+    for (const WorkItem& it : blocks) {
+      const int t0 = cut(it, best, i), t1 = cut(it, best, i + 1);
+      const int p0 = std::min(std::min(t0, tp) * BN, P), p1 = std::min(std::min(t1, tp) * BN, P);
+      const int o0 = std::max(t0 - tp, 0) * BN, o1 = std::min(std::max(t1 - tp, 0) * BN, it.nkeys);
+      per_head[it.c].push_back({it.g, it.row0, it.c, std::max(o1 - o0, 0), p0, i, p1 - p0, o0});
+    }
+  interleave_over_xcds(per_head, p.num_xcd, PAD_ITEM, p.range_items);
+}
+
 // Backward, dK/dV pass: one item per block of KEYS_PER_KEY_ITEM keys of a kv head.  A prefix
 // block streams the stacked rows of every rollout, all blocks of a kv head in the same order,
 // so (as in the prefix pass) one kv head's blocks are kept on a fixed subset of XCDs and share
@@ -488,12 +539,23 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
   const size_t rows = (size_t)p->T * desc->num_q_heads;
   const size_t o_bytes = align_up(rows * desc->head_dim * sizeof(float), 256);
   const size_t l_bytes = align_up(rows * sizeof(float), 256);
-  const size_t ks = (size_t)p->key_splits;  // the prefix pass leaves one partial per key split
+  const size_t ks = (size_t)p->key_splits;  // the prefix pass leaves one partial per key split, the suffix pass one more
+  try {
+    const size_t tiles = (size_t)p->tiles_prefix + p->tiles_suffix;
+    const size_t items = std::max({p->items[0].size(), p->items[1].size(), p->sweep_items.size()});
+    build_range_items(*p, l_bytes + desc->num_kv_heads * tiles * desc->head_dim * pa::KEYS_PER_TILE * 2 +
+                              items * pa::WAVES_PER_ITEM * sizeof(int32_t) + 4 * 256,
+                      o_bytes + l_bytes);
+  } catch (const std::bad_alloc&) {
+    delete p;
+    return PA_ERR_ALLOC;
+  }
+  const size_t slots = std::max(ks + 1, (size_t)p->key_ranges);
   p->off_o1 = 0;
   p->off_o2 = ks * o_bytes;
-  p->off_lse1 = (ks + 1) * o_bytes;
+  p->off_lse1 = slots * o_bytes;
   p->off_lse2 = p->off_lse1 + ks * l_bytes;
-  p->off_lse = p->off_lse2 + l_bytes;
+  p->off_lse = p->off_lse1 + slots * l_bytes;
   p->off_vtp = p->off_lse + l_bytes;
   size_t end = p->off_vtp;
   if (desc->dtype == PA_BF16) {  // transposed-V tile images, bf16 path only
@@ -502,7 +564,7 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
     end = p->off_vts + align_up((size_t)desc->num_kv_heads * p->tiles_suffix * image, 256);
     // one word per (work item, wavefront) of the longest work list: a pass's common kernel tells its careful
     // kernel which items to redo; the passes run one after the other and share the region
-    const size_t items = std::max({p->items[0].size(), p->items[1].size(), p->sweep_items.size()});
+    const size_t items = std::max({p->items[0].size(), p->items[1].size(), p->sweep_items.size(), p->range_items.size()});
     p->off_flags = end;
     end += align_up(items * pa::WAVES_PER_ITEM * sizeof(int32_t), 256);
   }
@@ -528,6 +590,11 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
         const size_t bytes = p->sweep_items.size() * sizeof(WorkItem);
         ok = hipMalloc((void**)&p->d_sweep_items, bytes) == hipSuccess &&
              hipMemcpy(p->d_sweep_items, p->sweep_items.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
+      }
+      if (ok && !p->range_items.empty()) {
+        const size_t bytes = p->range_items.size() * sizeof(WorkItem);
+        ok = hipMalloc((void**)&p->d_range_items, bytes) == hipSuccess &&
+             hipMemcpy(p->d_range_items, p->range_items.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
       }
       if (ok && !p->dq_items.empty()) {
         const size_t bytes = p->dq_items.size() * sizeof(WorkItem);
@@ -570,6 +637,7 @@ void prefix_attn_destroy(prefix_attn_plan_t* plan) {
   if (plan->d_key_sums) (void)hipFree(plan->d_key_sums);
   if (plan->d_dq_items) (void)hipFree(plan->d_dq_items);
   if (plan->d_sweep_items) (void)hipFree(plan->d_sweep_items);
+  if (plan->d_range_items) (void)hipFree(plan->d_range_items);
   delete plan;
 }
 

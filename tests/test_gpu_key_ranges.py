@@ -1,0 +1,53 @@
+"""Few rows: the keys [prefix | own keys] of every block of rows are cut into ranges, one work item each, and the n-way
+merge adds their partials.  Shapes where the cuts can go wrong: a ragged last prefix tile next to a cut, cuts inside
+the own keys (at or before the block's first position), blocks whose lengths differ, as many ranges as the prefix has
+tiles, whole calls with and without the caller's LSE and partials over a shard.  Against the fp64 oracle."""
+import numpy as np
+import pytest
+
+from oracle import cref
+from paper_2507_07966_amd import workloads as wl
+from tests.gpu_util import check, run_hip, to_device
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    (28, 4, 128, 1024, (128,)),            # 16 blocks
+    (28, 4, 128, 1000, (5, 3)),            # tiny rollouts, ragged last prefix tile
+    (4, 4, 128, 193, (900,)),              # own keys outweigh the prefix: cuts inside them
+    (1, 1, 64, 130, (2000,)),              # three prefix tiles
+    (16, 2, 128, 3000, (1500,)),           # 94 blocks: two ranges
+    (8, 2, 64, 5377, (40, 3, 300)),        # ragged everything
+]
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens", SHAPES)
+def test_key_ranges_whole_call_and_partial(Hq, Hkv, D, P, lens):
+    import torch
+    import paper_2507_07966_amd as pa
+    x = wl.make_custom("bf16", Hq, Hkv, D, P, lens, seed=P + Hq)
+    print(f"key ranges {Hq}/{Hkv}/{D} P={P} lens={lens}", flush=True)
+    ro, rl, _ = cref.prefix_shared_attention(x.q, x.k_prefix, x.v_prefix, x.k_suffix, x.v_suffix, x.suffix_lens, x.workload.scale)
+    out, lse = run_hip(x)
+    check(out, lse, ro, rl, f"key ranges {Hq}/{Hkv}/{D} P={P} {lens}")
+    dev = [to_device(x, n) for n in ("q", "k_prefix", "v_prefix", "k_suffix", "v_suffix")]
+    plan = pa.prefix_attn_plan(Hq, Hkv, D, P, list(lens), x.workload.scale, dtype="bf16", device=0)
+    T = sum(lens)
+    ws = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda").random_(0, 255)
+    o = torch.full((T, Hq, D), float("nan"), device="cuda")
+    l = torch.full((T, Hq), float("nan"), device="cuda")
+    pa.prefix_attn_forward_partial(plan, *dev, True, o, l, ws)
+    # static entry point: the merge writes the caller's [Hq, T] LSE itself, or none at all
+    so = torch.full((T, Hq, D), float("nan"), device="cuda", dtype=torch.bfloat16)
+    sl = torch.full((Hq, T), float("nan"), device="cuda")
+    if plan.workspace_bytes <= pa.STATIC_SCRATCH_BYTES:
+        pa.prefix_attn_forward_static(plan, *dev, so, sl)
+        torch.cuda.synchronize()
+        assert np.array_equal(so.double().cpu().numpy(), out) and np.array_equal(sl.double().cpu().numpy(), lse)
+        so.fill_(float("nan"))
+        pa.prefix_attn_forward_static(plan, *dev, so, None)
+        torch.cuda.synchronize()
+        assert np.array_equal(so.double().cpu().numpy(), out)
+    torch.cuda.synchronize()
+    plan.destroy()
+    check(o.double().cpu().numpy(), l.t().double().cpu().numpy(), ro, rl, f"key ranges, partial {Hq}/{Hkv}/{D} P={P} {lens}")
