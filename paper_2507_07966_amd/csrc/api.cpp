@@ -88,24 +88,7 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   a.scale = d.softmax_scale;
   a.part_rows = plan->T * d.num_q_heads;
   a.flags = reinterpret_cast<int32_t*>(ws + plan->off_flags);  // bf16 passes only
-  // Few rows: the passes leave one partial per key range in the workspace, and an n-way merge combines them.
   const int ks = plan->key_splits;
-  auto merge_ranges = [&](int n, void* dst, int32_t dst_dtype, float* lse_th, float* lse_ht) {
-    pa::MergeNArgs m{};
-    for (int i = 0; i < n; ++i) {
-      m.o[i] = o1 + (size_t)i * a.part_rows * d.head_dim;
-      m.lse[i] = lse1 + (size_t)i * a.part_rows;
-    }
-    m.out = dst;
-    m.lse_th_out = lse_th;
-    m.lse_out = lse_ht;
-    m.T = plan->T;
-    m.n = n;
-    m.Hq = d.num_q_heads;
-    m.D = d.head_dim;
-    m.dtype = dst_dtype;
-    return pa::launch_merge_n(m, hip_stream);
-  };
   hipStream_t hs = static_cast<hipStream_t>(hip_stream);
   if (ev && hipEventRecord(ev[0], hs) != hipSuccess) return PA_ERR_HIP;
   if (d.dtype == PA_BF16) {  // layout pre-pass: V^T tile images for the MFMA passes
@@ -143,10 +126,10 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
     if (ev && (hipEventRecord(ev[3], hs) != hipSuccess || hipEventRecord(ev[4], hs) != hipSuccess)) return PA_ERR_HIP;
     return lse_out ? prefix_attn_lse(plan, workspace, lse_out, hip_stream) : PA_OK;
   }
-  // few rows or a short prefix (the plan decides), own keys included: one sweep over [prefix | own keys] per
+  // a short prefix or blocks of rows that do not fill the chip (the plan decides), own keys included: one sweep over [prefix | own keys] per
   // block of rows does the work of the prefix pass, the suffix pass and the merge (the sweep list carries both
   // extents); it leaves the result of the call, or the fp32 partial of a shard that also holds the own keys
-  const bool ranges = with_suffix && !plan->range_items.empty();  // few rows: the same sweep, cut into key ranges
+  const bool ranges = with_suffix && !plan->range_items.empty();  // the same sweep, some blocks cut into key ranges
   const bool sweep = with_suffix && (ranges || !plan->sweep_items.empty());
   if (has_prefix && !sweep) {
     a.k = k_prefix;
@@ -164,7 +147,21 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   }
   if (ev && hipEventRecord(ev[2], hs) != hipSuccess) return PA_ERR_HIP;
   if (!with_suffix) {
-    if (ks > 1 && merge_ranges(ks, out, PA_F32, lse_partial, nullptr) != 0) return PA_ERR_HIP;
+    if (ks > 1) {  // few rows: the pass left one partial per key range in the workspace
+      pa::MergeNArgs m{};
+      for (int i = 0; i < ks; ++i) {
+        m.o[i] = o1 + (size_t)i * a.part_rows * d.head_dim;
+        m.lse[i] = lse1 + (size_t)i * a.part_rows;
+      }
+      m.out = out;
+      m.lse_th_out = lse_partial;
+      m.T = plan->T;
+      m.n = ks;
+      m.Hq = d.num_q_heads;
+      m.D = d.head_dim;
+      m.dtype = PA_F32;
+      if (pa::launch_merge_n(m, hip_stream) != 0) return PA_ERR_HIP;
+    }
     return PA_OK;
   }
   a.k = k_suffix;
@@ -177,9 +174,9 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   a.items = plan->d_items[1];
   a.num_items = (int64_t)plan->items[1].size();
   a.causal = true;
-  // bf16, whole call, keys not cut into ranges: the suffix pass combines its result with the prefix partial in its
-  // epilogue and writes `out` and the merged LSE itself (no merge launch, no suffix partial in memory)
-  const bool fused = mode == FULL && !ranges;
+  // bf16, whole call: the suffix pass combines its result with the prefix partial in its epilogue and writes `out` and
+  // the merged LSE itself (no merge launch, no suffix partial in memory)
+  const bool fused = mode == FULL;
   if (fused) {
     a.epilogue = (has_prefix && !sweep) ? 2 : 1;
     a.o1 = o1;
@@ -189,15 +186,18 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   }
   if (sweep) {
     a.sweep_prefix = true;
-    a.k_pre = k_prefix;
+    a.k_pre = has_prefix ? k_prefix : k_suffix;  // without a prefix no item reads it
     a.vt_pre = ws + plan->off_vtp;
     a.vt_pre_tiles_per_head = plan->tiles_prefix;
     a.items = ranges ? plan->d_range_items : plan->d_sweep_items;
     a.num_items = (int64_t)(ranges ? plan->range_items : plan->sweep_items).size();
     if (ranges) {
-      a.o_part = o1;
-      a.lse_part = lse1;
-    } else if (!fused) {  // a shard's partial: straight into the caller's buffers
+      a.ranges = true;
+      a.o_slots = o1;
+      a.lse_slots = reinterpret_cast<float*>(ws + plan->off_slot_lse);
+      a.lse_ht = lse_out;
+    }
+    if (!fused) {  // a shard's partial: straight into the caller's buffers
       a.o_part = static_cast<float*>(out);
       a.lse_part = lse_partial;
     }
@@ -205,16 +205,27 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   if (pa::launch_pass_bf16(a, hip_stream) != 0) return PA_ERR_HIP;
 
   if (ev && hipEventRecord(ev[3], hs) != hipSuccess) return PA_ERR_HIP;
-  if (fused || (sweep && !ranges)) {
-    if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;
-    return lse_out ? prefix_attn_lse(plan, workspace, lse_out, hip_stream) : PA_OK;
-  }
-  if (ranges) {
-    float* lse_th = mode == FULL ? (lse_out ? nullptr : lse) : lse_partial;
-    if (merge_ranges(plan->key_ranges, out, mode == FULL ? d.dtype : (int32_t)PA_F32, lse_th, lse_out) != 0)
-      return PA_ERR_HIP;
+  if (ranges) {  // the LSE goes where the whole items wrote theirs
+    pa::MergeNArgs m{};
+    m.sums = plan->d_range_sums;
+    m.num_sums = (int64_t)plan->range_sums.size();
+    m.o_slots = a.o_slots;
+    m.lse_slots = a.lse_slots;
+    m.out = out;
+    m.lse_out = lse_out;
+    m.lse_th_out = fused ? (lse_out ? nullptr : lse) : lse_partial;
+    m.T = plan->T;
+    m.Hq = d.num_q_heads;
+    m.D = d.head_dim;
+    m.group = plan->group;
+    m.dtype = fused ? d.dtype : (int32_t)PA_F32;
+    if (pa::launch_merge_n(m, hip_stream) != 0) return PA_ERR_HIP;
     if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;
     return PA_OK;
+  }
+  if (fused || sweep) {
+    if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;
+    return lse_out ? prefix_attn_lse(plan, workspace, lse_out, hip_stream) : PA_OK;
   }
   pa::MergeArgs m{};
   m.o1 = o1;

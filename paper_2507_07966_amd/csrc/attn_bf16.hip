@@ -115,10 +115,13 @@ __device__ inline float quad_sum(float x) { return pair_sum(x + __shfl_xor(x, 16
 // in bf16 with its LSE; 2 = combine with the prefix partial (o1, lse1) by log-sum-exp and write the result.
 // SWEEP (suffix pass with EPI 0 or 1): the item first sweeps the prefix keys [0, it.pkeys) (no mask) and then
 // the rollout's own keys, all in one online softmax, so its result is the result of the call (EPI 1) or the
-// fp32 partial over a prefix shard and the own keys together (EPI 0).  With EPI 0 an item may cover one range of that
-// key sequence only: prefix keys [it.key0, it.key0 + it.pkeys), then own keys [it.okey0, it.okey0 + it.nkeys), either of
-// them possibly none; the plan starts a range inside the own keys only where every row of the block sees its first key.
-template <int D, bool CAUSAL, int EPI, bool SWEEP, bool CAREFUL>
+// fp32 partial over a prefix shard and the own keys together (EPI 0).
+// RANGE (a sweep over the range list): an item may cover one range of that key sequence only: prefix keys [it.key0,
+// it.key0 + it.pkeys), then own keys [it.okey0, it.okey0 + it.nkeys), either of them possibly none; the plan starts a
+// range inside the own keys only where every row of the block sees its first key.  Such an item leaves an fp32 partial
+// in slot it.split (o_slots, lse_slots; 256 rows each); an item with split < 0 covers the whole sequence and writes the
+// result like any sweep.  lse_ht: if not null, where EPI 1 writes the LSE, in [Hq, T] order (the caller's array).
+template <int D, bool CAUSAL, int EPI, bool SWEEP, bool RANGE, bool CAREFUL>
 __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ vt,
     float* __restrict__ o_part, float* __restrict__ lse_part, const float* __restrict__ o1,
@@ -126,7 +129,9 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     const WorkItem* __restrict__ items,
     const int32_t* __restrict__ cu, const int32_t* __restrict__ vt_off, int64_t vt_tiles_per_head,
     const __bf16* __restrict__ k_pre, const __bf16* __restrict__ vt_pre, int64_t vt_pre_tiles_per_head,
-    int64_t part_rows, int Hq, int Hkv, int group, float scale, int32_t* __restrict__ flags) {
+    int64_t part_rows, int Hq, int Hkv, int group, float scale, int32_t* __restrict__ flags,
+    float* __restrict__ o_slots, float* __restrict__ lse_slots, float* __restrict__ lse_ht) {
+  static_assert(SWEEP || !RANGE, "ranges are ranges of a sweep");
   static_assert(EPI == 0 || CAUSAL, "only the suffix pass can finish the call");
   static_assert(!SWEEP || (CAUSAL && EPI != 2), "a sweep over prefix and own keys has nothing to combine with");
   using TL = Tile<D>;
@@ -154,7 +159,6 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
   const int nkeys = it.nkeys;
   const int64_t row_stride = (int64_t)Hkv * D;
   // prefix pass: the item sweeps prefix keys [key0, key0 + nkeys), key0 a multiple of the tile
-  constexpr bool RANGE = SWEEP && EPI == 0;
   const int okey0 = RANGE ? it.okey0 : 0;  // own keys and positions count from here
   const __bf16* kown = k + ((int64_t)(CAUSAL ? off_g + okey0 : it.key0) * Hkv + it.c) * D;
   const __bf16* vtbase = vt + ((int64_t)it.c * vt_tiles_per_head + (CAUSAL ? vt_off[it.g] + okey0 / BN : it.key0 / BN)) * (D * BN);
@@ -511,7 +515,16 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
   for (int nq = 0; nq < NQ; ++nq) {
     const float l = quad_sum(lsum[nq]);
     const int64_t row = out_row(nq);
-    if (EPI != 0) {
+    if (RANGE && it.split >= 0) {  // one range of the block's keys
+      if (row >= 0) {
+        const float inv = 1.0f / l;
+        const int64_t srow = (int64_t)it.split * ROWS_PER_ITEM + wave * ROWS_PER_WAVE + nq * 16 + l16;
+        float* op = o_slots + srow * D + 4 * g4;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f32x4*>(op + cb * 16) = O[cb][nq] * inv;
+        if (g4 == 0) lse_slots[srow] = mref[nq] * scale + __logf(l);
+      }
+    } else if (EPI != 0) {
       if (row >= 0) {
         float lse_f = mref[nq] * scale + __logf(l);
         float a1 = 0.f, a2 = 1.0f / l;
@@ -533,11 +546,18 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
           if (EPI == 2) w += a1 * *reinterpret_cast<const f32x4*>(p1 + cb * 16);
           *reinterpret_cast<bf16x4*>(op + cb * 16) = __builtin_convertvector(w, bf16x4);
         }
-        if (g4 == 0) lse_final[row] = lse_f;
+        if (g4 == 0) {
+          if (RANGE && lse_ht) {
+            const int64_t t = row / Hq;
+            lse_ht[(row - t * Hq) * (part_rows / Hq) + t] = lse_f;
+          } else {
+            lse_final[row] = lse_f;
+          }
+        }
       }
     } else if (row >= 0) {
       const float inv = 1.0f / l;
-      const int64_t prow = (CAUSAL && !RANGE ? 0 : (int64_t)it.split * part_rows) + row;  // key range s fills partial s
+      const int64_t prow = (CAUSAL ? 0 : (int64_t)it.split * part_rows) + row;  // key range s fills partial s
       float* op = o_part + prow * D + 4 * g4;
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f32x4*>(op + cb * 16) = O[cb][nq] * inv;
@@ -560,27 +580,30 @@ int launch_pass_bf16(const PassArgs& a, void* stream) {
   const __bf16* vtpre = static_cast<const __bf16*>(a.vt_pre);
 // Every pass is two launches over the same work list: the common kernel, whose step has no code for a moving
 // reference maximum, and the careful kernel, which redoes the items the first one gave up on (none, normally).
-#define PA_LAUNCH(DD, CC, EE, SS)                                                                                  \
+#define PA_LAUNCH(DD, CC, EE, SS, RR)                                                                                  \
   do {                                                                                                             \
-    pass_bf16_kernel<DD, CC, EE, SS, false><<<grid, NTHREADS, 0, s>>>(                                             \
+    pass_bf16_kernel<DD, CC, EE, SS, RR, false><<<grid, NTHREADS, 0, s>>>(                                             \
         q, k, vt, a.o_part, a.lse_part, a.o1, a.lse1, outf, a.lse_final, a.items, a.cu, a.vt_off,                  \
         a.vt_tiles_per_head, kpre, vtpre, a.vt_pre_tiles_per_head, a.part_rows, a.Hq, a.Hkv, a.group, a.scale,     \
-        a.flags);                                                                                                  \
-    pass_bf16_kernel<DD, CC, EE, SS, true><<<grid, NTHREADS, 0, s>>>(                                              \
+        a.flags, a.o_slots, a.lse_slots, a.lse_ht);                                                                \
+    pass_bf16_kernel<DD, CC, EE, SS, RR, true><<<grid, NTHREADS, 0, s>>>(                                              \
         q, k, vt, a.o_part, a.lse_part, a.o1, a.lse1, outf, a.lse_final, a.items, a.cu, a.vt_off,                  \
         a.vt_tiles_per_head, kpre, vtpre, a.vt_pre_tiles_per_head, a.part_rows, a.Hq, a.Hkv, a.group, a.scale,     \
-        a.flags);                                                                                                  \
+        a.flags, a.o_slots, a.lse_slots, a.lse_ht);                                                                \
   } while (0)
 #define PA_LAUNCH_D(DD)                                                                                            \
-  if (!a.causal) PA_LAUNCH(DD, false, 0, false);                                                                   \
-  else if (a.epilogue == 0 && a.sweep_prefix) PA_LAUNCH(DD, true, 0, true);                                        \
-  else if (a.epilogue == 0) PA_LAUNCH(DD, true, 0, false);                                                         \
-  else if (a.epilogue == 1 && a.sweep_prefix) PA_LAUNCH(DD, true, 1, true);                                        \
-  else if (a.epilogue == 1) PA_LAUNCH(DD, true, 1, false);                                                         \
-  else PA_LAUNCH(DD, true, 2, false)
+  if (!a.causal) PA_LAUNCH(DD, false, 0, false, false);                                                            \
+  else if (a.ranges && a.epilogue == 0) PA_LAUNCH(DD, true, 0, true, true);                                        \
+  else if (a.ranges) PA_LAUNCH(DD, true, 1, true, true);                                                           \
+  else if (a.epilogue == 0 && a.sweep_prefix) PA_LAUNCH(DD, true, 0, true, false);                                 \
+  else if (a.epilogue == 0) PA_LAUNCH(DD, true, 0, false, false);                                                  \
+  else if (a.epilogue == 1 && a.sweep_prefix) PA_LAUNCH(DD, true, 1, true, false);                                 \
+  else if (a.epilogue == 1) PA_LAUNCH(DD, true, 1, false, false);                                                  \
+  else PA_LAUNCH(DD, true, 2, false, false)
   if (!a.flags) return 1;
   if (a.epilogue < 0 || a.epilogue > 2 || (!a.causal && a.epilogue != 0)) return 1;
   if (a.sweep_prefix && (!a.causal || a.epilogue == 2 || !a.k_pre || !a.vt_pre)) return 1;
+  if (a.ranges && (!a.sweep_prefix || !a.o_slots || !a.lse_slots)) return 1;
   if (a.D == 128) {
     PA_LAUNCH_D(128);
   } else {

@@ -34,7 +34,8 @@ struct WorkItem {
   int32_t c;      // kv head
   int32_t nkeys;  // keys swept: the item's share of P in the prefix pass, causal extent in the suffix pass
   int32_t key0;   // prefix pass: first prefix key swept (a multiple of KEYS_PER_TILE); suffix pass: 0
-  int32_t split;  // prefix pass: which key split this is (its partial lands in slot `split`); else 0
+  int32_t split;  // prefix pass: which key split this is (its partial lands in slot `split`); range list: the
+                  //   slot of the item's partial, or -1: the item sweeps all keys of its block and writes the result; else 0
   int32_t pkeys;  // backward dQ list, sweep and range lists: prefix keys [key0, key0 + pkeys) swept before the nkeys own keys
   int32_t okey0;  // range list only: the own keys swept are [okey0, okey0 + nkeys), okey0 a multiple of KEYS_PER_TILE
 };
@@ -65,6 +66,14 @@ struct KeySum {
   int32_t key0;   // first key of the block: prefix index or packed token index
   int32_t c;      // kv head
   int32_t nkeys;
+  int32_t slot0, nslots;
+};
+
+// A block of rows whose keys were cut into ranges: its result is the log-sum-exp sum of slots [slot0, slot0 + nslots).
+struct RangeSum {
+  int32_t off_g;          // first packed token of the block's rollout
+  int32_t row0, c;        // the block, as in WorkItem
+  int32_t nrows;          // its rows (<= ROWS_PER_ITEM)
   int32_t slot0, nslots;
 };
 
@@ -103,6 +112,12 @@ struct PassArgs {
   int32_t num_cu;              // fp32 only: compute units of the plan's device
   const void* vt_pre;          // prefix V tile images
   int64_t vt_pre_tiles_per_head;
+  // bf16 sweep over the range list: 256-row fp32 partial slots of the items that cover a part of their block's keys, and
+  // where whole items write their LSE in [Hq, T] order (null: `lse_final`)
+  bool ranges;
+  float* o_slots;              // [slots][ROWS_PER_ITEM][D]
+  float* lse_slots;            // [slots][ROWS_PER_ITEM]
+  float* lse_ht;
   // bf16: one word per (work item, wavefront), written by the common kernel of a pass and read by its careful
   // kernel (see attn_bf16.hip); [num_items][WAVES_PER_ITEM]
   int32_t* flags;
@@ -148,6 +163,13 @@ struct MergeNArgs {
   float* lse_th_out;  // [T, Hq] or null
   int64_t T;
   int32_t n, Hq, D, dtype;
+  // Instead of n partials of all rows: the slots that the range list's items leave, one entry of `sums` per cut block of
+  // rows (sums null: the partials above).
+  const RangeSum* sums;
+  int64_t num_sums;
+  const float* o_slots;    // [slots][ROWS_PER_ITEM][D]
+  const float* lse_slots;  // [slots][ROWS_PER_ITEM]
+  int32_t group;
 };
 int launch_merge_n(const MergeNArgs& a, void* stream);
 int launch_lse_export(const float* lse_th, float* lse_ht, int64_t T, int32_t Hq, void* stream);
@@ -166,8 +188,9 @@ struct prefix_attn_plan {
   int32_t num_cu = pa::NUM_CU;         // compute units the schedule is sized for
   int32_t num_xcd = pa::NUM_XCD;       // XCDs the lists are interleaved over (1: no interleaving)
   std::vector<pa::WorkItem> items[2];  // 0 = prefix pass, 1 = suffix pass
-  // device-side copies (null for a host-only plan)
-  int32_t* d_cu = nullptr;             // cu followed by vt_off, one allocation
+  // device-side copies (null for a host-only plan), all of them inside the one allocation `d_lists`
+  void* d_lists = nullptr;
+  int32_t* d_cu = nullptr;
   int32_t* d_vt_off = nullptr;
   int32_t tiles_prefix = 0, tiles_suffix = 0;
   int32_t key_splits = 1;              // prefix-pass items per block of rows (> 1: few rows, the prefix keys are split)
@@ -179,13 +202,15 @@ struct prefix_attn_plan {
   // interleaved over the XCDs by kv head like the prefix pass, longest first inside a kv head
   std::vector<pa::WorkItem> sweep_items;
   pa::WorkItem* d_sweep_items = nullptr;
-  // Few rows: the keys [prefix | own keys] of every block of rows cut into `key_ranges` ranges, one sweep item each;
-  // range i leaves its fp32 partial in slot i and the n-way merge adds them.  Empty unless the plan uses it.
+  // The sweep with the keys [prefix | own keys] of some or all blocks of rows cut into ranges, for calls whose whole
+  // blocks would leave CUs idle; the cut blocks' partials are merged afterwards.  Empty unless the plan uses it.
   std::vector<pa::WorkItem> range_items;
   pa::WorkItem* d_range_items = nullptr;
-  int32_t key_ranges = 1;
+  std::vector<pa::RangeSum> range_sums;
+  pa::RangeSum* d_range_sums = nullptr;
+  int32_t range_slots = 0;
   // workspace layout, byte offsets
-  size_t off_o1 = 0, off_o2 = 0, off_lse1 = 0, off_lse2 = 0, off_lse = 0, off_vtp = 0, off_vts = 0, off_flags = 0,
+  size_t off_o1 = 0, off_o2 = 0, off_lse1 = 0, off_lse2 = 0, off_lse = 0, off_slot_lse = 0, off_vtp = 0, off_vts = 0, off_flags = 0,
          ws_bytes = 0;
   // backward: dK/dV work lists (0 = prefix key blocks, 1 = suffix key blocks) and workspace layout
   std::vector<pa::KeyItem> key_items[2];

@@ -170,55 +170,150 @@ void build_sweep_items(prefix_attn_plan_t& p) {
   interleave_over_xcds(per_head, p.num_xcd, PAD_ITEM, p.sweep_items);
 }
 
-// Forward, few rows (bf16, with a prefix): the keys [prefix | own keys] of every block of rows are cut into n ranges, so
-// one launch of n x blocks sweep items fills the chip and one merge finishes the call (prefix pass, suffix pass, their
-// careful kernels and the merge are five launches).  n minimises the time of one round plus the partials, from measured
-// rates: 1.56 us per key tile at D = 128, 5 tiles' time for an item's start and end, fp32 partials written and read at
-// 4 TB/s, 5 us for the merge launch.  128 tokens, 28 / 4 heads of 128, 1,024 prefix keys (6 ranges):
-// passes 37 -> 18 us, the whole call with its LSE 45.3 -> 29.3 us.
+// Into how many ranges of key tiles to cut each block of rows so that one workgroup per CU ends early.  Whole blocks take
+// ceil(blocks / CUs) rounds, and the last one may hold a single block; a call of few rows has fewer blocks than CUs.
+struct CutCosts {
+  double tile_us;    // one key tile of a block
+  double item_tiles; // an item's start and end, in tiles
+  double slot_us;    // a fp32 partial result written and read
+  double launch_us;  // the launch that adds them
+};
+// `tiles`: key tiles of the blocks of one kv head, longest first; `most`: ranges they can be cut into; `cus`: CUs that run
+// them; `whole_us`: what the uncut blocks cost (< 0: as estimated here).  Candidates are compared by list scheduling: up to
+// one block per CU, no range longer than 1 / n of the longest block; more blocks, those beyond full rounds cut into n ranges
+// each, so that they are spread over all CUs.  Empty: leave the blocks whole.
+std::vector<int> cut_blocks(const std::vector<int>& tiles, const std::vector<int>& most, int cus, const CutCosts& c,
+                            double whole_us, size_t max_slots) {
+  const int N = (int)tiles.size(), rest = N % cus;
+  std::vector<double> cost;
+  std::vector<int> pieces(N, 1), chosen;
+  auto estimate = [&]() {
+    size_t slots = 0, items = 0;
+    cost.clear();
+    for (int b = 0; b < N; ++b) {
+      if (pieces[b] > 1) slots += pieces[b];
+      items += pieces[b];
+    }
+    if (slots > 0 && items > (size_t)N + 2 * cus) return 1e30;  // two ranges a CU even out what there is to even out
+    for (int b = 0; b < N; ++b) {
+      for (int i = 0; i < pieces[b]; ++i) cost.push_back((tiles[b] + pieces[b] - 1) / pieces[b] + c.item_tiles);
+    }
+    if (slots > max_slots) return 1e30;
+    std::sort(cost.begin(), cost.end(), std::greater<double>());
+    double end = cost.empty() ? 0.0 : cost.front();
+    if ((int)cost.size() > cus) {
+      std::vector<double> heap(cus, 0.0);  // when each CU is free, the earliest first
+      for (double t : cost) {
+        std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
+        heap.back() += t;
+        end = std::max(end, heap.back());
+        std::push_heap(heap.begin(), heap.end(), std::greater<double>());
+      }
+    }
+    return c.tile_us * end + (slots ? (double)slots * c.slot_us + c.launch_us : 0.0);
+  };
+  double sum = 0.0;
+  for (int t : tiles) sum += t + c.item_tiles;
+  double best_us = whole_us >= 0.0 ? whole_us : 0.95 * estimate();
+  if (c.tile_us * sum / cus + c.launch_us >= best_us) return chosen;  // nothing to gain
+  auto consider = [&]() {
+    const double us = estimate();
+    if (us < best_us) {
+      best_us = us;
+      chosen = pieces;
+    }
+  };
+  for (int n = 2; n <= PA_MAX_PARTIALS; n += N <= cus ? 1 : n) {
+    const int limit = (tiles.front() + n - 1) / n;
+    for (int b = 0; b < N; ++b)
+      pieces[b] = std::min(most[b], N <= cus ? (tiles[b] + limit - 1) / limit : b < rest ? n : 1);
+    consider();
+  }
+  return chosen;
+}
+
+// CUs that run the blocks of one kv head when the lists are laid out by interleave_over_xcds, and whether they are.
+bool heads_apart(const prefix_attn_plan_t& p) { return p.desc.num_kv_heads <= p.num_xcd && p.num_xcd % p.desc.num_kv_heads == 0; }
+
+pa::RangeSum range_sum(const prefix_attn_plan_t& p, const WorkItem& it, int slot0, int n) {
+  return {p.cu[it.g], it.row0, it.c, std::min(pa::ROWS_PER_ITEM, p.lens[it.g] * p.group - it.row0), slot0, n};
+}
+
+// Cuts the blocks of items[1] into `pieces` ranges of their tile sequence [prefix | own keys] (of the first kv head's
+// blocks, or of all: see heads_apart), numbers the slots of the cut ones and lays the items out: longest first, ranges of
+// equal length in the order of their keys, so that neighbours share tiles in L2.  With `diagonal` no range starts inside
+// the own keys after the position of the block's first row.
+void lay_out_ranges(const prefix_attn_plan_t& p, const std::vector<int>& pieces, bool diagonal, std::vector<WorkItem>& out,
+                    std::vector<pa::RangeSum>& sums, int32_t& slots) {
+  const int P = (int)p.desc.prefix_len, tp = p.tiles_prefix, BN = pa::KEYS_PER_TILE, Hkv = p.desc.num_kv_heads;
+  const bool apart = heads_apart(p);
+  struct Range { int tiles; WorkItem it; };
+  std::vector<std::vector<Range>> per_head(apart ? Hkv : 1);
+  std::vector<size_t> next(Hkv, 0);  // the blocks of every kv head stand in the same order
+  for (const WorkItem& it : p.items[1]) {
+    const int n = pieces[next[apart ? it.c : 0]++];
+    const int total = tp + (it.nkeys + BN - 1) / BN, legal = diagonal ? tp + it.row0 / p.group / BN : total;
+    auto cut = [&](int i) {  // first tile of range i
+      return i == n ? total : std::max(i, std::min((int)((int64_t)total * i / n), legal - (n - 1 - i)));
+    };
+    if (n > 1)
+      sums.push_back(range_sum(p, it, slots, n));
+    for (int i = 0; i < n; ++i) {
+      const int t0 = cut(i), t1 = cut(i + 1);
+      const int p0 = std::min(std::min(t0, tp) * BN, P), p1 = std::min(std::min(t1, tp) * BN, P);
+      const int o0 = std::max(t0 - tp, 0) * BN, o1 = std::min(std::max(t1 - tp, 0) * BN, it.nkeys);
+      const int slot = n > 1 ? slots++ : -1;
+      per_head[apart ? it.c : 0].push_back(
+          {t1 - t0, {it.g, it.row0, it.c, std::max(o1 - o0, 0), p1 > p0 ? p0 : 0, slot, p1 - p0, o0}});
+    }
+  }
+  std::vector<std::vector<WorkItem>> lists(per_head.size());
+  for (size_t c = 0; c < per_head.size(); ++c) {
+    std::stable_sort(per_head[c].begin(), per_head[c].end(), [](const Range& a, const Range& b) {
+      return a.tiles != b.tiles ? a.tiles > b.tiles : a.it.key0 < b.it.key0;
+    });
+    for (const Range& r : per_head[c]) lists[c].push_back(r.it);
+  }
+  interleave_over_xcds(lists, p.num_xcd, PAD_ITEM, out);
+}
+
+// Forward, the sweep over [prefix | own keys] with some blocks of rows cut into ranges (cut_blocks), one launch and one
+// merge of the cut blocks.  Costs measured at D = 128 (64): 1.56 (0.9) us per key tile, 5 tiles' time for an item's start
+// and end, partials written and read at 4 TB/s, 5 us for the merge launch.  Up to two rounds of whole blocks: beyond
+// that the last round is at most a third of the call, its CUs run at a higher clock and the others' spread fills it.
+// 128 tokens, 28 / 4 heads of 128, 1,024 prefix keys (16 blocks, 6 ranges each): passes 37 -> 18 us, the whole call
+// with its LSE 45.3 -> 29.3 us.  88 blocks of a kv head for its 128 CUs (5,377
+// prefix keys, 5 rollouts of 37 ... 1,901 tokens, 14 / 2 heads of 64), two ranges each: pass 114 -> 84 us, merge 8 us.
 // Cuts inside the own keys stay at or before the position of the block's first row: every row then sees the first key
 // of every range, so no partial is empty.
 void build_range_items(prefix_attn_plan_t& p, size_t fixed_bytes, size_t slot_bytes) {
   p.range_items.clear();
-  p.key_ranges = 1;
-  const std::vector<WorkItem>& blocks = p.items[1];
-  const int P = (int)p.desc.prefix_len, tp = p.tiles_prefix, BN = pa::KEYS_PER_TILE;
-  if (p.desc.dtype != PA_BF16 || P == 0 || blocks.size() * 2 > (size_t)p.num_cu) return;
-  auto cut = [&](const WorkItem& it, int n, int i) {  // first tile of range i of the block's tile sequence
-    const int total = tp + (it.nkeys + BN - 1) / BN, legal = tp + it.row0 / p.group / BN;
-    return i == n ? total : std::max(i, std::min((int)((int64_t)total * i / n), legal - (n - 1 - i)));
-  };
-  const double tile_us = p.desc.head_dim == 128 ? 1.56 : 0.9;
-  const double slot_us = (double)p.T * p.desc.num_q_heads * p.desc.head_dim * 4 * 2 / 4e6;
-  auto cost = [&](int n) {
-    int longest = 0;
-    for (const WorkItem& it : blocks)
-      for (int i = 0; i < n; ++i) longest = std::max(longest, cut(it, n, i + 1) - cut(it, n, i));
-    return tile_us * (longest + 5) + (n > 1 ? n * slot_us + 5.0 : 0.0);
-  };
-  // what fitted the library's own workspace keeps fitting
-  const size_t had = fixed_bytes + (size_t)(p.key_splits + 1) * slot_bytes;
-  int best = 1;
-  double best_us = p.key_splits > 1 ? 1e30 : 0.95 * cost(1);
-  for (int n = 2; n <= PA_MAX_PARTIALS && n * blocks.size() <= (size_t)p.num_cu && n - 1 <= tp; ++n) {
-    const size_t flags = align_up((n * blocks.size() + 64) * pa::WAVES_PER_ITEM * sizeof(int32_t), 256);
-    if (n > p.key_splits + 1 && had <= PA_STATIC_SCRATCH_BYTES && fixed_bytes + n * slot_bytes + flags > PA_STATIC_SCRATCH_BYTES) break;
-    if (const double us = cost(n); us < best_us) {
-      best_us = us;
-      best = n;
-    }
+  p.range_sums.clear();
+  p.range_slots = 0;
+  const int tp = p.tiles_prefix, BN = pa::KEYS_PER_TILE, Hkv = p.desc.num_kv_heads;
+  if (p.desc.dtype != PA_BF16 || p.items[1].size() > 2 * (size_t)p.num_cu) return;
+  const bool apart = heads_apart(p);
+  std::vector<WorkItem> blocks;  // of the first kv head, or of all
+  for (const WorkItem& it : p.items[1])
+    if (!apart || it.c == 0) blocks.push_back(it);
+  const int heads = apart ? Hkv : 1;
+  std::vector<int> tiles, most;
+  for (const WorkItem& it : blocks) {
+    tiles.push_back(tp + (it.nkeys + BN - 1) / BN);
+    most.push_back(std::min(PA_MAX_PARTIALS, std::min(tiles.back(), tp + it.row0 / p.group / BN + 1)));
   }
-  if (best == 1) return;
-  p.key_ranges = best;
-  std::vector<std::vector<WorkItem>> per_head(p.desc.num_kv_heads);
-  for (int i = 0; i < best; ++i)
-    for (const WorkItem& it : blocks) {
-      const int t0 = cut(it, best, i), t1 = cut(it, best, i + 1);
-      const int p0 = std::min(std::min(t0, tp) * BN, P), p1 = std::min(std::min(t1, tp) * BN, P);
-      const int o0 = std::max(t0 - tp, 0) * BN, o1 = std::min(std::max(t1 - tp, 0) * BN, it.nkeys);
-      per_head[it.c].push_back({it.g, it.row0, it.c, std::max(o1 - o0, 0), p0, i, p1 - p0, o0});
-    }
-  interleave_over_xcds(per_head, p.num_xcd, PAD_ITEM, p.range_items);
+  const size_t bytes_per_slot = (size_t)pa::ROWS_PER_ITEM * (p.desc.head_dim + 1) * sizeof(float);
+  const CutCosts costs{p.desc.head_dim == 128 ? 1.56 : 0.9, 5.0, heads * (double)bytes_per_slot * 2 / 4e6, 5.0};
+  // what fitted the library's own workspace keeps fitting
+  const size_t had = (size_t)(p.key_splits + 1) * slot_bytes;
+  const size_t room = fixed_bytes + had <= PA_STATIC_SCRATCH_BYTES ? PA_STATIC_SCRATCH_BYTES - fixed_bytes : ~(size_t)0;
+  const size_t flags = 2 * (blocks.size() + p.num_xcd) * heads * pa::WAVES_PER_ITEM * sizeof(int32_t);
+  size_t max_slots = room == ~(size_t)0 ? room : room <= flags ? 0 : (room - flags) / (bytes_per_slot + 256) / heads;
+  const std::vector<int> pieces =
+      cut_blocks(tiles, most, p.num_cu / heads, costs, p.key_splits > 1 ? 1e30 : -1.0, max_slots);
+  if (pieces.empty()) return;
+
+  lay_out_ranges(p, pieces, true, p.range_items, p.range_sums, p.range_slots);
 }
 
 // Backward, dK/dV pass: one item per block of KEYS_PER_KEY_ITEM keys of a kv head.  A prefix
@@ -550,12 +645,14 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
     delete p;
     return PA_ERR_ALLOC;
   }
-  const size_t slots = std::max(ks + 1, (size_t)p->key_ranges);
   p->off_o1 = 0;
   p->off_o2 = ks * o_bytes;
-  p->off_lse1 = slots * o_bytes;
+  p->off_lse1 = (ks + 1) * o_bytes;
   p->off_lse2 = p->off_lse1 + ks * l_bytes;
-  p->off_lse = p->off_lse1 + slots * l_bytes;
+  // the range list's slots lie over the partials of the passes, which a call that uses it does not run
+  const size_t slot_rows = (size_t)p->range_slots * pa::ROWS_PER_ITEM;
+  p->off_slot_lse = align_up(slot_rows * desc->head_dim * sizeof(float), 256);
+  p->off_lse = std::max(p->off_lse1 + (ks + 1) * l_bytes, p->off_slot_lse + align_up(slot_rows * sizeof(float), 256));
   p->off_vtp = p->off_lse + l_bytes;
   size_t end = p->off_vtp;
   if (desc->dtype == PA_BF16) {  // transposed-V tile images, bf16 path only
@@ -575,41 +672,36 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
     int prev = 0;
     bool ok = hipGetDevice(&prev) == hipSuccess && hipSetDevice(desc->device) == hipSuccess;
     if (ok) {
-      const size_t n = p->cu.size();
-      ok = hipMalloc((void**)&p->d_cu, 2 * n * sizeof(int32_t)) == hipSuccess &&
-           hipMemcpy(p->d_cu, p->cu.data(), n * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess &&
-           hipMemcpy(p->d_cu + n, p->vt_off.data(), n * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
-      p->d_vt_off = p->d_cu + n;
-      for (int s = 0; ok && s < 2; ++s) {
-        if (p->items[s].empty() || (s == 0 && desc->dtype == PA_F32)) continue;  // fp32: no separate prefix pass
-        const size_t bytes = p->items[s].size() * sizeof(WorkItem);
-        ok = hipMalloc((void**)&p->d_items[s], bytes) == hipSuccess &&
-             hipMemcpy(p->d_items[s], p->items[s].data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
-      }
-      if (ok && !p->sweep_items.empty()) {
-        const size_t bytes = p->sweep_items.size() * sizeof(WorkItem);
-        ok = hipMalloc((void**)&p->d_sweep_items, bytes) == hipSuccess &&
-             hipMemcpy(p->d_sweep_items, p->sweep_items.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
-      }
-      if (ok && !p->range_items.empty()) {
-        const size_t bytes = p->range_items.size() * sizeof(WorkItem);
-        ok = hipMalloc((void**)&p->d_range_items, bytes) == hipSuccess &&
-             hipMemcpy(p->d_range_items, p->range_items.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
-      }
-      if (ok && !p->dq_items.empty()) {
-        const size_t bytes = p->dq_items.size() * sizeof(WorkItem);
-        ok = hipMalloc((void**)&p->d_dq_items, bytes) == hipSuccess &&
-             hipMemcpy(p->d_dq_items, p->dq_items.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
-      }
-      if (ok && !p->key_launch.empty()) {
-        const size_t bytes = p->key_launch.size() * sizeof(pa::KeyItem);
-        ok = hipMalloc((void**)&p->d_key_launch, bytes) == hipSuccess &&
-             hipMemcpy(p->d_key_launch, p->key_launch.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
-      }
-      if (ok && !p->key_sums.empty()) {
-        const size_t bytes = p->key_sums.size() * sizeof(pa::KeySum);
-        ok = hipMalloc((void**)&p->d_key_sums, bytes) == hipSuccess &&
-             hipMemcpy(p->d_key_sums, p->key_sums.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
+      // every list of the plan in one allocation and one copy (seven of each were a third of a plan's time)
+      std::vector<std::pair<void**, std::pair<const void*, size_t>>> lists;
+      size_t total = 0;
+      auto add = [&](auto** dst, const auto& v) {
+        if (v.empty()) return;
+        lists.push_back({(void**)dst, {v.data(), v.size() * sizeof(v[0])}});
+        total += align_up(v.size() * sizeof(v[0]), 256);
+      };
+      try {
+        add(&p->d_cu, p->cu);
+        add(&p->d_vt_off, p->vt_off);
+        if (desc->dtype != PA_F32) add(&p->d_items[0], p->items[0]);  // fp32: no separate prefix pass
+        add(&p->d_items[1], p->items[1]);
+        add(&p->d_sweep_items, p->sweep_items);
+        add(&p->d_range_items, p->range_items);
+        add(&p->d_range_sums, p->range_sums);
+        add(&p->d_dq_items, p->dq_items);
+        add(&p->d_key_launch, p->key_launch);
+        add(&p->d_key_sums, p->key_sums);
+        std::vector<char> host(total);
+        ok = hipMalloc(&p->d_lists, total) == hipSuccess;
+        size_t at = 0;
+        for (const auto& [dst, src] : lists) {
+          std::copy_n(static_cast<const char*>(src.first), src.second, host.data() + at);
+          *dst = static_cast<char*>(p->d_lists) + at;
+          at += align_up(src.second, 256);
+        }
+        ok = ok && hipMemcpy(p->d_lists, host.data(), total, hipMemcpyHostToDevice) == hipSuccess;
+      } catch (const std::bad_alloc&) {
+        ok = false;
       }
       // set-up for prefix_attn_forward_static: look its workspace up now, with the plan's device current,
       // so that the call itself only reads a table
@@ -630,14 +722,7 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
 
 void prefix_attn_destroy(prefix_attn_plan_t* plan) {
   if (!plan) return;
-  if (plan->d_cu) (void)hipFree(plan->d_cu);
-  for (int s = 0; s < 2; ++s)
-    if (plan->d_items[s]) (void)hipFree(plan->d_items[s]);
-  if (plan->d_key_launch) (void)hipFree(plan->d_key_launch);
-  if (plan->d_key_sums) (void)hipFree(plan->d_key_sums);
-  if (plan->d_dq_items) (void)hipFree(plan->d_dq_items);
-  if (plan->d_sweep_items) (void)hipFree(plan->d_sweep_items);
-  if (plan->d_range_items) (void)hipFree(plan->d_range_items);
+  if (plan->d_lists) (void)hipFree(plan->d_lists);
   delete plan;
 }
 

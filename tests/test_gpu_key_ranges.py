@@ -1,5 +1,5 @@
-"""Few rows: the keys [prefix | own keys] of every block of rows are cut into ranges, one work item each, and the n-way
-merge adds their partials.  Shapes where the cuts can go wrong: a ragged last prefix tile next to a cut, cuts inside
+"""The keys [prefix | own keys] of some or all blocks of rows are cut into ranges, one work item each, and a merge adds
+their partials.  Shapes where the cuts can go wrong: a ragged last prefix tile next to a cut, cuts inside
 the own keys (at or before the block's first position), blocks whose lengths differ, as many ranges as the prefix has
 tiles, whole calls with and without the caller's LSE and partials over a shard.  Against the fp64 oracle."""
 import numpy as np
@@ -18,6 +18,11 @@ SHAPES = [
     (1, 1, 64, 130, (2000,)),              # three prefix tiles
     (16, 2, 128, 3000, (1500,)),           # 94 blocks: two ranges
     (8, 2, 64, 5377, (40, 3, 300)),        # ragged everything
+    (28, 4, 128, 1000, (2100, 400)),       # 69 blocks of a kv head for 64 CUs: five cut, the others whole in the same launch
+    (6, 3, 64, 700, (9000, 77)),           # kv heads that share no layout over the XCDs, 213 blocks
+    (14, 2, 64, 5377, (1500, 37, 1200, 1901, 60)),   # 130 blocks of a kv head for 128 CUs
+    (4, 4, 128, 0, (3000,)),               # own keys only: cut up to the diagonal, the first blocks whole
+    (8, 8, 64, 0, (1, 63, 64, 65, 1025)),
 ]
 
 
