@@ -141,10 +141,10 @@ int enqueue_backward(const prefix_attn_plan_t* plan, const BackwardArgs& x, void
   a.Mpad = plan->Mpad;
   a.dq = x.dq;
   a.dq_partial = reinterpret_cast<float*>(ws + plan->boff_dqpart);
-  a.key_splits = plan->key_splits;
-  a.T = plan->T;
-  a.items = plan->d_dq_items;
-  a.num_items = (int64_t)plan->dq_items.size();
+  a.sums = plan->d_dq_sums;
+  a.num_sums = (int64_t)plan->dq_sums.size();
+  a.items = plan->d_dq_launch;
+  a.num_items = (int64_t)plan->dq_launch.size();
   a.cu = plan->d_cu;
   a.vt_off = plan->d_vt_off;
   a.P = d.prefix_len;

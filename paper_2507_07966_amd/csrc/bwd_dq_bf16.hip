@@ -24,15 +24,16 @@ using namespace mt;
 constexpr int DQ_WAVES = ROWS_PER_ITEM / 32;
 constexpr int DQ_THREADS = DQ_WAVES * 64;
 
-// PARTIAL (calls with few rows): the item sweeps only the prefix keys [key0, key0 + pkeys) (split 0:
-// also the own keys) and leaves an unscaled fp32 partial dQ in slot `split`; a reduction adds the slots.
+// PARTIAL (calls some or all of whose blocks are cut into key ranges): an item sweeps the prefix keys [key0, key0 + pkeys)
+// and the own keys [okey0, okey0 + nkeys); with split >= 0 it leaves an unscaled fp32 partial dQ in slot `split` (256 rows
+// each) and a reduction adds the slots of a block, with split < 0 it covers its block's keys and writes dQ.
 template <int D, bool PARTIAL>
 __global__ __launch_bounds__(DQ_THREADS, 512 / DQ_THREADS) void bwd_dq_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ d_out, const __bf16* __restrict__ k_prefix,
     const __bf16* __restrict__ v_prefix, const __bf16* __restrict__ k_suffix, const __bf16* __restrict__ v_suffix,
     const __bf16* __restrict__ kt_prefix, const __bf16* __restrict__ kt_suffix, const float* __restrict__ lse2s,
     const float* __restrict__ deltas, int64_t Mpad, __bf16* __restrict__ dq, float* __restrict__ dq_partial,
-    int64_t part_rows, const WorkItem* __restrict__ items, const int32_t* __restrict__ cu,
+    const WorkItem* __restrict__ items, const int32_t* __restrict__ cu,
     const int32_t* __restrict__ vt_off, int tiles_prefix, int tiles_suffix, int Hq, int Hkv, int group, float scale) {
   using G = Geo<D>;
   constexpr int KK = G::KK, DB = G::DB;
@@ -47,7 +48,8 @@ __global__ __launch_bounds__(DQ_THREADS, 512 / DQ_THREADS) void bwd_dq_kernel(
   const int off_g = cu[it.g];
   const int S_g = cu[it.g + 1] - off_g;
   const int nrows = S_g * group;
-  const int nkeys = it.nkeys;  // causal extent of the item's last row (0: this split sweeps prefix keys only)
+  const int nkeys = it.nkeys;  // causal extent of the item's last row, from okey0 on (0: prefix keys only)
+  const int okey0 = PARTIAL ? it.okey0 : 0;  // own keys and positions count from here (a multiple of the tile)
   const int P = it.pkeys;      // prefix keys this item sweeps, starting at it.key0 (a multiple of the tile)
   const int64_t row_stride = (int64_t)Hkv * D;
 
@@ -60,7 +62,7 @@ __global__ __launch_bounds__(DQ_THREADS, 512 / DQ_THREADS) void bwd_dq_kernel(
     const int m = it.row0 + wave * 32 + l32;
     if (m < nrows) {
       const int i = m / group, hh = m - i * group;
-      pos = i;
+      pos = i - okey0;  // negative: the query sees no own key of this range
       orow = (int64_t)(off_g + i) * Hq + it.c * group + hh;
       const __bf16* qp = q + orow * D + 8 * hf;
       const __bf16* dp = d_out + orow * D + 8 * hf;
@@ -93,14 +95,14 @@ __global__ __launch_bounds__(DQ_THREADS, 512 / DQ_THREADS) void bwd_dq_kernel(
   // tiles 0 .. tp-1 cover the prefix, tp .. tp+ts-1 the rollout's own keys
   const int tp = (P + TILE - 1) / TILE;
   const int ts = (nkeys + TILE - 1) / TILE;
-  const int first_pos = it.row0 / group;  // smallest causal bound among the item's rows
+  const int first_pos = it.row0 / group - okey0;  // smallest causal bound among the item's rows
   const int ntiles = tp + ts;
   const __bf16* kpb = k_prefix + ((int64_t)it.key0 * Hkv + it.c) * D;
   const __bf16* vpb = v_prefix + ((int64_t)it.key0 * Hkv + it.c) * D;
-  const __bf16* ksb = k_suffix + ((int64_t)off_g * Hkv + it.c) * D;
-  const __bf16* vsb = v_suffix + ((int64_t)off_g * Hkv + it.c) * D;
+  const __bf16* ksb = k_suffix + ((int64_t)(off_g + okey0) * Hkv + it.c) * D;
+  const __bf16* vsb = v_suffix + ((int64_t)(off_g + okey0) * Hkv + it.c) * D;
   const __bf16* ktpb = kt_prefix + ((int64_t)it.c * tiles_prefix + it.key0 / TILE) * (D * TILE);
-  const __bf16* ktsb = kt_suffix + ((int64_t)it.c * tiles_suffix + vt_off[it.g]) * (D * TILE);
+  const __bf16* ktsb = kt_suffix + ((int64_t)it.c * tiles_suffix + vt_off[it.g] + okey0 / TILE) * (D * TILE);
 
   // The loads of a tile are issued in three pieces so they can be spread over the MFMA stream.
   RowTileOffsets<D, DQ_WAVES> lane_off;
@@ -231,9 +233,9 @@ __global__ __launch_bounds__(DQ_THREADS, 512 / DQ_THREADS) void bwd_dq_kernel(
   }
 
   // ---- epilogue: register i of block db is channel db*32 + 8*(i/4) + 4*hf + i%4 of this lane's query
-  if (PARTIAL) {
+  if (PARTIAL && it.split >= 0) {
     if (orow >= 0) {
-      float* op = dq_partial + ((int64_t)it.split * part_rows + orow) * D + 4 * hf;
+      float* op = dq_partial + ((int64_t)it.split * ROWS_PER_ITEM + wave * 32 + l32) * D + 4 * hf;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -255,16 +257,22 @@ __global__ __launch_bounds__(DQ_THREADS, 512 / DQ_THREADS) void bwd_dq_kernel(
   }
 }
 
-// dq = scale * (sum of the key splits' fp32 partials), 4 channels per thread, fixed order.
+// dq = scale * (sum of a cut block's fp32 partials), 4 channels of a row per thread, fixed order; 256 / (D / 4) rows of a
+// block per workgroup.
+template <int D>
 __global__ __launch_bounds__(256) void bwd_dq_reduce_kernel(const float* __restrict__ partial, __bf16* __restrict__ dq,
-                                                            int64_t n4, int splits, float scale) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < splits; ++s) acc += *reinterpret_cast<const f32x4*>(partial + ((int64_t)s * n4 + i) * 4);
-    acc *= scale;
-    *reinterpret_cast<bf16x4*>(dq + i * 4) = __builtin_convertvector(acc, bf16x4);
-  }
+                                                            const RangeSum* __restrict__ sums, int Hq, int group, float scale) {
+  constexpr int PER_ROW = D / 4, ROWS = 256 / PER_ROW, PARTS = ROWS_PER_ITEM / ROWS;
+  const RangeSum b = sums[blockIdx.x / PARTS];
+  const int r = (blockIdx.x % PARTS) * ROWS + threadIdx.x / PER_ROW, ch = threadIdx.x % PER_ROW;
+  if (r >= b.nrows) return;
+  const float* p = partial + ((int64_t)b.slot0 * ROWS_PER_ITEM + r) * D + ch * 4;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int i = 0; i < b.nslots; ++i) acc += *reinterpret_cast<const f32x4*>(p + (int64_t)i * (ROWS_PER_ITEM * D));
+  acc *= scale;
+  const int m = b.row0 + r, t = b.off_g + m / group, h = b.c * group + m % group;
+  *reinterpret_cast<bf16x4*>(dq + ((int64_t)t * Hq + h) * D + ch * 4) = __builtin_convertvector(acc, bf16x4);
 }
 
 }  // namespace
@@ -274,12 +282,11 @@ int launch_bwd_dq_bf16(const BwdDqArgs& a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   auto b = [](const void* p) { return static_cast<const __bf16*>(p); };
   const unsigned grid = (unsigned)a.num_items;
-  const bool part = a.key_splits > 1;
-  const int64_t part_rows = a.T * a.Hq;
+  const bool part = a.num_sums > 0;
 #define PA_LAUNCH(DD, PP)                                                                                          \
   bwd_dq_kernel<DD, PP><<<grid, DQ_THREADS, 0, s>>>(                                                               \
       b(a.q), b(a.d_out), b(a.k_prefix), b(a.v_prefix), b(a.k_suffix), b(a.v_suffix), b(a.kt_prefix), b(a.kt_suffix), \
-      a.lse2s, a.deltas, a.Mpad, static_cast<__bf16*>(a.dq), a.dq_partial, part_rows, a.items, a.cu, a.vt_off,     \
+      a.lse2s, a.deltas, a.Mpad, static_cast<__bf16*>(a.dq), a.dq_partial, a.items, a.cu, a.vt_off,                \
       a.tiles_prefix, a.tiles_suffix, a.Hq, a.Hkv, a.group, a.scale)
   if (a.D == 128) {
     if (part) PA_LAUNCH(128, true); else PA_LAUNCH(128, false);
@@ -289,10 +296,10 @@ int launch_bwd_dq_bf16(const BwdDqArgs& a, void* stream) {
 #undef PA_LAUNCH
   if (hipGetLastError() != hipSuccess) return 1;
   if (part) {
-    const int64_t n4 = part_rows * a.D / 4;
-    const int64_t want = (n4 + 255) / 256;
-    bwd_dq_reduce_kernel<<<(unsigned)(want < 8192 ? want : 8192), 256, 0, s>>>(
-        a.dq_partial, static_cast<__bf16*>(a.dq), n4, a.key_splits, a.scale);
+    const unsigned blocks = (unsigned)(a.num_sums * (ROWS_PER_ITEM * a.D / 4 / 256));
+    __bf16* dq = static_cast<__bf16*>(a.dq);
+    if (a.D == 128) bwd_dq_reduce_kernel<128><<<blocks, 256, 0, s>>>(a.dq_partial, dq, a.sums, a.Hq, a.group, a.scale);
+    else bwd_dq_reduce_kernel<64><<<blocks, 256, 0, s>>>(a.dq_partial, dq, a.sums, a.Hq, a.group, a.scale);
   }
   return (int)hipGetLastError();
 }

@@ -34,10 +34,10 @@ struct WorkItem {
   int32_t c;      // kv head
   int32_t nkeys;  // keys swept: the item's share of P in the prefix pass, causal extent in the suffix pass
   int32_t key0;   // prefix pass: first prefix key swept (a multiple of KEYS_PER_TILE); suffix pass: 0
-  int32_t split;  // prefix pass: which key split this is (its partial lands in slot `split`); range list: the
+  int32_t split;  // prefix pass: which key split this is (its partial lands in slot `split`); range and dQ launch lists: the
                   //   slot of the item's partial, or -1: the item sweeps all keys of its block and writes the result; else 0
   int32_t pkeys;  // backward dQ list, sweep and range lists: prefix keys [key0, key0 + pkeys) swept before the nkeys own keys
-  int32_t okey0;  // range list only: the own keys swept are [okey0, okey0 + nkeys), okey0 a multiple of KEYS_PER_TILE
+  int32_t okey0;  // range and dQ launch lists: the own keys swept are [okey0, okey0 + nkeys), okey0 a multiple of KEYS_PER_TILE
 };
 
 // Backward tile geometry.  The key-stationary pass (dK/dV) gives a workgroup KEYS_PER_KEY_ITEM
@@ -197,7 +197,13 @@ struct prefix_attn_plan {
   pa::WorkItem* d_items[2] = {nullptr, nullptr};
   // backward dQ pass: the suffix list, each block of rows once per key split (split 0 also sweeps the own keys)
   std::vector<pa::WorkItem> dq_items;
-  pa::WorkItem* d_dq_items = nullptr;
+  // what its launch runs: those items, or the blocks cut into key ranges where whole ones would leave CUs idle; partials
+  // of cut blocks are added afterwards
+  std::vector<pa::WorkItem> dq_launch;
+  pa::WorkItem* d_dq_launch = nullptr;
+  std::vector<pa::RangeSum> dq_sums;
+  pa::RangeSum* d_dq_sums = nullptr;
+  int32_t dq_slots = 0;
   // forward sweep over [prefix | own keys] (whole bf16 calls with an unsplit prefix): every block of rows once,
   // interleaved over the XCDs by kv head like the prefix pass, longest first inside a kv head
   std::vector<pa::WorkItem> sweep_items;

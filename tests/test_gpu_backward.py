@@ -207,3 +207,18 @@ def test_backward_own_key_blocks_cut_into_row_ranges_full_tensor(Hq, Hkv, D, P, 
     # few-keys term of few_keys_floor bounds it, as for the one-key prefix above
     check_grads(run_hip_backward(x, do, bits), oracle_backward(x, do), "bf16", f"own blocks cut {Hq}/{Hkv}/{D} P={P} {lens}",
                 few_keys_floor(x, do))
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens", [
+    (28, 4, 128, 200, (2100, 400)),                # 69 blocks of a kv head for 64 CUs: five cut, the others whole
+    (14, 2, 64, 1377, (1500, 37, 1200, 60)),       # fewer blocks than CUs: all cut, at and inside the own keys
+    (6, 3, 64, 70, (6100,)),                       # kv heads that share no layout over the XCDs
+    (8, 2, 64, 0, (4200, 1)),                      # own keys only: ranges that some or all rows of a wavefront do not see
+])
+def test_backward_dq_blocks_cut_into_key_ranges_full_tensor(Hq, Hkv, D, P, lens):
+    """dQ of blocks of rows that do not fill the chip in whole rounds: ranges of [prefix | own keys] with fp32 partials,
+    beside whole blocks, against the fp64 oracle."""
+    x = wl.make_custom("bf16", Hq, Hkv, D, P, lens, seed=37)
+    do, bits = wl.make_d_out(x)
+    check_grads(run_hip_backward(x, do, bits), oracle_backward(x, do), "bf16", f"dq ranges {Hq}/{Hkv}/{D} P={P} {lens}",
+                few_keys_floor(x, do))
