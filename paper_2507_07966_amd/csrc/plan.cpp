@@ -344,7 +344,8 @@ void build_range_items(prefix_attn_plan_t& p, size_t fixed_bytes, size_t slot_by
   // what fitted the library's own workspace keeps fitting
   const size_t had = (size_t)(p.key_splits + 1) * slot_bytes;
   const size_t room = fixed_bytes + had <= PA_STATIC_SCRATCH_BYTES ? PA_STATIC_SCRATCH_BYTES - fixed_bytes : ~(size_t)0;
-  const size_t flags = 2 * (blocks.size() + p.num_xcd) * heads * pa::WAVES_PER_ITEM * sizeof(int32_t);
+  // flags of at most two ranges a CU beside the blocks, and the pads of the layout over the XCDs
+  const size_t flags = (blocks.size() * heads + 2 * (size_t)p.num_cu + p.num_xcd) * pa::WAVES_PER_ITEM * sizeof(int32_t) + 4 * 256;
   size_t max_slots = room == ~(size_t)0 ? room : room <= flags ? 0 : (room - flags) / (bytes_per_slot + 256) / heads;
   const std::vector<int> pieces =
       cut_blocks(tiles, most, p.num_cu / heads, costs, p.key_splits > 1 ? 1e30 : -1.0, max_slots);
