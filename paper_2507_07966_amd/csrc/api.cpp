@@ -88,7 +88,28 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   a.scale = d.softmax_scale;
   a.part_rows = plan->T * d.num_q_heads;
   a.flags = reinterpret_cast<int32_t*>(ws + plan->off_flags);  // bf16 passes only
+  // With key splits the prefix pass leaves `ks` partials in the workspace; an n-way merge combines them (and the
+  // suffix partial, where the call covers the own keys).
   const int ks = plan->key_splits;
+  auto merge_splits = [&](bool suffix_too, void* dst, int32_t dst_dtype, float* lse_th) {
+    pa::MergeNArgs m{};
+    for (int i = 0; i < ks; ++i) {
+      m.o[i] = o1 + (size_t)i * a.part_rows * d.head_dim;
+      m.lse[i] = lse1 + (size_t)i * a.part_rows;
+    }
+    if (suffix_too) {
+      m.o[ks] = o2;
+      m.lse[ks] = lse2;
+    }
+    m.out = dst;
+    m.lse_th_out = lse_th;
+    m.T = plan->T;
+    m.n = ks + (suffix_too ? 1 : 0);
+    m.Hq = d.num_q_heads;
+    m.D = d.head_dim;
+    m.dtype = dst_dtype;
+    return pa::launch_merge_n(m, hip_stream);
+  };
   hipStream_t hs = static_cast<hipStream_t>(hip_stream);
   if (ev && hipEventRecord(ev[0], hs) != hipSuccess) return PA_ERR_HIP;
   if (d.dtype == PA_BF16) {  // layout pre-pass: V^T tile images for the MFMA passes
@@ -147,21 +168,7 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   }
   if (ev && hipEventRecord(ev[2], hs) != hipSuccess) return PA_ERR_HIP;
   if (!with_suffix) {
-    if (ks > 1) {  // few rows: the pass left one partial per key range in the workspace
-      pa::MergeNArgs m{};
-      for (int i = 0; i < ks; ++i) {
-        m.o[i] = o1 + (size_t)i * a.part_rows * d.head_dim;
-        m.lse[i] = lse1 + (size_t)i * a.part_rows;
-      }
-      m.out = out;
-      m.lse_th_out = lse_partial;
-      m.T = plan->T;
-      m.n = ks;
-      m.Hq = d.num_q_heads;
-      m.D = d.head_dim;
-      m.dtype = PA_F32;
-      if (pa::launch_merge_n(m, hip_stream) != 0) return PA_ERR_HIP;
-    }
+    if (ks > 1 && merge_splits(false, out, PA_F32, lse_partial) != 0) return PA_ERR_HIP;
     return PA_OK;
   }
   a.k = k_suffix;
@@ -174,9 +181,9 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   a.items = plan->d_items[1];
   a.num_items = (int64_t)plan->items[1].size();
   a.causal = true;
-  // bf16, whole call: the suffix pass combines its result with the prefix partial in its epilogue and writes `out` and
-  // the merged LSE itself (no merge launch, no suffix partial in memory)
-  const bool fused = mode == FULL;
+  // bf16, whole call, unsplit prefix or a sweep: the suffix pass combines its result with the prefix partial (if there is
+  // one) in its epilogue and writes `out` and the merged LSE itself (no merge launch, no suffix partial in memory)
+  const bool fused = mode == FULL && (ks == 1 || sweep);
   if (fused) {
     a.epilogue = (has_prefix && !sweep) ? 2 : 1;
     a.o1 = o1;
@@ -224,6 +231,12 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
     return PA_OK;
   }
   if (fused || sweep) {
+    if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;
+    return lse_out ? prefix_attn_lse(plan, workspace, lse_out, hip_stream) : PA_OK;
+  }
+  if (ks > 1) {  // a split prefix whose blocks the plan could not cut into ranges: the partials of every range
+    if (merge_splits(true, out, mode == FULL ? d.dtype : (int32_t)PA_F32, mode == FULL ? lse : lse_partial) != 0)
+      return PA_ERR_HIP;
     if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;
     return lse_out ? prefix_attn_lse(plan, workspace, lse_out, hip_stream) : PA_OK;
   }

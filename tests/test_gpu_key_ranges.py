@@ -56,3 +56,36 @@ def test_key_ranges_whole_call_and_partial(Hq, Hkv, D, P, lens):
     torch.cuda.synchronize()
     plan.destroy()
     check(o.double().cpu().numpy(), l.t().double().cpu().numpy(), ro, rl, f"key ranges, partial {Hq}/{Hkv}/{D} P={P} {lens}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens", [
+    (28, 4, 128, 50000, (8,) * 16), (28, 4, 128, 60000, (1,) * 8), (28, 4, 128, 40000, (1,) * 32),
+    (4, 4, 128, 29000, (300,) * 16), (16, 8, 128, 26000, (32,) * 8), (16, 8, 64, 49000, (64,) * 16),
+    (16, 8, 128, 15360, (32,) * 16), (16, 8, 128, 20000, (32,) * 16), (16, 8, 128, 25344, (32,) * 16),
+])
+def test_split_prefix_near_the_size_of_the_static_workspace(Hq, Hkv, D, P, lens):
+    """Few short blocks of rows over a long prefix: the values' layout copy leaves little of the library's own workspace,
+    so the blocks may not be cut into ranges; the prefix pass's partials of every key range then have to be merged."""
+    import torch
+    import paper_2507_07966_amd as pa
+    x = wl.make_custom("bf16", Hq, Hkv, D, P, lens, seed=P + Hq)
+    label = f"split prefix {Hq}/{Hkv}/{D} P={P} {len(lens)} x {lens[0]}"
+    print(label, flush=True)
+    rows = np.arange(0, sum(lens), max(1, Hq * P * sum(lens) // 100_000_000))   # what the oracle does in about a second
+    ro, rl, _ = cref.prefix_shared_attention(x.q, x.k_prefix, x.v_prefix, x.k_suffix, x.v_suffix, x.suffix_lens,
+                                             x.workload.scale, rows=rows)
+    out, lse, plan, dev, ws, _, _ = run_hip(x, return_plan=True)
+    check(out[rows], lse[:, rows], ro, rl, label)
+    assert len({int(k) for k in plan.items(0)[:, 4]}) > 1 and plan.workspace_bytes <= pa.STATIC_SCRATCH_BYTES
+    T = sum(lens)
+    names = ("q", "k_prefix", "v_prefix", "k_suffix", "v_suffix")
+    so = torch.full((T, Hq, D), float("nan"), device="cuda", dtype=torch.bfloat16)
+    sl = torch.full((Hq, T), float("nan"), device="cuda")
+    pa.prefix_attn_forward_static(plan, *[dev[n] for n in names], so, sl)
+    o = torch.full((T, Hq, D), float("nan"), device="cuda")
+    l = torch.full((T, Hq), float("nan"), device="cuda")
+    pa.prefix_attn_forward_partial(plan, *[dev[n] for n in names], True, o, l, ws)
+    torch.cuda.synchronize()
+    plan.destroy()
+    assert np.array_equal(so.double().cpu().numpy(), out) and np.array_equal(sl.double().cpu().numpy(), lse)
+    check(o[rows].double().cpu().numpy(), l[rows].t().double().cpu().numpy(), ro, rl, f"{label}, partial")
