@@ -20,6 +20,8 @@
 // 62 us (67 TFLOP/s); 28 / 4 heads, 9,600 tokens over 4,000 + 600 keys 102 TFLOP/s, two thirds of the fp32 matrix rate.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace pa {
@@ -42,8 +44,8 @@ template <int D, int NQ>
 __global__ __launch_bounds__(F32_WAVES * 64, 2) void pass_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k_pre, const float* __restrict__ v_pre,
     const float* __restrict__ k_own, const float* __restrict__ v_own, float* __restrict__ out, float* __restrict__ lse,
-    const WorkItem* __restrict__ items, const int32_t* __restrict__ cu, int P, bool with_own, int Hq, int Hkv, int group,
-    float scale) {
+    const WorkItem* __restrict__ items, int64_t num_items, const int32_t* __restrict__ cu, int P, bool with_own, int Hq,
+    int Hkv, int group, float scale) {
   constexpr int ROWS = 16 * NQ, SUB = ROWS_PER_ITEM / ROWS;  // rows of a workgroup; workgroups per work item
   constexpr int KB = NQ == 1 ? 2 : 1;                        // 16-key blocks per step of a wavefront
   constexpr int KS = D / 16, VB = D / 64;                    // 16-byte loads per key: along its row / per key of a step
@@ -51,8 +53,10 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void pass_f32_kernel(
   __shared__ __attribute__((aligned(16))) float o_s[F32_WAVES][ROWS][LD];
   __shared__ float m_s[F32_WAVES][ROWS], l_s[F32_WAVES][ROWS];
 
-  const WorkItem it = items[blockIdx.x / SUB];
-  const int row0 = it.row0 + (int)(blockIdx.x % SUB) * ROWS;
+  const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (block >= num_items * SUB) return;
+  const WorkItem it = items[block / SUB];
+  const int row0 = it.row0 + (int)(block % SUB) * ROWS;
   const int off_g = cu[it.g];
   const int nrows = (cu[it.g + 1] - off_g) * group;
   if (row0 >= nrows) return;
@@ -223,10 +227,13 @@ int launch_pass_f32(const PassArgs& a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   auto f = [](const void* p) { return static_cast<const float*>(p); };
   const int P = a.k_pre ? (int)a.P : 0;
+  auto grid_of = [](int64_t blocks) {
+    return dim3((unsigned)std::min(blocks, MAX_GRID_X), (unsigned)((blocks + MAX_GRID_X - 1) / MAX_GRID_X));
+  };
 #define PA_LAUNCH(DD, NQ)                                                                                          \
-  pass_f32_kernel<DD, NQ><<<(unsigned)(a.num_items * (ROWS_PER_ITEM / (16 * NQ))), F32_WAVES * 64, 0, s>>>(        \
-      f(a.q), f(a.k_pre), f(a.v_pre), f(a.k), f(a.v), a.o_part, a.lse_part, a.items, a.cu, P, a.causal, a.Hq,      \
-      a.Hkv, a.group, a.scale)
+  pass_f32_kernel<DD, NQ><<<grid_of(a.num_items * (ROWS_PER_ITEM / (16 * NQ))), F32_WAVES * 64, 0, s>>>(           \
+      f(a.q), f(a.k_pre), f(a.v_pre), f(a.k), f(a.v), a.o_part, a.lse_part, a.items, a.num_items, a.cu, P, a.causal, \
+      a.Hq, a.Hkv, a.group, a.scale)
   // One workgroup runs per CU at a time, so a launch takes ceil(workgroups / CUs) rounds, and a round of 32-row
   // workgroups takes 1.5 to 1.65 times one of 16-row workgroups (measured, 8 / 2 heads of 128 channels, 1,000 prefix
   // keys, us with 16 / 32 rows: 370 blocks of 16 rows 72 / 62, 600 blocks 106 / 104, 1,024 blocks 152 / 121, 2,400 blocks

@@ -27,6 +27,10 @@ constexpr int NUM_CU = 256;
 // slower at 3,600; break-even near 1,000).
 constexpr int SWEEP_MAX_PREFIX_TILES = 1024;
 
+// A launch dimension holds fewer than 2^32 work-items (a larger one wraps around in silence), so kernels that may need
+// more workgroups than this lay them out over grid rows of MAX_GRID_X and number them blockIdx.y * gridDim.x + blockIdx.x.
+constexpr int64_t MAX_GRID_X = (int64_t)1 << 22;
+
 // One entry of a pass's work list.  g < 0 marks a padding entry (the workgroup exits).
 struct WorkItem {
   int32_t g;      // rollout

@@ -27,8 +27,10 @@
 // logp = z_target - LSE.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <utility>
 
+#include "common.h"
 #include "logprob.h"
 #include "mfma_tiles.h"
 
@@ -248,7 +250,7 @@ __global__ __launch_bounds__(FIN_TOKENS * FIN_GROUPS) void logprob_finalize_kern
     float* __restrict__ logprob, float* __restrict__ lse_out, int64_t N, int nparts, int V) {
   __shared__ float2 sm[FIN_GROUPS][FIN_TOKENS];
   const int tl = threadIdx.x % FIN_TOKENS, grp = threadIdx.x / FIN_TOKENS;
-  const int64_t tok = (int64_t)blockIdx.x * FIN_TOKENS + tl;
+  const int64_t tok = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * FIN_TOKENS + tl;
   float m = -INFINITY, l = 0.f;
   if (tok < N)
     for (int p0 = grp; p0 < nparts; p0 += FIN_GROUPS * FIN_DEPTH) {
@@ -342,7 +344,9 @@ int launch_logprob(const LogprobArgs& a, void* stream) {
                : nb == 6 ? launch_tiles<6>(a, TV, s)
                : nb == 4 ? launch_tiles<4>(a, TV, s) : launch_tiles<2>(a, TV, s);
   if (st != 0) return 1;
-  logprob_finalize_kernel<<<(unsigned)((a.N + FIN_TOKENS - 1) / FIN_TOKENS), FIN_TOKENS * FIN_GROUPS, 0, s>>>(
+  const int64_t blocks = (a.N + FIN_TOKENS - 1) / FIN_TOKENS;
+  const dim3 grid((unsigned)std::min(blocks, MAX_GRID_X), (unsigned)((blocks + MAX_GRID_X - 1) / MAX_GRID_X));
+  logprob_finalize_kernel<<<grid, FIN_TOKENS * FIN_GROUPS, 0, s>>>(
       reinterpret_cast<const float2*>(a.partials), a.target_logit, a.targets, a.logprob, a.lse, a.N, TV, a.V);
   return (int)hipGetLastError();
 }

@@ -50,3 +50,46 @@ def test_f32_bitwise_reproducible():
     for n in a:
         if isinstance(a[n], np.ndarray):
             assert np.array_equal(a[n], b[n]), n
+
+
+def test_f32_a_million_one_token_rollouts():
+    """More blocks of rows than one launch dimension holds work-items for (2^32): forward and backward against a
+    float64 evaluation of the four keys that each row sees.  Tolerance on the largest error, relative to each tensor's
+    root mean square: 1e-4.  A dot product of 64 N(0, 1) channels has partial sums of at most 40 (five sigma), so it is
+    off by up to sqrt(64) 2^-24 40 = 2e-5, dS (a difference of two) by 4e-5 p; times a key element of up to 5.7 and
+    the scale 1/8 that is 2.7e-5 on dQ, whose elements are 0.4 in size: 7e-5 of it.  The output, dV and dK are products
+    of fewer rounded terms; a prefix gradient is a sum of 10^6 terms of mixed sign, added in fp32 by eight
+    wavefronts: 3 * 10^4 additions each of a sum of up to 400 terms' size, off by sqrt(3e4) 2^-24 = 1e-5 of it."""
+    import torch
+    import paper_2507_07966_amd as pa
+    G, P, D = 1_100_000, 3, 64
+    print(f"fp32 {G} one-token rollouts", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    q, ks, vs, do = (rand(G, 1, D) for _ in range(4))
+    kp, vp = rand(P, 1, D), rand(P, 1, D)
+    plan = pa.prefix_attn_plan(1, 1, D, P, np.ones(G, dtype=np.int32), D ** -0.5, dtype="f32", device=0)
+    ws = torch.empty(max(plan.workspace_bytes, plan.backward_workspace_bytes), dtype=torch.uint8, device="cuda")
+    out, lse = torch.full_like(q, float("nan")), torch.full((1, G), float("nan"), device="cuda")
+    pa.prefix_attn_forward(plan, q, kp, vp, ks, vs, out, ws)
+    pa.prefix_attn_lse(plan, ws, lse)
+    torch.cuda.synchronize()
+    grads = [torch.full_like(t, float("nan")) for t in (q, kp, vp, ks, vs)]
+    pa.prefix_attn_backward(plan, q, kp, vp, ks, vs, out, do, lse, *grads, ws)
+    torch.cuda.synchronize()
+    plan.destroy()
+    q6, ks6, vs6, do6, kp6, vp6 = (t[:, 0].double() for t in (q, ks, vs, do, kp, vp))
+    s = torch.cat([(q6[:, None, :] * kp6[None]).sum(-1), (q6 * ks6).sum(-1, keepdim=True)], 1) * D ** -0.5
+    l6 = torch.logsumexp(s, 1)
+    p = torch.exp(s - l6[:, None])
+    o6 = sum(p[:, j:j + 1] * vp6[j] for j in range(P)) + p[:, P:] * vs6
+    dw = torch.cat([(do6[:, None, :] * vp6[None]).sum(-1), (do6 * vs6).sum(-1, keepdim=True)], 1)
+    ds = p * (dw - (do6 * o6).sum(-1, keepdim=True)) * D ** -0.5
+    want = [sum(ds[:, j:j + 1] * kp6[j] for j in range(P)) + ds[:, P:] * ks6,
+            torch.stack([(ds[:, j:j + 1] * q6).sum(0) for j in range(P)]),
+            torch.stack([(p[:, j:j + 1] * do6).sum(0) for j in range(P)]), ds[:, P:] * q6, p[:, P:] * do6]
+    assert (lse[0].double() - l6).abs().max() < 1e-5
+    for name, got, ref in zip(("out", "dq", "dk_prefix", "dv_prefix", "dk_suffix", "dv_suffix"), [out] + grads, [o6] + want):
+        err = (got[:, 0].double() - ref).abs().max() / ref.square().mean().sqrt()
+        print(f"{name}: {float(err):.2e}", flush=True)
+        assert err < 1e-4, name

@@ -128,3 +128,25 @@ def test_group_advantages():
     want = np.stack([ref.group_advantages(g) for g in r])
     assert np.abs(got - want).max() < 1e-5
     assert (got[3] == 0).all()
+
+
+def test_logprob_more_tokens_than_one_launch_dimension_holds():
+    """2^28 tokens and 17 more (a small head): the finalize kernel uses 16 threads a token, so its work-items pass 2^32.
+    All tokens but the last are zero vectors, whose log-probability is -ln V."""
+    import torch
+    import paper_2507_07966_amd as pa
+    N, d, V = (1 << 28) + 17, 64, 10
+    x = custom(40, d, V, seed=9)
+    print(f"logprob N={N}", flush=True)
+    hidden = torch.zeros((N, d), dtype=torch.bfloat16, device="cuda")
+    hidden[-40:] = torch.from_numpy(x.bits["hidden"].view(np.int16)).cuda().view(torch.bfloat16)
+    head = torch.from_numpy(x.bits["lm_head"].view(np.int16)).cuda().view(torch.bfloat16)
+    targets = torch.zeros(N, dtype=torch.int32, device="cuda")
+    targets[-40:] = torch.from_numpy(x.targets).cuda()
+    lp, lse = (torch.full((N,), float("nan"), device="cuda") for _ in range(2))
+    ws = torch.empty(pa.token_logprob_workspace(N, d, V), dtype=torch.uint8, device="cuda")
+    pa.token_logprob_forward(hidden, head, targets, 1.0, lp, lse, ws)
+    torch.cuda.synchronize()
+    rp, rl = ref.token_logprobs(x.hidden, x.lm_head, x.targets, 1.0)
+    assert np.abs(lp[-40:].cpu().numpy() - rp).max() <= TOL and np.abs(lse[-40:].cpu().numpy() - rl).max() <= TOL
+    assert (lp[:-40] + np.log(V)).abs().max() <= TOL and (lse[:-40] - np.log(V)).abs().max() <= TOL
