@@ -136,12 +136,13 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
     a.k_pre = has_prefix ? k_prefix : nullptr;
     a.v_pre = v_prefix;
     a.P = d.prefix_len;
-    a.num_cu = plan->num_cu;
     a.causal = with_suffix;
     a.o_part = static_cast<float*>(out);
     a.lse_part = mode == FULL ? lse : lse_partial;
-    a.items = plan->d_items[1];
-    a.num_items = (int64_t)plan->items[1].size();
+    a.items = plan->d_f32_blocks[0];
+    a.num_items = (int64_t)plan->f32_blocks[0].size();
+    a.block_rows = plan->f32_rows;
+    a.block_waves = plan->f32_waves;
     if (ev && hipEventRecord(ev[2], hs) != hipSuccess) return PA_ERR_HIP;
     if (pa::launch_pass_f32(a, hip_stream) != 0) return PA_ERR_HIP;
     if (ev && (hipEventRecord(ev[3], hs) != hipSuccess || hipEventRecord(ev[4], hs) != hipSuccess)) return PA_ERR_HIP;

@@ -14,7 +14,8 @@
 //     operand of O^T += V^T P^T when step j contracts over keys 4 g4 + j: P needs no data movement at all.
 //   - V^T operands: a lane loads 4 consecutive channels of key 4 g4 + j, one for each of four MFMAs; row r of
 //     accumulator (B, e) is channel 64 B + 4 r + e.
-// NQ = 2 reads every key once for 32 rows (half the L2 traffic), NQ = 1 has twice the workgroups: see launch_pass_f32.
+// NQ = 2 reads every key once for 32 rows (half the L2 traffic), NQ = 1 has twice the workgroups; with few keys a block
+// has one wavefront (WAVES = 1) and takes 16 keys at a time: build_f32_blocks in plan.cpp chooses.
 // Measured against one wavefront per row with scalar products (what this replaced): one head of 64 channels, 192 rows,
 // 256 + 96 keys 2,223 -> 22 us for the call; 8 / 2 heads of 128 channels, 740 tokens over 1,000 + 70..300 keys 13.3 ms ->
 // 62 us (67 TFLOP/s); 28 / 4 heads, 9,600 tokens over 4,000 + 600 keys 102 TFLOP/s, two thirds of the fp32 matrix rate.
@@ -29,8 +30,6 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int F32_WAVES = 8;
-
 __device__ inline float quad_max(float x) {  // over the lanes l16, l16 + 16, l16 + 32, l16 + 48 of a query column
   x = fmaxf(x, __shfl_xor(x, 16));
   return fmaxf(x, __shfl_xor(x, 32));
@@ -40,26 +39,24 @@ __device__ inline float quad_sum(float x) {
   return x + __shfl_xor(x, 32);
 }
 
-template <int D, int NQ>
-__global__ __launch_bounds__(F32_WAVES * 64, 2) void pass_f32_kernel(
+template <int D, int NQ, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 2) void pass_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k_pre, const float* __restrict__ v_pre,
     const float* __restrict__ k_own, const float* __restrict__ v_own, float* __restrict__ out, float* __restrict__ lse,
     const WorkItem* __restrict__ items, int64_t num_items, const int32_t* __restrict__ cu, int P, bool with_own, int Hq,
     int Hkv, int group, float scale) {
-  constexpr int ROWS = 16 * NQ, SUB = ROWS_PER_ITEM / ROWS;  // rows of a workgroup; workgroups per work item
-  constexpr int KB = NQ == 1 ? 2 : 1;                        // 16-key blocks per step of a wavefront
+  constexpr int ROWS = 16 * NQ;                              // rows of a workgroup
+  constexpr int KB = NQ == 1 && WAVES > 1 ? 2 : 1;              // 16-key blocks per step of a wavefront
   constexpr int KS = D / 16, VB = D / 64;                    // 16-byte loads per key: along its row / per key of a step
   constexpr int LD = D + 4;                                  // padded row of the combine buffer (bank spread)
-  __shared__ __attribute__((aligned(16))) float o_s[F32_WAVES][ROWS][LD];
-  __shared__ float m_s[F32_WAVES][ROWS], l_s[F32_WAVES][ROWS];
+  __shared__ __attribute__((aligned(16))) float o_s[WAVES][ROWS][LD];
+  __shared__ float m_s[WAVES][ROWS], l_s[WAVES][ROWS];
 
   const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  if (block >= num_items * SUB) return;
-  const WorkItem it = items[block / SUB];
-  const int row0 = it.row0 + (int)(block % SUB) * ROWS;
-  const int off_g = cu[it.g];
+  if (block >= num_items) return;
+  const WorkItem it = items[block];
+  const int row0 = it.row0, off_g = cu[it.g];
   const int nrows = (cu[it.g + 1] - off_g) * group;
-  if (row0 >= nrows) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
   auto packed_row = [&](int m) { return (int64_t)(off_g + m / group) * Hq + it.c * group + m % group; };
@@ -121,7 +118,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void pass_f32_kernel(
   };
 
   if (wave * KB < nb) load_k(wave * KB);
-  for (int b0 = wave * KB; b0 < nb; b0 += F32_WAVES * KB) {
+  for (int b0 = wave * KB; b0 < nb; b0 += WAVES * KB) {
     load_v(b0);
     f32x4 S[KB][NQ];
 #pragma unroll
@@ -137,7 +134,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void pass_f32_kernel(
 #pragma unroll
           for (int nq = 0; nq < NQ; ++nq)
             S[kb][nq] = __builtin_amdgcn_mfma_f32_16x16x4f32(K[kb][s][j], Q[nq][s][j], S[kb][nq], 0, 0, 0);
-    if (b0 + F32_WAVES * KB < nb) load_k(b0 + F32_WAVES * KB);
+    if (b0 + WAVES * KB < nb) load_k(b0 + WAVES * KB);
     // register i of S[kb][nq]: key 4 g4 + i of block b0 + kb, query column l16
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq) {
@@ -200,16 +197,16 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void pass_f32_kernel(
     }
   }
   __syncthreads();
-  for (int n = threadIdx.x; n < ROWS * (D / 4); n += F32_WAVES * 64) {
+  for (int n = threadIdx.x; n < ROWS * (D / 4); n += WAVES * 64) {
     const int r = n / (D / 4), ch = n % (D / 4) * 4;
     if (row0 + r >= nrows) continue;
     float m = m_s[0][r];
 #pragma unroll
-    for (int w = 1; w < F32_WAVES; ++w) m = fmaxf(m, m_s[w][r]);  // finite: every row sees a key
+    for (int w = 1; w < WAVES; ++w) m = fmaxf(m, m_s[w][r]);  // finite: every row sees a key
     float l = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < F32_WAVES; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
       const float a = expf(m_s[w][r] - m);  // a wavefront without a visible key: exp(-inf) = 0
       l += a * l_s[w][r];
       acc += a * *reinterpret_cast<const f32x4*>(&o_s[w][r][ch]);
@@ -227,25 +224,20 @@ int launch_pass_f32(const PassArgs& a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   auto f = [](const void* p) { return static_cast<const float*>(p); };
   const int P = a.k_pre ? (int)a.P : 0;
-  auto grid_of = [](int64_t blocks) {
-    return dim3((unsigned)std::min(blocks, MAX_GRID_X), (unsigned)((blocks + MAX_GRID_X - 1) / MAX_GRID_X));
-  };
-#define PA_LAUNCH(DD, NQ)                                                                                          \
-  pass_f32_kernel<DD, NQ><<<grid_of(a.num_items * (ROWS_PER_ITEM / (16 * NQ))), F32_WAVES * 64, 0, s>>>(           \
-      f(a.q), f(a.k_pre), f(a.v_pre), f(a.k), f(a.v), a.o_part, a.lse_part, a.items, a.num_items, a.cu, P, a.causal, \
-      a.Hq, a.Hkv, a.group, a.scale)
-  // One workgroup runs per CU at a time, so a launch takes ceil(workgroups / CUs) rounds, and a round of 32-row
-  // workgroups takes 1.5 to 1.65 times one of 16-row workgroups (measured, 8 / 2 heads of 128 channels, 1,000 prefix
-  // keys, us with 16 / 32 rows: 370 blocks of 16 rows 72 / 62, 600 blocks 106 / 104, 1,024 blocks 152 / 121, 2,400 blocks
-  // 352 / 273; up to 256 blocks 16 rows take one round and 32 rows leave half the CUs idle).
-  const int64_t blocks = (a.part_rows + 15) / 16;
-  const int64_t rounds16 = (blocks + a.num_cu - 1) / a.num_cu, rounds32 = ((blocks + 1) / 2 + a.num_cu - 1) / a.num_cu;
-  const bool wide = 3 * rounds32 <= 2 * rounds16;
+  const dim3 grid((unsigned)std::min(a.num_items, MAX_GRID_X), (unsigned)((a.num_items + MAX_GRID_X - 1) / MAX_GRID_X));
+#define PA_LAUNCH(DD, NQ, WAVES)                                                                                   \
+  pass_f32_kernel<DD, NQ, WAVES><<<grid, WAVES * 64, 0, s>>>(f(a.q), f(a.k_pre), f(a.v_pre), f(a.k), f(a.v), a.o_part, \
+      a.lse_part, a.items, a.num_items, a.cu, P, a.causal, a.Hq, a.Hkv, a.group, a.scale)
+#define PA_LAUNCH_D(DD)                                                                                            \
+  if (a.block_rows == 32) PA_LAUNCH(DD, 2, 8);                                                                     \
+  else if (a.block_waves == 8) PA_LAUNCH(DD, 1, 8);                                                                \
+  else PA_LAUNCH(DD, 1, 1)
   if (a.D == 128) {
-    if (wide) PA_LAUNCH(128, 2); else PA_LAUNCH(128, 1);
+    PA_LAUNCH_D(128);
   } else {
-    if (wide) PA_LAUNCH(64, 2); else PA_LAUNCH(64, 1);
+    PA_LAUNCH_D(64);
   }
+#undef PA_LAUNCH_D
 #undef PA_LAUNCH
   return (int)hipGetLastError();
 }

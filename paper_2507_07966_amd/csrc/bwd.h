@@ -97,7 +97,7 @@ struct BwdF32Args {
   void* dv_prefix;
   void* dk_suffix;
   void* dv_suffix;
-  const WorkItem* items;  // dQ: the plan's suffix list (every block of rows once)
+  const WorkItem* items;  // dQ: the plan's blocks of 16 rows
   int64_t num_items;
   const int32_t* cu;
   int64_t T, P;

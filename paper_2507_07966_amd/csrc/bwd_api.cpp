@@ -108,8 +108,8 @@ int enqueue_backward(const prefix_attn_plan_t* plan, const BackwardArgs& x, void
     f.dv_prefix = x.dv_prefix;
     f.dk_suffix = x.dk_suffix;
     f.dv_suffix = x.dv_suffix;
-    f.items = plan->d_items[1];
-    f.num_items = (int64_t)plan->items[1].size();
+    f.items = plan->d_f32_blocks[1];
+    f.num_items = (int64_t)plan->f32_blocks[1].size();
     f.cu = plan->d_cu;
     f.T = plan->T;
     f.P = d.prefix_len;

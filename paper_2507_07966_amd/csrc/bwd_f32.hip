@@ -98,14 +98,11 @@ __global__ __launch_bounds__(BF_WAVES * 64, 2) void bwd_dq_f32_kernel(
     const WorkItem* __restrict__ items, int64_t num_items, const int32_t* __restrict__ cu, int P, int Hq, int Hkv, int group,
     float scale) {
   __shared__ __attribute__((aligned(16))) Partials<D> part;
-  constexpr int SUB = ROWS_PER_ITEM / 16;
   const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  if (block >= num_items * SUB) return;
-  const WorkItem it = items[block / SUB];
-  const int row0 = it.row0 + (int)(block % SUB) * 16;
-  const int off_g = cu[it.g];
+  if (block >= num_items) return;
+  const WorkItem it = items[block];
+  const int row0 = it.row0, off_g = cu[it.g];
   const int nrows = (cu[it.g + 1] - off_g) * group;
-  if (row0 >= nrows) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
   auto packed_row = [&](int m) { return (int64_t)(off_g + m / group) * Hq + it.c * group + m % group; };
@@ -265,7 +262,7 @@ dim3 grid_of(int64_t blocks) {
 int launch_bwd_dq_f32(const BwdF32Args& a, void* stream) {
   if (a.num_items == 0) return 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const dim3 grid = grid_of(a.num_items * (ROWS_PER_ITEM / 16));
+  const dim3 grid = grid_of(a.num_items);
 #define PA_LAUNCH(DD)                                                                                           \
   bwd_dq_f32_kernel<DD><<<grid, BF_WAVES * 64, 0, s>>>(f(a.q), f(a.d_out), f(a.k_prefix), f(a.v_prefix),        \
                                                        f(a.k_suffix), f(a.v_suffix), a.lse, a.delta, fw(a.dq),  \

@@ -113,7 +113,7 @@ struct PassArgs {
   const void* k_pre;           // [P, Hkv, D]; fp32: null when the call covers no prefix keys
   const void* v_pre;           // fp32 only: [P, Hkv, D]
   int64_t P;                   // fp32 only: prefix keys
-  int32_t num_cu;              // fp32 only: compute units of the plan's device
+  int32_t block_rows, block_waves;  // fp32 only: rows of an item, 16 or 32; wavefronts that share its keys, 8 or 1
   const void* vt_pre;          // prefix V tile images
   int64_t vt_pre_tiles_per_head;
   // bf16 sweep over the range list: 256-row fp32 partial slots of the items that cover a part of their block's keys, and
@@ -219,6 +219,11 @@ struct prefix_attn_plan {
   std::vector<pa::RangeSum> range_sums;
   pa::RangeSum* d_range_sums = nullptr;
   int32_t range_slots = 0;
+  // fp32: the blocks of rows that exist, one workgroup each, in the order of the suffix list: of f32_rows rows for the
+  // forward, of 16 rows for the backward's dQ (only g, row0, c are read)
+  int32_t f32_rows = 16, f32_waves = 8;
+  std::vector<pa::WorkItem> f32_blocks[2];
+  pa::WorkItem* d_f32_blocks[2] = {nullptr, nullptr};
   // workspace layout, byte offsets
   size_t off_o1 = 0, off_o2 = 0, off_lse1 = 0, off_lse2 = 0, off_lse = 0, off_slot_lse = 0, off_vtp = 0, off_vts = 0, off_flags = 0,
          ws_bytes = 0;

@@ -133,6 +133,51 @@ void build_suffix_items(prefix_attn_plan_t& p) {
   std::stable_sort(out.begin(), out.end(), [](const WorkItem& a, const WorkItem& b) { return a.nkeys > b.nkeys; });
 }
 
+// fp32: the suffix list's blocks in pieces of 16 or 32 rows, one workgroup each.  One workgroup of 8 wavefronts runs per CU
+// at a time, so a launch takes ceil(workgroups / CUs) rounds, and a round of 32-row workgroups takes 1.5 to 1.65 times one
+// of 16-row workgroups (measured, 8 / 2 heads of 128 channels, 1,000 prefix keys, us with 16 / 32 rows: 370 blocks of 16
+// rows 72 / 62, 600 blocks 106 / 104, 1,024 blocks 152 / 121, 2,400 blocks 352 / 273; up to 256 blocks 16 rows take one
+// round and 32 rows leave half the CUs idle).
+// Only pieces that hold rows are listed.  (A workgroup for each of the 16 pieces of a 256-row item ran empty ones where
+// rollouts are short, and left the work to one XCD, as workgroup n runs on XCD n % 8: 1,000 one-token rollouts, 1,000 prefix
+// keys, 8 / 2 heads of 128: forward 2,770 -> 240 us, backward 5,210 -> 560.)
+// With at most 128 keys a block on average, sharing them between 8 wavefronts leaves most of those without work; where that
+// ends earlier (us per round of 8 / of 1 wavefront a block, from calls of one kind of block) a block then gets one
+// wavefront, 8 blocks run per CU: 20,000 one-token rollouts, 4 heads of 64, no prefix 888 -> 93 us; 10,000 of 8 tokens,
+// 8 / 2 heads of 128 671 -> 197 us.
+void build_f32_blocks(prefix_attn_plan_t& p) {
+  for (auto& v : p.f32_blocks) v.clear();
+  p.f32_rows = 16;
+  p.f32_waves = 8;
+  if (p.desc.dtype != PA_F32) return;
+  auto pieces = [&](int rows, std::vector<WorkItem>& out) {
+    for (const WorkItem& it : p.items[1]) {
+      const int end = std::min(it.row0 + pa::ROWS_PER_ITEM, p.lens[it.g] * p.group);
+      for (int row0 = it.row0; row0 < end; row0 += rows) out.push_back({it.g, row0, it.c, 0, 0, 0, 0, 0});
+    }
+  };
+  pieces(16, p.f32_blocks[1]);
+  pieces(32, p.f32_blocks[0]);
+  auto rounds = [&](size_t blocks, int at_once) { return (double)((blocks + at_once - 1) / at_once); };
+  const double rounds16 = rounds(p.f32_blocks[1].size(), p.num_cu), rounds32 = rounds(p.f32_blocks[0].size(), p.num_cu);
+  if (3 * rounds32 <= 2 * rounds16) p.f32_rows = 32;
+  const double prefix_blocks = (double)((p.desc.prefix_len + 15) / 16);  // of 16 keys
+  double sum = 0.0, longest = 0.0;
+  for (const WorkItem& it : p.f32_blocks[1]) {
+    const double n = prefix_blocks + it.row0 / p.group / 16 + 1;
+    sum += n;
+    longest = std::max(longest, n);
+  }
+  const double mean = sum / (double)p.f32_blocks[1].size();
+  const double shared = std::min(rounds16, 1.55 * rounds32) * (5.0 + 0.45 * mean);
+  const double alone = std::max(rounds(p.f32_blocks[1].size(), 8 * p.num_cu) * (2.0 + 2.6 * mean), 2.0 + 2.6 * longest);
+  if (mean <= 8.0 && alone < shared) {
+    p.f32_rows = 16;
+    p.f32_waves = 1;
+  }
+  if (p.f32_rows == 16) p.f32_blocks[0] = p.f32_blocks[1];
+}
+
 // Backward, dQ pass: the suffix pass's blocks of rows (longest first); each sweeps the prefix and
 // then its own keys.  With key splits (few rows, see build_prefix_items) a block appears once per
 // prefix key range; split 0 also sweeps the own keys, and the fp32 partial dQ are added afterwards.
@@ -660,6 +705,7 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
     p->group = desc->num_q_heads / desc->num_kv_heads;
     build_prefix_items(*p);
     build_suffix_items(*p);
+    build_f32_blocks(*p);
     build_dq_items(*p);
     build_sweep_items(*p);
     p->Mpad = ((int64_t)p->T * p->group + pa::ROWS_PER_ROW_TILE - 1) / pa::ROWS_PER_ROW_TILE * pa::ROWS_PER_ROW_TILE;
@@ -722,8 +768,11 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
       try {
         add(&p->d_cu, p->cu);
         add(&p->d_vt_off, p->vt_off);
-        if (desc->dtype != PA_F32) add(&p->d_items[0], p->items[0]);  // fp32: no separate prefix pass
-        add(&p->d_items[1], p->items[1]);
+        if (desc->dtype != PA_F32) {  // fp32: one sweep over its own blocks of rows
+          add(&p->d_items[0], p->items[0]);
+          add(&p->d_items[1], p->items[1]);
+        }
+        for (int s = 0; s < 2; ++s) add(&p->d_f32_blocks[s], p->f32_blocks[s]);
         add(&p->d_sweep_items, p->sweep_items);
         add(&p->d_range_items, p->range_items);
         add(&p->d_range_sums, p->range_sums);

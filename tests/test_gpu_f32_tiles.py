@@ -26,6 +26,9 @@ SHAPES = [
     (28, 4, 128, 40, (300, 1)),               # 527 blocks: three rounds of 16-row blocks
     (16, 2, 64, 33, (1000, 31)),              # 1,031 blocks, head_dim 64: 16-row blocks, 5 rounds
     (16, 2, 64, 300, (900, 90)),              # 990 blocks: 32-row blocks, ragged against both sizes
+    (4, 4, 128, 0, (1, 2, 17) * 100),         # many short rollouts: one wavefront a block, one or two 16-key blocks each
+    (8, 2, 64, 33, (1, 5) * 150),             # the same with a ragged prefix
+    (6, 1, 128, 1000, (1,) * 600),            # many blocks that are nearly empty, over many keys
 ]
 
 
