@@ -24,11 +24,12 @@
 #include <algorithm>
 
 #include "common.h"
+#include "f32_rows.h"
 
 namespace pa {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+using namespace f32rows;
 
 __device__ inline float quad_max(float x) {  // over the lanes l16, l16 + 16, l16 + 32, l16 + 48 of a query column
   x = fmaxf(x, __shfl_xor(x, 16));
@@ -75,6 +76,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void pass_f32_kernel(
   const int nown = with_own ? (min(row0 + ROWS, nrows) - 1) / group + 1 : 0;  // own keys the last row sees
   const int np = (P + 15) / 16, nb = np + (nown + 15) / 16;                   // 16-key blocks: prefix, then own
 
+  const int diagonal = np + (row0 / group + 1) / 16;  // own blocks from here on hold keys that some rows do not see
+
   f32x4 O[NQ][4 * VB];
   float m_run[NQ], l_run[NQ];
 #pragma unroll
@@ -117,6 +120,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void pass_f32_kernel(
     }
   };
 
+  bool bad = false;  // some value of the diagonal blocks is not finite
   if (wave * KB < nb) load_k(wave * KB);
   for (int b0 = wave * KB; b0 < nb; b0 += WAVES * KB) {
     load_v(b0);
@@ -168,6 +172,12 @@ __global__ __launch_bounds__(WAVES * 64, 2) void pass_f32_kernel(
         }
     }
 #pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const int b = b0 + kb, keys = b >= nb ? 0 : b < np ? P - b * 16 : nown - (b - np) * 16;  // that exist in the block
+      if (keys < 16) clear_rows_from(V[kb], keys, g4);
+      if (b >= diagonal && clear_bad(V[kb])) bad = true;
+    }
+#pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -179,6 +189,24 @@ __global__ __launch_bounds__(WAVES * 64, 2) void pass_f32_kernel(
             for (int nq = 0; nq < NQ; ++nq)
               O[nq][4 * B + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(V[kb][j][B][e], S[kb][nq][j], O[nq][4 * B + e], 0, 0, 0);
   }
+  if (bad)  // the values that were cleared, for the rows that see them
+    for (int b = diagonal; b < nb; ++b) {
+      if (b / KB % WAVES != wave) continue;
+      load_k(b);
+#pragma unroll
+      for (int nq = 0; nq < NQ; ++nq) {
+        f32x4 p = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) p = __builtin_amdgcn_mfma_f32_16x16x4f32(K[0][s][j], Q[nq][s][j], p, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = expf(p[i] * scale - m_run[nq]);
+        const int key0 = (b - np) * 16;
+        add_bad<D>(O[nq], p, min(16, nown - key0), lane, [&](int r) { return key0 + r <= pos[nq]; },
+                   [&](int r) { return v_own + ((int64_t)(off_g + key0 + r) * Hkv + it.c) * D; });
+      }
+    }
 
   // ---- combine the wavefronts: register i of O[nq][4 B + e] is channel 64 B + 4 (4 g4 + i) + e of query column l16
 #pragma unroll

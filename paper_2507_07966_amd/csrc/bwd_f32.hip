@@ -18,11 +18,12 @@
 #include <algorithm>
 
 #include "bwd.h"
+#include "f32_rows.h"
 
 namespace pa {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+using namespace f32rows;
 
 constexpr int BF_WAVES = 8;
 
@@ -115,7 +116,9 @@ __global__ __launch_bounds__(BF_WAVES * 64, 2) void bwd_dq_f32_kernel(
   const float l = lse[row], dl = delta[row];
   const int nown = (min(row0 + 16, nrows) - 1) / group + 1;
   const int np = (P + 15) / 16, nb = np + (nown + 15) / 16;
+  const int diagonal = np + (row0 / group + 1) / 16;  // own blocks from here on hold keys that some rows do not see
   const int64_t stride = (int64_t)Hkv * D;
+  bool bad = false;  // some value of the diagonal blocks is not finite
 
   f32x4 acc[D / 16];
 #pragma unroll
@@ -142,8 +145,25 @@ __global__ __launch_bounds__(BF_WAVES * 64, 2) void bwd_dq_f32_kernel(
     f32x4 ds;
 #pragma unroll
     for (int i = 0; i < 4; ++i) ds[i] = key0 + i <= limit ? expf(scale * S[i] - l) * (W[i] - dl) : 0.f;
+    const int there = b < np ? P - b * 16 : nown - (b - np) * 16;  // keys that exist in the block
+    if (there < 16) clear_rows_from(KR.x, there, g4);
+    if (b >= diagonal && clear_bad(KR.x)) bad = true;
     outer16<D>(acc, KR, ds);
   }
+  if (bad)  // the values that were cleared, for the rows that see them
+    for (int b = wave; b < nb; b += BF_WAVES) {
+      if (b < diagonal) continue;
+      const int key0 = (b - np) * 16;
+      Col<D> V;
+      K.load(base(k_prefix, k_suffix, b) + key_of(b, l16) * stride, g4);
+      V.load(base(v_prefix, v_suffix, b) + key_of(b, l16) * stride, g4);
+      const f32x4 S = dot16<D>(K, Q), W = dot16<D>(V, dO);
+      f32x4 ds;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ds[i] = expf(scale * S[i] - l) * (W[i] - dl);
+      add_bad<D>(acc, ds, min(16, nown - key0), lane, [&](int r) { return key0 + r <= pos; },
+                 [&](int r) { return base(k_prefix, k_suffix, b) + (key0 + r) * stride; });
+    }
   part.put(acc, wave, l16, g4);
   __syncthreads();
   for (int n = threadIdx.x; n < 16 * (D / 4); n += BF_WAVES * 64) {
@@ -194,6 +214,8 @@ __global__ __launch_bounds__(BF_WAVES * 64, 2) void bwd_dkv_f32_kernel(
   V.load((g < 0 ? v_prefix : v_suffix) + first + key * stride, g4);
   const int m_key = g < 0 ? 0 : (off_g + key) * group;              // first stacked row that sees this lane's key
   const int m0 = g < 0 ? 0 : (off_g + key0) * group, m1 = t_end * group;
+  const int m_all = g < 0 ? 0 : (off_g + min(key0 + 15, nkeys - 1)) * group;  // rows from here on see every key
+  bool bad = false;  // some value of the rows before is not finite
 
   f32x4 dK[D / 16], dV[D / 16];
 #pragma unroll
@@ -222,9 +244,13 @@ __global__ __launch_bounds__(BF_WAVES * 64, 2) void bwd_dkv_f32_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int m = mrow + 4 * g4 + i;
-      p[i] = m >= m_key && m < m1 ? expf(scale * S[i] - l[i]) : 0.f;
-      ds[i] = p[i] * (W[i] - dl[i]);
+      const bool seen = m >= m_key && m < m1;
+      p[i] = seen ? expf(scale * S[i] - l[i]) : 0.f;
+      ds[i] = seen ? p[i] * (W[i] - dl[i]) : 0.f;
     }
+    const int there = m1 - mrow;  // rows that exist
+    if (there < 16) clear_rows_from(R.x, there, g4);
+    if (mrow < m_all && clear_bad(R.x)) bad = true;
     Rows<D> R2;
     R2.load(q, rows, D, l16);
     outer16<D>(dV, R, p);
@@ -233,8 +259,31 @@ __global__ __launch_bounds__(BF_WAVES * 64, 2) void bwd_dkv_f32_kernel(
       row = (unsigned)packed_row(next + l16);
       Q.load(q + (int64_t)row * D, g4);
     }
+    if (there < 16) clear_rows_from(R2.x, there, g4);
+    if (mrow < m_all && clear_bad(R2.x)) bad = true;
     outer16<D>(dK, R2, ds);
   }
+  if (bad)  // the values that were cleared, for the keys that see their rows
+    for (mrow = m0 + wave * 16; mrow < m_all; mrow += BF_WAVES * 16) {
+      row = (unsigned)packed_row(mrow + l16);
+      Col<D> dO;
+      Q.load(q + (int64_t)row * D, g4);
+      dO.load(d_out + (int64_t)row * D, g4);
+      const f32x4 S = dot16<D>(Q, K), W = dot16<D>(dO, V);
+      f32x4 p, ds;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned at = (unsigned)__shfl((int)row, 4 * g4 + i);
+        p[i] = expf(scale * S[i] - lse[at]);
+        ds[i] = p[i] * (W[i] - delta[at]);
+      }
+      auto seen = [&](int r) { return mrow + r >= m_key; };
+      auto row_of = [&](const float* x) {
+        return [x, row](int r) { return x + (int64_t)(unsigned)__shfl((int)row, r) * D; };
+      };
+      add_bad<D>(dV, p, min(16, m1 - mrow), lane, seen, row_of(d_out));
+      add_bad<D>(dK, ds, min(16, m1 - mrow), lane, seen, row_of(q));
+    }
   float* dk = (g < 0 ? dk_prefix : dk_suffix) + first;
   float* dv = (g < 0 ? dv_prefix : dv_suffix) + first;
   auto finish = [&](float* dst, float factor) {

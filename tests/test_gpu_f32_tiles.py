@@ -96,3 +96,53 @@ def test_f32_a_million_one_token_rollouts():
         err = (got[:, 0].double() - ref).abs().max() / ref.square().mean().sqrt()
         print(f"{name}: {float(err):.2e}", flush=True)
         assert err < 1e-4, name
+
+
+BAD = 37   # token whose value (key, query, upstream gradient) is not finite: inside a 16-row block, a 16-key block
+CH = 5
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens", [(1, 1, 64, 0, (90,)), (4, 2, 128, 19, (130, 33)), (28, 4, 128, 40, (300, 1)),
+                                             (4, 4, 128, 0, (47,) + (1, 2, 17) * 100)])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_f32_non_finite_values_reach_only_the_rows_that_see_them(Hq, Hkv, D, P, lens, bad):
+    """One bad value of the first rollout, or of the last prefix key (which masked steps past the prefix's end repeat),
+    must leave every result that does not depend on it as it is without it; forward, dQ and dK / dV."""
+    print(f"fp32 non-finite {bad} {Hq}/{Hkv}/{D} P={P} lens={lens}", flush=True)
+
+    def run(name, row, value):
+        x = wl.make_custom("f32", Hq, Hkv, D, P, lens, seed=33)
+        do, _ = wl.make_d_out(x)
+        (do if name == "d_out" else getattr(x, name))[row, 0, CH] = value
+        out, lse = run_hip(x)
+        return dict(run_hip_backward(x, do), out=out, lse=lse.T)   # all [tokens, heads ...]
+
+    T, group = sum(lens), Hq // Hkv
+    seen = np.arange(BAD, lens[0])
+    rest = np.setdiff1d(np.arange(T), seen)
+    before = np.setdiff1d(np.arange(T), np.arange(BAD + 1))   # keys that the bad row does not see
+    same = lambda a, b: np.allclose(a, b, rtol=1e-5, atol=1e-6)
+    # a value: one channel of the rows that see it, nothing else of the forward
+    clean, got = run("v_suffix", BAD, 0.5), run("v_suffix", BAD, bad)
+    want = got["out"][seen, :group, CH]
+    assert np.isnan(want).all() if np.isnan(bad) else (want == bad).all()
+    got["out"][seen, :group, CH] = clean["out"][seen, :group, CH]
+    assert same(got["out"], clean["out"]) and same(got["lse"], clean["lse"])
+    # a key: the rows that see it
+    clean, got = run("k_suffix", BAD, 0.5), run("k_suffix", BAD, bad)
+    for n in ("out", "lse", "dq"):
+        assert same(got[n][rest], clean[n][rest]) and same(got[n][:, group:], clean[n][:, group:]), n
+    # a query row or its upstream gradient: its own dQ, and the keys it sees
+    for name in ("q", "d_out"):
+        clean, got = run(name, BAD, 0.5), run(name, BAD, bad)
+        other = np.setdiff1d(np.arange(T), [BAD])
+        for n in ("out", "lse", "dq"):
+            assert same(got[n][other], clean[n][other]), (name, n)
+        for n in ("dk_suffix", "dv_suffix"):
+            assert same(got[n][before], clean[n][before]) and same(got[n][:, 1:], clean[n][:, 1:]), (name, n)
+    if P:
+        clean, got = run("v_prefix", P - 1, 0.5), run("v_prefix", P - 1, bad)
+        want = got["out"][:, :group, CH]
+        assert np.isnan(want).all() if np.isnan(bad) else (want == bad).all()
+        got["out"][:, :group, CH] = clean["out"][:, :group, CH]
+        assert same(got["out"], clean["out"]) and same(got["lse"], clean["lse"])
