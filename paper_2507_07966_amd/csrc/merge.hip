@@ -123,9 +123,11 @@ __global__ __launch_bounds__(256) void merge_slots_kernel(SlotArgs a) {
     acc *= old;
 #pragma unroll
     for (int e = 0; e < STEP; ++e) {
-      const float w = i0 + e < b.nslots ? expf(l[e] - top) : 0.f;
-      tot += w;
-      acc += w * o[e];
+      if (i0 + e < b.nslots) {  // a repeated slot is left out, not weighted by 0: it may hold an infinity
+        const float w = expf(l[e] - top);
+        tot += w;
+        acc += w * o[e];
+      }
     }
     mx = top;
   }

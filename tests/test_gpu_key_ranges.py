@@ -89,3 +89,17 @@ def test_split_prefix_near_the_size_of_the_static_workspace(Hq, Hkv, D, P, lens)
     plan.destroy()
     assert np.array_equal(so.double().cpu().numpy(), out) and np.array_equal(sl.double().cpu().numpy(), lse)
     check(o[rows].double().cpu().numpy(), l[rows].t().double().cpu().numpy(), ro, rl, f"{label}, partial")
+
+
+def test_key_ranges_keep_an_infinite_value_infinite():
+    """An infinity in the value of a rollout's first token, which every row sees: the channel is infinite in every row of
+    its kv head, and nothing else changes (the merge reads the last range, which holds it, several times)."""
+    x = wl.make_custom("bf16", 28, 4, 128, 960, (128,), seed=43)
+    print("infinite value", flush=True)
+    clean, clean_lse = run_hip(x)
+    x.v_suffix[0, 0, 5] = np.inf
+    x.bits["v_suffix"], _ = wl.round_to_bf16(x.v_suffix)
+    out, lse = run_hip(x)
+    assert np.isposinf(out[:, :7, 5]).all()
+    out[:, :7, 5] = clean[:, :7, 5]
+    assert np.array_equal(out, clean) and np.array_equal(lse, clean_lse)
