@@ -277,6 +277,12 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
 #pragma unroll
   for (int nq = 0; nq < NQ; ++nq) lsum[nq] = 0.f;
   const float c_log2 = scale * 1.4426950408889634f;
+  // Scores may be minus infinity (keys hidden by a bias channel).  In an uncut sequence of keys they weigh nothing next to
+  // the others; a range may hold no others, and then has to leave the weight 0 and the LSE minus infinity.  The common
+  // kernel gives such an item up (its probabilities are NaN); the careful one takes them against 0 until a row's reference
+  // is a number.
+  constexpr bool HIDDEN = RANGE && CAREFUL;
+  auto reference = [&](float m) { return HIDDEN && m == -INFINITY ? 0.f : m * c_log2; };
 
   auto zero = [](f32x4 (&S)[4][NQ]) {
 #pragma unroll
@@ -368,7 +374,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     // each p <= this lane's partial sum of its column; !(x <= bound) is also true for NaN
     bool unsafe = false;
 #pragma unroll
-    for (int nq = 0; nq < NQ; ++nq) unsafe = unsafe || !(lacc[nq] <= SAFE_SUM);
+    for (int nq = 0; nq < NQ; ++nq) unsafe = unsafe || !(lacc[nq] <= SAFE_SUM) || (HIDDEN && mref[nq] == -INFINITY);
     if (!CAREFUL) {
       bad = bad || __any(unsafe);
     } else if (__any(unsafe)) {
@@ -376,7 +382,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
 #pragma unroll
       for (int nq = 0; nq < NQ; ++nq) {
         const float mnew = fmaxf(mref[nq], row_max(S, nq));
-        const float alpha = __builtin_amdgcn_exp2f((mref[nq] - mnew) * c_log2);
+        const float alpha = HIDDEN && mref[nq] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mref[nq] - mnew) * c_log2);
         lsum[nq] *= alpha;
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
@@ -384,7 +390,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
           for (int i = 0; i < 4; ++i) O[cb][nq][i] *= alpha;
         mref[nq] = mnew;
         lacc[nq] = 0.f;
-        mc2[nq] = mnew * c_log2;
+        mc2[nq] = reference(mnew);
       }
 #pragma unroll
       for (int j = 0; j < 4 * NQ; ++j) prob_slice(S, j, mc2, Pn, lacc);
@@ -412,7 +418,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     constexpr int NOP = 2 * CB;  // operands of the tile: [32-key chunk][channel block]
     float mc[NQ];
 #pragma unroll
-    for (int nq = 0; nq < NQ; ++nq) mc[nq] = mref[nq] * c_log2;
+    for (int nq = 0; nq < NQ; ++nq) mc[nq] = reference(mref[nq]);
     auto v_operand = [&](int t) {
       return *reinterpret_cast<const bf16x8*>(vbuf + (t % CB) * 16 * 128 + voff[t / CB]);
     };
@@ -452,8 +458,8 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     float lacc[NQ], mc[NQ];
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq) {
-      mref[nq] = row_max(S, nq);  // finite: key 0 is visible to every row
-      mc[nq] = mref[nq] * c_log2;
+      mref[nq] = row_max(S, nq);  // finite, the first key being visible to every row, unless the scores are not
+      mc[nq] = reference(mref[nq]);
       lacc[nq] = 0.f;
     }
 #pragma unroll
@@ -517,7 +523,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     const int64_t row = out_row(nq);
     if (RANGE && it.split >= 0) {  // one range of the block's keys
       if (row >= 0) {
-        const float inv = 1.0f / l;
+        const float inv = l == 0.f ? 0.f : 1.0f / l;  // 0: no key of the range counts, its LSE is -infinity
         const int64_t srow = (int64_t)it.split * ROWS_PER_ITEM + wave * ROWS_PER_WAVE + nq * 16 + l16;
         float* op = o_slots + srow * D + 4 * g4;
 #pragma unroll

@@ -117,14 +117,15 @@ __global__ __launch_bounds__(256) void merge_slots_kernel(SlotArgs a) {
     }
     float top = mx;
 #pragma unroll
-    for (int e = 0; e < STEP; ++e) top = fmaxf(top, l[e]);  // finite: no range is empty for any row
-    const float old = expf(mx - top);
+    for (int e = 0; e < STEP; ++e) top = fmaxf(top, l[e]);
+    const float ref = top == -INFINITY ? 0.f : top;  // no key that counts so far (see the range kernel): weights of 0
+    const float old = expf(mx - ref);
     tot *= old;
     acc *= old;
 #pragma unroll
     for (int e = 0; e < STEP; ++e) {
       if (i0 + e < b.nslots) {  // a repeated slot is left out, not weighted by 0: it may hold an infinity
-        const float w = expf(l[e] - top);
+        const float w = expf(l[e] - ref);
         tot += w;
         acc += w * o[e];
       }

@@ -91,6 +91,37 @@ def test_split_prefix_near_the_size_of_the_static_workspace(Hq, Hkv, D, P, lens)
     check(o[rows].double().cpu().numpy(), l[rows].t().double().cpu().numpy(), ro, rl, f"{label}, partial")
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,hidden", [
+    (28, 4, 128, 960, (128,), (256, 704)),           # whole ranges of prefix keys, and first tiles of ranges
+    (4, 4, 128, 0, (3000,), (700, 1900)),            # own keys
+    (14, 2, 64, 5377, (1500, 37, 1200, 1901, 60), (1000, 4500)),   # beside whole blocks
+])
+def test_key_ranges_whose_scores_are_all_minus_infinity(Hq, Hkv, D, P, lens, hidden):
+    """Keys that a bias channel of minus infinity hides: a range may then hold no key that counts, and adds nothing."""
+    import torch
+    import paper_2507_07966_amd as pa
+    x = wl.make_custom("bf16", Hq, Hkv, D, P, lens, seed=41)
+    print(f"hidden keys {Hq}/{Hkv}/{D} P={P} lens={lens}", flush=True)
+    x.q[:, :, 0] = 1.0
+    for k in (x.k_prefix, x.k_suffix):
+        k[:, :, 0] = 0.0
+    (x.k_prefix if P else x.k_suffix)[hidden[0]:hidden[1], :, 0] = -np.inf
+    for n in ("q", "k_prefix", "k_suffix"):
+        x.bits[n], _ = wl.round_to_bf16(getattr(x, n))
+    step = max(1, sum(lens) // 300)
+    rows = np.arange(0, sum(lens), step)
+    ro, rl, _ = cref.prefix_shared_attention(x.q, x.k_prefix, x.v_prefix, x.k_suffix, x.v_suffix, x.suffix_lens,
+                                             x.workload.scale, rows=rows)
+    out, lse, plan, dev, ws, _, _ = run_hip(x, return_plan=True)
+    check(out[rows], lse[:, rows], ro, rl, "hidden keys")
+    o = torch.full((sum(lens), Hq, D), float("nan"), device="cuda")
+    l = torch.full((sum(lens), Hq), float("nan"), device="cuda")
+    pa.prefix_attn_forward_partial(plan, *[dev[n] for n in ("q", "k_prefix", "v_prefix", "k_suffix", "v_suffix")], True, o, l, ws)
+    torch.cuda.synchronize()
+    plan.destroy()
+    check(o[rows].double().cpu().numpy(), l[rows].t().double().cpu().numpy(), ro, rl, "hidden keys, partial")
+
+
 def test_key_ranges_keep_an_infinite_value_infinite():
     """An infinity in the value of a rollout's first token, which every row sees: the channel is infinite in every row of
     its kv head, and nothing else changes (the merge reads the last range, which holds it, several times)."""
