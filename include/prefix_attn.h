@@ -266,9 +266,9 @@ int64_t prefix_attn_plan_num_items(const prefix_attn_plan_t* plan, int32_t pass)
  * padding items.
  * Single sweep (whole bf16 calls whose prefix is at most 1,024 tiles and not cut into key
  * ranges run as one pass per block of rows instead of prefix pass + suffix pass): like the
- * dQ pass with key0 = 0 and pkeys = P, laid out over the XCDs like the prefix pass.  Whole calls with
- * few rows cut [prefix | own keys] of every block into ranges of tiles instead and merge their partials;
- * the prefix pass's ranges then serve partials over the prefix keys only. */
+ * dQ pass with key0 = 0 and pkeys = P, laid out over the XCDs like the prefix pass.
+ * Calls whose blocks of rows do not fill whole rounds of compute units run other lists, with the keys of
+ * some blocks cut into ranges: see prefix_attn_plan_launch_items. */
 int prefix_attn_plan_items(const prefix_attn_plan_t* plan, int32_t pass, int32_t* items_out);
 
 /* Work lists of the backward dK/dV pass, padding entries included.  pass 0 = prefix key blocks, 1 = the
@@ -281,11 +281,32 @@ int prefix_attn_plan_items(const prefix_attn_plan_t* plan, int32_t pass, int32_t
  * masked item streams the tiles that hold rows needing the causal mask (its diagonal) plus, via
  * prefix_attn_plan_key_item_extra_tiles, the rollout's last tile when rows of the next rollout share it; its
  * mask-free item streams the tiles between; together they cover every tile from the block's first key to the
- * rollout's end exactly once.  A launch of few items may cut a masked item's tiles into several workgroups. */
+ * rollout's end exactly once.  The launch runs them in the order of prefix_attn_plan_launch_items, and may cut a
+ * masked item's tiles into several workgroups. */
 int64_t prefix_attn_plan_num_key_items(const prefix_attn_plan_t* plan, int32_t pass);
 int prefix_attn_plan_key_items(const prefix_attn_plan_t* plan, int32_t pass, int32_t* items_out);
 /* tiles_out [num_items] (HOST): for pass 1 the one row tile an item streams after [tile0, tile1), or -1. */
 int prefix_attn_plan_key_item_extra_tiles(const prefix_attn_plan_t* plan, int32_t pass, int32_t* tiles_out);
+
+/* The lists that calls run where they differ from those above: the work of a pass with some blocks cut, so that no compute
+ * unit is left idle.  list 0 = the forward of whole calls and of partials that hold the own keys (empty: the lists above),
+ * 1 = the backward's dQ, 2 = its dK/dV, 3 = the fp32 forward, 4 = the fp32 backward's dQ.  items_out [num_items][8]
+ * (HOST), in launch order, padding items (g = -1, for list 2 c = -1) included:
+ * Lists 0, 1 (bf16): {g, first stacked row, kv head c, nkeys, key0, pkeys, okey0, slot}: the item sweeps the prefix keys
+ * [key0, key0 + pkeys), then the rollout's own keys [okey0, okey0 + nkeys); slot -1: all keys of its block, and it writes
+ * the result; otherwise a part of them, and it leaves a partial result in that slot.
+ * List 2 (bf16): {g (-1: prefix keys, -2: own keys, mask-free kernel), key0, c, nkeys, tile0, tile1, extra tile, slot}, with
+ * the meanings of prefix_attn_plan_key_items.
+ * Lists 3, 4 (fp32): {g, first stacked row, c, rows of the block, wavefronts that share its keys, 0, 0, -1}. */
+int64_t prefix_attn_plan_num_launch_items(const prefix_attn_plan_t* plan, int32_t list);
+int prefix_attn_plan_launch_items(const prefix_attn_plan_t* plan, int32_t list, int32_t* items_out);
+/* Lists 0 ... 2: the blocks whose partial results are added afterwards, sums_out [num_sums][6] (HOST):
+ * {first packed token of the rollout, first stacked row, c, rows, first slot, slots}, for list 2 {1: own keys / 0: prefix
+ * keys, first key (packed token index / prefix index), c, keys, first slot, slots}; and the number of slots in use, of 256 rows
+ * (list 0: D + 1 words each, list 1: D) or 2 x 128 keys (list 2: D words each) of fp32 in the workspace. */
+int64_t prefix_attn_plan_num_launch_sums(const prefix_attn_plan_t* plan, int32_t list);
+int prefix_attn_plan_launch_sums(const prefix_attn_plan_t* plan, int32_t list, int32_t* sums_out);
+int64_t prefix_attn_plan_launch_slots(const prefix_attn_plan_t* plan, int32_t list);
 
 /* Total suffix tokens T of the plan. */
 int64_t prefix_attn_plan_total_tokens(const prefix_attn_plan_t* plan);

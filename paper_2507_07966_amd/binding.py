@@ -25,7 +25,9 @@ EXPORTED_SYMBOLS = ("prefix_attn_plan", "prefix_attn_forward", "prefix_attn_forw
                     "prefix_attn_status_string", "prefix_attn_plan_tiles", "prefix_attn_plan_num_items",
                     "prefix_attn_plan_items", "prefix_attn_plan_total_tokens", "prefix_attn_backward_workspace",
                     "prefix_attn_backward", "prefix_attn_backward_timed", "prefix_attn_plan_num_key_items",
-                    "prefix_attn_plan_key_items", "prefix_attn_plan_key_item_extra_tiles", "prefix_attn_forward_partial", "prefix_attn_merge_partials")
+                    "prefix_attn_plan_key_items", "prefix_attn_plan_key_item_extra_tiles", "prefix_attn_plan_num_launch_items",
+                    "prefix_attn_plan_launch_items", "prefix_attn_plan_num_launch_sums", "prefix_attn_plan_launch_sums",
+                    "prefix_attn_plan_launch_slots", "prefix_attn_forward_partial", "prefix_attn_merge_partials")
 EXPORTED_SYMBOLS_OTHER = ("token_logprob_workspace", "token_logprob_forward", "grpo_group_advantages")
 
 
@@ -106,6 +108,12 @@ def load_library():
     lib.prefix_attn_plan_key_items.argtypes = [vp, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
     lib.prefix_attn_plan_key_item_extra_tiles.restype = ctypes.c_int
     lib.prefix_attn_plan_key_item_extra_tiles.argtypes = [vp, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
+    for n in ("num_launch_items", "num_launch_sums", "launch_slots"):
+        getattr(lib, f"prefix_attn_plan_{n}").restype = ctypes.c_int64
+        getattr(lib, f"prefix_attn_plan_{n}").argtypes = [vp, ctypes.c_int32]
+    for n in ("launch_items", "launch_sums"):
+        getattr(lib, f"prefix_attn_plan_{n}").restype = ctypes.c_int
+        getattr(lib, f"prefix_attn_plan_{n}").argtypes = [vp, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
     _lib = lib
     return lib
 
@@ -188,6 +196,32 @@ class PrefixAttnPlan:
             if st:
                 raise PrefixAttnError(st, "prefix_attn_plan_key_items")
         return out
+
+    def _launch(self, what: str, which: int, width: int) -> np.ndarray:
+        lib = load_library()
+        n = getattr(lib, f"prefix_attn_plan_num_{what}")(self.handle, which)
+        if n < 0:
+            raise PrefixAttnError(2, f"prefix_attn_plan_num_{what}")
+        out = np.zeros((n, width), dtype=np.int32)
+        if n:
+            st = getattr(lib, f"prefix_attn_plan_{what}")(self.handle, which, out.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)))
+            if st:
+                raise PrefixAttnError(st, f"prefix_attn_plan_{what}")
+        return out
+
+    def launch_items(self, which: int) -> np.ndarray:
+        """The list a launch runs: 0 (forward, empty unless blocks are cut) and 1 (dQ): int32 [n, 8] = (g, row0, c, nkeys,
+        key0, pkeys, okey0, slot); 2 (dK/dV): (g, key0, c, nkeys, tile0, tile1, extra tile, slot); 3 and 4 (fp32 forward and
+        dQ): (g, row0, c, rows, wavefronts, 0, 0, -1)."""
+        return self._launch("launch_items", which, 8)
+
+    def launch_sums(self, which: int) -> np.ndarray:
+        """Blocks whose partial results are added after launch list 0, 1 or 2: int32 [n, 6], the last two columns the
+        first slot and the number of slots."""
+        return self._launch("launch_sums", which, 6)
+
+    def launch_slots(self, which: int) -> int:
+        return int(load_library().prefix_attn_plan_launch_slots(self.handle, which))
 
     def destroy(self):
         if self._h is not None:

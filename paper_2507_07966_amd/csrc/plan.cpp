@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <cmath>
 #include <functional>
+#include <initializer_list>
 #include <map>
 #include <new>
 #include <queue>
@@ -357,6 +358,7 @@ void build_dq_launch(prefix_attn_plan_t& p) {
     if (!pieces.empty()) return lay_out_ranges(p, pieces, false, p.dq_launch, p.dq_sums, p.dq_slots);
   }
   p.dq_launch = p.dq_items;
+  for (WorkItem& it : p.dq_launch) it.split = -1;
 }
 
 // Forward, the sweep over [prefix | own keys] with some blocks of rows cut into ranges (cut_blocks), one launch and one
@@ -854,6 +856,60 @@ int prefix_attn_plan_items(const prefix_attn_plan_t* plan, int32_t pass, int32_t
     items_out[6 * n + 5] = v[n].pkeys;
   }
   return PA_OK;
+}
+
+int64_t prefix_attn_plan_num_launch_items(const prefix_attn_plan_t* plan, int32_t list) {
+  if (!plan || list < 0 || list > 4) return -1;
+  if (list == 2) return (int64_t)plan->key_launch.size();
+  return (int64_t)(list == 0 ? plan->range_items : list == 1 ? plan->dq_launch : plan->f32_blocks[list - 3]).size();
+}
+
+int prefix_attn_plan_launch_items(const prefix_attn_plan_t* plan, int32_t list, int32_t* items_out) {
+  if (!plan || !items_out) return PA_ERR_NULL;
+  if (list < 0 || list > 4) return PA_ERR_SHAPE;
+  auto put = [&](size_t n, std::initializer_list<int32_t> v) { std::copy(v.begin(), v.end(), items_out + 8 * n); };
+  if (list == 2) {
+    for (size_t n = 0; n < plan->key_launch.size(); ++n) {
+      const pa::KeyItem& it = plan->key_launch[n];
+      put(n, {it.g, it.key0, it.c, it.nkeys, it.tile0, it.tile1, it.extra_tile, it.slot});
+    }
+  } else if (list >= 3) {
+    for (size_t n = 0; n < plan->f32_blocks[list - 3].size(); ++n) {
+      const WorkItem& it = plan->f32_blocks[list - 3][n];
+      put(n, {it.g, it.row0, it.c, list == 3 ? plan->f32_rows : 16, list == 3 ? plan->f32_waves : 8, 0, 0, -1});
+    }
+  } else {
+    const std::vector<WorkItem>& v = list == 0 ? plan->range_items : plan->dq_launch;
+    for (size_t n = 0; n < v.size(); ++n)
+      put(n, {v[n].g, v[n].row0, v[n].c, v[n].nkeys, v[n].key0, v[n].pkeys, v[n].okey0, v[n].split});
+  }
+  return PA_OK;
+}
+
+int64_t prefix_attn_plan_num_launch_sums(const prefix_attn_plan_t* plan, int32_t list) {
+  if (!plan || list < 0 || list > 2) return -1;
+  return (int64_t)(list == 0 ? plan->range_sums.size() : list == 1 ? plan->dq_sums.size() : plan->key_sums.size());
+}
+
+int prefix_attn_plan_launch_sums(const prefix_attn_plan_t* plan, int32_t list, int32_t* sums_out) {
+  if (!plan || !sums_out) return PA_ERR_NULL;
+  if (list < 0 || list > 2) return PA_ERR_SHAPE;
+  auto put = [&](size_t n, std::initializer_list<int32_t> v) { std::copy(v.begin(), v.end(), sums_out + 6 * n); };
+  if (list == 2) {
+    for (size_t n = 0; n < plan->key_sums.size(); ++n) {
+      const pa::KeySum& s = plan->key_sums[n];
+      put(n, {s.own, s.key0, s.c, s.nkeys, s.slot0, s.nslots});
+    }
+  } else {
+    const std::vector<pa::RangeSum>& v = list == 0 ? plan->range_sums : plan->dq_sums;
+    for (size_t n = 0; n < v.size(); ++n) put(n, {v[n].off_g, v[n].row0, v[n].c, v[n].nrows, v[n].slot0, v[n].nslots});
+  }
+  return PA_OK;
+}
+
+int64_t prefix_attn_plan_launch_slots(const prefix_attn_plan_t* plan, int32_t list) {
+  if (!plan || list < 0 || list > 2) return -1;
+  return list == 0 ? plan->range_slots : list == 1 ? plan->dq_slots : plan->key_slots;
 }
 
 int64_t prefix_attn_plan_total_tokens(const prefix_attn_plan_t* plan) { return plan ? plan->T : -1; }

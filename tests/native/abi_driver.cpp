@@ -99,6 +99,30 @@ void exercise(int Hq, int Hkv, int D, int64_t P, const std::vector<int32_t>& len
     }
     CHECK(keys_seen == (pass == 0 ? P : T) * Hkv);
   }
+  for (int list = 0; list < 5; ++list) {  // the lists that the launches run
+    const int64_t n = prefix_attn_plan_num_launch_items(plan, list), s = prefix_attn_plan_num_launch_sums(plan, list);
+    CHECK(n >= 0 && (list < 3 ? s >= 0 : s == -1));
+    CHECK((n > 0) == (list == 0 ? n > 0 : (list < 3) == (dtype == PA_BF16)));
+    items.assign((size_t)n * 8 + 1, -7);
+    CHECK(prefix_attn_plan_launch_items(plan, list, items.data()) == PA_OK && items[(size_t)n * 8] == -7);
+    int64_t left = 0, most = -1;
+    for (int64_t i = 0; i < n; ++i) {
+      const int32_t slot = items[(size_t)i * 8 + 7];
+      if (list < 3 && items[(size_t)i * 8 + (list == 2 ? 2 : 0)] >= 0 && slot >= 0) {
+        ++left;
+        most = slot > most ? slot : most;
+      }
+    }
+    if (list >= 3) continue;
+    CHECK(left == prefix_attn_plan_launch_slots(plan, list) && most < left);
+    items.assign((size_t)s * 6 + 1, -7);
+    CHECK(prefix_attn_plan_launch_sums(plan, list, items.data()) == PA_OK && items[(size_t)s * 6] == -7);
+    int64_t added = 0;
+    for (int64_t i = 0; i < s; ++i) added += items[(size_t)i * 6 + 5];
+    CHECK(added == left);
+  }
+  CHECK(prefix_attn_plan_num_launch_items(plan, 5) == -1 && prefix_attn_plan_launch_items(plan, -1, items.data()) == PA_ERR_SHAPE);
+  CHECK(prefix_attn_plan_launch_sums(plan, 3, items.data()) == PA_ERR_SHAPE && prefix_attn_plan_launch_slots(plan, 3) == -1);
   size_t bws = 0;
   CHECK(prefix_attn_backward_workspace(plan, &bws) == PA_OK);
   // argument checks of the entry points; a host-only plan never launches
