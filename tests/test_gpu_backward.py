@@ -209,15 +209,23 @@ def test_backward_own_key_blocks_cut_into_row_ranges_full_tensor(Hq, Hkv, D, P, 
                 few_keys_floor(x, do))
 
 
-@pytest.mark.parametrize("Hq,Hkv,D,P,lens", [
-    (28, 4, 128, 200, (2100, 400)),                # 69 blocks of a kv head for 64 CUs: five cut, the others whole
-    (14, 2, 64, 1377, (1500, 37, 1200, 60)),       # fewer blocks than CUs: all cut, at and inside the own keys
-    (6, 3, 64, 70, (6100,)),                       # kv heads that share no layout over the XCDs
-    (8, 2, 64, 0, (4200, 1)),                      # own keys only: ranges that some or all rows of a wavefront do not see
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,whole", [
+    (28, 4, 128, 3000, (2400, 100), True),         # 69 blocks of a kv head for 64 CUs: five cut, the others whole
+    (14, 2, 128, 1377, (1500, 37, 1200, 60), False),   # fewer blocks than CUs: all cut, at and inside the own keys
+    (14, 2, 128, 700, (2600,), True),              # the longest blocks cut, the others whole
+    (6, 3, 64, 70, (6100,), True),                 # kv heads that share no layout over the XCDs
+    (8, 2, 64, 0, (4200, 1), True),                # own keys only: ranges that some or all rows of a wavefront do not see
 ])
-def test_backward_dq_blocks_cut_into_key_ranges_full_tensor(Hq, Hkv, D, P, lens):
+def test_backward_dq_blocks_cut_into_key_ranges_full_tensor(Hq, Hkv, D, P, lens, whole):
     """dQ of blocks of rows that do not fill the chip in whole rounds: ranges of [prefix | own keys] with fp32 partials,
     beside whole blocks, against the fp64 oracle."""
+    import paper_2507_07966_amd as pa
+    plan = pa.prefix_attn_plan(Hq, Hkv, D, P, list(lens), D ** -0.5, dtype="bf16", device=0)
+    items = plan.launch_items(1)
+    plan.destroy()
+    real = items[items[:, 0] >= 0]
+    cut = real[real[:, 7] >= 0]
+    assert len(cut) and (cut[:, 6] > 0).any() and (len(cut) < len(real)) == whole
     x = wl.make_custom("bf16", Hq, Hkv, D, P, lens, seed=37)
     do, bits = wl.make_d_out(x)
     check_grads(run_hip_backward(x, do, bits), oracle_backward(x, do), "bf16", f"dq ranges {Hq}/{Hkv}/{D} P={P} {lens}",

@@ -11,23 +11,25 @@ from tests.gpu_util import check, run_hip, to_device
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [
+SHAPES = [  # all have cut blocks (asserted); `whole`: whole blocks beside them in the same launch
     (28, 4, 128, 1024, (128,)),            # 16 blocks
     (28, 4, 128, 1000, (5, 3)),            # tiny rollouts, ragged last prefix tile
     (4, 4, 128, 193, (900,)),              # own keys outweigh the prefix: cuts inside them
     (1, 1, 64, 130, (2000,)),              # three prefix tiles
     (16, 2, 128, 3000, (1500,)),           # 94 blocks: two ranges
     (8, 2, 64, 5377, (40, 3, 300)),        # ragged everything
-    (28, 4, 128, 1000, (2100, 400)),       # 69 blocks of a kv head for 64 CUs: five cut, the others whole in the same launch
-    (6, 3, 64, 700, (9000, 77)),           # kv heads that share no layout over the XCDs, 213 blocks
-    (14, 2, 64, 5377, (1500, 37, 1200, 1901, 60)),   # 130 blocks of a kv head for 128 CUs
+]
+SHAPES = [s + (False,) for s in SHAPES] + [s + (True,) for s in [
+    (28, 4, 128, 3000, (2400, 100)),       # 69 blocks of a kv head for 64 CUs: five cut, the others whole in the same launch
+    (6, 3, 64, 700, (9000, 77)),           # kv heads that share no layout over the XCDs, 216 blocks
+    (14, 2, 64, 5377, (1500, 37, 1200, 1901, 60)),   # 131 blocks of a kv head for 128 CUs
     (4, 4, 128, 0, (3000,)),               # own keys only: cut up to the diagonal, the first blocks whole
     (8, 8, 64, 0, (1, 63, 64, 65, 1025)),
-]
+]]
 
 
-@pytest.mark.parametrize("Hq,Hkv,D,P,lens", SHAPES)
-def test_key_ranges_whole_call_and_partial(Hq, Hkv, D, P, lens):
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,whole", SHAPES)
+def test_key_ranges_whole_call_and_partial(Hq, Hkv, D, P, lens, whole):
     import torch
     import paper_2507_07966_amd as pa
     x = wl.make_custom("bf16", Hq, Hkv, D, P, lens, seed=P + Hq)
@@ -37,6 +39,9 @@ def test_key_ranges_whole_call_and_partial(Hq, Hkv, D, P, lens):
     check(out, lse, ro, rl, f"key ranges {Hq}/{Hkv}/{D} P={P} {lens}")
     dev = [to_device(x, n) for n in ("q", "k_prefix", "v_prefix", "k_suffix", "v_suffix")]
     plan = pa.prefix_attn_plan(Hq, Hkv, D, P, list(lens), x.workload.scale, dtype="bf16", device=0)
+    items = plan.launch_items(0)
+    slots = items[items[:, 0] >= 0][:, 7]
+    assert (slots >= 0).any() and (slots < 0).any() == whole
     T = sum(lens)
     ws = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda").random_(0, 255)
     o = torch.full((T, Hq, D), float("nan"), device="cuda")
@@ -76,7 +81,8 @@ def test_split_prefix_near_the_size_of_the_static_workspace(Hq, Hkv, D, P, lens)
                                              x.workload.scale, rows=rows)
     out, lse, plan, dev, ws, _, _ = run_hip(x, return_plan=True)
     check(out[rows], lse[:, rows], ro, rl, label)
-    assert len({int(k) for k in plan.items(0)[:, 4]}) > 1 and plan.workspace_bytes <= pa.STATIC_SCRATCH_BYTES
+    assert len({int(k) for k in plan.items(0)[:, 4]}) > 1 and len(plan.launch_items(0)) == 0
+    assert plan.workspace_bytes <= pa.STATIC_SCRATCH_BYTES
     T = sum(lens)
     names = ("q", "k_prefix", "v_prefix", "k_suffix", "v_suffix")
     so = torch.full((T, Hq, D), float("nan"), device="cuda", dtype=torch.bfloat16)
@@ -113,6 +119,7 @@ def test_key_ranges_whose_scores_are_all_minus_infinity(Hq, Hkv, D, P, lens, hid
     ro, rl, _ = cref.prefix_shared_attention(x.q, x.k_prefix, x.v_prefix, x.k_suffix, x.v_suffix, x.suffix_lens,
                                              x.workload.scale, rows=rows)
     out, lse, plan, dev, ws, _, _ = run_hip(x, return_plan=True)
+    assert plan.launch_slots(0) > 0
     check(out[rows], lse[:, rows], ro, rl, "hidden keys")
     o = torch.full((sum(lens), Hq, D), float("nan"), device="cuda")
     l = torch.full((sum(lens), Hq), float("nan"), device="cuda")
@@ -130,7 +137,8 @@ def test_key_ranges_keep_an_infinite_value_infinite():
     clean, clean_lse = run_hip(x)
     x.v_suffix[0, 0, 5] = np.inf
     x.bits["v_suffix"], _ = wl.round_to_bf16(x.v_suffix)
-    out, lse = run_hip(x)
+    out, lse, plan, *_ = run_hip(x, return_plan=True)
+    assert plan.launch_slots(0) > 0
     assert np.isposinf(out[:, :7, 5]).all()
     out[:, :7, 5] = clean[:, :7, 5]
     assert np.array_equal(out, clean) and np.array_equal(lse, clean_lse)
