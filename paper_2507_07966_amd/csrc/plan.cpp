@@ -10,9 +10,7 @@
 #include <cmath>
 #include <functional>
 #include <initializer_list>
-#include <map>
 #include <new>
-#include <queue>
 #include <utility>
 
 #include "common.h"
@@ -216,6 +214,38 @@ void build_sweep_items(prefix_attn_plan_t& p) {
   interleave_over_xcds(per_head, p.num_xcd, PAD_ITEM, p.sweep_items);
 }
 
+// When the last of `cost` (whole units) ends, the longest first on whichever of `at_once` workers is free; a value of at least
+// `enough` if that is certain beforehand or on the way.  Sorts `cost`.
+int list_schedule(std::vector<int>& cost, int at_once, double enough) {
+  int64_t sum = 0;
+  int longest = 0;
+  for (int t : cost) {
+    sum += t;
+    longest = std::max(longest, t);
+  }
+  if ((int)cost.size() <= at_once) return longest;
+  const int least = std::max(longest, (int)std::min<int64_t>((sum + at_once - 1) / at_once, INT32_MAX));
+  if (least >= enough) return least;
+  std::sort(cost.begin(), cost.end(), std::greater<int>());
+  // a heap of the times at which the workers are free, the earliest at the top
+  std::vector<int> free(cost.begin(), cost.begin() + at_once);
+  std::reverse(free.begin(), free.end());  // ascending: a heap already
+  int end = longest;
+  for (size_t n = at_once; n < cost.size(); ++n) {
+    const int t = free[0] + cost[n];
+    end = std::max(end, t);
+    if (end >= enough) return end;
+    size_t at = 0;
+    for (size_t child; (child = 2 * at + 1) < free.size(); at = child) {
+      if (child + 1 < free.size() && free[child + 1] < free[child]) ++child;
+      if (free[child] >= t) break;
+      free[at] = free[child];
+    }
+    free[at] = t;
+  }
+  return end;
+}
+
 // Into how many ranges of key tiles to cut each block of rows so that one workgroup per CU ends early.  Whole blocks take
 // ceil(blocks / CUs) rounds, and the last one may hold a single block; a call of few rows has fewer blocks than CUs.
 struct CutCosts {
@@ -231,39 +261,28 @@ struct CutCosts {
 std::vector<int> cut_blocks(const std::vector<int>& tiles, const std::vector<int>& most, int cus, const CutCosts& c,
                             double whole_us, size_t max_slots) {
   const int N = (int)tiles.size(), rest = N % cus;
-  std::vector<double> cost;
+  std::vector<int> cost;  // tiles
   std::vector<int> pieces(N, 1), chosen;
-  auto estimate = [&]() {
+  const int item_tiles = (int)c.item_tiles;
+  auto estimate = [&](double enough_us) {
     size_t slots = 0, items = 0;
-    cost.clear();
     for (int b = 0; b < N; ++b) {
       if (pieces[b] > 1) slots += pieces[b];
       items += pieces[b];
     }
     if (slots > 0 && items > (size_t)N + 2 * cus) return 1e30;  // two ranges a CU even out what there is to even out
-    for (int b = 0; b < N; ++b) {
-      for (int i = 0; i < pieces[b]; ++i) cost.push_back((tiles[b] + pieces[b] - 1) / pieces[b] + c.item_tiles);
-    }
     if (slots > max_slots) return 1e30;
-    std::sort(cost.begin(), cost.end(), std::greater<double>());
-    double end = cost.empty() ? 0.0 : cost.front();
-    if ((int)cost.size() > cus) {
-      std::vector<double> heap(cus, 0.0);  // when each CU is free, the earliest first
-      for (double t : cost) {
-        std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
-        heap.back() += t;
-        end = std::max(end, heap.back());
-        std::push_heap(heap.begin(), heap.end(), std::greater<double>());
-      }
-    }
-    return c.tile_us * end + (slots ? (double)slots * c.slot_us + c.launch_us : 0.0);
+    cost.clear();
+    for (int b = 0; b < N; ++b) cost.insert(cost.end(), pieces[b], (tiles[b] + pieces[b] - 1) / pieces[b] + item_tiles);
+    const double extra = slots ? (double)slots * c.slot_us + c.launch_us : 0.0;
+    return c.tile_us * list_schedule(cost, cus, (enough_us - extra) / c.tile_us) + extra;
   };
   double sum = 0.0;
   for (int t : tiles) sum += t + c.item_tiles;
-  double best_us = whole_us >= 0.0 ? whole_us : 0.95 * estimate();
+  double best_us = whole_us >= 0.0 ? whole_us : 0.95 * estimate(1e30);
   if (c.tile_us * sum / cus + c.launch_us >= best_us) return chosen;  // nothing to gain
   auto consider = [&]() {
-    const double us = estimate();
+    const double us = estimate(best_us);
     if (us < best_us) {
       best_us = us;
       chosen = pieces;
@@ -485,10 +504,10 @@ void build_key_items(prefix_attn_plan_t& p) {
         if (p.suffix_split && r.tile_e_full > r.tile_full) {
           suf.push_back({g, key0, c, n, r.tile_b, r.tile_full, 0, r.tile_e_full < r.tile_e ? r.tile_e_full : -1});
           // the mask-free kernel indexes keys over all packed tokens: key0 is the packed token index here
-          full.push_back({-2, p.cu[g] + key0, c, n, r.tile_full, r.tile_e_full, 1, -1});
+          full.push_back({-2, p.cu[g] + key0, c, n, r.tile_full, r.tile_e_full, g, -1});
         } else {
           suf.push_back({g, key0, c, n, r.tile_b, r.tile_e, 0, -1});
-          if (p.suffix_split) full.push_back({-1, p.cu[g] + key0, c, n, 0, 0, 1, -1});  // no tiles
+          if (p.suffix_split) full.push_back({-1, p.cu[g] + key0, c, n, 0, 0, g, -1});  // no tiles
         }
       }
   auto tiles_of = [](const pa::KeyItem& a) { return a.tile1 - a.tile0 + (a.extra_tile >= 0 ? 1 : 0); };
@@ -510,8 +529,12 @@ void build_key_items(prefix_attn_plan_t& p) {
 //
 // A launch with fewer than two items per CU is as long as its longest item, and that is often an own block (the first
 // keys of a rollout are seen by all of its rows).  Those blocks are then cut into ranges of at most `limit` row
-// tiles, each leaving a partial; the limit is the one for which list scheduling over the CUs ends first.  Launches
-// with more items keep whole blocks: their partials would be re-read for a tail that is short anyway.
+// tiles, each leaving a partial; the limit is the one for which list scheduling over the CUs ends first, the time of the
+// partials (written and read at 4 TB/s, and the launch that adds them) included.  Time of a row tile: 1.87 (1.0) us at
+// D = 128 (64).  Backward pass with 2 ... 16 ranges a block: 4 heads of 128, 9,115 tokens 402 us whole, 352 (2 ranges,
+// taken), 373 (16); 28 / 4 heads, 2,600 tokens 565 whole, 240 (5, taken), 265 (16); 4,096 prefix keys, 2 x 1,250 tokens 746
+// whole, 590 (5, taken).  Launches with more items keep whole blocks: their partials would be re-read for a tail that is
+// short anyway.
 void build_key_launch(prefix_attn_plan_t& p) {
   p.key_launch.clear();
   p.key_sums.clear();
@@ -521,72 +544,71 @@ void build_key_launch(prefix_attn_plan_t& p) {
   const bool cut_prefix = p.row_splits > 1;
   auto tiles_of = [](const pa::KeyItem& a) { return a.tile1 - a.tile0 + (a.extra_tile >= 0 ? 1 : 0); };
 
-  std::vector<int> others;  // tiles of the items that are not cut here
+  size_t prefix_real = 0;
+  int prefix_tiles = 0;
   for (const pa::KeyItem& it : p.key_items[0])
-    if (it.c >= 0) others.push_back(it.tile1 - it.tile0);
+    if (it.c >= 0) {
+      ++prefix_real;
+      prefix_tiles = std::max(prefix_tiles, it.tile1 - it.tile0);
+    }
   int limit = 0;  // most row tiles of an own item; 0: no limit
-  if (!p.suffix_split && !p.key_items[1].empty() && others.size() + p.key_items[1].size() < 2 * (size_t)p.num_cu) {
+  if (!p.suffix_split && !p.key_items[1].empty() && prefix_real + p.key_items[1].size() < 2 * (size_t)p.num_cu) {
+    const double tile_us = p.desc.head_dim == 128 ? 1.87 : 1.0;
+    const double slot_us = 2.0 * pa::KEYS_PER_KEY_ITEM * p.desc.head_dim * 4 * 2 / 4e6, launch_us = 5.0;
     const int longest = tiles_of(p.key_items[1].front());
-    auto makespan = [&](int lim) {
-      std::vector<double> cost;
-      for (int t : others) cost.push_back(t + 3.0);
-      for (const pa::KeyItem& it : p.key_items[1]) {
-        const int t = tiles_of(it), n = lim ? (t + lim - 1) / lim : 1;
-        for (int i = 0; i < n; ++i) cost.push_back((double)t / n + (n > 1 ? 3.5 : 3.0));
-      }
-      std::sort(cost.begin(), cost.end(), std::greater<double>());
-      std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
-      for (int i = 0; i < p.num_cu; ++i) cu.push(0.0);
-      double end = 0.0;
-      for (double c : cost) {
-        const double t = cu.top() + c;
-        cu.pop();
-        cu.push(t);
-        end = std::max(end, t);
-      }
-      return end;
-    };
-    double best = 0.95 * makespan(0) - 4.0;  // the sum of partials is one more launch (about 4 tiles' time)
-    for (int n = 2; n <= 16 && longest / n >= 16; ++n) {
+    std::vector<int> cost;  // half tiles
+    double best = 1e30;
+    for (int n = 1; n <= 16 && (n == 1 || longest / n >= 16); n += 1 + n / 6) {
       const int lim = (longest + n - 1) / n;
-      const double m = makespan(lim);
-      if (m < best) {
-        best = m;
+      size_t slots = 0;
+      cost.clear();
+      for (const pa::KeyItem& it : p.key_items[0])
+        if (it.c >= 0) cost.push_back(2 * (it.tile1 - it.tile0) + 6);
+      for (const pa::KeyItem& it : p.key_items[1]) {
+        const int t = tiles_of(it), k = n == 1 ? 1 : (t + lim - 1) / lim;
+        if (k > 1) slots += k;
+        for (int i = 0; i < k; ++i) cost.push_back(2 * t / k + (k > 1 ? 7 : 6));
+      }
+      if (slots > 4 * (size_t)p.num_cu) continue;  // at most 128 (64) MiB of workspace; the best cuts above have 100 to 570
+      const double extra = slots ? slots * slot_us + launch_us : 0.0;
+      const double end = list_schedule(cost, p.num_cu, 2.0 * (best - extra) / tile_us) / 2.0;  // stops beyond what could win
+      if (n == 1) best = 0.95 * end * tile_us;
+      else if (end * tile_us + extra < best) {
+        best = end * tile_us + extra;
         limit = lim;
       }
     }
   }
 
   // slots: those of a block are adjacent, in the order in which the reduction adds them
-  std::vector<pa::KeyItem> prefix, own;
+  std::vector<int> first;  // of a prefix block
+  const int prefix_blocks = (int)((p.desc.prefix_len + pa::KEYS_PER_KEY_ITEM - 1) / pa::KEYS_PER_KEY_ITEM);
   if (cut_prefix) {
-    std::vector<std::vector<int>> first(p.desc.num_kv_heads, std::vector<int>((p.desc.prefix_len + pa::KEYS_PER_KEY_ITEM - 1) / pa::KEYS_PER_KEY_ITEM, -1));
-    for (pa::KeyItem it : p.key_items[0]) {
-      if (it.c >= 0) {
-        int& slot0 = first[it.c][it.key0 / pa::KEYS_PER_KEY_ITEM];
-        if (slot0 < 0) {
-          slot0 = p.key_slots;
-          p.key_slots += p.row_splits;
-          p.key_sums.push_back({0, it.key0, it.c, it.nkeys, slot0, p.row_splits});
-        }
-        it.slot = slot0 + it.slot;  // the prefix list's items carry their range's number
-      }
-      prefix.push_back(it);
-    }
-  } else {
-    for (pa::KeyItem it : p.key_items[0]) {
-      it.slot = -1;
-      prefix.push_back(it);
+    first.assign((size_t)p.desc.num_kv_heads * prefix_blocks, -1);
+    for (const pa::KeyItem& it : p.key_items[0]) {
+      if (it.c < 0) continue;
+      int& slot0 = first[(size_t)it.c * prefix_blocks + it.key0 / pa::KEYS_PER_KEY_ITEM];
+      if (slot0 >= 0) continue;
+      slot0 = p.key_slots;
+      p.key_slots += p.row_splits;
+      p.key_sums.push_back({0, it.key0, it.c, it.nkeys, slot0, p.row_splits});
     }
   }
-  std::map<std::pair<int, int>, int> masked_slot;  // split pass: (kv head, packed first key) -> slot of the masked item
+  std::vector<pa::KeyItem> own;
+  // split pass: where the masked item of a block stands in `own`.  Blocks of a kv head are numbered cu[g] / KB + g + key0 / KB
+  // (unique: a rollout leaves at most one number unused)
+  const int KB = pa::KEYS_PER_KEY_ITEM;
+  const int64_t numbers = p.T / KB + p.desc.num_rollouts;
+  std::vector<int> masked(p.suffix_split ? numbers * p.desc.num_kv_heads : 0);
+  auto number = [&](int c, int g, int key0) { return c * numbers + p.cu[g] / KB + g + key0 / KB; };
+  own.reserve(p.key_items[1].size());
   for (pa::KeyItem it : p.key_items[1]) {
     const int t = tiles_of(it), n = limit ? (t + limit - 1) / limit : 1;
     const int packed = p.cu[it.g] + it.key0;
     it.slot = -1;
     if (it.extra_tile >= 0 || n == 1) {
+      if (p.suffix_split) masked[number(it.c, it.g, it.key0)] = (int)own.size();
       own.push_back(it);
-      masked_slot[{it.c, packed}] = (int)own.size() - 1;
       continue;
     }
     p.key_sums.push_back({1, packed, it.c, it.nkeys, p.key_slots, n});
@@ -599,9 +621,10 @@ void build_key_launch(prefix_attn_plan_t& p) {
     }
   }
   std::vector<pa::KeyItem> full;
+  full.reserve(p.key_items_full.size());
   for (pa::KeyItem it : p.key_items_full) {
     if (it.c >= 0 && it.tile1 > it.tile0) {  // masked item and mask-free item: one partial each
-      pa::KeyItem& m = own[masked_slot[{it.c, it.key0}]];
+      pa::KeyItem& m = own[masked[number(it.c, it.slot, it.key0 - p.cu[it.slot])]];
       p.key_sums.push_back({1, it.key0, it.c, it.nkeys, p.key_slots, 2});
       m.slot = p.key_slots++;
       it.slot = p.key_slots++;
@@ -613,20 +636,25 @@ void build_key_launch(prefix_attn_plan_t& p) {
   std::stable_sort(own.begin(), own.end(), [&](const pa::KeyItem& a, const pa::KeyItem& b) { return tiles_of(a) > tiles_of(b); });
 
   // launch order; the lists laid out over the XCDs start at a multiple of the XCD count
+  size_t real = own.size() + prefix_real;
+  for (const pa::KeyItem& it : full) real += it.c >= 0;
+  p.key_launch.reserve(full.size() + p.key_items[0].size() + own.size() + 4 * p.num_xcd);
   auto append = [&](const pa::KeyItem* b, const pa::KeyItem* e) {
-    while ( p.key_launch.size() % p.num_xcd != 0) p.key_launch.push_back(pad);
+    while (p.key_launch.size() % p.num_xcd != 0) p.key_launch.push_back(pad);
     p.key_launch.insert(p.key_launch.end(), b, e);
   };
-  int prefix_tiles = 0;
-  for (const pa::KeyItem& it : prefix)
-    if (it.c >= 0) prefix_tiles = std::max(prefix_tiles, it.tile1 - it.tile0);
-  size_t real = own.size();
-  for (const auto* v : {&prefix, &full})
-    for (const pa::KeyItem& it : *v) real += it.c >= 0;
+  auto append_prefix = [&]() {
+    append(nullptr, nullptr);
+    for (pa::KeyItem it : p.key_items[0]) {
+      // the prefix list's items carry their row range's number
+      it.slot = it.c >= 0 && cut_prefix ? first[(size_t)it.c * prefix_blocks + it.key0 / pa::KEYS_PER_KEY_ITEM] + it.slot : -1;
+      p.key_launch.push_back(it);
+    }
+  };
   p.key_mask_free = -1;
+  append(full.data(), full.data() + full.size());
   if (real >= 4 * (size_t)p.num_cu) {
-    append(full.data(), full.data() + full.size());
-    append(prefix.data(), prefix.data() + prefix.size());
+    append_prefix();
     append(nullptr, nullptr);  // pads, so that the count below is where the masked items begin
     p.key_mask_free = (int64_t)p.key_launch.size();
     append(own.data(), own.data() + own.size());
@@ -634,9 +662,8 @@ void build_key_launch(prefix_attn_plan_t& p) {
   }
   size_t long_own = 0;
   while (long_own < own.size() && full.empty() && tiles_of(own[long_own]) > prefix_tiles) ++long_own;
-  append(full.data(), full.data() + full.size());
   append(own.data(), own.data() + long_own);
-  append(prefix.data(), prefix.data() + prefix.size());
+  append_prefix();
   append(own.data() + long_own, own.data() + own.size());
 }
 
