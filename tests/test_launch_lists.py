@@ -175,3 +175,24 @@ def test_launch_list_arguments():
     assert lib.prefix_attn_plan_num_launch_sums(plan.handle, 3) == -1 and lib.prefix_attn_plan_launch_slots(plan.handle, -1) == -1
     f32 = host_plan(dtype="f32")
     assert all(len(f32.launch_items(w)) == 0 for w in (0, 1, 2)) and all(len(plan.launch_items(w)) == 0 for w in (3, 4))
+
+
+def best_plan_time(repeats=12, **kw):
+    import time
+    best = float("inf")
+    for _ in range(repeats):
+        t = time.perf_counter()
+        host_plan(**kw)
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+@pytest.mark.parametrize("heads,D,lens", [((4, 4), 64, 15976), ((4, 4), 128, 15000), ((14, 2), 64, 4400)])
+def test_search_for_cuts_is_a_small_part_of_making_a_plan(heads, D, lens):
+    """A plan whose own key blocks are candidates for cuts against one of twice the length, which has too many blocks for
+    the search: 1.4 to 2.2 times its time.  (A search that scheduled every candidate took 7 to 13 times.)  And the cuts are
+    bounded: four partial-gradient slots per CU."""
+    kw = dict(num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=D, prefix_len=0)
+    plan = host_plan(suffix_lens=[lens], **kw)
+    assert plan.launch_slots(2) <= 4 * 256
+    assert best_plan_time(suffix_lens=[lens], **kw) < 5 * best_plan_time(suffix_lens=[2 * lens], **kw)
