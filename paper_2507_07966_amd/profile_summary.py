@@ -17,31 +17,29 @@ import sys
 
 
 def short_name(k: str) -> str:
-    # mangled template arguments: <head_dim, causal, epilogue, sweep, careful> / <head_dim, causal, partial> / <head_dim, partial>
-    if "pass_bf16_kernel" in k:
-        m = re.search(r"pass_bf16_kernelILi\d+ELb(\d)ELi(\d)ELb(\d)ELb(\d)E", k)
+    if "pass_bf16_kernel" in k:     # mangled template arguments <head_dim, causal, epilogue, sweep, ranges, careful>
+        m = re.search(r"pass_bf16_kernelILi\d+ELb(\d)ELi(\d)ELb(\d)ELb(\d)ELb(\d)EEE", k)
         if m is None:
             return "attention pass (bf16 MFMA)"
-        causal, epi, sweep, careful = (int(v) for v in m.groups())
+        causal, epi, sweep, ranges, careful = (int(v) for v in m.groups())
         if careful:     # second launch of every pass: redoes the items the common kernel gave up on (none, normally)
-            return "careful kernel of the " + ("prefix pass" if not causal else "sweep" if sweep else "suffix pass")
+            return "careful kernel of the " + ("prefix pass" if not causal else "key ranges" if ranges else
+                                               "sweep" if sweep else "suffix pass")
         if not causal:
             return "prefix_pass (bf16 MFMA)"
         if sweep:
-            return "attention_sweep (bf16 MFMA)" + (", fp32 partial" if epi == 0 else "")
+            return f"attention_{'ranges' if ranges else 'sweep'} (bf16 MFMA)" + (", fp32 partial" if epi == 0 else "")
         return "suffix_pass (bf16 MFMA)" + ("" if epi == 0 else ", final" if epi == 1 else ", merging")
     if "bwd_dkv_reduce" in k:
         return "bwd_dkv: add partial gradients"
     if "bwd_dq_reduce" in k:
         return "bwd_dq: add key splits"
-    if "bwd_dkv_kernel" in k:      # <head_dim, masked, partial gradients>
-        if "ELb1ELb0E" in k:
-            return "bwd_dkv_suffix (bf16 MFMA)"
+    if "bwd_dkv_kernel" in k:      # <head_dim, mask-free items, masked items>
         if "ELb1ELb1E" in k:
-            return "bwd_dkv_suffix (bf16 MFMA), masked tiles, partials"
-        # mask-free: the prefix keys, or (with partial gradients) their row splits and a long rollout's own keys
-        return "bwd_dkv mask-free (bf16 MFMA), partials" if "ELb0ELb1E" in k else "bwd_dkv_prefix (bf16 MFMA)"
-    if "bwd_dq_kernel" in k:
+            return "bwd_dkv_one_launch (bf16 MFMA)"
+        # mask-free: the prefix keys, and the tiles of long rollouts' own keys that every row sees; masked: own keys
+        return "bwd_dkv_mask_free (bf16 MFMA)" if "ELb1ELb0E" in k else "bwd_dkv_masked (bf16 MFMA)"
+    if "bwd_dq_kernel" in k:       # <head_dim, some blocks cut into key ranges>
         return "bwd_dq (bf16 MFMA)" + (", key splits" if "ELb1E" in k else "")
     if "bwd_prep" in k:
         return "bwd_prepass"
@@ -55,6 +53,8 @@ def short_name(k: str) -> str:
         return "attention pass (fp32)"
     if "merge_n_kernel" in k:
         return "merge_partials (n-way)"
+    if "merge_slots_kernel" in k:
+        return "merge of key ranges"
     if "merge_kernel" in k:
         return "merge"
     if "vt_image_kernel" in k:      # <head_dim, key order of the 32x32x16 products>: the backward's images of K
@@ -62,6 +62,8 @@ def short_name(k: str) -> str:
         return "k_layout_prepass (backward)" if re.search(r"vt_image_kernel(ILi\d+ELb1E|<\d+, true>)", k) else "v_layout_prepass"
     if "lse_export" in k:
         return "lse_export"
+    if "group_advantages" in k:
+        return "group_advantages"
     if "elementwise" in k and "Mul" in k or "mul" in k.lower() and "elementwise" in k:
         return "plain copy kernel (torch mul by 1)"
     return k[:60]
