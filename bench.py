@@ -230,6 +230,9 @@ def main():
     achieved = dom_flop / (dom_ms * 1e-3) * 1e-12
     e = 2 if w.dtype == "bf16" else 4
     merge_bytes = T * w.num_q_heads * (w.head_dim * ((8 if P else 4) + e) + (12 if P else 8))
+    if plan.launch_slots(0):   # blocks of rows cut into key ranges: their partials are read, their rows written
+        merge_bytes = (plan.launch_slots(0) * 256 * (w.head_dim + 1) * 4
+                       + int(plan.launch_sums(0)[:, 3].sum()) * (w.head_dim * e + 4))
     result = {
         "metric": "effective attention TFLOP/s",
         "value": round(tflops, 2),
@@ -256,7 +259,7 @@ def main():
         "plan_ms": round(plan_ms, 3),
         "plan_first_call_ms": round(plan_first_ms, 3),
         "kernel_ms": {"v_layout_prepass": round(k_prepass_ms, 4), "prefix_pass": round(k_prefix_ms, 4), "suffix_pass": round(k_suffix_ms, 4), "merge": round(k_merge_ms, 4)},
-        # bf16 calls combine the two partials in the suffix pass's epilogue: no merge launch (its slot reads ~0)
+        # no merge launch (its slot reads ~0) where a pass writes the result itself; otherwise it adds key ranges
         "merge_hbm_gbs": round(merge_bytes / (k_merge_ms * 1e-3) * 1e-9, 1) if k_merge_ms > 0.01 else None,
         "rocm_smi": state,
         "roofline": {"kernel": dom_name, "bound": "mfma", "achieved": round(achieved, 2), "peak": MFMA_BF16_PEAK_TFLOPS,
@@ -632,8 +635,11 @@ def backward_main(args, pa, wl, torch, w, x, dev, plan, out, lse):
     pairs = wl.visible_pairs(P, x.suffix_lens)
     flop = wl.backward_flop(w.num_q_heads, w.head_dim, P, x.suffix_lens)
     tflops = flop / (ms_per_step * 1e-3) * 1e-12
-    # dominant kernel: the dK/dV pass over the prefix keys executes four products (S, dW, dV, dK) per pair
-    if has_p:
+    # dominant kernel: the dK/dV pass over the prefix keys executes four products (S, dW, dV, dK) per pair; where own keys
+    # run in the same launch, the pass over all keys
+    if has_p and (plan.mask_free_items() < 0 or len(plan.key_items(2))):
+        dom_name, dom_flop, dom_ms = "bwd_dkv", 8 * w.head_dim * w.num_q_heads * pairs, float(kms[2] + kms[3])
+    elif has_p:
         dom_name, dom_flop, dom_ms = "bwd_dkv_prefix", 8 * w.head_dim * w.num_q_heads * T * P, float(kms[2])
     else:
         dom_name, dom_flop, dom_ms = "bwd_dkv_suffix", 8 * w.head_dim * w.num_q_heads * pairs, float(kms[3])

@@ -201,7 +201,9 @@ int prefix_attn_backward(const prefix_attn_plan_t* plan, const void* q, const vo
  * and the call WAITS for them.  kernel_ms (HOST [4]) receives the durations in milliseconds of
  * {pre-pass (delta, layouts), dQ pass, dK/dV pass over the prefix keys, dK/dV pass over the
  * rollouts' own keys and sums of partial gradients}; own keys whose items share the launch of the
- * prefix keys (calls with few key blocks) count in entry 2; for fp32 plans entry 2 is the whole dK/dV kernel and entry 3 is ~0. */
+ * prefix keys count in entry 2 (all of them in calls with few key blocks, the mask-free items of long
+ * rollouts: see prefix_attn_plan_mask_free_items); for fp32 plans entry 2 is the whole dK/dV kernel and
+ * entry 3 is ~0. */
 int prefix_attn_backward_timed(const prefix_attn_plan_t* plan, const void* q, const void* k_prefix,
                                const void* v_prefix, const void* k_suffix, const void* v_suffix,
                                const void* out, const void* d_out, const float* lse,
@@ -307,6 +309,9 @@ int prefix_attn_plan_launch_items(const prefix_attn_plan_t* plan, int32_t list, 
 int64_t prefix_attn_plan_num_launch_sums(const prefix_attn_plan_t* plan, int32_t list);
 int prefix_attn_plan_launch_sums(const prefix_attn_plan_t* plan, int32_t list, int32_t* sums_out);
 int64_t prefix_attn_plan_launch_slots(const prefix_attn_plan_t* plan, int32_t list);
+/* List 2: how many of its items, the mask-free ones, are a launch of their own before that of the masked ones; -1 if all
+ * items are one launch. */
+int64_t prefix_attn_plan_mask_free_items(const prefix_attn_plan_t* plan);
 
 /* Total suffix tokens T of the plan. */
 int64_t prefix_attn_plan_total_tokens(const prefix_attn_plan_t* plan);

@@ -939,6 +939,8 @@ int64_t prefix_attn_plan_launch_slots(const prefix_attn_plan_t* plan, int32_t li
   return list == 0 ? plan->range_slots : list == 1 ? plan->dq_slots : plan->key_slots;
 }
 
+int64_t prefix_attn_plan_mask_free_items(const prefix_attn_plan_t* plan) { return plan ? plan->key_mask_free : -1; }
+
 int64_t prefix_attn_plan_total_tokens(const prefix_attn_plan_t* plan) { return plan ? plan->T : -1; }
 
 int prefix_attn_backward_workspace(const prefix_attn_plan_t* plan, size_t* workspace_bytes_out) {

@@ -81,6 +81,10 @@ def check_key_list(plan, P, lens, group):
             cut.setdefault((own, at, c), []).append(slot)
         else:
             assert len(tiles[(own, at, c)]) == len(streamed)   # it writes the result: the block's only item
+    first = plan.mask_free_items()                    # a launch of the mask-free kernel, then one of the masked kernel
+    if first >= 0:
+        items = plan.launch_items(2)
+        assert (items[:first, 0][items[:first, 2] >= 0] < 0).all() and (items[first:, 0][items[first:, 2] >= 0] >= 0).all()
     heads = plan_heads(plan)
     want = {(0, k, c): range(row_tiles) for k in range(0, P, KEYS) for c in range(heads)}
     for g, n in enumerate(lens):
