@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <utility>
 
 #include "common.h"
@@ -134,8 +135,9 @@ __global__ __launch_bounds__(LP_THREADS, NB == 2 ? 4 : 2) void logprob_tile_kern
 #pragma unroll
     for (int b = 0; b < NB; ++b) C[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Per-lane LDS addresses of the operand reads, one set per buffer (the second buffer lies 64 KiB on,
-  // beyond the reach of a read's immediate offset), so the main loop itself holds no address arithmetic.
+  // Per-lane LDS addresses of the operand reads, one set per buffer (the second buffer lies 40 to 64 KiB on: with
+  // the panels' own offsets beyond the reach of a read's 16-bit immediate), so the main loop itself holds no address
+  // arithmetic.
   // (Row blocks of 16 share the swizzle of rows 0..15.)
   const unsigned char* wop[2][BK / 32];
   const unsigned char* hop[2][BK / 32];
@@ -307,9 +309,22 @@ __global__ __launch_bounds__(64) void group_advantages_kernel(const float* __res
 
 namespace {
 
-constexpr int64_t CUS = 256;
+// Compute units of the current device, asked once per device (a partitioned GPU has fewer than 256).
+int compute_units() {
+  static std::atomic<int> known[64];
+  int device = 0, cus = 0;
+  if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return NUM_CU;
+  cus = known[device].load(std::memory_order_relaxed);
+  if (cus > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1) {
+    (void)hipGetLastError();
+    return NUM_CU;
+  }
+  known[device].store(cus, std::memory_order_relaxed);
+  return cus;
+}
 
-int64_t tile_rounds(int nb, int64_t N, int TV) { return ((N + 32 * nb - 1) / (32 * nb) * TV + CUS - 1) / CUS; }
+int64_t tile_rounds(int nb, int64_t N, int TV, int64_t cus) { return ((N + 32 * nb - 1) / (32 * nb) * TV + cus - 1) / cus; }
 
 template <int NB>
 int launch_tiles(const LogprobArgs& a, int TV, hipStream_t s) {
@@ -332,10 +347,11 @@ int launch_logprob(const LogprobArgs& a, void* stream) {
   // Against 256-token tiles, V = 152,064: 333 tokens 489 -> 447 us, 128 tokens 297 -> 276; V = 50,000, d = 1536:
   // 640 tokens 121 -> 101, 4100 tokens 568 -> 544.  A smaller tile has to promise 2 %.  Up to 64 tokens the call is
   // bound by reading W: two 64-token workgroups per CU keep more loads in flight (314 -> 229 us, 4.8 TB/s).
+  const int cus = compute_units();
   int nb = 8;
-  double best = 0.98 * tile_rounds(8, a.N, TV);
+  double best = 0.98 * tile_rounds(8, a.N, TV, cus);
   for (const auto& [smaller, t] : {std::pair{6, 0.78}, {4, 0.62}})
-    if (const double cost = tile_rounds(smaller, a.N, TV) * t; cost < best) {
+    if (const double cost = tile_rounds(smaller, a.N, TV, cus) * t; cost < best) {
       best = cost;
       nb = smaller;
     }
