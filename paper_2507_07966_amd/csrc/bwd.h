@@ -77,7 +77,7 @@ struct BwdDkvArgs {
   int64_t num_items, num_sums, Mpad;
   int32_t Hkv, D;
   float scale;
-  enum { BOTH, MASK_FREE, MASKED } kinds;  // of the items of this launch
+  enum { BOTH, MASK_FREE, OWN_MASK_FREE, MASKED } kinds;  // of the items of this launch; OWN_MASK_FREE: own keys only
   bool sum_partials;     // false: the pass over the items; true (afterwards): the sums of its partial gradients
 };
 int launch_bwd_dkv_bf16(const BwdDkvArgs& a, void* stream);

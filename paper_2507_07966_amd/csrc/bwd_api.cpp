@@ -191,8 +191,8 @@ int enqueue_backward(const prefix_attn_plan_t* plan, const BackwardArgs& x, void
   // without a prefix all of it is stage 3
   if (ev && !has_prefix && hipEventRecord(ev[3], hs) != hipSuccess) return PA_ERR_HIP;
   const int64_t items = (int64_t)plan->key_launch.size(), mask_free = plan->key_mask_free;
-  if (mask_free < 0 ? !launch(0, items, pa::BwdDkvArgs::BOTH) : !launch(0, mask_free, pa::BwdDkvArgs::MASK_FREE))
-    return PA_ERR_HIP;
+  const auto kinds = mask_free < 0 ? pa::BwdDkvArgs::BOTH : has_prefix ? pa::BwdDkvArgs::MASK_FREE : pa::BwdDkvArgs::OWN_MASK_FREE;
+  if (!launch(0, mask_free < 0 ? items : mask_free, kinds)) return PA_ERR_HIP;
   if (ev && has_prefix && hipEventRecord(ev[3], hs) != hipSuccess) return PA_ERR_HIP;
   if (mask_free >= 0 && !launch(mask_free, items, pa::BwdDkvArgs::MASKED)) return PA_ERR_HIP;
   kv.sum_partials = true;

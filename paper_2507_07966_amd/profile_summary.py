@@ -34,11 +34,15 @@ def short_name(k: str) -> str:
         return "bwd_dkv: add partial gradients"
     if "bwd_dq_reduce" in k:
         return "bwd_dq: add key splits"
-    if "bwd_dkv_kernel" in k:      # <head_dim, mask-free items, masked items>
-        if "ELb1ELb1E" in k:
+    if "bwd_dkv_kernel" in k:      # <head_dim, mask-free items, masked items, own keys only>
+        m = re.search(r"bwd_dkv_kernelILi\d+ELb(\d)ELb(\d)ELb(\d)E", k)
+        if m is None:
+            return "bwd_dkv (bf16 MFMA)"
+        free, masked, own = (int(v) for v in m.groups())
+        if free and masked:
             return "bwd_dkv_one_launch (bf16 MFMA)"
         # mask-free: the prefix keys, and the tiles of long rollouts' own keys that every row sees; masked: own keys
-        return "bwd_dkv_mask_free (bf16 MFMA)" if "ELb1ELb0E" in k else "bwd_dkv_masked (bf16 MFMA)"
+        return "bwd_dkv_masked (bf16 MFMA)" if masked else f"bwd_dkv_{'own_' if own else ''}mask_free (bf16 MFMA)"
     if "bwd_dq_kernel" in k:       # <head_dim, some blocks cut into key ranges>
         return "bwd_dq (bf16 MFMA)" + (", key splits" if "ELb1E" in k else "")
     if "bwd_prep" in k:

@@ -38,7 +38,7 @@ def test_every_kernel_of_the_library_has_a_label_of_its_own():
         kinds.setdefault(label, set()).add(base)
     assert all(len(v) == 1 for v in kinds.values()), {k: v for k, v in kinds.items() if len(v) > 1}
     dkv = {short_name(n) for n in names if "bwd_dkv_kernel" in n}
-    assert dkv == {f"bwd_dkv_{k} (bf16 MFMA)" for k in ("one_launch", "mask_free", "masked")}
+    assert dkv == {f"bwd_dkv_{k} (bf16 MFMA)" for k in ("one_launch", "mask_free", "own_mask_free", "masked")}
     passes = {re.sub("ILi64E", "ILi128E", n) for n in names if "pass_bf16_kernel" in n}
     assert len({short_name(n) for n in passes if n.split("EEEv")[0].endswith("Lb0")}) == 8   # every common kernel its own
 
