@@ -13,11 +13,12 @@
  *       s_j = softmax_scale * <q, k_j>,   LSE = ln sum_j exp(s_j),
  *       out = sum_j exp(s_j - LSE) v_j.
  *
- *   The library computes this in three steps: a prefix pass (no mask; all rollouts'
- *   rows of one kv head stacked against LDS-staged prefix K/V tiles), a causal suffix
- *   pass, and a log-sum-exp merge of the two partial results (a kernel of its own on the
- *   fp32 path; on the bf16 path the suffix pass does it in its epilogue).  On the bf16
- *   path a small layout pre-pass first rewrites V into transposed, LDS-ready tile images.
+ *   The library computes this in one to three steps.  bf16: a small layout pre-pass rewrites V into
+ *   transposed, LDS-ready tile images; then either one sweep over [prefix | own keys] (all rollouts'
+ *   rows of one kv head stacked against LDS-staged K/V tiles), where blocks of rows whose keys were cut
+ *   into ranges leave partial results that a log-sum-exp merge adds, or, for long prefixes, a prefix
+ *   pass (no mask) and a causal suffix pass that merges the two partial results in its epilogue (a
+ *   prefix cut into key ranges: an n-way merge of its partials and the suffix pass's).  fp32: one sweep.
  *
  * Conventions
  *   - No C++ types, no exceptions and no printing cross this boundary.  Every call

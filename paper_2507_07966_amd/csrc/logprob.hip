@@ -21,8 +21,8 @@
 // the tiles, walked in bands of four vocabulary tiles, so the 32 tiles running together on one XCD form an
 // 8-token-tile x 4-vocabulary-tile block: 12 distinct panels per step share that XCD's L2 instead of 64.
 // (Dealing whole token tiles to the XCDs instead left most of the chip idle when their number was not a
-// multiple of 8: 2,100 tokens x 152,064 words 6.04 ms, now 1.95; 8,200 tokens 12.97, now 7.20; 16,384 tokens,
-// where it was balanced, 13.84, now 13.48.)
+// multiple of 8: 2,100 tokens x 152,064 words 6.04 ms, now 1.95; 8,200 tokens 12.97, now 7.20; at 16,384 tokens,
+// where it was balanced, the two are within 1 %, 13.97 and 13.83.)
 // Kernel 2 combines the (m, l) pairs of a token over all vocabulary blocks: LSE = m + ln l,
 // logp = z_target - LSE.
 #include <hip/hip_runtime.h>

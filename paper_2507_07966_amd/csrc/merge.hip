@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void merge_n_kernel(MergeNArgs a) {
 // Merge of the range slots of the cut blocks: one thread handles 4 channels of one row, a workgroup 256 / (D / 4) rows of
 // one block.  A call of a few blocks is bound by the latency of the loads, so the slots are taken four at a time, with all
 // loads of a step in flight together and the weights rescaled when a later step holds a larger LSE (two loops over the
-// slots, the LSEs first, took 8.7 us for 128 tokens of 28 heads in 6 ranges; now 4.5).
+// slots, the LSEs first, took 8.7 us for 128 tokens of 28 heads in 6 ranges; now 4.1).
 struct SlotArgs {  // what the kernel reads of MergeNArgs
   const RangeSum* sums;
   const float* o_slots;

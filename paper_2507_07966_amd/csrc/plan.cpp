@@ -385,7 +385,7 @@ void build_dq_launch(prefix_attn_plan_t& p) {
 // and end, partials written and read at 4 TB/s, 5 us for the merge launch.  Up to two rounds of whole blocks: beyond
 // that the last round is at most a third of the call, its CUs run at a higher clock and the others' spread fills it.
 // 128 tokens, 28 / 4 heads of 128, 1,024 prefix keys (16 blocks, 6 ranges each): passes 37 -> 18 us, the whole call
-// with its LSE 45.3 -> 29.3 us.  88 blocks of a kv head for its 128 CUs (5,377
+// with its LSE 45.3 -> 27.5 us.  88 blocks of a kv head for its 128 CUs (5,377
 // prefix keys, 5 rollouts of 37 ... 1,901 tokens, 14 / 2 heads of 64), two ranges each: pass 114 -> 84 us, merge 8 us.
 // Cuts inside the own keys stay at or before the position of the block's first row: every row then sees the first key
 // of every range, so no partial is empty.
@@ -523,9 +523,10 @@ void build_key_items(prefix_attn_plan_t& p) {
 // The launch list of the bf16 dK/dV pass.  With fewer than four items per CU, prefix blocks, mask-free and masked own
 // blocks run in one launch, longest items first, so that the last round of one kind is filled with items of another:
 // 5,377 prefix keys, 5 rollouts of 37 ... 1,901 tokens, 14 / 2 heads of 64: 131 + 199 us in two launches, 155 in one
-// (own blocks cut, see below); 4,096 prefix keys, 8 rollouts of 1,152, 28 / 4 heads of 128: 1,196 -> 1,128.  Larger
-// launches lose nothing to their last round, and the kernel that holds both kinds runs the mask-free items 1 % slower
-// (32,768 own keys: 13.44 ms in two launches, 13.52 in one), so they stay two launches.
+// (own blocks cut, see below); 4,096 prefix keys, 8 rollouts of 1,152, 28 / 4 heads of 128: the whole backward pass 1 %
+// faster (2,090 -> 2,067 us in alternating calls).  Larger launches lose nothing to their last round, and the kernel that
+// holds both kinds runs the mask-free items 1 % slower (32,768 own keys: 13.44 ms in two launches, 13.52 in one), so they
+// stay two launches.
 //
 // A launch with fewer than two items per CU is as long as its longest item, and that is often an own block (the first
 // keys of a rollout are seen by all of its rows).  Those blocks are then cut into ranges of at most `limit` row
@@ -557,7 +558,7 @@ void build_key_launch(prefix_attn_plan_t& p) {
     const double slot_us = 2.0 * pa::KEYS_PER_KEY_ITEM * p.desc.head_dim * 4 * 2 / 4e6, launch_us = 5.0;
     const int longest = tiles_of(p.key_items[1].front());
     std::vector<int> cost;  // half tiles
-    double best = 1e30;
+    double whole = 1e30, best = 1e30;
     for (int n = 1; n <= 16 && (n == 1 || longest / n >= 16); n += 1 + n / 6) {
       const int lim = (longest + n - 1) / n;
       size_t slots = 0;
@@ -571,10 +572,11 @@ void build_key_launch(prefix_attn_plan_t& p) {
       }
       if (slots > 4 * (size_t)p.num_cu) continue;  // at most 128 (64) MiB of workspace; the best cuts above have 100 to 570
       const double extra = slots ? slots * slot_us + launch_us : 0.0;
-      const double end = list_schedule(cost, p.num_cu, 2.0 * (best - extra) / tile_us) / 2.0;  // stops beyond what could win
-      if (n == 1) best = 0.95 * end * tile_us;
-      else if (end * tile_us + extra < best) {
-        best = end * tile_us + extra;
+      const double enough = std::min(whole, 1.02 * best);  // of two that are within 2 % the one with shorter items
+      const double us = list_schedule(cost, p.num_cu, 2.0 * (enough - extra) / tile_us) / 2.0 * tile_us + extra;
+      if (n == 1) whole = best = 0.95 * us;
+      else if (us < enough) {
+        best = std::min(best, us);
         limit = lim;
       }
     }
