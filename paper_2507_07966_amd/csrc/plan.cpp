@@ -382,11 +382,16 @@ void build_dq_launch(prefix_attn_plan_t& p) {
 
 // Forward, the sweep over [prefix | own keys] with some blocks of rows cut into ranges (cut_blocks), one launch and one
 // merge of the cut blocks.  Costs measured at D = 128 (64): 1.56 (0.9) us per key tile, 5 tiles' time for an item's start
-// and end, partials written and read at 4 TB/s, 5 us for the merge launch.  Up to two rounds of whole blocks: beyond
-// that the last round is at most a third of the call, its CUs run at a higher clock and the others' spread fills it.
+// and end, partials written and read at 4 TB/s, 8 us for the merge launch (4 us of its own, but
+// a small call is bound by the rate of launches: with 5 here calls of 5 to 12 prefix tiles were cut, 20.5 -> 22.5 us).  Up
+// to two rounds of whole blocks: beyond that the last round is at most a third of the call, its CUs run at a higher clock and the others' spread fills it.
 // 128 tokens, 28 / 4 heads of 128, 1,024 prefix keys (16 blocks, 6 ranges each): passes 37 -> 18 us, the whole call
 // with its LSE 45.3 -> 27.5 us.  88 blocks of a kv head for its 128 CUs (5,377
 // prefix keys, 5 rollouts of 37 ... 1,901 tokens, 14 / 2 heads of 64), two ranges each: pass 114 -> 84 us, merge 8 us.
+// With few rows the alternative is the prefix pass over key ranges (one partial of every row a range), a suffix pass and the
+// n-way merge.  Cuts win (7,922 keys, 4 rollouts of up to 9 tokens, 4 heads of 128: 32 us, else 44) unless the 64 MiB
+// workspace has too little room for the 256-row slots of short blocks; then the two are compared as they fit: 54,411 keys, 6
+// rollouts of up to 19 tokens, 4 heads of 128: 392 us in the cuts that fit, 166 with 10 key ranges of the prefix.
 // Cuts inside the own keys stay at or before the position of the block's first row: every row then sees the first key
 // of every range, so no partial is empty.
 void build_range_items(prefix_attn_plan_t& p, size_t fixed_bytes, size_t slot_bytes) {
@@ -406,15 +411,27 @@ void build_range_items(prefix_attn_plan_t& p, size_t fixed_bytes, size_t slot_by
     most.push_back(std::min(PA_MAX_PARTIALS, std::min(tiles.back(), tp + it.row0 / p.group / BN + 1)));
   }
   const size_t bytes_per_slot = (size_t)pa::ROWS_PER_ITEM * (p.desc.head_dim + 1) * sizeof(float);
-  const CutCosts costs{p.desc.head_dim == 128 ? 1.56 : 0.9, 5.0, heads * (double)bytes_per_slot * 2 / 4e6, 5.0};
+  const CutCosts costs{p.desc.head_dim == 128 ? 1.56 : 0.9, 5.0, heads * (double)bytes_per_slot * 2 / 4e6, 8.0};
   // what fitted the library's own workspace keeps fitting
   const size_t had = (size_t)(p.key_splits + 1) * slot_bytes;
   const size_t room = fixed_bytes + had <= PA_STATIC_SCRATCH_BYTES ? PA_STATIC_SCRATCH_BYTES - fixed_bytes : ~(size_t)0;
   // flags of at most two ranges a CU beside the blocks, and the pads of the layout over the XCDs
   const size_t flags = (blocks.size() * heads + 2 * (size_t)p.num_cu + p.num_xcd) * pa::WAVES_PER_ITEM * sizeof(int32_t) + 4 * 256;
   size_t max_slots = room == ~(size_t)0 ? room : room <= flags ? 0 : (room - flags) / (bytes_per_slot + 256) / heads;
-  const std::vector<int> pieces =
-      cut_blocks(tiles, most, p.num_cu / heads, costs, p.key_splits > 1 ? 1e30 : -1.0, max_slots);
+  const int KS = p.key_splits;
+  const double whole_us = KS > 1 ? 1e30 : -1.0;
+  std::vector<int> pieces = cut_blocks(tiles, most, p.num_cu / heads, costs, whole_us, KS > 1 ? ~(size_t)0 : max_slots);
+  size_t slots = 0;
+  for (int n : pieces) slots += n > 1 ? n : 0;
+  if (KS > 1 && slots > max_slots) {
+    const double rows = (double)p.T * p.desc.num_q_heads;
+    const double partials_us = (KS + 1) * rows * (p.desc.head_dim + 1) * 4 * 2 / 4e6;
+    CutCosts short_blocks = costs;  // of a slot only the block's rows are written and read
+    short_blocks.slot_us *= rows / ((double)p.items[1].size() * pa::ROWS_PER_ITEM);
+    const double other_us = costs.tile_us * ((tp + KS - 1) / KS + tiles.front() - tp + 2 * costs.item_tiles) + partials_us +
+                            2 * costs.launch_us;
+    pieces = cut_blocks(tiles, most, p.num_cu / heads, short_blocks, other_us, max_slots);
+  }
   if (pieces.empty()) return;
 
   lay_out_ranges(p, pieces, true, p.range_items, p.range_sums, p.range_slots);

@@ -24,7 +24,7 @@ SHAPES = [s + (False,) for s in SHAPES] + [s + (True,) for s in [
     (6, 3, 64, 700, (9000, 77)),           # kv heads that share no layout over the XCDs, 216 blocks
     (14, 2, 64, 5377, (1500, 37, 1200, 1901, 60)),   # 131 blocks of a kv head for 128 CUs
     (4, 4, 128, 0, (3000,)),               # own keys only: cut up to the diagonal, the first blocks whole
-    (8, 8, 64, 0, (1, 63, 64, 65, 1025)),
+    (8, 8, 64, 0, (1, 63, 64, 65, 1281)),
 ]]
 
 

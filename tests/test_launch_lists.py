@@ -200,3 +200,15 @@ def test_search_for_cuts_is_a_small_part_of_making_a_plan(heads, D, lens):
     plan = host_plan(suffix_lens=[lens], **kw)
     assert plan.launch_slots(2) <= 4 * 256
     assert best_plan_time(suffix_lens=[lens], **kw) < 5 * best_plan_time(suffix_lens=[2 * lens], **kw)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,cut", [
+    (4, 4, 128, 54411, (1, 3, 19, 2, 7, 1), False), (16, 8, 128, 30115, (9, 2), False), (4, 4, 128, 46606, (5, 132, 127, 24, 42, 1), False),
+    (4, 4, 128, 7922, (9, 2, 5, 1), True), (28, 4, 128, 1024, (128,), True), (28, 4, 128, 100000, (2, 3), True),
+])
+def test_cuts_that_the_workspace_limits_yield_to_key_ranges_of_the_prefix(Hq, Hkv, D, P, lens, cut):
+    """Few short blocks over a long prefix: the 256-row slots that fit beside the layout copy allow a few ranges a block
+    only (392 us for the first shape), fewer than the prefix pass has (166 us).  Calls whose cuts have room keep them."""
+    plan, fwd, _ = check_plan(Hq, Hkv, D, P, lens)
+    assert (fwd[0] > 0) == cut
+    assert len({int(k) for k in plan.items(0)[:, 4]}) > 1
