@@ -203,8 +203,8 @@ int prefix_attn_backward(const prefix_attn_plan_t* plan, const void* q, const vo
  * {pre-pass (delta, layouts), dQ pass, dK/dV pass over the prefix keys, dK/dV pass over the
  * rollouts' own keys and sums of partial gradients}; own keys whose items share the launch of the
  * prefix keys count in entry 2 (all of them in calls with few key blocks, the mask-free items of long
- * rollouts: see prefix_attn_plan_mask_free_items); for fp32 plans entry 2 is the whole dK/dV kernel and
- * entry 3 is ~0. */
+ * rollouts: see prefix_attn_plan_mask_free_items); for fp32 plans entry 2 is the whole dK/dV kernel
+ * with the sums of partial gradients and entry 3 is ~0. */
 int prefix_attn_backward_timed(const prefix_attn_plan_t* plan, const void* q, const void* k_prefix,
                                const void* v_prefix, const void* k_suffix, const void* v_suffix,
                                const void* out, const void* d_out, const float* lse,
@@ -300,13 +300,17 @@ int prefix_attn_plan_key_item_extra_tiles(const prefix_attn_plan_t* plan, int32_
  * the result; otherwise a part of them, and it leaves a partial result in that slot.
  * List 2 (bf16): {g (-1: prefix keys, -2: own keys, mask-free kernel), key0, c, nkeys, tile0, tile1, extra tile, slot}, with
  * the meanings of prefix_attn_plan_key_items.
- * Lists 3, 4 (fp32): {g, first stacked row, c, rows of the block, wavefronts that share its keys, 0, 0, -1}. */
+ * Lists 3, 4 (fp32): {g, first stacked row, c, rows of the block, wavefronts that share its keys, 0, 0, -1}.
+ * Lists 6, 7 (fp32; empty unless the backward's launches hold few blocks, which are then cut): 6, dQ = {g, first stacked row, c,
+ * nkeys, key0, 0, 0, slot}: a block of 16 rows, its 16-key blocks [key0, key0 + nkeys), prefix first; 7, dK/dV = {g (-1: prefix
+ * keys), key0, c, keys, row0, row1, -1, slot}: a block of 16 keys, the stacked rows [row0, row1). */
 int64_t prefix_attn_plan_num_launch_items(const prefix_attn_plan_t* plan, int32_t list);
 int prefix_attn_plan_launch_items(const prefix_attn_plan_t* plan, int32_t list, int32_t* items_out);
-/* Lists 0 ... 2: the blocks whose partial results are added afterwards, sums_out [num_sums][6] (HOST):
- * {first packed token of the rollout, first stacked row, c, rows, first slot, slots}, for list 2 {1: own keys / 0: prefix
+/* Lists 0 ... 2, 6, 7: the blocks whose partial results are added afterwards, sums_out [num_sums][6] (HOST):
+ * {first packed token of the rollout, first stacked row, c, rows, first slot, slots}, for lists 2, 7 {1: own keys / 0: prefix
  * keys, first key (packed token index / prefix index), c, keys, first slot, slots}; and the number of slots in use, of 256 rows
- * (list 0: D + 1 words each, list 1: D) or 2 x 128 keys (list 2: D words each) of fp32 in the workspace. */
+ * (list 0: D + 1 words each, list 1: D) or 2 x 128 keys (list 2: D words each) of fp32 in the workspace; 16 rows and
+ * 2 x 16 keys for lists 6, 7. */
 int64_t prefix_attn_plan_num_launch_sums(const prefix_attn_plan_t* plan, int32_t list);
 int prefix_attn_plan_launch_sums(const prefix_attn_plan_t* plan, int32_t list, int32_t* sums_out);
 int64_t prefix_attn_plan_launch_slots(const prefix_attn_plan_t* plan, int32_t list);

@@ -214,11 +214,11 @@ class PrefixAttnPlan:
     def launch_items(self, which: int) -> np.ndarray:
         """The list a launch runs: 0 (forward, empty unless blocks are cut) and 1 (dQ): int32 [n, 8] = (g, row0, c, nkeys,
         key0, pkeys, okey0, slot); 2 (dK/dV): (g, key0, c, nkeys, tile0, tile1, extra tile, slot); 3 and 4 (fp32 forward and
-        dQ): (g, row0, c, rows, wavefronts, 0, 0, -1)."""
+        dQ): (g, row0, c, rows, wavefronts, 0, 0, -1); 6 and 7 (fp32 dQ and dK/dV, empty unless cut): as 1 and 2, in blocks of 16."""
         return self._launch("launch_items", which, 8)
 
     def launch_sums(self, which: int) -> np.ndarray:
-        """Blocks whose partial results are added after launch list 0, 1 or 2: int32 [n, 6], the last two columns the
+        """Blocks whose partial results are added after launch list 0, 1, 2, 6 or 7: int32 [n, 6], the last two columns the
         first slot and the number of slots."""
         return self._launch("launch_sums", which, 6)
 

@@ -97,14 +97,21 @@ struct BwdF32Args {
   void* dv_prefix;
   void* dk_suffix;
   void* dv_suffix;
-  const WorkItem* items;  // dQ: the plan's blocks of 16 rows
+  const WorkItem* items;  // dQ: the plan's blocks of 16 rows, or the ranges they are cut into
   int64_t num_items;
+  const KeyItem* key_items;  // dK/dV of a launch of few blocks: ranges of rows (num_key_items 0: every block of 16 keys whole)
+  int64_t num_key_items;
+  float* dq_partial;         // unscaled partial sums of the items with a slot: [slots][16][D]
+  float* key_partial;        // [slots][2][16][D]: dK, dV
+  const RangeSum* dq_sums;
+  const KeySum* key_sums;
+  int64_t num_dq_sums, num_key_sums;
   const int32_t* cu;
   int64_t T, P;
   int32_t G, Hq, Hkv, D, group;
   float scale;
 };
 int launch_bwd_dq_f32(const BwdF32Args& a, void* stream);
-int launch_bwd_dkv_f32(const BwdF32Args& a, void* stream);
+int launch_bwd_dkv_f32(const BwdF32Args& a, void* stream);  // after dQ: adds the partial sums of both
 
 }  // namespace pa

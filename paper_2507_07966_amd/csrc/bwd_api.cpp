@@ -108,8 +108,17 @@ int enqueue_backward(const prefix_attn_plan_t* plan, const BackwardArgs& x, void
     f.dv_prefix = x.dv_prefix;
     f.dk_suffix = x.dk_suffix;
     f.dv_suffix = x.dv_suffix;
-    f.items = plan->d_f32_blocks[1];
-    f.num_items = (int64_t)plan->f32_blocks[1].size();
+    const bool cut = !plan->dq_launch.empty();
+    f.items = cut ? plan->d_dq_launch : plan->d_f32_blocks[1];
+    f.num_items = (int64_t)(cut ? plan->dq_launch : plan->f32_blocks[1]).size();
+    f.key_items = plan->d_key_launch;
+    f.num_key_items = (int64_t)plan->key_launch.size();
+    f.dq_partial = reinterpret_cast<float*>(ws + plan->boff_dqpart);
+    f.key_partial = reinterpret_cast<float*>(ws + plan->boff_part);
+    f.dq_sums = plan->d_dq_sums;
+    f.num_dq_sums = (int64_t)plan->dq_sums.size();
+    f.key_sums = plan->d_key_sums;
+    f.num_key_sums = (int64_t)plan->key_sums.size();
     f.cu = plan->d_cu;
     f.T = plan->T;
     f.P = d.prefix_len;

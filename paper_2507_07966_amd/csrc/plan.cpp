@@ -226,7 +226,7 @@ int list_schedule(std::vector<int>& cost, int at_once, double enough) {
   if ((int)cost.size() <= at_once) return longest;
   const int least = std::max(longest, (int)std::min<int64_t>((sum + at_once - 1) / at_once, INT32_MAX));
   if (least >= enough) return least;
-  std::sort(cost.begin(), cost.end(), std::greater<int>());
+  if (!std::is_sorted(cost.begin(), cost.end(), std::greater<int>())) std::sort(cost.begin(), cost.end(), std::greater<int>());
   // a heap of the times at which the workers are free, the earliest at the top
   std::vector<int> free(cost.begin(), cost.begin() + at_once);
   std::reverse(free.begin(), free.end());  // ascending: a heap already
@@ -686,6 +686,111 @@ void build_key_launch(prefix_attn_plan_t& p) {
   append(own.data() + long_own, own.data() + own.size());
 }
 
+// How many 16-key or 16-row blocks an item of an fp32 backward launch may hold at most (0: no limit) so that one workgroup
+// per CU ends early.  blocks: those that each whole item streams; a workgroup's 8 wavefronts take one each at a time, one such
+// step lasting step_us, its start and end OVERHEAD steps.
+int f32_limit(const std::vector<int>& blocks, int cus, double step_us, double slot_us) {
+  constexpr int OVERHEAD = 2;
+  constexpr double LAUNCH_US = 6.0;  // the sums
+  if (blocks.empty() || blocks.size() >= 4 * (size_t)cus) return 0;
+  const int longest = (*std::max_element(blocks.begin(), blocks.end()) + 7) / 8;
+  int limit = 0;
+  double best = 0.0;
+  std::vector<int> cost, of_length(longest + 1);  // items by their steps: counted, not sorted
+  for (int n = 1; n <= 16 && (n == 1 || longest / n >= 2); n += 1 + n / 6) {
+    const int most = 8 * ((longest + n - 1) / n);
+    size_t slots = 0;
+    std::fill(of_length.begin(), of_length.end(), 0);
+    for (int b : blocks) {
+      const int k = (b + most - 1) / most;
+      if (k > 1) slots += k;
+      of_length[((b + k - 1) / k + 7) / 8] += k;
+    }
+    if (slots > 4 * (size_t)cus) break;  // more ranges would only have more
+    cost.clear();
+    for (int t = longest; t > 0; --t) cost.insert(cost.end(), of_length[t], t + OVERHEAD);
+    const double extra = slots ? slots * slot_us + LAUNCH_US : 0.0;
+    const double us = list_schedule(cost, cus, n == 1 ? 1e30 : (best - extra) / step_us) * step_us + extra;
+    if (n == 1) {
+      best = 0.95 * us;
+    } else if (us < best) {
+      best = us;
+      limit = most;
+    }
+  }
+  return limit;
+}
+
+// fp32 backward launches of few blocks, cut like the bf16 ones: blocks of 16 rows into ranges of 16-key blocks (dQ), blocks
+// of 16 keys into ranges of stacked rows (dK/dV), in the lists that the bf16 path uses for the same purpose (empty: whole
+// blocks), with slots of 16 rows or 2 x 16 keys.  The step times were measured at D = 128 (dQ 3.75 us, dK/dV 4.7 us; whole
+// blocks and 2 ... 6 ranges of the longest): 8 / 2 heads of 128, 900 tokens of 4 rollouts over 1,000 prefix keys, 126 + 114
+// blocks of keys: dK/dV 147 us whole, 124 / 109 / 123 / 111 / 121 in 2 ... 6 ranges (3 taken, the sums 5 us); dQ 90 us whole
+// (452 blocks of rows, left so), 99 / 110 / 105 in 2 / 3 / 4.  Launches of four blocks a CU and more stay whole: their last
+// round is short against the rest.
+void build_f32_cuts(prefix_attn_plan_t& p) {
+  if (p.desc.dtype != PA_F32) return;
+  const int np = (int)((p.desc.prefix_len + 15) / 16), Hkv = p.desc.num_kv_heads;
+  const bool d128 = p.desc.head_dim == 128;
+  const double slot_us = 16.0 * p.desc.head_dim * 4 * 2 / 4e6;
+  std::vector<int> blocks;
+  if (p.f32_blocks[1].size() < 4 * (size_t)p.num_cu)
+    for (const WorkItem& it : p.f32_blocks[1])
+      blocks.push_back(np + ((std::min(it.row0 + 16, p.lens[it.g] * p.group) - 1) / p.group + 16) / 16);
+  if (const int limit = f32_limit(blocks, p.num_cu, d128 ? 3.75 : 2.0, slot_us)) {
+    std::vector<std::pair<int, WorkItem>> items;
+    for (size_t n = 0; n < blocks.size(); ++n) {
+      WorkItem it = p.f32_blocks[1][n];
+      const int k = (blocks[n] + limit - 1) / limit;
+      if (k > 1) {
+        p.dq_sums.push_back({p.cu[it.g], it.row0, it.c, std::min(16, p.lens[it.g] * p.group - it.row0), p.dq_slots, k});
+        for (int i = 0; i < k; ++i) {
+          it.key0 = (int)((int64_t)blocks[n] * i / k);
+          it.nkeys = (int)((int64_t)blocks[n] * (i + 1) / k) - it.key0;
+          it.split = p.dq_slots++;
+          items.push_back({it.nkeys, it});
+        }
+      } else {
+        it.nkeys = blocks[n];
+        it.split = -1;
+        items.push_back({blocks[n], it});
+      }
+    }
+    std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+    for (const auto& it : items) p.dq_launch.push_back(it.second);
+  }
+
+  blocks.clear();
+  std::vector<pa::KeyItem> keys;
+  if ((np + p.T / 16 + p.desc.num_rollouts) * Hkv < 4 * (int64_t)p.num_cu && (int64_t)p.T * p.group < (int64_t)1 << 30) {
+    auto add = [&](int g, int n, int first_row, int end_row) {
+      for (int key0 = 0; key0 < n; key0 += 16)
+        for (int c = 0; c < Hkv; ++c) {
+          const int row0 = first_row + (g < 0 ? 0 : key0 * p.group);
+          keys.push_back({g, key0, c, std::min(16, n - key0), row0, end_row, -1, -1});
+          blocks.push_back((end_row - row0 + 15) / 16);
+        }
+    };
+    add(-1, (int)p.desc.prefix_len, 0, (int)p.T * p.group);
+    for (int g = 0; g < p.desc.num_rollouts; ++g) add(g, p.lens[g], p.cu[g] * p.group, p.cu[g + 1] * p.group);
+  }
+  if (const int limit = f32_limit(blocks, p.num_cu, d128 ? 4.7 : 2.5, 2.0 * slot_us)) {
+    for (size_t n = 0; n < blocks.size(); ++n) {
+      pa::KeyItem it = keys[n];
+      const int k = (blocks[n] + limit - 1) / limit, row0 = it.tile0, end = it.tile1;
+      if (k > 1) p.key_sums.push_back({it.g >= 0, it.key0 + (it.g >= 0 ? p.cu[it.g] : 0), it.c, it.nkeys, p.key_slots, k});
+      for (int i = 0; i < k; ++i) {
+        it.tile0 = row0 + 16 * (int)((int64_t)blocks[n] * i / k);
+        it.tile1 = std::min(end, row0 + 16 * (int)((int64_t)blocks[n] * (i + 1) / k));
+        it.slot = k > 1 ? p.key_slots++ : -1;
+        p.key_launch.push_back(it);
+      }
+    }
+    std::stable_sort(p.key_launch.begin(), p.key_launch.end(),
+                     [](const pa::KeyItem& a, const pa::KeyItem& b) { return a.tile1 - a.tile0 > b.tile1 - b.tile0; });
+  }
+}
+
 // Backward workspace: delta and the re-ordered LSE (used by the fp32 path); for bf16 also the stacked Q/dO copies, the
 // per-row statistics and the transposed K images.
 void layout_backward_workspace(prefix_attn_plan_t& p) {
@@ -711,6 +816,10 @@ void layout_backward_workspace(prefix_attn_plan_t& p) {
     end += align_up((size_t)p.key_slots * 2 * pa::KEYS_PER_KEY_ITEM * d.head_dim * sizeof(float), 256);
     p.boff_dqpart = end;  // fp32 partial dQ: [dq_slots][ROWS_PER_ITEM][D]
     end += align_up((size_t)p.dq_slots * pa::ROWS_PER_ITEM * d.head_dim * sizeof(float), 256);
+  } else {  // partial sums of cut blocks: [key_slots][2][16][D], [dq_slots][16][D]
+    p.boff_part = end;
+    p.boff_dqpart = p.boff_part + (size_t)p.key_slots * 2 * 16 * d.head_dim * sizeof(float);
+    end = p.boff_dqpart + (size_t)p.dq_slots * 16 * d.head_dim * sizeof(float);
   }
   p.bws_bytes = end;
 }
@@ -760,6 +869,7 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
     build_key_items(*p);
     build_key_launch(*p);
     build_dq_launch(*p);
+    build_f32_cuts(*p);
   } catch (const std::bad_alloc&) {
     delete p;
     return PA_ERR_ALLOC;
@@ -904,22 +1014,30 @@ int prefix_attn_plan_items(const prefix_attn_plan_t* plan, int32_t pass, int32_t
   return PA_OK;
 }
 
+// Lists 6 and 7, the cut launches of the fp32 backward, are kept where a bf16 plan keeps its lists 1 and 2.
+static bool kept(const prefix_attn_plan_t* plan, int32_t list) {
+  const bool f32 = plan->desc.dtype == PA_F32;
+  return list < 3 ? !f32 : f32;
+}
+
 int64_t prefix_attn_plan_num_launch_items(const prefix_attn_plan_t* plan, int32_t list) {
-  if (!plan || list < 0 || list > 4) return -1;
-  if (list == 2) return (int64_t)plan->key_launch.size();
-  return (int64_t)(list == 0 ? plan->range_items : list == 1 ? plan->dq_launch : plan->f32_blocks[list - 3]).size();
+  if (!plan || list < 0 || list == 5 || list > 7) return -1;
+  if (!kept(plan, list)) return 0;
+  if (list % 5 == 2) return (int64_t)plan->key_launch.size();
+  return (int64_t)(list == 0 ? plan->range_items : list % 5 == 1 ? plan->dq_launch : plan->f32_blocks[list - 3]).size();
 }
 
 int prefix_attn_plan_launch_items(const prefix_attn_plan_t* plan, int32_t list, int32_t* items_out) {
   if (!plan || !items_out) return PA_ERR_NULL;
-  if (list < 0 || list > 4) return PA_ERR_SHAPE;
+  if (list < 0 || list == 5 || list > 7) return PA_ERR_SHAPE;
+  if (!kept(plan, list)) return PA_OK;
   auto put = [&](size_t n, std::initializer_list<int32_t> v) { std::copy(v.begin(), v.end(), items_out + 8 * n); };
-  if (list == 2) {
+  if (list % 5 == 2) {
     for (size_t n = 0; n < plan->key_launch.size(); ++n) {
       const pa::KeyItem& it = plan->key_launch[n];
       put(n, {it.g, it.key0, it.c, it.nkeys, it.tile0, it.tile1, it.extra_tile, it.slot});
     }
-  } else if (list >= 3) {
+  } else if (list == 3 || list == 4) {
     for (size_t n = 0; n < plan->f32_blocks[list - 3].size(); ++n) {
       const WorkItem& it = plan->f32_blocks[list - 3][n];
       put(n, {it.g, it.row0, it.c, list == 3 ? plan->f32_rows : 16, list == 3 ? plan->f32_waves : 8, 0, 0, -1});
@@ -933,15 +1051,17 @@ int prefix_attn_plan_launch_items(const prefix_attn_plan_t* plan, int32_t list, 
 }
 
 int64_t prefix_attn_plan_num_launch_sums(const prefix_attn_plan_t* plan, int32_t list) {
-  if (!plan || list < 0 || list > 2) return -1;
-  return (int64_t)(list == 0 ? plan->range_sums.size() : list == 1 ? plan->dq_sums.size() : plan->key_sums.size());
+  if (!plan || list < 0 || (list > 2 && list < 6) || list > 7) return -1;
+  if (!kept(plan, list)) return 0;
+  return (int64_t)(list == 0 ? plan->range_sums.size() : list % 5 == 1 ? plan->dq_sums.size() : plan->key_sums.size());
 }
 
 int prefix_attn_plan_launch_sums(const prefix_attn_plan_t* plan, int32_t list, int32_t* sums_out) {
   if (!plan || !sums_out) return PA_ERR_NULL;
-  if (list < 0 || list > 2) return PA_ERR_SHAPE;
+  if (list < 0 || (list > 2 && list < 6) || list > 7) return PA_ERR_SHAPE;
+  if (!kept(plan, list)) return PA_OK;
   auto put = [&](size_t n, std::initializer_list<int32_t> v) { std::copy(v.begin(), v.end(), sums_out + 6 * n); };
-  if (list == 2) {
+  if (list % 5 == 2) {
     for (size_t n = 0; n < plan->key_sums.size(); ++n) {
       const pa::KeySum& s = plan->key_sums[n];
       put(n, {s.own, s.key0, s.c, s.nkeys, s.slot0, s.nslots});
@@ -954,8 +1074,9 @@ int prefix_attn_plan_launch_sums(const prefix_attn_plan_t* plan, int32_t list, i
 }
 
 int64_t prefix_attn_plan_launch_slots(const prefix_attn_plan_t* plan, int32_t list) {
-  if (!plan || list < 0 || list > 2) return -1;
-  return list == 0 ? plan->range_slots : list == 1 ? plan->dq_slots : plan->key_slots;
+  if (!plan || list < 0 || (list > 2 && list < 6) || list > 7) return -1;
+  if (!kept(plan, list)) return 0;
+  return list == 0 ? plan->range_slots : list % 5 == 1 ? plan->dq_slots : plan->key_slots;
 }
 
 int64_t prefix_attn_plan_mask_free_items(const prefix_attn_plan_t* plan) { return plan ? plan->key_mask_free : -1; }

@@ -146,3 +146,16 @@ def test_f32_non_finite_values_reach_only_the_rows_that_see_them(Hq, Hkv, D, P, 
         assert np.isnan(want).all() if np.isnan(bad) else (want == bad).all()
         got["out"][:, :group, CH] = clean["out"][:, :group, CH]
         assert same(got["out"], clean["out"]) and same(got["lse"], clean["lse"])
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens", [
+    (1, 1, 64, 3000, (200, 50)), (7, 1, 128, 0, (900,)), (2, 1, 64, 65, (700,)), (4, 2, 128, 1, (513, 1, 700)), (2, 1, 128, 3000, (257, 9)),
+])
+def test_f32_backward_cut_into_ranges(Hq, Hkv, D, P, lens):
+    """Launches of few blocks, whose blocks of rows or keys are cut into ranges with partial sums: ranges that end inside a
+    rollout, on its diagonal and in its ragged last block; a value that is not finite in the first of them."""
+    import paper_2507_07966_amd as pa
+    plan = pa.prefix_attn_plan(Hq, Hkv, D, P, lens, D ** -0.5, dtype="f32", device=-1)
+    assert len(plan.launch_sums(6)) + len(plan.launch_sums(7)) > 0
+    test_f32_forward_and_backward_tiles(Hq, Hkv, D, P, lens)
+    test_f32_non_finite_values_reach_only_the_rows_that_see_them(Hq, Hkv, D, P, lens, float("inf"))

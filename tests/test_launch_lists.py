@@ -170,6 +170,55 @@ def test_f32_blocks_cover_every_row_once(Hq, Hkv, D, P, lens):
     assert plan.launch_items(3)[0, 4] == (1 if many_short else 8)
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,cut", [
+    (8, 2, 128, 1000, (70, 300, 111, 299), (False, True)), (1, 1, 64, 3000, (200, 50), (True, False)),
+    (7, 1, 128, 0, (900,), (False, True)), (2, 1, 64, 65, (700,), (True, True)), (3, 3, 64, 17, (16, 1, 15), (False, False)),
+    (4, 2, 128, 1, (513, 1, 700), (False, True)), (2, 1, 128, 3000, (257, 9), (True, False)),
+])
+def test_f32_backward_cuts_cover_every_pair_once(Hq, Hkv, D, P, lens, cut):
+    """Lists 6 and 7 (empty: whole blocks): every 16-key block of a block of rows, every stacked row of a block of keys,
+    in exactly one item; the slots of a block side by side and summed once."""
+    plan = host_plan(num_q_heads=Hq, num_kv_heads=Hkv, head_dim=D, prefix_len=P, suffix_lens=list(lens), dtype="f32")
+    group, off, np_ = Hq // Hkv, np.concatenate([[0], np.cumsum(lens)]).tolist(), -(-P // 16)
+    rows, keys = plan.launch_items(6).tolist(), plan.launch_items(7).tolist()
+    assert (len(plan.launch_sums(6)) > 0, len(plan.launch_sums(7)) > 0) == cut
+    parts, slots = {}, {}
+    for g, row0, c, nkeys, key0, _, _, slot in rows:
+        parts.setdefault((g, row0, c), []).append((key0, key0 + nkeys))
+        if slot >= 0:
+            slots.setdefault((g, row0, c), []).append(slot)
+    if rows:
+        want = {(g, r, c): np_ + ((min(r + 16, n * group) - 1) // group + 16) // 16
+                for g, n in enumerate(lens) for r in range(0, n * group, 16) for c in range(Hkv)}
+        check_parts(parts, {b: (0, n) for b, n in want.items()})
+    sums = {(off.index(o), r, c): (first, n) for o, r, c, nrows, first, n in plan.launch_sums(6).tolist()
+            if nrows == min(16, lens[off.index(o)] * group - r)}
+    check_slots({b: sorted(s) for b, s in slots.items()}, sums, plan.launch_slots(6))
+    parts, slots = {}, {}
+    for g, key0, c, nkeys, r0, r1, _, slot in keys:
+        assert nkeys == min(16, (P if g < 0 else lens[g]) - key0)
+        parts.setdefault((g, key0, c), []).append((r0, r1))
+        if slot >= 0:
+            slots.setdefault((int(g >= 0), key0 + (off[g] if g >= 0 else 0), c), []).append(slot)
+    if keys:
+        want = {(-1, k, c): (0, off[-1] * group) for k in range(0, P, 16) for c in range(Hkv)}
+        want.update({(g, k, c): ((off[g] + k) * group, off[g + 1] * group)
+                     for g, n in enumerate(lens) for k in range(0, n, 16) for c in range(Hkv)})
+        check_parts(parts, want)
+    sums = {(own, k, c): (first, n) for own, k, c, _, first, n in plan.launch_sums(7).tolist()}
+    check_slots({b: sorted(s) for b, s in slots.items()}, sums, plan.launch_slots(7))
+    need = plan.launch_slots(6) * 16 * D * 4 + plan.launch_slots(7) * 2 * 16 * D * 4 + 2 * sum(lens) * Hq * 4
+    assert need <= plan.backward_workspace_bytes <= need + 2 * 256
+
+
+def check_parts(parts, want):
+    assert set(parts) == set(want)
+    for block, p in parts.items():
+        p.sort()
+        assert (p[0][0], p[-1][1]) == want[block] and all(a < b for a, b in p)
+        assert all(a[1] == b[0] for a, b in zip(p, p[1:])), block
+
+
 def test_launch_list_arguments():
     from paper_2507_07966_amd import binding
     lib = binding.load_library()
