@@ -112,7 +112,8 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   };
   hipStream_t hs = static_cast<hipStream_t>(hip_stream);
   if (ev && hipEventRecord(ev[0], hs) != hipSuccess) return PA_ERR_HIP;
-  if (d.dtype == PA_BF16) {  // layout pre-pass: V^T tile images for the MFMA passes
+  const bool short_call = mode == FULL && plan->short_call;  // reads V as it is
+  if (d.dtype == PA_BF16 && !short_call) {  // layout pre-pass: V^T tile images for the MFMA passes
     pa::VtArgs t{};
     t.v_prefix = v_prefix;
     t.v_suffix = v_suffix;
@@ -153,6 +154,7 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   // extents); it leaves the result of the call, or the fp32 partial of a shard that also holds the own keys
   const bool ranges = with_suffix && !plan->range_items.empty();  // the same sweep, some blocks cut into key ranges
   const bool sweep = with_suffix && (ranges || !plan->sweep_items.empty());
+  a.short_call = short_call;
   if (has_prefix && !sweep) {
     a.k = k_prefix;
     a.v = v_prefix;
@@ -210,6 +212,12 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
       a.lse_part = lse_partial;
     }
   }
+  if (short_call) {
+    a.sweep_prefix = true;  // without a prefix: over the suffix list, whose items have no prefix keys
+    a.k_pre = has_prefix ? k_prefix : k_suffix;
+    a.v_pre = has_prefix ? v_prefix : v_suffix;
+    a.lse_ht = lse_out;
+  }
   if (pa::launch_pass_bf16(a, hip_stream) != 0) return PA_ERR_HIP;
 
   if (ev && hipEventRecord(ev[3], hs) != hipSuccess) return PA_ERR_HIP;
@@ -233,7 +241,7 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
   }
   if (fused || sweep) {
     if (ev && hipEventRecord(ev[4], hs) != hipSuccess) return PA_ERR_HIP;
-    return lse_out ? prefix_attn_lse(plan, workspace, lse_out, hip_stream) : PA_OK;
+    return lse_out && !short_call ? prefix_attn_lse(plan, workspace, lse_out, hip_stream) : PA_OK;
   }
   if (ks > 1) {  // a split prefix whose blocks the plan could not cut into ranges: the partials of every range
     if (merge_splits(true, out, mode == FULL ? d.dtype : (int32_t)PA_F32, mode == FULL ? lse : lse_partial) != 0)

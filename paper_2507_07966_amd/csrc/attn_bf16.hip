@@ -121,34 +121,25 @@ __device__ inline float quad_sum(float x) { return pair_sum(x + __shfl_xor(x, 16
 // range inside the own keys only where every row of the block sees its first key.  Such an item leaves an fp32 partial
 // in slot it.split (o_slots, lse_slots; 256 rows each); an item with split < 0 covers the whole sequence and writes the
 // result like any sweep.  lse_ht: if not null, where EPI 1 writes the LSE, in [Hq, T] order (the caller's array).
-template <int D, bool CAUSAL, int EPI, bool SWEEP, bool RANGE, bool CAREFUL>
-__global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
-    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ vt,
-    float* __restrict__ o_part, float* __restrict__ lse_part, const float* __restrict__ o1,
+// DIRECT: V tiles are copied to LDS as they are ([64 keys][D], like K) and read transposed (ds_read_b64_tr_b16, two per operand)
+// instead of as images that a pre-pass made; v and v_pre stand in the places of vt and vt_pre.
+// Returns (CAREFUL: false) whether this wavefront gave the item up.
+template <int D, bool CAUSAL, int EPI, bool SWEEP, bool RANGE, bool CAREFUL, bool DIRECT>
+__device__ __forceinline__ bool pass_item(
+    unsigned char* smem, const WorkItem& it, const __bf16* __restrict__ q, const __bf16* __restrict__ k,
+    const __bf16* __restrict__ vt, float* __restrict__ o_part, float* __restrict__ lse_part, const float* __restrict__ o1,
     const float* __restrict__ lse1, __bf16* __restrict__ out_final, float* __restrict__ lse_final,
-    const WorkItem* __restrict__ items,
     const int32_t* __restrict__ cu, const int32_t* __restrict__ vt_off, int64_t vt_tiles_per_head,
     const __bf16* __restrict__ k_pre, const __bf16* __restrict__ vt_pre, int64_t vt_pre_tiles_per_head,
-    int64_t part_rows, int Hq, int Hkv, int group, float scale, int32_t* __restrict__ flags,
+    int64_t part_rows, int Hq, int Hkv, int group, float scale,
     float* __restrict__ o_slots, float* __restrict__ lse_slots, float* __restrict__ lse_ht) {
-  static_assert(SWEEP || !RANGE, "ranges are ranges of a sweep");
+  static_assert(SWEEP || (!RANGE && !DIRECT), "ranges are ranges of a sweep");
   static_assert(EPI == 0 || CAUSAL, "only the suffix pass can finish the call");
   static_assert(!SWEEP || (CAUSAL && EPI != 2), "a sweep over prefix and own keys has nothing to combine with");
   using TL = Tile<D>;
   constexpr int KK = D / 16;  // 16-channel halves of the contraction steps (granularity of the load placement)
   constexpr int KS = D / 32;  // contraction steps of QK^T (32 channels per MFMA)
   constexpr int CB = D / 16;  // 16-channel blocks of the output
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * TL::STAGE];
-
-  const WorkItem it = items[blockIdx.x];
-  if (it.g < 0) return;
-  int32_t* const item_flags = flags + (int64_t)blockIdx.x * NWAVES;
-  if (CAREFUL) {  // only the items on which a wavefront of the common kernel gave up
-    int any = 0;
-#pragma unroll
-    for (int w = 0; w < NWAVES; ++w) any |= item_flags[w];
-    if (any == 0) return;
-  }
   bool bad = false;  // common kernel: a tile's probabilities left the safe range (the whole wavefront agrees)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -161,7 +152,8 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
   // prefix pass: the item sweeps prefix keys [key0, key0 + nkeys), key0 a multiple of the tile
   const int okey0 = RANGE ? it.okey0 : 0;  // own keys and positions count from here
   const __bf16* kown = k + ((int64_t)(CAUSAL ? off_g + okey0 : it.key0) * Hkv + it.c) * D;
-  const __bf16* vtbase = vt + ((int64_t)it.c * vt_tiles_per_head + (CAUSAL ? vt_off[it.g] + okey0 / BN : it.key0 / BN)) * (D * BN);
+  const __bf16* vtbase = DIRECT ? vt + ((int64_t)(off_g + okey0) * Hkv + it.c) * D
+                                : vt + ((int64_t)it.c * vt_tiles_per_head + (CAUSAL ? vt_off[it.g] + okey0 / BN : it.key0 / BN)) * (D * BN);
 
   // ---- this lane's two query columns: query block nq (16 rows) of the wavefront's 32 rows, column l16; the
   //      lane holds channels 32*ks + 8*g4 .. +7 of each contraction step ks
@@ -202,6 +194,12 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
   int voff[2];   // V^T operand (channel = cb*16 + l16, 32-key chunk c32, this lane's 8 keys of it): chunk 4c32 + g4
 #pragma unroll
   for (int c32 = 0; c32 < 2; ++c32) voff[c32] = l16 * 128 + (((4 * c32 + g4) ^ swizzle_term(l16, 128)) << 4);
+  int vtr[DIRECT ? CB : 1];  // transposed reads: this lane addresses key 4 g4 + l16 / 4, channels 16 cb + 4 (l16 % 4) .. of a 16-key chunk
+#pragma unroll
+  for (int cb = 0; cb < (DIRECT ? CB : 0); ++cb) {
+    const int r = 4 * g4 + (l16 >> 2);
+    vtr[cb] = r * TL::ROWB + (((2 * cb + ((l16 & 3) >> 1)) ^ swizzle_term_tr(r, TL::ROWB)) << 4) + (l16 & 1) * 8;
+  }
 
   // ---- per-lane source of the direct-to-LDS K loads: lane writes LDS chunk `lane` of its block.
   //      Address = uniform tile base (scalar registers) + a per-lane 32-bit byte offset.
@@ -220,12 +218,15 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
   const int ntiles = tp + (nkeys + BN - 1) / BN;
   const int pkey0 = RANGE ? it.key0 : 0;
   const __bf16* kpre = SWEEP ? k_pre + ((int64_t)pkey0 * Hkv + it.c) * D : nullptr;
-  const __bf16* vtpre = SWEEP ? vt_pre + ((int64_t)it.c * vt_pre_tiles_per_head + pkey0 / BN) * (D * BN) : nullptr;
+  const __bf16* vtpre = !SWEEP ? nullptr : DIRECT ? vt_pre + ((int64_t)pkey0 * Hkv + it.c) * D
+                                                  : vt_pre + ((int64_t)it.c * vt_pre_tiles_per_head + pkey0 / BN) * (D * BN);
   // Whole tiles are fetched with buffer loads: uniform tile offset in a scalar register plus the lane's
   // constant 32-bit offset.  Every such access lies inside the arrays (a ragged last K tile takes the
   // clamped path below), so the descriptors' range (2 GiB) never comes into play.
-  const rsrc_t krs_own = make_rsrc(kown), vrs_own = make_rsrc(vtbase);
-  const rsrc_t krs_pre = make_rsrc(SWEEP ? kpre : kown), vrs_pre = make_rsrc(SWEEP ? vtpre : vtbase);
+  // (DIRECT: the range of V ends with its last key, so that the rows past it read as zero, as they are in an image.)
+  auto v_bytes = [&](int keys) { return !DIRECT ? (int64_t)0x7fffffff : keys ? ((keys - 1) * row_stride + D) * 2 : (int64_t)0; };
+  const rsrc_t krs_own = make_rsrc(kown), vrs_own = make_rsrc(vtbase, v_bytes(nkeys));
+  const rsrc_t krs_pre = make_rsrc(SWEEP ? kpre : kown), vrs_pre = make_rsrc(SWEEP ? vtpre : vtbase, v_bytes(P));
 
   // LEAN (a compile-time flag of the sweep's prefix loop): the tile is a whole prefix tile, so neither the
   // choice between the two key sets nor the ragged-tile path is in the instruction stream.
@@ -256,14 +257,21 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     }
   };
   const unsigned voffs = (unsigned)(((wave * TL::VBLOCKS_PER_WAVE) * 512 + lane * 8) * 2);
+  unsigned vdir[DIRECT ? TL::VBLOCKS_PER_WAVE : 1];  // like koffs, with the swizzle of transposed reads
+#pragma unroll
+  for (int n = 0; n < (DIRECT ? TL::VBLOCKS_PER_WAVE : 0); ++n) {
+    const int row = (wave * TL::VBLOCKS_PER_WAVE + n) * ROWS_PER_BLOCK + lane / LANES_PER_ROW;
+    vdir[n] = (unsigned)((row * row_stride + ((lane % LANES_PER_ROW) ^ swizzle_term_tr(row, TL::ROWB)) * 8) * 2);
+  }
   auto issue_v = [&](int gtile, auto buf_c, auto lean_c) {  // V^T image -> V buffer buf (a linear copy)
     unsigned char* dst = smem + VBUF0 + decltype(buf_c)::value * TL::VBYTES;
     const bool pre = decltype(lean_c)::value || (SWEEP && gtile < tp);
-    const unsigned soff = (unsigned)((pre ? gtile : gtile - tp) * (D * BN * 2));
+    const unsigned soff = (unsigned)((pre ? gtile : gtile - tp) * (DIRECT ? ktile_bytes : D * BN * 2));
 #pragma unroll
     for (int n = 0; n < TL::VBLOCKS_PER_WAVE; ++n) {
       unsigned char* d = dst + (wave * TL::VBLOCKS_PER_WAVE + n) * 1024;
-      if (pre) load_chunk_to_lds(vrs_pre, d, voffs + n * 1024, soff); else load_chunk_to_lds(vrs_own, d, voffs + n * 1024, soff);
+      const unsigned off = DIRECT ? vdir[DIRECT ? n : 0] : voffs + n * 1024;
+      if (pre) load_chunk_to_lds(vrs_pre, d, off, soff); else load_chunk_to_lds(vrs_own, d, off, soff);
     }
   };
 
@@ -420,6 +428,10 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq) mc[nq] = reference(mref[nq]);
     auto v_operand = [&](int t) {
+      if constexpr (DIRECT) {
+        const unsigned char* p = vbuf + (t / CB) * 32 * TL::ROWB + vtr[t % CB];
+        return lds_operand_tr(p, p + 16 * TL::ROWB);
+      }
       return *reinterpret_cast<const bf16x8*>(vbuf + (t % CB) * 16 * 128 + voff[t / CB]);
     };
     bf16x8 va[RING];
@@ -511,10 +523,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
     pv(smem + VBUF0 + ((ntiles - 1) & 1) * TL::VBYTES, std::false_type{}, Pn, lacc);
   }
 
-  if (!CAREFUL) {  // tell the careful kernel whether it has to redo this item (every wavefront owns a word)
-    if (lane == 0) item_flags[wave] = bad ? 1 : 0;
-    if (bad) return;
-  }
+  if (!CAREFUL && bad) return true;
   // ---- epilogue: normalise and write.  Register i of block (cb, nq) is channel 16*cb + 4*g4 + i of query
   //      column nq of this lane.
 #pragma unroll
@@ -553,7 +562,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
           *reinterpret_cast<bf16x4*>(op + cb * 16) = __builtin_convertvector(w, bf16x4);
         }
         if (g4 == 0) {
-          if (RANGE && lse_ht) {
+          if ((RANGE || DIRECT) && lse_ht) {
             const int64_t t = row / Hq;
             lse_ht[(row - t * Hq) * (part_rows / Hq) + t] = lse_f;
           } else {
@@ -570,7 +579,60 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(
       if (g4 == 0) lse_part[prow] = mref[nq] * scale + __logf(l);
     }
   }
+  return false;
 }
+
+#define PA_PASS_PARAMS                                                                                             \
+  const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ vt,                       \
+      float *__restrict__ o_part, float *__restrict__ lse_part, const float *__restrict__ o1,                      \
+      const float *__restrict__ lse1, __bf16 *__restrict__ out_final, float *__restrict__ lse_final,               \
+      const WorkItem *__restrict__ items, const int32_t *__restrict__ cu, const int32_t *__restrict__ vt_off,      \
+      int64_t vt_tiles_per_head, const __bf16 *__restrict__ k_pre, const __bf16 *__restrict__ vt_pre,              \
+      int64_t vt_pre_tiles_per_head, int64_t part_rows, int Hq, int Hkv, int group, float scale,                   \
+      int32_t *__restrict__ flags, float *__restrict__ o_slots, float *__restrict__ lse_slots,                     \
+      float *__restrict__ lse_ht
+#define PA_PASS_ARGS                                                                                               \
+  q, k, vt, o_part, lse_part, o1, lse1, out_final, lse_final, cu, vt_off, vt_tiles_per_head, k_pre, vt_pre,        \
+      vt_pre_tiles_per_head, part_rows, Hq, Hkv, group, scale, o_slots, lse_slots, lse_ht
+
+template <int D, bool CAUSAL, int EPI, bool SWEEP, bool RANGE, bool CAREFUL>
+__global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(PA_PASS_PARAMS) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * Tile<D>::STAGE];
+  const WorkItem it = items[blockIdx.x];
+  if (it.g < 0) return;
+  int32_t* const item_flags = flags + (int64_t)blockIdx.x * NWAVES;
+  if (CAREFUL) {  // only the items on which a wavefront of the common kernel gave up
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < NWAVES; ++w) any |= item_flags[w];
+    if (any == 0) return;
+  }
+  const bool bad = pass_item<D, CAUSAL, EPI, SWEEP, RANGE, CAREFUL, false>(smem, it, PA_PASS_ARGS);
+  // tell the careful kernel whether it has to redo this item (every wavefront owns a word)
+  if (!CAREFUL && (threadIdx.x & 63) == 0) item_flags[threadIdx.x >> 6] = bad ? 1 : 0;
+}
+
+// Short calls: no image pre-pass (V tiles are read as they are) and no second launch, the workgroup itself redoes an item
+// that one of its wavefronts gave up.
+template <int D, bool RANGE>
+__global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void short_pass_bf16_kernel(PA_PASS_PARAMS) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * Tile<D>::STAGE];
+  const WorkItem it = items[blockIdx.x];
+  if (it.g < 0) return;
+  const bool bad = pass_item<D, true, 1, true, RANGE, false, true>(smem, it, PA_PASS_ARGS);
+  __syncthreads();  // every wavefront is done with the tiles
+  int* const words = reinterpret_cast<int*>(smem);
+  if ((threadIdx.x & 63) == 0) words[threadIdx.x >> 6] = bad ? 1 : 0;
+  __syncthreads();
+  int any = 0;
+#pragma unroll
+  for (int w = 0; w < NWAVES; ++w) any |= words[w];
+  if (__builtin_amdgcn_readfirstlane(any) == 0) return;
+  __syncthreads();  // the words are read
+  pass_item<D, true, 1, true, RANGE, true, true>(smem, it, PA_PASS_ARGS);
+}
+#undef PA_PASS_PARAMS
+#undef PA_PASS_ARGS
 
 }  // namespace
 
@@ -606,6 +668,22 @@ int launch_pass_bf16(const PassArgs& a, void* stream) {
   else if (a.epilogue == 1 && a.sweep_prefix) PA_LAUNCH(DD, true, 1, true, false);                                 \
   else if (a.epilogue == 1) PA_LAUNCH(DD, true, 1, false, false);                                                  \
   else PA_LAUNCH(DD, true, 2, false, false)
+#define PA_LAUNCH_SHORT(DD, RR)                                                                                    \
+  short_pass_bf16_kernel<DD, RR><<<grid, NTHREADS, 0, s>>>(                                                        \
+      q, k, static_cast<const __bf16*>(a.v), a.o_part, a.lse_part, a.o1, a.lse1, outf, a.lse_final, a.items, a.cu,      \
+      a.vt_off, 0, kpre, static_cast<const __bf16*>(a.v_pre), 0, a.part_rows, a.Hq, a.Hkv, a.group, a.scale, nullptr, \
+      a.o_slots, a.lse_slots, a.lse_ht)
+  if (a.short_call) {
+    if (!a.sweep_prefix || !a.causal || a.epilogue != 1 || !a.k_pre || !a.v_pre) return 1;
+    if (a.ranges && (!a.o_slots || !a.lse_slots)) return 1;
+    if (a.D == 128) {
+      if (a.ranges) PA_LAUNCH_SHORT(128, true); else PA_LAUNCH_SHORT(128, false);
+    } else {
+      if (a.ranges) PA_LAUNCH_SHORT(64, true); else PA_LAUNCH_SHORT(64, false);
+    }
+    return (int)hipGetLastError();
+  }
+#undef PA_LAUNCH_SHORT
   if (!a.flags) return 1;
   if (a.epilogue < 0 || a.epilogue > 2 || (!a.causal && a.epilogue != 0)) return 1;
   if (a.sweep_prefix && (!a.causal || a.epilogue == 2 || !a.k_pre || !a.vt_pre)) return 1;

@@ -111,7 +111,7 @@ struct PassArgs {
   // online softmax, so the call is one pass over [prefix | own keys] per block of rows.
   bool sweep_prefix;
   const void* k_pre;           // [P, Hkv, D]; fp32: null when the call covers no prefix keys
-  const void* v_pre;           // fp32 only: [P, Hkv, D]
+  const void* v_pre;           // fp32 and short calls: [P, Hkv, D]
   int64_t P;                   // fp32 only: prefix keys
   int32_t block_rows, block_waves;  // fp32 only: rows of an item, 16 or 32; wavefronts that share its keys, 8 or 1
   const void* vt_pre;          // prefix V tile images
@@ -122,6 +122,9 @@ struct PassArgs {
   float* o_slots;              // [slots][ROWS_PER_ITEM][D]
   float* lse_slots;            // [slots][ROWS_PER_ITEM]
   float* lse_ht;
+  // bf16 whole call (epilogue 1; the sweep's or range list, or the suffix list of a call without prefix) in one launch that needs no
+  // images and no flags; lse_ht as for ranges
+  bool short_call;
   // bf16: one word per (work item, wavefront), written by the common kernel of a pass and read by its careful
   // kernel (see attn_bf16.hip); [num_items][WAVES_PER_ITEM]
   int32_t* flags;
@@ -219,6 +222,7 @@ struct prefix_attn_plan {
   std::vector<pa::RangeSum> range_sums;
   pa::RangeSum* d_range_sums = nullptr;
   int32_t range_slots = 0;
+  bool short_call = false;             // bf16: whole calls are one launch without images (see mark_short_calls in plan.cpp)
   // fp32: the blocks of rows that exist, one workgroup each, in the order of the suffix list: of f32_rows rows for the
   // forward, of 16 rows for the backward's dQ (only g, row0, c are read)
   int32_t f32_rows = 16, f32_waves = 8;

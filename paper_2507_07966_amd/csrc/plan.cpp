@@ -437,6 +437,28 @@ void build_range_items(prefix_attn_plan_t& p, size_t fixed_bytes, size_t slot_by
   lay_out_ranges(p, pieces, true, p.range_items, p.range_sums, p.range_slots);
 }
 
+// Whole bf16 calls of few key tiles (those of the longest item, times the rounds of items) run as one launch (and the merge of cut
+// blocks): V is read as it is instead of from images, and the workgroup itself redoes an item whose scores leave the common
+// kernel's range, so neither the image pre-pass nor the launch of the careful kernel is needed.  What these cost, 4 to 8 us, against
+// transposed reads of V (two for one, and 3 to 4 % of the pass): forward and LSE export, 28 / 4 heads of 128, 12 blocks of 6 tiles
+// 29.6 -> 22.2 us, 18 tiles 53.0 -> 49.5, 72 tiles 121.7 -> 118.0, 126 tiles 114.4 -> 112.1, 136 tiles 204.7 -> 202.8, 264 tiles
+// 378.5 -> 381.2, 328 tiles 498 -> 504; 14 / 2 heads of 64, 21 tiles 40.5 -> 36.1, 204 tiles 147.4 -> 143.4, 276 tiles 173.4 -> 168.3,
+// 532 tiles the same.
+void mark_short_calls(prefix_attn_plan_t& p) {
+  p.short_call = false;
+  const int most = p.desc.head_dim == 128 ? 128 : 256;
+  const bool no_prefix = p.desc.prefix_len == 0;
+  const std::vector<WorkItem>& v = !p.range_items.empty() ? p.range_items : no_prefix ? p.items[1] : p.sweep_items;
+  if (p.desc.dtype != PA_BF16 || v.empty() || (int64_t)v.size() > (int64_t)most * p.num_cu) return;
+  int64_t items = 0, longest = 0;
+  for (const WorkItem& it : v) {
+    if (it.g < 0) continue;
+    ++items;
+    longest = std::max<int64_t>(longest, (it.nkeys + pa::KEYS_PER_TILE - 1) / pa::KEYS_PER_TILE + (it.pkeys + pa::KEYS_PER_TILE - 1) / pa::KEYS_PER_TILE);
+  }
+  p.short_call = (items + p.num_cu - 1) / p.num_cu * longest <= most;
+}
+
 // Backward, dK/dV pass: one item per block of KEYS_PER_KEY_ITEM keys of a kv head.  A prefix
 // block streams the stacked rows of every rollout, all blocks of a kv head in the same order,
 // so (as in the prefix pass) one kv head's blocks are kept on a fixed subset of XCDs and share
@@ -884,6 +906,7 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
     build_range_items(*p, l_bytes + desc->num_kv_heads * tiles * desc->head_dim * pa::KEYS_PER_TILE * 2 +
                               items * pa::WAVES_PER_ITEM * sizeof(int32_t) + 4 * 256,
                       o_bytes + l_bytes);
+    mark_short_calls(*p);
   } catch (const std::bad_alloc&) {
     delete p;
     return PA_ERR_ALLOC;

@@ -111,3 +111,26 @@ def test_late_maximum_in_shard_partials(D):
     ro, rl, _ = cref.prefix_shared_attention(x.q, x.k_prefix, x.v_prefix, x.k_suffix, x.v_suffix, x.suffix_lens,
                                              x.workload.scale)
     check_peaked(out, lse, ro, rl, x, f"late maximum, shard partials D={D}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,every", [
+    # calls of few key tiles (one launch, V read as it is): blocks cut into ranges and whole, without a prefix, ragged last tiles
+    (28, 4, 128, 130, (70,), 1), (28, 4, 128, 1021, (67, 200), 1), (7, 1, 128, 0, (321, 65), 1), (8, 8, 128, 127, (300, 7, 99), 1),
+    (14, 2, 64, 515, (129, 300), 1), (4, 4, 64, 0, (700, 1, 64), 1),
+    # calls above the limit (128 tiles at D = 128, 256 at 64): V^T images and a second launch for the items given up
+    (28, 4, 128, 20000, (333, 400, 67, 90), 19), (14, 2, 64, 60000, (300, 400, 500, 77), 41), (8, 2, 128, 0, (8300,), 41),
+    (4, 2, 64, 0, (16500,), 401),
+])
+def test_late_maximum_in_short_and_long_calls(Hq, Hkv, D, P, lens, every):
+    print(f"late maximum, short and long calls {Hq}/{Hkv}/{D} P={P} lens={lens}", flush=True)
+    x = late_maximum_inputs(Hq, Hkv, D, P, lens, seed=34)
+    off = ref.suffix_offsets(x.suffix_lens)
+    moved = sum(rows_that_move(x, np.concatenate([x.k_prefix, x.k_suffix[off[g]:off[g + 1]]]), range(max(off[g], off[g + 1] - 2), off[g + 1]))
+                for g in range(len(lens)))
+    assert moved > 0
+    out, lse = run_hip(x)
+    assert np.isfinite(out).all() and np.isfinite(lse).all()
+    rows = np.unique(np.concatenate([np.arange(0, x.total_suffix, every), off[1:] - 1]))
+    ro, rl, _ = cref.prefix_shared_attention(x.q, x.k_prefix, x.v_prefix, x.k_suffix, x.v_suffix, x.suffix_lens,
+                                             x.workload.scale, rows=rows)
+    check_peaked(out[rows], lse[:, rows], ro, rl, x, f"late maximum D={D} P={P} {lens}")
