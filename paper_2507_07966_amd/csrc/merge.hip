@@ -46,8 +46,10 @@ __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ o1
   }
 }
 
-// n-way merge: one thread handles 4 consecutive channels of one (token, head) row.
-template <bool OUT_BF16>
+// n-way merge: one thread handles 4 consecutive channels of one (token, head) row.  Bound by reading the partials; STEP of
+// them (a divisor of n) are in flight together, as non-temporal loads since nothing reads them again.  8 partials of 18,432
+// tokens x 28 heads x 128 channels: 457 us one after the other, 423 us now (2.24 GB at 5.3 TB/s).
+template <bool OUT_BF16, int STEP>
 __global__ __launch_bounds__(256) void merge_n_kernel(MergeNArgs a) {
   const int per_row = a.D / 4;
   const int64_t rows = a.T * a.Hq;
@@ -57,13 +59,21 @@ __global__ __launch_bounds__(256) void merge_n_kernel(MergeNArgs a) {
     const int64_t row = idx / per_row;
     const int ch = (int)(idx - row * per_row);
     float m = -INFINITY;
-    for (int i = 0; i < a.n; ++i) m = fmaxf(m, a.lse[i][row]);
+    for (int i = 0; i < a.n; i += STEP)
+#pragma unroll
+      for (int e = 0; e < STEP; ++e) m = fmaxf(m, a.lse[i + e][row]);
     float tot = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int i = 0; i < a.n; ++i) {
-      const float w = expf(a.lse[i][row] - m);  // a partial over no keys has LSE = -inf and weight 0
-      tot += w;
-      acc += w * *reinterpret_cast<const f32x4*>(a.o[i] + idx * 4);
+    for (int i = 0; i < a.n; i += STEP) {
+      f32x4 o[STEP];
+#pragma unroll
+      for (int e = 0; e < STEP; ++e) o[e] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(a.o[i + e] + idx * 4));
+#pragma unroll
+      for (int e = 0; e < STEP; ++e) {
+        const float w = expf(a.lse[i + e][row] - m);  // a partial over no keys has LSE = -inf and weight 0
+        tot += w;
+        acc += w * o[e];
+      }
     }
     const f32x4 r = acc * (1.0f / tot);
     if (OUT_BF16) {
@@ -191,10 +201,19 @@ int launch_merge_n(const MergeNArgs& a, void* stream) {
   const int64_t want = (total + 255) / 256;
   const int blocks = (int)(want < 256 * 32 ? want : 256 * 32);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (a.dtype == PA_BF16)
-    merge_n_kernel<true><<<blocks, 256, 0, s>>>(a);
-  else
-    merge_n_kernel<false><<<blocks, 256, 0, s>>>(a);
+#define PA_MERGE(STEP)                                                          \
+  if (a.dtype == PA_BF16) merge_n_kernel<true, STEP><<<blocks, 256, 0, s>>>(a); \
+  else merge_n_kernel<false, STEP><<<blocks, 256, 0, s>>>(a)
+  if (a.n % 8 == 0) {
+    PA_MERGE(8);
+  } else if (a.n % 4 == 0) {
+    PA_MERGE(4);
+  } else if (a.n % 2 == 0) {
+    PA_MERGE(2);
+  } else {
+    PA_MERGE(1);
+  }
+#undef PA_MERGE
   return (int)hipGetLastError();
 }
 
