@@ -130,6 +130,7 @@ class PrefixAttnPlan:
     def __init__(self, handle, workspace_bytes, desc_kw):
         self._h = handle
         self.workspace_bytes = int(workspace_bytes)
+        self._backward_workspace_bytes = None
         self.__dict__.update(desc_kw)
 
     @property
@@ -165,11 +166,14 @@ class PrefixAttnPlan:
 
     @property
     def backward_workspace_bytes(self) -> int:
-        n = ctypes.c_size_t()
-        st = load_library().prefix_attn_backward_workspace(self.handle, ctypes.byref(n))
-        if st:
-            raise PrefixAttnError(st, "prefix_attn_backward_workspace")
-        return int(n.value)
+        handle = self.handle
+        if self._backward_workspace_bytes is None:   # a property of the plan
+            n = ctypes.c_size_t()
+            st = load_library().prefix_attn_backward_workspace(handle, ctypes.byref(n))
+            if st:
+                raise PrefixAttnError(st, "prefix_attn_backward_workspace")
+            self._backward_workspace_bytes = int(n.value)
+        return self._backward_workspace_bytes
 
     def key_item_extra_tiles(self, which: int) -> np.ndarray:
         """int32 [n]: the one row tile an item of dK/dV list `which` streams after [tile0, tile1), or -1."""
@@ -264,17 +268,26 @@ def prefix_attn_plan(num_q_heads: int, num_kv_heads: int, head_dim: int, prefix_
 
 
 def _ptr(t) -> Optional[int]:
-    if t is None:
-        return None
-    if isinstance(t, int):
+    if t is None or isinstance(t, int):
         return t
-    return int(t.data_ptr())
+    return t.data_ptr()
+
+
+_torch_c = None   # torch._C, once it has the calls that _stream uses
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
+        # The current stream's handle, without the Stream object that torch.cuda.current_stream() makes: short calls are bound
+        # by the host (prefix_attn_forward and prefix_attn_lse on one head and 192 rows: 22.4 us for 11 us of kernels).
+        global _torch_c
+        if _torch_c is None:
+            import torch
+            torch.cuda.current_stream()   # initialises the device once
+            if not hasattr(torch._C, "_cuda_getCurrentRawStream") or not hasattr(torch._C, "_cuda_getDevice"):
+                return int(torch.cuda.current_stream().cuda_stream) or None
+            _torch_c = torch._C
+        return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice()) or None
     if isinstance(stream, int):
         return stream or None
     return int(stream.cuda_stream) or None
