@@ -615,7 +615,7 @@ __global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void pass_bf16_kernel(PA_
 // Short calls: no image pre-pass (V tiles are read as they are) and no second launch, the workgroup itself redoes an item
 // that one of its wavefronts gave up.
 template <int D, bool RANGE>
-__global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void short_pass_bf16_kernel(PA_PASS_PARAMS) {
+__global__ __launch_bounds__(NTHREADS, 512 / NTHREADS) void short_call_bf16_kernel(PA_PASS_PARAMS) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * Tile<D>::STAGE];
   const WorkItem it = items[blockIdx.x];
   if (it.g < 0) return;
@@ -669,7 +669,7 @@ int launch_pass_bf16(const PassArgs& a, void* stream) {
   else if (a.epilogue == 1) PA_LAUNCH(DD, true, 1, false, false);                                                  \
   else PA_LAUNCH(DD, true, 2, false, false)
 #define PA_LAUNCH_SHORT(DD, RR)                                                                                    \
-  short_pass_bf16_kernel<DD, RR><<<grid, NTHREADS, 0, s>>>(                                                        \
+  short_call_bf16_kernel<DD, RR><<<grid, NTHREADS, 0, s>>>(                                                        \
       q, k, static_cast<const __bf16*>(a.v), a.o_part, a.lse_part, a.o1, a.lse1, outf, a.lse_final, a.items, a.cu,      \
       a.vt_off, 0, kpre, static_cast<const __bf16*>(a.v_pre), 0, a.part_rows, a.Hq, a.Hkv, a.group, a.scale, nullptr, \
       a.o_slots, a.lse_slots, a.lse_ht)

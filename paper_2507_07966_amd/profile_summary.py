@@ -30,6 +30,8 @@ def short_name(k: str) -> str:
         if sweep:
             return f"attention_{'ranges' if ranges else 'sweep'} (bf16 MFMA)" + (", fp32 partial" if epi == 0 else "")
         return "suffix_pass (bf16 MFMA)" + ("" if epi == 0 else ", final" if epi == 1 else ", merging")
+    if "short_call_bf16_kernel" in k:   # whole calls of few key tiles, key ranges or whole blocks
+        return "attention_short_call (bf16 MFMA)"
     if "bwd_dkv_reduce" in k:
         return "bwd_dkv: add partial gradients"
     if "bwd_dq_reduce" in k:
@@ -47,6 +49,8 @@ def short_name(k: str) -> str:
         return "bwd_dq (bf16 MFMA)" + (", key splits" if "ELb1E" in k else "")
     if "bwd_prep" in k:
         return "bwd_prepass"
+    if "bwd_f32_sum" in k:
+        return "backward (fp32): add partial sums"
     if "bwd_dq_f32" in k or "bwd_dkv_f32" in k or "bwd_delta_f32" in k:
         return "backward (fp32) " + ("dq" if "dq" in k else "dkv" if "dkv" in k else "delta")
     if "logprob_tile_kernel" in k:
