@@ -127,7 +127,6 @@ int enqueue_forward(const prefix_attn_plan_t* plan, const void* q, const void* k
     t.G = d.num_rollouts;
     t.Hkv = d.num_kv_heads;
     t.D = d.head_dim;
-    t.order_32x32 = false;  // the attention passes contract with 16 x 16 x 32 MFMAs
     if (pa::launch_vt_images(t, hip_stream) != 0) return PA_ERR_HIP;
   }
   if (ev && hipEventRecord(ev[1], hs) != hipSuccess) return PA_ERR_HIP;

@@ -29,6 +29,7 @@ struct BwdPrepArgs {
   int64_t T;
   int64_t Mpad;        // stacked rows per kv head rounded up to ROWS_PER_ROW_TILE
   int32_t Hq, Hkv, D, group, dtype;
+  VtArgs images;       // bf16 path only: K^T tile images for the dQ pass, made by the same launch
 };
 int launch_bwd_prep(const BwdPrepArgs& a, void* stream);
 

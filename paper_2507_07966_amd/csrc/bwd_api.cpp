@@ -73,9 +73,8 @@ int enqueue_backward(const prefix_attn_plan_t* plan, const BackwardArgs& x, void
     p.deltas = reinterpret_cast<float*>(ws + plan->boff_deltas);
     p.toks = reinterpret_cast<int32_t*>(ws + plan->boff_toks);
   }
-  if (pa::launch_bwd_prep(p, hip_stream) != 0) return PA_ERR_HIP;
   if (bf16) {  // the same tile-image builder as for V in the forward, applied to K
-    pa::VtArgs t{};
+    pa::VtArgs& t = p.images;
     t.v_prefix = x.k_prefix;
     t.v_suffix = x.k_suffix;
     t.vt_prefix = ws + plan->boff_ktp;
@@ -88,9 +87,8 @@ int enqueue_backward(const prefix_attn_plan_t* plan, const BackwardArgs& x, void
     t.G = d.num_rollouts;
     t.Hkv = d.num_kv_heads;
     t.D = d.head_dim;
-    t.order_32x32 = true;  // the dQ pass contracts with 32 x 32 x 16 MFMAs
-    if (pa::launch_vt_images(t, hip_stream) != 0) return PA_ERR_HIP;
   }
+  if (pa::launch_bwd_prep(p, hip_stream) != 0) return PA_ERR_HIP;
   if (ev && hipEventRecord(ev[1], hs) != hipSuccess) return PA_ERR_HIP;
 
   if (!bf16) {

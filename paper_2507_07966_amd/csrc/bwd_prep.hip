@@ -7,17 +7,20 @@
 //   - per row: LSE * log2(e), -delta and the packed token index.
 // Rows past the last stacked row are zero, with a huge LSE (their weights become exactly 0)
 // and token index INT32_MAX.  Cost: Q, dO and O are read once and Q, dO written once.
+// The K^T tile images that the dQ pass reads are made by further workgroups of the same launch, as neither needs the other: 5,377
+// prefix keys, 5 rollouts of 37 ... 1,901 tokens, 14 / 2 heads of 64: 6.4 + 5.0 us in two launches, 6.9 in one; 4,096 keys, 8 x
+// 1,152 tokens, 28 / 4 heads of 128: 54.8 + 7.1 and 57.8.
 #include <hip/hip_runtime.h>
 
 #include <climits>
 
 #include "bwd.h"
+#include "vt_image.h"
 
 namespace pa {
 namespace {
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+using vt::u32x4;
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LSE_PAST_END = 1.0e30f;
@@ -39,7 +42,15 @@ __global__ __launch_bounds__(256) void bwd_prep_bf16_kernel(
     const unsigned short* __restrict__ q, const unsigned short* __restrict__ out,
     const unsigned short* __restrict__ d_out, const float* __restrict__ lse, unsigned short* __restrict__ qs, unsigned short* __restrict__ dos,
     float* __restrict__ lse2s, float* __restrict__ deltas,
-    int32_t* __restrict__ toks, int64_t T, int64_t Mpad, int Hq, int group) {
+    int32_t* __restrict__ toks, int64_t T, int64_t Mpad, int Hq, int group, unsigned row_blocks, VtArgs im) {
+  if (blockIdx.x >= row_blocks) {
+    __shared__ vt::ImageTile<D> tile;
+    auto u = [](const void* p) { return static_cast<const unsigned short*>(p); };
+    auto w = [](void* p) { return static_cast<unsigned short*>(p); };
+    vt::make_image<D, true>(tile.t, blockIdx.x - row_blocks, u(im.v_prefix), u(im.v_suffix), w(im.vt_prefix), w(im.vt_suffix),
+                            im.cu, im.vt_off, im.P, im.tiles_prefix, im.tiles_suffix, im.G, im.Hkv);
+    return;
+  }
   constexpr int CPR = D / 8;  // 16-byte chunks per row
   const int64_t tiles_per_head = Mpad / ROWS_PER_ROW_TILE;
   const int c = (int)(blockIdx.x / tiles_per_head);
@@ -117,16 +128,17 @@ int launch_bwd_prep(const BwdPrepArgs& a, void* stream) {
     return (int)hipGetLastError();
   }
   const int64_t blocks = (int64_t)a.Hkv * (a.Mpad / ROWS_PER_ROW_TILE);
+  const int64_t images = (int64_t)a.images.Hkv * (a.images.tiles_prefix + a.images.tiles_suffix);
   auto u = [](const void* p) { return static_cast<const unsigned short*>(p); };
   auto w = [](void* p) { return static_cast<unsigned short*>(p); };
   if (a.D == 128)
-    bwd_prep_bf16_kernel<128><<<(unsigned)blocks, 256, 0, s>>>(u(a.q), u(a.out), u(a.d_out), a.lse, w(a.qs),
+    bwd_prep_bf16_kernel<128><<<(unsigned)(blocks + images), 256, 0, s>>>(u(a.q), u(a.out), u(a.d_out), a.lse, w(a.qs),
                                                                 w(a.dos), a.lse2s, a.deltas,
-                                                                a.toks, a.T, a.Mpad, a.Hq, a.group);
+                                                                a.toks, a.T, a.Mpad, a.Hq, a.group, (unsigned)blocks, a.images);
   else
-    bwd_prep_bf16_kernel<64><<<(unsigned)blocks, 256, 0, s>>>(u(a.q), u(a.out), u(a.d_out), a.lse, w(a.qs),
+    bwd_prep_bf16_kernel<64><<<(unsigned)(blocks + images), 256, 0, s>>>(u(a.q), u(a.out), u(a.d_out), a.lse, w(a.qs),
                                                                w(a.dos), a.lse2s, a.deltas,
-                                                               a.toks, a.T, a.Mpad, a.Hq, a.group);
+                                                               a.toks, a.T, a.Mpad, a.Hq, a.group, (unsigned)blocks, a.images);
   return (int)hipGetLastError();
 }
 

@@ -145,7 +145,7 @@ struct MergeArgs {
 // Launchers; each returns a hipError_t value as int (0 = success).  `stream` is a hipStream_t.
 int launch_pass_bf16(const PassArgs& a, void* stream);
 int launch_pass_f32(const PassArgs& a, void* stream);
-// Builds the transposed-V tile images of both passes for the bf16 path.
+// Builds the transposed-V tile images of both passes for the bf16 path (the backward's pre-pass makes those of K).
 struct VtArgs {
   const void* v_prefix;   // [P, Hkv, D] bf16 (may be null when P == 0)
   const void* v_suffix;   // [T, Hkv, D] bf16
@@ -155,9 +155,6 @@ struct VtArgs {
   const int32_t* vt_off;  // [G+1]
   int64_t P;
   int32_t tiles_prefix, tiles_suffix, G, Hkv, D;
-  // order of the 64 keys inside a row of an image: false = as the 16 x 16 x 32 MFMAs of the forward passes deliver
-  // a query's probabilities, true = as the 32 x 32 x 16 MFMAs of the backward's dQ pass deliver its dS
-  bool order_32x32;
 };
 int launch_vt_images(const VtArgs& a, void* stream);
 int launch_merge(const MergeArgs& a, void* stream);
