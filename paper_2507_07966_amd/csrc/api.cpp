@@ -1,5 +1,5 @@
 // prefix_attn_forward / prefix_attn_lse: argument checks on the host, then the launches
-// (prefix pass, suffix pass, and a merge where the suffix pass does not do it) on the caller's stream.  Nothing here allocates or
+// (prefix pass, suffix pass, and a merge where the suffix pass does not do it; short calls one pass) on the caller's stream.  Nothing here allocates or
 // synchronises.
 #include <hip/hip_runtime.h>
 

@@ -43,6 +43,9 @@
 //     column's first-tile maximum by 16 / (scale log2 e), 125 at D = 128.  Splitting the two is what keeps the
 //     common kernel inside 256 registers without spills (the rescue code joins renamed copies of all 64
 //     accumulators into the main loop); an empty second launch costs a few microseconds.
+//   - Calls of few key tiles, where launches count, run one kernel of both (short_call_bf16_kernel): the common item, and after
+//     a barrier the careful one if a wavefront gave up; and it reads V without the image pre-pass.  One after the other, the two
+//     do not share registers: the common loops hold no scratch access.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

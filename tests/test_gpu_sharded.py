@@ -84,3 +84,33 @@ def test_c3_eight_prefix_shards_sampled_rows():
     d = np.abs(out - full_out)
     print(f"sharded vs unsharded: out max {d.max():.3e} lse max {np.abs(lse - full_lse).max():.3e}", flush=True)
     assert d.max() <= 2e-2 and np.abs(lse - full_lse).max() <= 1e-4
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 6, 8, 12, 16])
+@pytest.mark.parametrize("D,dtype", [(128, "f32"), (64, "f32"), (128, "bf16")])
+def test_merge_of_any_number_of_partials(n, D, dtype):
+    """The merge loads 8, 4, 2 or 1 partials together, whichever divides their number.  Against float64; every third row of the
+    last partial covers no key (LSE minus infinity).  A weight is off by at most |l - m| 2^-24 + 2^-23 < 1e-6 relative, and so is
+    each of the two sums of n <= 16 positive or bounded terms: 4e-6 of the largest |o| covers both; bf16 rounds the result."""
+    import torch
+    import paper_2507_07966_amd as pa
+    Hq, Hkv, T = 6, 2, 37
+    print(f"merge of {n} partials D={D} {dtype}", flush=True)
+    plan = pa.prefix_attn_plan(Hq, Hkv, D, 5, [30, 7], D ** -0.5, dtype=dtype, device=0)
+    gen = torch.Generator().manual_seed(50 + n)
+    o = torch.randn(n, T, Hq, D, generator=gen)
+    l = 3.0 * torch.randn(n, T, Hq, generator=gen)
+    if n > 1:
+        l[-1, ::3] = -float("inf")
+    out = torch.empty(T, Hq, D, device="cuda", dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    lse = torch.empty(Hq, T, device="cuda")
+    os, ls = [x.cuda() for x in o], [x.cuda() for x in l]   # each an allocation of its own (16-byte aligned)
+    pa.prefix_attn_merge_partials(plan, os, ls, out, lse)
+    torch.cuda.synchronize()
+    want_lse = torch.logsumexp(l.double(), 0)
+    want = (torch.exp(l.double() - want_lse)[..., None] * o.double()).sum(0)
+    err = (out.cpu().double() - want).abs()
+    bound = 4e-6 * o.abs().max() + (want.abs() * 2.0 ** -8 if dtype == "bf16" else 0.0)
+    print(f"merge: out max-abs {err.max():.2e}, lse {(lse.cpu().double() - want_lse.T).abs().max():.2e}", flush=True)
+    assert (err <= bound).all() and (lse.cpu().double() - want_lse.T).abs().max() < 4e-6
+    plan.destroy()
