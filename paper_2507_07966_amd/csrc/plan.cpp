@@ -710,31 +710,54 @@ void build_key_launch(prefix_attn_plan_t& p) {
 
 // How many 16-key or 16-row blocks an item of an fp32 backward launch may hold at most (0: no limit) so that one workgroup
 // per CU ends early.  blocks: those that each whole item streams; a workgroup's 8 wavefronts take one each at a time, one such
-// step lasting step_us, its start and end OVERHEAD steps.
+// step lasting step_us, its start and end OVERHEAD steps.  Candidates are compared by list scheduling as in list_schedule, but
+// over the few lengths that occur and not item by item: every fp32 plan pays for the search, also one that only runs forwards.
 int f32_limit(const std::vector<int>& blocks, int cus, double step_us, double slot_us) {
   constexpr int OVERHEAD = 2;
   constexpr double LAUNCH_US = 6.0;  // the sums
   if (blocks.empty() || blocks.size() >= 4 * (size_t)cus) return 0;
-  const int longest = (*std::max_element(blocks.begin(), blocks.end()) + 7) / 8;
+  std::vector<std::pair<int, int>> runs;  // neighbours of equal length: {length, how many}
+  for (int b : blocks)
+    if (!runs.empty() && runs.back().first == b) ++runs.back().second; else runs.push_back({b, 1});
+  const int longest = (std::max_element(runs.begin(), runs.end())->first + 7) / 8;
+  int64_t steps = 0;                           // of all items, their starts and ends among them
+  for (const auto& [b, times] : runs) steps += (int64_t)times * ((b + 7) / 8 + OVERHEAD);
+  std::vector<int> of_length(longest + 1);     // items by their steps
+  std::vector<std::pair<int, int>> free;       // {when, how many CUs} are free then, ascending from `head` on
+  // When the last item ends, in steps, longest first on whichever CU is free; at least `enough` if that is certain.
+  auto schedule = [&](double enough) {
+    free.assign(1, {0, cus});
+    size_t head = 0;
+    int end = 0;
+    for (int t = longest; t > 0; --t)
+      for (int left = of_length[t]; left > 0;) {
+        const int n = std::min(left, free[head].second), at = free[head].first + t + OVERHEAD;
+        left -= n;
+        end = std::max(end, at);
+        if (end >= enough) return end;
+        if ((free[head].second -= n) == 0) ++head;
+        auto pos = std::lower_bound(free.begin() + head, free.end(), std::make_pair(at, 0));
+        if (pos != free.end() && pos->first == at) pos->second += n; else free.insert(pos, {at, n});
+      }
+    return end;
+  };
   int limit = 0;
   double best = 0.0;
-  std::vector<int> cost, of_length(longest + 1);  // items by their steps: counted, not sorted
   for (int n = 1; n <= 16 && (n == 1 || longest / n >= 2); n += 1 + n / 6) {
     const int most = 8 * ((longest + n - 1) / n);
     size_t slots = 0;
     std::fill(of_length.begin(), of_length.end(), 0);
-    for (int b : blocks) {
+    for (const auto& [b, times] : runs) {
       const int k = (b + most - 1) / most;
-      if (k > 1) slots += k;
-      of_length[((b + k - 1) / k + 7) / 8] += k;
+      if (k > 1) slots += (size_t)k * times;
+      of_length[((b + k - 1) / k + 7) / 8] += k * times;
     }
     if (slots > 4 * (size_t)cus) break;  // more ranges would only have more
-    cost.clear();
-    for (int t = longest; t > 0; --t) cost.insert(cost.end(), of_length[t], t + OVERHEAD);
     const double extra = slots ? slots * slot_us + LAUNCH_US : 0.0;
-    const double us = list_schedule(cost, cus, n == 1 ? 1e30 : (best - extra) / step_us) * step_us + extra;
+    const double us = schedule(n == 1 ? 1e30 : (best - extra) / step_us) * step_us + extra;
     if (n == 1) {
       best = 0.95 * us;
+      if ((double)steps / cus * step_us + LAUNCH_US >= best) return 0;  // nothing to gain: cuts only add steps
     } else if (us < best) {
       best = us;
       limit = most;
@@ -756,6 +779,7 @@ void build_f32_cuts(prefix_attn_plan_t& p) {
   const bool d128 = p.desc.head_dim == 128;
   const double slot_us = 16.0 * p.desc.head_dim * 4 * 2 / 4e6;
   std::vector<int> blocks;
+  blocks.reserve(4 * (size_t)p.num_cu);
   if (p.f32_blocks[1].size() < 4 * (size_t)p.num_cu)
     for (const WorkItem& it : p.f32_blocks[1])
       blocks.push_back(np + ((std::min(it.row0 + 16, p.lens[it.g] * p.group) - 1) / p.group + 16) / 16);
@@ -785,6 +809,7 @@ void build_f32_cuts(prefix_attn_plan_t& p) {
   blocks.clear();
   std::vector<pa::KeyItem> keys;
   if ((np + p.T / 16 + p.desc.num_rollouts) * Hkv < 4 * (int64_t)p.num_cu && (int64_t)p.T * p.group < (int64_t)1 << 30) {
+    keys.reserve(4 * (size_t)p.num_cu);
     auto add = [&](int g, int n, int first_row, int end_row) {
       for (int key0 = 0; key0 < n; key0 += 16)
         for (int c = 0; c < Hkv; ++c) {
