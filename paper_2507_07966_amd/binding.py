@@ -276,6 +276,15 @@ def _ptr(t) -> Optional[int]:
 _torch_c = None   # torch._C, once it has the calls that _stream uses
 
 
+def _forget_torch_c() -> None:
+    global _torch_c
+    _torch_c = None
+
+
+# A forked child may not go on with the parent's device: there torch.cuda.current_stream() has to be asked again (and refuses).
+os.register_at_fork(after_in_child=_forget_torch_c)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         # The current stream's handle, without the Stream object that torch.cuda.current_stream() makes: short calls are bound

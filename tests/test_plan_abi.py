@@ -405,6 +405,33 @@ def test_loading_the_library_first_does_not_bring_in_a_second_hip_runtime():
     assert out.stdout.strip() == "1"
 
 
+def test_a_forked_child_asks_torch_for_the_stream_again():
+    """A process that has used the device forks: the child may not go on with the parent's stream handle, torch has to be asked
+    and refuses.  A fresh process with a stand-in for torch, whose handle the parent has."""
+    import subprocess
+    import sys
+    code = """
+import os, sys, types
+from paper_2507_07966_amd import binding
+def refuse():
+    raise RuntimeError("Cannot re-initialize CUDA in forked subprocess")
+sys.modules["torch"] = types.SimpleNamespace(cuda=types.SimpleNamespace(current_stream=refuse))
+binding._torch_c = types.SimpleNamespace(_cuda_getDevice=lambda: 0, _cuda_getCurrentRawStream=lambda device: 4096)
+assert binding._stream(None) == 4096
+pid = os.fork()
+if pid == 0:
+    try:
+        binding._stream(None)
+    except RuntimeError:
+        os._exit(0)
+    os._exit(1)
+assert os.waitpid(pid, 0)[1] == 0, "the child went on with the parent's handle"
+assert binding._stream(None) == 4096
+"""
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+
+
 def test_bf16_key_sets_of_2_gib_are_unsupported():
     """The bf16 kernels address the prefix (and each rollout) with 32-bit byte offsets: 2 GiB of K rows is refused
     at plan time, just below passes; fp32 plans have no such limit."""
