@@ -317,6 +317,10 @@ int64_t prefix_attn_plan_launch_slots(const prefix_attn_plan_t* plan, int32_t li
 /* List 2: how many of its items, the mask-free ones, are a launch of their own before that of the masked ones; -1 if all
  * items are one launch. */
 int64_t prefix_attn_plan_mask_free_items(const prefix_attn_plan_t* plan);
+/* 1: whole bf16 calls (prefix_attn_forward, _static, _timed) of this plan are one launch, that reads the values as they are
+ * (and a merge of cut blocks); 0: layout pre-pass, passes and their second kernels; -1 for a null plan.  List 0 says in both cases
+ * whether blocks are cut; partials are never such calls. */
+int prefix_attn_plan_short_call(const prefix_attn_plan_t* plan);
 
 /* Total suffix tokens T of the plan. */
 int64_t prefix_attn_plan_total_tokens(const prefix_attn_plan_t* plan);

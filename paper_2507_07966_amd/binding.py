@@ -27,7 +27,7 @@ EXPORTED_SYMBOLS = ("prefix_attn_plan", "prefix_attn_forward", "prefix_attn_forw
                     "prefix_attn_backward", "prefix_attn_backward_timed", "prefix_attn_plan_num_key_items",
                     "prefix_attn_plan_key_items", "prefix_attn_plan_key_item_extra_tiles", "prefix_attn_plan_num_launch_items",
                     "prefix_attn_plan_launch_items", "prefix_attn_plan_num_launch_sums", "prefix_attn_plan_launch_sums",
-                    "prefix_attn_plan_launch_slots", "prefix_attn_plan_mask_free_items", "prefix_attn_forward_partial", "prefix_attn_merge_partials")
+                    "prefix_attn_plan_launch_slots", "prefix_attn_plan_mask_free_items", "prefix_attn_plan_short_call", "prefix_attn_forward_partial", "prefix_attn_merge_partials")
 EXPORTED_SYMBOLS_OTHER = ("token_logprob_workspace", "token_logprob_forward", "grpo_group_advantages")
 
 
@@ -113,6 +113,8 @@ def load_library():
         getattr(lib, f"prefix_attn_plan_{n}").argtypes = [vp, ctypes.c_int32]
     lib.prefix_attn_plan_mask_free_items.restype = ctypes.c_int64
     lib.prefix_attn_plan_mask_free_items.argtypes = [vp]
+    lib.prefix_attn_plan_short_call.restype = ctypes.c_int
+    lib.prefix_attn_plan_short_call.argtypes = [vp]
     for n in ("launch_items", "launch_sums"):
         getattr(lib, f"prefix_attn_plan_{n}").restype = ctypes.c_int
         getattr(lib, f"prefix_attn_plan_{n}").argtypes = [vp, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
@@ -232,6 +234,11 @@ class PrefixAttnPlan:
     def mask_free_items(self) -> int:
         """Items of launch list 2 in a launch of their own, before the masked ones; -1: one launch."""
         return int(load_library().prefix_attn_plan_mask_free_items(self.handle))
+
+    @property
+    def short_call(self) -> bool:
+        """Whole bf16 calls are one launch that reads V as it is (and a merge of cut blocks)."""
+        return load_library().prefix_attn_plan_short_call(self.handle) == 1
 
     def destroy(self):
         if self._h is not None:

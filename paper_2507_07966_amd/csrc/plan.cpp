@@ -1129,6 +1129,8 @@ int64_t prefix_attn_plan_launch_slots(const prefix_attn_plan_t* plan, int32_t li
 
 int64_t prefix_attn_plan_mask_free_items(const prefix_attn_plan_t* plan) { return plan ? plan->key_mask_free : -1; }
 
+int prefix_attn_plan_short_call(const prefix_attn_plan_t* plan) { return plan ? plan->short_call : -1; }
+
 int64_t prefix_attn_plan_total_tokens(const prefix_attn_plan_t* plan) { return plan ? plan->T : -1; }
 
 int prefix_attn_backward_workspace(const prefix_attn_plan_t* plan, size_t* workspace_bytes_out) {

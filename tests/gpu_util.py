@@ -14,6 +14,21 @@ def to_device(x, name):
     return torch.from_numpy(getattr(x, name)).cuda()
 
 
+def forward_variant(plan):
+    """Which kernels a whole bf16 forward of this plan runs: "short" (one launch, V read as it is) or "short, cut" (and a
+    merge of the cut blocks); with V^T images and a second launch for the items given up: "sweep" over [prefix | own keys],
+    "ranges" (some blocks cut), "own keys" (no prefix), "separate" passes, or "key ranges" of the prefix with the n-way merge."""
+    if len(plan.launch_items(0)):
+        return "short, cut" if plan.short_call else "ranges"
+    if plan.short_call:
+        return "short"
+    if plan.prefix_len == 0:
+        return "own keys"
+    if len(plan.items(3)):
+        return "sweep"
+    return "key ranges" if len({int(k) for k in plan.items(0)[:, 4]}) > 1 else "separate"
+
+
 def run_hip(x, scale=None, return_plan=False):
     """Run plan + forward + lse through the C ABI.  Returns out [T,Hq,D] float64, lse [Hq,T] float64."""
     import torch

@@ -219,6 +219,40 @@ def check_parts(parts, want):
         assert all(a[1] == b[0] for a, b in zip(p, p[1:])), block
 
 
+def tiles_in_a_row(plan):
+    """Key tiles of the longest item of a whole bf16 call, times the rounds that its items take on 256 CUs."""
+    items = plan.launch_items(0) if len(plan.launch_items(0)) else plan.items(3) if plan.prefix_len else plan.items(1)
+    items = items[items[:, 0] >= 0]
+    return -(-len(items) // 256) * int((-(-items[:, 3] // TILE) + -(-items[:, 5] // TILE)).max())
+
+
+CUT = (333, 400, 67, 90)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,tiles,cut", [
+    (4, 4, 128, 64 * 124, (256,) * 64, 128, False), (4, 4, 128, 64 * 124 + 1, (256,) * 64, 129, False),   # whole blocks, one round
+    (4, 4, 64, 64 * 252, (256,) * 64, 256, False), (4, 4, 64, 64 * 252 + 1, (256,) * 64, 257, False),
+    (28, 4, 128, 64 * 249, CUT, 128, True), (28, 4, 128, 64 * 249 + 1, CUT, 129, True),     # two ranges of the longest block
+    (28, 4, 64, 64 * 505, CUT, 256, True), (28, 4, 64, 64 * 505 + 1, CUT, 257, True),
+    (8, 8, 128, 0, (2688,) * 8, 126, False), (8, 8, 128, 0, (2689,) * 8, 129, False),       # no prefix, three rounds of 42 and 43
+    (8, 8, 64, 0, (5440,) * 4, 255, False), (8, 8, 64, 0, (5441,) * 4, 258, False),
+])
+def test_short_calls_end_at_their_limit(Hq, Hkv, D, P, lens, tiles, cut):
+    """Up to 128 (D = 64: 256) key tiles in a row are a short call."""
+    plan = host_plan(num_q_heads=Hq, num_kv_heads=Hkv, head_dim=D, prefix_len=P, suffix_lens=list(lens))
+    assert (len(plan.launch_items(0)) > 0) == cut and tiles_in_a_row(plan) == tiles
+    assert plan.short_call == (tiles <= (128 if D == 128 else 256))
+
+
+def test_short_calls_are_whole_bf16_calls():
+    from paper_2507_07966_amd import binding
+    assert host_plan(prefix_len=256, suffix_lens=[100]).short_call
+    assert not host_plan(prefix_len=256, suffix_lens=[100], dtype="f32").short_call
+    assert not host_plan(prefix_len=32768, suffix_lens=[2304] * 8).short_call          # the 32K-prefix workload: one sweep
+    assert not host_plan(prefix_len=230400, suffix_lens=[2304] * 8).short_call         # separate passes
+    assert binding.load_library().prefix_attn_plan_short_call(None) == -1
+
+
 def test_launch_list_arguments():
     from paper_2507_07966_amd import binding
     lib = binding.load_library()
