@@ -4,16 +4,17 @@ attention passes.
 The forward takes a tile's probabilities against the maximum of a row's first tile and only checks, from the
 tile's row sum, that they stay in a safe range; rows that leave it are redone by the second kernel of the pass
 with a full online softmax.  N(0,1)-like scores never need that, so these cases construct it: wide scores
-(std 2.5) and the largest keys at the very end of the prefix and of every rollout's own keys.  One case per
-variant of the pass (one sweep, separate prefix and merging suffix pass, prefix keys split into ranges with the
-n-way merge, shard partials with and without the own keys), at both head dimensions."""
+(std 2.5) and the largest keys at the very end of the prefix and of every rollout's own keys.  Cases for every
+variant of the pass (short calls, whole and cut; one sweep, whole and cut; no prefix; separate prefix and merging suffix pass;
+prefix keys split into ranges with the n-way merge; shard partials with and without the own keys), at both head dimensions;
+each asserts that it runs the variant it names."""
 import numpy as np
 import pytest
 
 from oracle import cref
 from oracle import ref_attention as ref
 from paper_2507_07966_amd import workloads as wl
-from tests.gpu_util import LSE_MAX_ABS, OUT_MEAN_ABS, run_hip
+from tests.gpu_util import LSE_MAX_ABS, OUT_MEAN_ABS, forward_variant, run_hip
 
 pytestmark = pytest.mark.gpu
 
@@ -61,23 +62,23 @@ def rows_that_move(x, keys, rows):
 
 
 CASES = [
-    # (Hq, Hkv, D, P, lens, sweep expected, compare every n-th row (1: the full tensor))
-    (8, 2, 64, 700, (150, 90), True, 1),          # one sweep, D = 64
-    # more than 1,024 prefix tiles and more than 128 blocks of rows: unsplit prefix pass + merging suffix pass
+    # (Hq, Hkv, D, P, lens, variant expected (see forward_variant), compare every n-th row (1: the full tensor))
+    (8, 2, 64, 700, (150, 90), "short", 1),
+    # more than 1,024 prefix tiles, 140 blocks of rows in three ranges each
     # (a row costs the oracle 65,700 keys: every 6th row, and the first and last 8 rows of every rollout)
-    (28, 4, 128, 65700, (400, 333, 267, 200), False, 6),
-    (16, 4, 64, 65700, (600, 500, 500, 500), False, 6),
-    (8, 2, 128, 3000, (90, 70), False, 1),        # few rows: prefix keys in ranges, plain suffix partial, n-way merge
-    (14, 2, 64, 66000, (150, 90), False, 1),      # the same with long ranges (4,416 keys each), D = 64
+    (28, 4, 128, 65700, (400, 333, 267, 200), "ranges", 6),
+    (16, 4, 64, 65700, (600, 500, 500, 500), "ranges", 6),
+    (8, 2, 128, 3000, (90, 70), "short, cut", 1),        # few rows, ranges of four tiles
+    (14, 2, 64, 66000, (150, 90), "short, cut", 1),      # the same with long ranges (65 tiles each), D = 64
 ]
 
 
-@pytest.mark.parametrize("Hq,Hkv,D,P,lens,sweep,every", CASES)
-def test_late_maximum_in_every_forward_variant(Hq, Hkv, D, P, lens, sweep, every):
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,variant,every", CASES)
+def test_late_maximum_in_every_forward_variant(Hq, Hkv, D, P, lens, variant, every):
     import paper_2507_07966_amd as pa
     print(f"late maximum {Hq}/{Hkv}/{D} P={P} lens={lens}", flush=True)
     plan = pa.prefix_attn_plan(Hq, Hkv, D, P, list(lens), D ** -0.5, dtype="bf16", device=-1)
-    assert (len(plan.items(3)) > 0) == sweep
+    assert forward_variant(plan) == variant
     plan.destroy()
     x = late_maximum_inputs(Hq, Hkv, D, P, lens, seed=31)
     off = ref.suffix_offsets(x.suffix_lens)
@@ -113,20 +114,32 @@ def test_late_maximum_in_shard_partials(D):
     check_peaked(out, lse, ro, rl, x, f"late maximum, shard partials D={D}")
 
 
-@pytest.mark.parametrize("Hq,Hkv,D,P,lens,every", [
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,variant,every", [
     # calls of few key tiles (one launch, V read as it is): blocks cut into ranges and whole, without a prefix, ragged last tiles
-    (28, 4, 128, 130, (70,), 1), (28, 4, 128, 1021, (67, 200), 1), (7, 1, 128, 0, (321, 65), 1), (8, 8, 128, 127, (300, 7, 99), 1),
-    (14, 2, 64, 515, (129, 300), 1), (4, 4, 64, 0, (700, 1, 64), 1),
+    (28, 4, 128, 130, (70,), "short", 1), (28, 4, 128, 1021, (67, 200), "short, cut", 1), (7, 1, 128, 0, (321, 65), "short", 1),
+    (8, 8, 128, 127, (300, 7, 99), "short", 1), (14, 2, 64, 515, (129, 300), "short", 1), (4, 4, 64, 0, (700, 1, 64), "short", 1),
     # calls above the limit (128 tiles at D = 128, 256 at 64): V^T images and a second launch for the items given up
-    (28, 4, 128, 20000, (333, 400, 67, 90), 19), (14, 2, 64, 60000, (300, 400, 500, 77), 41), (8, 2, 128, 0, (8300,), 41),
-    (4, 2, 64, 0, (16500,), 401),
+    (28, 4, 128, 20000, (333, 400, 67, 90), "ranges", 19), (14, 2, 64, 60000, (300, 400, 500, 77), "ranges", 41),
+    (8, 2, 128, 0, (8300,), "own keys", 41), (4, 2, 64, 0, (16500,), "own keys", 401),
+    # whole blocks, of 130 and 258 tiles (one round) and of 82 in four rounds; ragged last tiles of both key sets
+    (4, 4, 128, 8059, (250,) * 64, "sweep", 61), (4, 4, 64, 16253, (250,) * 64, "sweep", 61),
+    (28, 4, 128, 4090, (1152,) * 8, "sweep", 97),
+    # more than 1,024 prefix tiles and blocks that fill the CUs: unsplit prefix pass + merging suffix pass
+    (4, 4, 128, 65700, (250,) * 64, "separate", 401), (4, 4, 64, 65700, (250,) * 64, "separate", 401),
+    # few short blocks, for whose slots the static workspace has no room: prefix keys in ranges, plain suffix partial, n-way merge
+    (4, 4, 128, 54411, (9, 13, 19, 12), "key ranges", 1),
+    (16, 8, 64, 49000, (64,) * 16, "key ranges", 64),
 ])
-def test_late_maximum_in_short_and_long_calls(Hq, Hkv, D, P, lens, every):
+def test_late_maximum_in_short_and_long_calls(Hq, Hkv, D, P, lens, variant, every):
+    import paper_2507_07966_amd as pa
     print(f"late maximum, short and long calls {Hq}/{Hkv}/{D} P={P} lens={lens}", flush=True)
+    plan = pa.prefix_attn_plan(Hq, Hkv, D, P, list(lens), D ** -0.5, dtype="bf16", device=-1)
+    assert forward_variant(plan) == variant
+    plan.destroy()
     x = late_maximum_inputs(Hq, Hkv, D, P, lens, seed=34)
     off = ref.suffix_offsets(x.suffix_lens)
     moved = sum(rows_that_move(x, np.concatenate([x.k_prefix, x.k_suffix[off[g]:off[g + 1]]]), range(max(off[g], off[g + 1] - 2), off[g + 1]))
-                for g in range(len(lens)))
+                for g in range(min(4, len(lens))))
     assert moved > 0
     out, lse = run_hip(x)
     assert np.isfinite(out).all() and np.isfinite(lse).all()
