@@ -7,7 +7,7 @@ import pytest
 from oracle import cref
 from oracle import ref_attention as ref
 from paper_2507_07966_amd import workloads as wl
-from tests.gpu_util import check, run_hip
+from tests.gpu_util import check, forward_variant, run_hip
 
 pytestmark = pytest.mark.gpu
 
@@ -55,13 +55,14 @@ def test_edge_shapes_full_tensor(dtype, Hq, Hkv, D, P, lens):
 
 def test_long_prefix_takes_the_separate_passes_full_tensor():
     """A prefix of more than 1,024 tiles with enough rows to leave it unsplit: prefix pass, then the suffix pass
-    that merges in its epilogue (shorter prefixes run as one sweep); head_dim 64, one head per kv head, ragged,
-    full tensor."""
+    that merges in its epilogue (shorter prefixes run as one sweep); head_dim 64, one head per kv head, ragged, short
+    rollouts among them so that the blocks fill the CUs and none is cut; full tensor."""
     import paper_2507_07966_amd as pa
-    shape = (4, 4, 64, 65600, (3000, 2500, 2756))
+    shape = (4, 4, 64, 65600, (3000, 2500, 2756) + (1, 7, 20, 13) * 7 + (5, 30, 2))
     plan = pa.prefix_attn_plan(*shape[:4], list(shape[4]), 0.125, dtype="bf16", device=-1)
     assert len(plan.items(3)) == 0
     assert len(plan.items(0)) >= 129 and len(set(plan.items(0)[:, 4].tolist())) == 1        # unsplit prefix keys
+    assert forward_variant(plan) == "separate"
     x = wl.make_custom("bf16", *shape, seed=13)
     out, lse = run_hip(x)
     ro, rl, _ = cref.prefix_shared_attention(x.q, x.k_prefix, x.v_prefix, x.k_suffix, x.v_suffix, x.suffix_lens,
@@ -75,12 +76,13 @@ def test_graded_code_path_full_tensor():
     tile, swept together with each block's own keys in one launch (the prefix part in the loop that carries no
     mask and no choice of key set); ragged rollouts, so blocks of rows end inside positions and rollouts."""
     import paper_2507_07966_amd as pa
-    shape = (28, 4, 128, 16500, (700, 333, 517, 129, 650, 71))
+    shape = (28, 4, 128, 16500, (700, 333, 517, 129, 500, 36))
     plan = pa.prefix_attn_plan(*shape[:4], list(shape[4]), 128 ** -0.5, dtype="bf16", device=-1)
     sw = plan.items(3)
     sw = sw[sw[:, 0] >= 0]
     assert len(sw) == sum((s * 7 + 255) // 256 for s in shape[4]) * 4 >= 256      # every block of rows once
     assert (sw[:, 4] == 0).all() and (sw[:, 5] == 16500).all()                    # each sweeps the whole prefix
+    assert forward_variant(plan) == "sweep"                                       # none of them cut
     plan.destroy()
     x = wl.make_custom("bf16", *shape, seed=17)
     out, lse = run_hip(x)
@@ -93,12 +95,13 @@ def test_separate_passes_d128_group7_full_tensor():
     tiles (ragged last tile) stays unsplit and runs as prefix pass + suffix pass with the merging epilogue,
     head_dim 128, 7 heads per kv head, ragged rollouts."""
     import paper_2507_07966_amd as pa
-    shape = (28, 4, 128, 65700, (400, 333, 267, 200))
+    shape = (28, 4, 128, 65700, (240, 133, 100, 60) + (1, 7, 20, 5) * 12)   # 64 blocks a kv head: none is cut
     plan = pa.prefix_attn_plan(*shape[:4], list(shape[4]), 128 ** -0.5, dtype="bf16", device=-1)
     pre = plan.items(0)
     pre = pre[pre[:, 0] >= 0]
     assert len(plan.items(3)) == 0                                                # no single sweep
-    assert len(pre) == 140 and (pre[:, 4] == 0).all() and (pre[:, 3] == 65700).all()   # one key range: the whole prefix
+    assert len(pre) == 256 and (pre[:, 4] == 0).all() and (pre[:, 3] == 65700).all()   # one key range: the whole prefix
+    assert forward_variant(plan) == "separate"
     plan.destroy()
     x = wl.make_custom("bf16", *shape, seed=23)
     out, lse = run_hip(x)

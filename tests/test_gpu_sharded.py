@@ -6,7 +6,7 @@ import pytest
 
 from oracle import cref
 from paper_2507_07966_amd import workloads as wl
-from tests.gpu_util import check, run_hip, to_device
+from tests.gpu_util import check, forward_variant, run_hip, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -51,8 +51,8 @@ CASES = [
     ("bf16", 8, 1, 128, 0, (65, 64), [0, 0], 0),                            # no prefix at all
     ("bf16", 8, 2, 128, 3000, (20, 9), [0, 1500, 3000], 1),                 # few rows: each shard's keys are split again inside the call
     # the shard with the own keys has more than 1,024 key tiles and enough rows to stay unsplit: prefix pass,
-    # suffix pass and the two-way merge into an fp32 partial instead of one sweep
-    ("bf16", 2, 2, 64, 66000, (9000, 7600), [0, 65800, 66000], 0),
+    # suffix pass and the two-way merge into an fp32 partial instead of one sweep (short rollouts: the blocks fill the CUs, none is cut)
+    ("bf16", 2, 2, 64, 66000, (9000, 7600) + (3,) * 62, [0, 65800, 66000], 0),
     ("f32", 4, 2, 64, 100, (33, 70), [0, 30, 100], 1),
 ]
 
@@ -61,6 +61,11 @@ CASES = [
 def test_sharded_prefix_matches_oracle(dtype, Hq, Hkv, D, P, lens, bounds, suffix_shard):
     x = wl.make_custom(dtype, Hq, Hkv, D, P, lens, seed=21)
     print(f"sharded case {dtype} {Hq}/{Hkv}/{D} P={P} lens={lens} bounds={bounds}", flush=True)
+    if P > 65536:
+        import paper_2507_07966_amd as pa
+        plan = pa.prefix_attn_plan(Hq, Hkv, D, bounds[1], list(lens), x.workload.scale, dtype=dtype, device=-1)
+        assert forward_variant(plan) == "separate"
+        plan.destroy()
     out, lse = run_sharded(x, bounds, suffix_shard)
     ro, rl, _ = cref.prefix_shared_attention(x.q, x.k_prefix, x.v_prefix, x.k_suffix, x.v_suffix, x.suffix_lens,
                                              x.workload.scale)

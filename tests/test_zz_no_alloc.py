@@ -8,7 +8,7 @@ import pytest
 
 from oracle import cref
 from paper_2507_07966_amd import workloads as wl
-from tests.gpu_util import check, run_hip, to_device
+from tests.gpu_util import check, forward_variant, run_hip, to_device
 
 
 def run_static(x):
@@ -35,16 +35,19 @@ def run_static(x):
 
 @pytest.mark.gpu
 def test_static_workspace_forward_two_calls_second_smaller():
-    cases = [wl.make_custom("bf16", 2, 2, 64, 65600, (9000, 7600), seed=40),         # prefix pass + merging suffix pass
-             wl.make_custom("bf16", 28, 4, 128, 700, (300, 129, 77), seed=41),       # smaller: one sweep
-             wl.make_custom("bf16", 28, 4, 128, 5000, (40, 3), seed=42),             # prefix key ranges + n-way merge
-             wl.make_custom("f32", 4, 2, 64, 100, (33, 70), seed=43)]                # fp32: stand-alone merge kernel
+    cases = [(wl.make_custom("bf16", 2, 2, 64, 65600, (9000, 7600) + (3,) * 62, seed=40), "separate"),   # prefix pass + merging suffix pass
+             (wl.make_custom("bf16", 2, 2, 64, 65600, (4600, 4000), seed=45), "ranges"),
+             (wl.make_custom("bf16", 4, 4, 64, 16253, (250, 33) * 32, seed=44), "sweep"),
+             (wl.make_custom("bf16", 28, 4, 128, 700, (300, 129, 77), seed=41), "short"),       # smaller: one launch
+             (wl.make_custom("bf16", 28, 4, 128, 5000, (40, 3), seed=42), "short, cut"),        # and a merge
+             (wl.make_custom("f32", 4, 2, 64, 100, (33, 70), seed=43), None)]
     import paper_2507_07966_amd as pa
-    probe = pa.prefix_attn_plan(2, 2, 64, 65600, [9000, 7600], 64 ** -0.5, dtype="bf16", device=-1)
-    assert len(probe.items(3)) == 0 and len(set(probe.items(0)[:, 5].tolist())) == 1   # no sweep, one key range
-    probe.destroy()
-    for x in cases:
+    for x, variant in cases:
         w = x.workload
+        if variant:
+            probe = pa.prefix_attn_plan(w.num_q_heads, w.num_kv_heads, w.head_dim, w.prefix_len, x.suffix_lens, w.scale, dtype="bf16", device=-1)
+            assert forward_variant(probe) == variant
+            probe.destroy()
         print(f"static workspace case {w.dtype} P={w.prefix_len} lens={x.suffix_lens.tolist()}", flush=True)
         out_s, lse_s = run_static(x)
         out_w, lse_w = run_hip(x)
@@ -67,8 +70,10 @@ def test_static_workspace_rejects_a_plan_that_does_not_fit():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("Hq,Hkv,D,P,lens", [(28, 4, 128, 700, (300, 129, 77)),     # one sweep
-                                              (28, 4, 128, 5000, (40, 3))])           # prefix key ranges + n-way merge
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens", [(28, 4, 128, 700, (300, 129, 77)),     # a short call, one launch
+                                              (28, 4, 128, 5000, (40, 3)),            # a short call whose blocks are cut
+                                              (28, 4, 128, 8200, (18,) * 64),         # one sweep and its second kernel
+                                              (14, 2, 64, 60000, (300, 400, 500, 77))])   # the same over ranges, and a merge
 def test_static_workspace_forward_replays_in_a_captured_graph(Hq, Hkv, D, P, lens):
     """One of the callers the allocation-free entry point is for: a captured HIP graph.  The call is captured
     once and replayed three times, each time on new inputs copied into the same buffers, with the program's own
