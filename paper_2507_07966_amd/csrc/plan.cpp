@@ -1062,69 +1062,104 @@ int prefix_attn_plan_items(const prefix_attn_plan_t* plan, int32_t pass, int32_t
   return PA_OK;
 }
 
-// Lists 6 and 7, the cut launches of the fp32 backward, are kept where a bf16 plan keeps its lists 1 and 2.
-static bool kept(const prefix_attn_plan_t* plan, int32_t list) {
+namespace {
+
+// What a launch list consists of; a list that the plan's data type does not have is empty.  (The plan keeps the cut launches of
+// a backward, lists 1 and 2 in bf16 and 6 and 7 in fp32, in the same members.)
+struct LaunchList {
+  bool exists = false, summed = false;  // summed: its cut blocks leave partial results in slots
+  const std::vector<WorkItem>* rows = nullptr;
+  const std::vector<pa::KeyItem>* keys = nullptr;
+  const std::vector<pa::RangeSum>* row_sums = nullptr;
+  const std::vector<pa::KeySum>* key_sums = nullptr;
+  int64_t slots = 0;
+  int rows_per_block = 0, waves = 0;  // lists of whole fp32 blocks
+};
+
+LaunchList launch_list(const prefix_attn_plan_t* plan, int32_t list) {
+  LaunchList l;
+  if (!plan) return l;
   const bool f32 = plan->desc.dtype == PA_F32;
-  return list < 3 ? !f32 : f32;
+  auto rows = [&](bool here, const std::vector<WorkItem>& items, const std::vector<pa::RangeSum>& sums, int32_t slots) {
+    l.summed = true;
+    if (here) {
+      l.rows = &items;
+      l.row_sums = &sums;
+      l.slots = slots;
+    }
+  };
+  auto keys = [&](bool here) {
+    l.summed = true;
+    if (here) {
+      l.keys = &plan->key_launch;
+      l.key_sums = &plan->key_sums;
+      l.slots = plan->key_slots;
+    }
+  };
+  auto whole = [&](int which, int rows_per_block, int waves) {
+    if (!f32) return;
+    l.rows = &plan->f32_blocks[which];
+    l.rows_per_block = rows_per_block;
+    l.waves = waves;
+  };
+  l.exists = true;
+  switch (list) {
+    case 0: rows(!f32, plan->range_items, plan->range_sums, plan->range_slots); break;
+    case 1: rows(!f32, plan->dq_launch, plan->dq_sums, plan->dq_slots); break;
+    case 2: keys(!f32); break;
+    case 3: whole(0, plan->f32_rows, plan->f32_waves); break;
+    case 4: whole(1, 16, 8); break;
+    case 6: rows(f32, plan->dq_launch, plan->dq_sums, plan->dq_slots); break;
+    case 7: keys(f32); break;
+    default: l.exists = false;
+  }
+  return l;
 }
 
+}  // namespace
+
 int64_t prefix_attn_plan_num_launch_items(const prefix_attn_plan_t* plan, int32_t list) {
-  if (!plan || list < 0 || list == 5 || list > 7) return -1;
-  if (!kept(plan, list)) return 0;
-  if (list % 5 == 2) return (int64_t)plan->key_launch.size();
-  return (int64_t)(list == 0 ? plan->range_items : list % 5 == 1 ? plan->dq_launch : plan->f32_blocks[list - 3]).size();
+  const LaunchList l = launch_list(plan, list);
+  if (!l.exists) return -1;
+  return (int64_t)(l.keys ? l.keys->size() : l.rows ? l.rows->size() : 0);
 }
 
 int prefix_attn_plan_launch_items(const prefix_attn_plan_t* plan, int32_t list, int32_t* items_out) {
   if (!plan || !items_out) return PA_ERR_NULL;
-  if (list < 0 || list == 5 || list > 7) return PA_ERR_SHAPE;
-  if (!kept(plan, list)) return PA_OK;
-  auto put = [&](size_t n, std::initializer_list<int32_t> v) { std::copy(v.begin(), v.end(), items_out + 8 * n); };
-  if (list % 5 == 2) {
-    for (size_t n = 0; n < plan->key_launch.size(); ++n) {
-      const pa::KeyItem& it = plan->key_launch[n];
-      put(n, {it.g, it.key0, it.c, it.nkeys, it.tile0, it.tile1, it.extra_tile, it.slot});
+  const LaunchList l = launch_list(plan, list);
+  if (!l.exists) return PA_ERR_SHAPE;
+  auto put = [&](std::initializer_list<int32_t> v) { items_out = std::copy(v.begin(), v.end(), items_out); };
+  if (l.keys)
+    for (const pa::KeyItem& it : *l.keys) put({it.g, it.key0, it.c, it.nkeys, it.tile0, it.tile1, it.extra_tile, it.slot});
+  if (l.rows)
+    for (const WorkItem& it : *l.rows) {
+      if (l.waves) put({it.g, it.row0, it.c, l.rows_per_block, l.waves, 0, 0, -1});
+      else put({it.g, it.row0, it.c, it.nkeys, it.key0, it.pkeys, it.okey0, it.split});
     }
-  } else if (list == 3 || list == 4) {
-    for (size_t n = 0; n < plan->f32_blocks[list - 3].size(); ++n) {
-      const WorkItem& it = plan->f32_blocks[list - 3][n];
-      put(n, {it.g, it.row0, it.c, list == 3 ? plan->f32_rows : 16, list == 3 ? plan->f32_waves : 8, 0, 0, -1});
-    }
-  } else {
-    const std::vector<WorkItem>& v = list == 0 ? plan->range_items : plan->dq_launch;
-    for (size_t n = 0; n < v.size(); ++n)
-      put(n, {v[n].g, v[n].row0, v[n].c, v[n].nkeys, v[n].key0, v[n].pkeys, v[n].okey0, v[n].split});
-  }
   return PA_OK;
 }
 
 int64_t prefix_attn_plan_num_launch_sums(const prefix_attn_plan_t* plan, int32_t list) {
-  if (!plan || list < 0 || (list > 2 && list < 6) || list > 7) return -1;
-  if (!kept(plan, list)) return 0;
-  return (int64_t)(list == 0 ? plan->range_sums.size() : list % 5 == 1 ? plan->dq_sums.size() : plan->key_sums.size());
+  const LaunchList l = launch_list(plan, list);
+  if (!l.summed) return -1;
+  return (int64_t)(l.key_sums ? l.key_sums->size() : l.row_sums ? l.row_sums->size() : 0);
 }
 
 int prefix_attn_plan_launch_sums(const prefix_attn_plan_t* plan, int32_t list, int32_t* sums_out) {
   if (!plan || !sums_out) return PA_ERR_NULL;
-  if (list < 0 || (list > 2 && list < 6) || list > 7) return PA_ERR_SHAPE;
-  if (!kept(plan, list)) return PA_OK;
-  auto put = [&](size_t n, std::initializer_list<int32_t> v) { std::copy(v.begin(), v.end(), sums_out + 6 * n); };
-  if (list % 5 == 2) {
-    for (size_t n = 0; n < plan->key_sums.size(); ++n) {
-      const pa::KeySum& s = plan->key_sums[n];
-      put(n, {s.own, s.key0, s.c, s.nkeys, s.slot0, s.nslots});
-    }
-  } else {
-    const std::vector<pa::RangeSum>& v = list == 0 ? plan->range_sums : plan->dq_sums;
-    for (size_t n = 0; n < v.size(); ++n) put(n, {v[n].off_g, v[n].row0, v[n].c, v[n].nrows, v[n].slot0, v[n].nslots});
-  }
+  const LaunchList l = launch_list(plan, list);
+  if (!l.summed) return PA_ERR_SHAPE;
+  auto put = [&](std::initializer_list<int32_t> v) { sums_out = std::copy(v.begin(), v.end(), sums_out); };
+  if (l.key_sums)
+    for (const pa::KeySum& s : *l.key_sums) put({s.own, s.key0, s.c, s.nkeys, s.slot0, s.nslots});
+  if (l.row_sums)
+    for (const pa::RangeSum& s : *l.row_sums) put({s.off_g, s.row0, s.c, s.nrows, s.slot0, s.nslots});
   return PA_OK;
 }
 
 int64_t prefix_attn_plan_launch_slots(const prefix_attn_plan_t* plan, int32_t list) {
-  if (!plan || list < 0 || (list > 2 && list < 6) || list > 7) return -1;
-  if (!kept(plan, list)) return 0;
-  return list == 0 ? plan->range_slots : list % 5 == 1 ? plan->dq_slots : plan->key_slots;
+  const LaunchList l = launch_list(plan, list);
+  return l.summed ? l.slots : -1;
 }
 
 int64_t prefix_attn_plan_mask_free_items(const prefix_attn_plan_t* plan) { return plan ? plan->key_mask_free : -1; }
