@@ -26,6 +26,8 @@ uint32_t rnd(uint32_t n) {  // a small LCG: the shapes only have to vary
   return (uint32_t)(rng_state >> 33) % n;
 }
 
+int f32_cut_lists[2] = {0, 0};  // plans whose list 6, 7 was not empty
+
 prefix_attn_desc_t make_desc(int Hq, int Hkv, int D, int64_t P, const std::vector<int32_t>& lens, int dtype) {
   prefix_attn_desc_t d{};
   d.num_q_heads = Hq;
@@ -99,21 +101,23 @@ void exercise(int Hq, int Hkv, int D, int64_t P, const std::vector<int32_t>& len
     }
     CHECK(keys_seen == (pass == 0 ? P : T) * Hkv);
   }
-  for (int list = 0; list < 5; ++list) {  // the lists that the launches run
+  for (int list : {0, 1, 2, 3, 4, 6, 7}) {  // the lists that the launches run
     const int64_t n = prefix_attn_plan_num_launch_items(plan, list), s = prefix_attn_plan_num_launch_sums(plan, list);
-    CHECK(n >= 0 && (list < 3 ? s >= 0 : s == -1));
-    CHECK((n > 0) == (list == 0 ? n > 0 : (list < 3) == (dtype == PA_BF16)));
+    const bool summed = list < 3 || list > 5, here = (list < 3) == (dtype == PA_BF16), may_be_empty = list == 0 || list > 5;
+    CHECK(n >= 0 && (summed ? s >= 0 : s == -1));
+    CHECK(here ? n > 0 || may_be_empty : n == 0);
     items.assign((size_t)n * 8 + 1, -7);
     CHECK(prefix_attn_plan_launch_items(plan, list, items.data()) == PA_OK && items[(size_t)n * 8] == -7);
+    if (list > 5 && n > 0) ++f32_cut_lists[list - 6];
     int64_t left = 0, most = -1;
     for (int64_t i = 0; i < n; ++i) {
       const int32_t slot = items[(size_t)i * 8 + 7];
-      if (list < 3 && items[(size_t)i * 8 + (list == 2 ? 2 : 0)] >= 0 && slot >= 0) {
+      if (summed && items[(size_t)i * 8 + (list == 2 || list == 7 ? 2 : 0)] >= 0 && slot >= 0) {
         ++left;
         most = slot > most ? slot : most;
       }
     }
-    if (list >= 3) continue;
+    if (!summed) continue;
     CHECK(left == prefix_attn_plan_launch_slots(plan, list) && most < left);
     items.assign((size_t)s * 6 + 1, -7);
     CHECK(prefix_attn_plan_launch_sums(plan, list, items.data()) == PA_OK && items[(size_t)s * 6] == -7);
@@ -121,8 +125,15 @@ void exercise(int Hq, int Hkv, int D, int64_t P, const std::vector<int32_t>& len
     for (int64_t i = 0; i < s; ++i) added += items[(size_t)i * 6 + 5];
     CHECK(added == left);
   }
-  CHECK(prefix_attn_plan_num_launch_items(plan, 5) == -1 && prefix_attn_plan_launch_items(plan, -1, items.data()) == PA_ERR_SHAPE);
-  CHECK(prefix_attn_plan_launch_sums(plan, 3, items.data()) == PA_ERR_SHAPE && prefix_attn_plan_launch_slots(plan, 3) == -1);
+  for (int list : {-1, 5, 8}) {
+    CHECK(prefix_attn_plan_num_launch_items(plan, list) == -1 && prefix_attn_plan_launch_items(plan, list, items.data()) == PA_ERR_SHAPE);
+    CHECK(prefix_attn_plan_num_launch_sums(plan, list) == -1 && prefix_attn_plan_launch_slots(plan, list) == -1);
+  }
+  for (int list : {3, 4, 5})
+    CHECK(prefix_attn_plan_launch_sums(plan, list, items.data()) == PA_ERR_SHAPE && prefix_attn_plan_launch_slots(plan, list) == -1);
+  CHECK(prefix_attn_plan_num_launch_items(nullptr, 0) == -1 && prefix_attn_plan_launch_items(plan, 5, nullptr) == PA_ERR_NULL);
+  const int is_short = prefix_attn_plan_short_call(plan);
+  CHECK(is_short == 0 || (is_short == 1 && dtype == PA_BF16));
   size_t bws = 0;
   CHECK(prefix_attn_backward_workspace(plan, &bws) == PA_OK);
   // argument checks of the entry points; a host-only plan never launches
@@ -174,6 +185,12 @@ int main() {
   exercise(8, 2, 64, 300, {1500, 700, 1}, PA_BF16);   // row ranges in the backward
   exercise(6, 3, 128, 300, {100, 57}, PA_BF16);       // lists not interleaved over XCDs
   exercise(3, 3, 128, 65, {1, 2, 3}, PA_F32);
+  exercise(1, 1, 64, 3000, {200, 50}, PA_F32);        // fp32 backward: dQ cut
+  CHECK(f32_cut_lists[0] == 1 && f32_cut_lists[1] == 0);
+  exercise(8, 2, 128, 1000, {70, 300, 111, 299}, PA_F32);  // dK/dV cut
+  CHECK(f32_cut_lists[0] == 1 && f32_cut_lists[1] == 1);
+  exercise(2, 1, 64, 65, {700}, PA_F32);              // both
+  CHECK(f32_cut_lists[0] == 2 && f32_cut_lists[1] == 2);
   for (int i = 0; i < 200; ++i) {  // seeded random shapes
     const int Hkv = 1 + (int)rnd(4), group = 1 + (int)rnd(8), D = rnd(2) ? 64 : 128;
     const int64_t P = rnd(4) == 0 ? 0 : (int64_t)rnd(20000);
