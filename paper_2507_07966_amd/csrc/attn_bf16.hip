@@ -560,8 +560,14 @@ __device__ __forceinline__ bool pass_item(
         const float* p1 = o1 + row * D + 4 * g4;
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
-          f32x4 w = O[cb][nq] * a2;
-          if (EPI == 2) w += a1 * *reinterpret_cast<const f32x4*>(p1 + cb * 16);
+          f32x4 w;
+          if constexpr (EPI == 2) {  // written out: which product is rounded first would otherwise change from build to build
+            const f32x4 prefix = a1 * *reinterpret_cast<const f32x4*>(p1 + cb * 16);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = __builtin_fmaf(O[cb][nq][i], a2, prefix[i]);
+          } else {
+            w = O[cb][nq] * a2;
+          }
           *reinterpret_cast<bf16x4*>(op + cb * 16) = __builtin_convertvector(w, bf16x4);
         }
         if (g4 == 0) {
