@@ -13,12 +13,13 @@
  *       s_j = softmax_scale * <q, k_j>,   LSE = ln sum_j exp(s_j),
  *       out = sum_j exp(s_j - LSE) v_j.
  *
- *   The library computes this in one to three steps.  bf16: a small layout pre-pass rewrites V into
- *   transposed, LDS-ready tile images; then either one sweep over [prefix | own keys] (all rollouts'
- *   rows of one kv head stacked against LDS-staged K/V tiles), where blocks of rows whose keys were cut
- *   into ranges leave partial results that a log-sum-exp merge adds, or, for long prefixes, a prefix
- *   pass (no mask) and a causal suffix pass that merges the two partial results in its epilogue (a
- *   prefix cut into key ranges: an n-way merge of its partials and the suffix pass's).  fp32: one sweep.
+ *   The library computes this in one to three steps.  bf16: either one sweep over [prefix | own keys]
+ *   (all rollouts' rows of one kv head stacked against LDS-staged K/V tiles), where blocks of rows whose
+ *   keys were cut into ranges leave partial results that a log-sum-exp merge adds, or, for long
+ *   prefixes, a prefix pass (no mask) and a causal suffix pass that merges the two partial results in
+ *   its epilogue (a prefix cut into key ranges: an n-way merge of its partials and the suffix pass's).
+ *   Before them a small layout pre-pass rewrites V into transposed, LDS-ready tile images, except in
+ *   whole calls of few key tiles, whose sweep reads V as it is.  fp32: one sweep.
  *
  * Conventions
  *   - No C++ types, no exceptions and no printing cross this boundary.  Every call
@@ -92,6 +93,7 @@ int prefix_attn_plan(const prefix_attn_desc_t* desc, prefix_attn_plan_t** plan_o
  *   workspace              scratch of at least the planned size; holds the two fp32
  *                          partial results, the merged LSE and (bf16) the V tile images
  *                          and the per-work-item flags the two kernels of a pass share
+ *                          (calls that run without some of these leave their room unused)
  * Argument errors are reported before anything is launched. */
 int prefix_attn_forward(const prefix_attn_plan_t* plan, const void* q, const void* k_prefix,
                         const void* v_prefix, const void* k_suffix, const void* v_suffix, void* out,
@@ -118,8 +120,9 @@ int prefix_attn_forward_static(const prefix_attn_plan_t* plan, const void* q, co
  * kernel_ms (HOST [4]) receives the durations in milliseconds of {V layout pre-pass, prefix
  * pass, suffix pass, merge}; the prefix entry is ~0 when P == 0 or when the plan runs the
  * single sweep (then timed in the suffix-pass entry), the pre-pass entry is ~0 for fp32
- * plans, and the merge entry is ~0 when the suffix pass merges in its epilogue.  Creates and destroys events, so it is not for stream capture or
- * latency-critical loops. */
+ * plans and for short calls (prefix_attn_plan_short_call), and the merge entry is ~0 when the
+ * suffix pass merges in its epilogue or a sweep has no cut blocks.  Creates and destroys events, so
+ * it is not for stream capture or latency-critical loops. */
 int prefix_attn_forward_timed(const prefix_attn_plan_t* plan, const void* q, const void* k_prefix,
                               const void* v_prefix, const void* k_suffix, const void* v_suffix,
                               void* out, void* workspace, size_t workspace_bytes, void* hip_stream,
@@ -173,8 +176,8 @@ int prefix_attn_merge_partials(const prefix_attn_plan_t* plan, int32_t n, const 
  * (Sec. 5.1).  The LSE is treated as a saved statistic, not as a differentiated output. */
 
 /* Bytes of backward workspace a plan needs (per-row statistics; for bf16 also re-laid-out
- * copies of Q, dO and K, and for a short prefix fp32 partial prefix gradients of the row ranges
- * its key blocks are split over). */
+ * copies of Q, dO and K; and fp32 partial gradients of the blocks that are split over rows or keys:
+ * launch lists 1, 2, 6 and 7 below). */
 int prefix_attn_backward_workspace(const prefix_attn_plan_t* plan, size_t* workspace_bytes_out);
 
 /* Enqueue the backward on `hip_stream`.  All tensors are DEVICE pointers, 16-byte aligned, in

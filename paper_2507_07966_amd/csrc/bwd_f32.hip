@@ -15,8 +15,9 @@
 // lanes on 16 rows, 16 bytes each: the address unit took about 64 cycles per load, as long as all the MFMAs, and every row was fetched
 // twice.)
 // Measured, 8 / 2 heads of 128 channels, 900 tokens over 1,000 + 179..289 keys: dQ 105 us with the loads into registers, 90 now
-// (73 TFLOP/s); dK/dV 178 -> 147 us, and 110 + 5 us with its few long blocks cut into ranges of rows (61 TFLOP/s; the matrix
-// pipe is then busy about half of the time: 80 % inside the loop, the rest is the start and end of two items a CU and the uneven third).
+// (73 TFLOP/s); dK/dV 178 -> 147 us, and 110 + 5 us with its few long blocks cut into ranges of rows (61 TFLOP/s).  The matrix
+// pipe is then busy 55 % of the cycles (dQ: 51 %): about 80 % inside the loops (a step, by blocks of different length, takes 4.6 ... 5.0 us
+// for 8,192 MFMA cycles a SIMD at 2.1 GHz, dQ 3.7 us for 6,144), the rest is the start and end of two items a CU and the uneven third.
 // (4 wavefronts a workgroup, two workgroups a CU: 87 and 101 us here, but half the wavefronts where blocks are few.)
 #include <hip/hip_runtime.h>
 

@@ -202,12 +202,12 @@ struct prefix_attn_plan {
   // backward dQ pass: the suffix list, each block of rows once per key split (split 0 also sweeps the own keys)
   std::vector<pa::WorkItem> dq_items;
   // what its launch runs: those items, or the blocks cut into key ranges where whole ones would leave CUs idle; partials
-  // of cut blocks are added afterwards
+  // of cut blocks are added afterwards.  fp32: blocks of 16 rows, some cut into ranges of 16-key blocks (empty: f32_blocks[1])
   std::vector<pa::WorkItem> dq_launch;
   pa::WorkItem* d_dq_launch = nullptr;
   std::vector<pa::RangeSum> dq_sums;
   pa::RangeSum* d_dq_sums = nullptr;
-  int32_t dq_slots = 0;
+  int32_t dq_slots = 0;                // of ROWS_PER_ITEM x D (fp32 plans: 16 x D) words each
   // forward sweep over [prefix | own keys] (whole bf16 calls with an unsplit prefix): every block of rows once,
   // interleaved over the XCDs by kv head like the prefix pass, longest first inside a kv head
   std::vector<pa::WorkItem> sweep_items;
@@ -237,14 +237,15 @@ struct prefix_attn_plan {
   // kernel the rest (key_items_full); both leave fp32 partials that a reduction adds.
   bool suffix_split = false;
   std::vector<pa::KeyItem> key_items_full;
-  // What the dK/dV launch runs (bf16): the items of the three lists, own key blocks cut further where the launch has
-  // few items, in launch order; and the key blocks whose partial gradients have to be added.
+  // What the dK/dV launch runs.  bf16: the items of the three lists, own key blocks cut further where the launch has
+  // few items, in launch order; and the key blocks whose partial gradients have to be added.  fp32: blocks of 16 keys, some
+  // cut into ranges of stacked rows (tile0, tile1: rows); empty where the launch runs whole blocks, which need no list.
   std::vector<pa::KeyItem> key_launch;
   pa::KeyItem* d_key_launch = nullptr;
   int64_t key_mask_free = -1;          // -1: one launch; else two, the first of this many (mask-free) items
   std::vector<pa::KeySum> key_sums;
   pa::KeySum* d_key_sums = nullptr;
-  int32_t key_slots = 0;               // partial-gradient slots in use, 2 x KEYS_PER_KEY_ITEM x D fp32 each
+  int32_t key_slots = 0;               // partial-gradient slots in use, of 2 x KEYS_PER_KEY_ITEM x D (fp32 plans: 2 x 16 x D) words each
   size_t boff_delta = 0, boff_lse_th = 0, boff_qs = 0, boff_dos = 0, boff_lse2s = 0, boff_deltas = 0,
          boff_toks = 0, boff_ktp = 0, boff_kts = 0, boff_part = 0, boff_dqpart = 0, bws_bytes = 0;
 };

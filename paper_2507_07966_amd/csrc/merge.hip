@@ -48,7 +48,9 @@ __global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ o1
 
 // n-way merge: one thread handles 4 consecutive channels of one (token, head) row.  Bound by reading the partials; STEP of
 // them (a divisor of n) are in flight together, as non-temporal loads since nothing reads them again.  8 partials of 18,432
-// tokens x 28 heads x 128 channels: 457 us one after the other, 423 us now (2.24 GB at 5.3 TB/s).
+// tokens x 28 heads x 128 channels: 457 us one after the other, 423 us now (2.24 GB at 5.3 TB/s).  Whole calls back to back, one after
+// the other -> now: 1 partial 85 -> 80 us, 2 130 -> 119, 3 179 -> 174, 4 232 -> 227, 5 288 -> 282, 6 343 -> 316, 7 398 -> 391, 8 453 -> 436,
+// 10 566 -> 516, 16 897 -> 842; an odd n keeps one load in flight and gains by the non-temporal loads only.
 template <bool OUT_BF16, int STEP>
 __global__ __launch_bounds__(256) void merge_n_kernel(MergeNArgs a) {
   const int per_row = a.D / 4;

@@ -382,9 +382,12 @@ void build_dq_launch(prefix_attn_plan_t& p) {
 
 // Forward, the sweep over [prefix | own keys] with some blocks of rows cut into ranges (cut_blocks), one launch and one
 // merge of the cut blocks.  Costs measured at D = 128 (64): 1.56 (0.9) us per key tile, 5 tiles' time for an item's start
-// and end, partials written and read at 4 TB/s, 8 us for the merge launch (4 us of its own, but
-// a small call is bound by the rate of launches: with 5 here calls of 5 to 12 prefix tiles were cut, 20.5 -> 22.5 us).  Up
-// to two rounds of whole blocks: beyond that the last round is at most a third of the call, its CUs run at a higher clock and the others' spread fills it.
+// and end, partials written and read at 4 TB/s, 8 us for the merge launch (4 us of its own; a small call was bound
+// by the rate of launches while it also had an image pre-pass and a careful launch: with 5 here calls of 5 to 12 prefix tiles were
+// cut, 20.5 -> 22.5 us).  For short calls (mark_short_calls), which have neither, 8 us is too much: 128 tokens, 28 / 4 heads of 128
+// (14 / 2 of 64), whole, as this rule has them, and cut as 4 us would: 6 prefix tiles 21.0 and 19.2 us, 8 tiles 23.8 and 20.4 (16.1 and
+// 12.6), 10 tiles of 64 channels 18.0 and 12.7; up to 4 tiles whole is as fast or faster, from 12 tiles on both cut alike
+// (12 tiles 29.2 whole, 22.2 cut).  Up to two rounds of whole blocks: beyond that the last round is at most a third of the call, its CUs run at a higher clock and the others' spread fills it.
 // 128 tokens, 28 / 4 heads of 128, 1,024 prefix keys (16 blocks, 6 ranges each): passes 37 -> 18 us, the whole call
 // with its LSE 45.3 -> 27.5 us.  88 blocks of a kv head for its 128 CUs (5,377
 // prefix keys, 5 rollouts of 37 ... 1,901 tokens, 14 / 2 heads of 64), two ranges each: pass 114 -> 84 us, merge 8 us.
@@ -768,11 +771,14 @@ int f32_limit(const std::vector<int>& blocks, int cus, double step_us, double sl
 
 // fp32 backward launches of few blocks, cut like the bf16 ones: blocks of 16 rows into ranges of 16-key blocks (dQ), blocks
 // of 16 keys into ranges of stacked rows (dK/dV), in the lists that the bf16 path uses for the same purpose (empty: whole
-// blocks), with slots of 16 rows or 2 x 16 keys.  The step times were measured at D = 128 (dQ 3.75 us, dK/dV 4.7 us; whole
-// blocks and 2 ... 6 ranges of the longest): 8 / 2 heads of 128, 900 tokens of 4 rollouts over 1,000 prefix keys, 126 + 114
+// blocks), with slots of 16 rows or 2 x 16 keys.  Step times measured by whole blocks of different length, at D = 128 (64): dQ
+// 3.7 (2.1) us, dK/dV 4.6 ... 5.0 (2.6 ... 2.8).  8 / 2 heads of 128, 900 tokens of 4 rollouts over 1,000 prefix keys, 126 + 118
 // blocks of keys: dK/dV 147 us whole, 124 / 109 / 123 / 111 / 121 in 2 ... 6 ranges (3 taken, the sums 5 us); dQ 90 us whole
-// (452 blocks of rows, left so), 99 / 110 / 105 in 2 / 3 / 4.  Launches of four blocks a CU and more stay whole: their last
-// round is short against the rest.
+// (452 blocks of rows, left so), 99 / 110 / 105 in 2 / 3 / 4.  A like call at D = 64: dK/dV and sums 82 us whole, 73 / 66 / 75 in 2 / 3 / 4
+// (3 taken, 70); dQ 50 whole, 48 / 49 / 47.  The whole backward of 24 shapes of 96 ... 2,000 tokens, what the rule takes against whole
+// blocks and against the kernels before rows went through LDS: D = 128 0.29 ... 1.0 and 0.24 ... 0.89, D = 64 0.33 ... 1.0 and
+// 0.32 ... 0.95 of their time, none slower.  (At D = 64 two dQ workgroups fit a CU; the rule counts one and cuts too little there: 342 blocks
+// of rows 48 us, 38 in two ranges each.)  Launches of four blocks a CU and more stay whole: their last round is short against the rest.
 void build_f32_cuts(prefix_attn_plan_t& p) {
   if (p.desc.dtype != PA_F32) return;
   const int np = (int)((p.desc.prefix_len + 15) / 16), Hkv = p.desc.num_kv_heads;

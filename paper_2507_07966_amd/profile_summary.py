@@ -65,7 +65,7 @@ def short_name(k: str) -> str:
         return "merge of key ranges"
     if "merge_kernel" in k:
         return "merge"
-    if "vt_image_kernel" in k:      # <head_dim, key order of the 32x32x16 products>: the backward's images of K
+    if "vt_image_kernel" in k:      # in records of builds whose backward launched it too: <head_dim, images of K>
         # (rocprofv3 prints short names demangled, long ones mangled)
         return "k_layout_prepass (backward)" if re.search(r"vt_image_kernel(ILi\d+ELb1E|<\d+, true>)", k) else "v_layout_prepass"
     if "lse_export" in k:
