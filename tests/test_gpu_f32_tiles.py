@@ -13,27 +13,33 @@ from tests.gpu_util import check, check_grads, run_hip, run_hip_backward
 
 pytestmark = pytest.mark.gpu
 
+# Hq, Hkv, D, P, suffix_lens, the forward's blocks (rows of a block, wavefronts that share its keys)
 SHAPES = [
-    # Hq, Hkv, D, P, suffix_lens
-    (1, 1, 64, 0, (1,)),                      # one row, one key: seven of the eight wavefronts see nothing
-    (2, 1, 128, 1, (1, 2)),
-    (1, 1, 128, 15, (16, 17, 15)),            # edges of the row and key blocks
-    (3, 1, 64, 16, (5, 6)),                   # 15 and 18 stacked rows
-    (7, 1, 128, 129, (33, 64)),               # one key into a second round of the wavefronts
-    (4, 2, 64, 257, (128, 1, 130)),
-    (28, 4, 128, 500, (90, 70)),              # 7 heads per kv head, 16-row blocks
-    (28, 4, 128, 200, (150, 55)),             # 359 blocks of 16 rows: 32-row blocks (one round of workgroups, not two)
-    (28, 4, 128, 40, (300, 1)),               # 527 blocks: three rounds of 16-row blocks
-    (16, 2, 64, 33, (1000, 31)),              # 1,031 blocks, head_dim 64: 16-row blocks, 5 rounds
-    (16, 2, 64, 300, (900, 90)),              # 990 blocks: 32-row blocks, ragged against both sizes
-    (4, 4, 128, 0, (1, 2, 17) * 100),         # many short rollouts: one wavefront a block, one or two 16-key blocks each
-    (8, 2, 64, 33, (1, 5) * 150),             # the same with a ragged prefix
-    (6, 1, 128, 1000, (1,) * 600),            # many blocks that are nearly empty, over many keys
+    (1, 1, 64, 0, (1,), (16, 1)),             # one row, one key
+    (2, 1, 128, 1, (1, 2), (16, 8)),          # seven of the eight wavefronts see nothing
+    (1, 1, 128, 15, (16, 17, 15), (16, 8)),   # edges of the row and key blocks
+    (3, 1, 64, 16, (5, 6), (16, 8)),          # 15 and 18 stacked rows
+    (7, 1, 128, 129, (33, 64), (16, 8)),      # one key into a second round of the wavefronts
+    (4, 2, 64, 257, (128, 1, 130), (16, 8)),
+    (28, 4, 128, 500, (90, 70), (32, 8)),     # 7 heads per kv head; 284 blocks of 16 rows: 32-row blocks (one round of workgroups, not two)
+    (28, 4, 128, 200, (150, 55), (32, 8)),
+    (28, 4, 128, 40, (300, 1), (32, 8)),      # 532 blocks of 16 rows, three rounds; 268 of 32 rows, two
+    (16, 2, 64, 33, (1000, 31), (32, 8)),     # 1,032 and 516 blocks, head_dim 64
+    (16, 2, 64, 300, (900, 90), (32, 8)),     # 990 blocks: 32-row blocks, ragged against both sizes
+    (28, 4, 128, 500, (90,) + (1,) * 60, (16, 8)),   # 400 blocks of 16 rows or 320 of 32, two rounds either way: 16-row blocks
+    (16, 2, 64, 300, (700,) + (1,) * 90, (16, 8)),   # the same with head_dim 64: four rounds of 880 blocks, three of 530
+    (4, 4, 128, 0, (1, 2, 17) * 100, (16, 1)),       # many short rollouts: one wavefront a block, one or two 16-key blocks each
+    (8, 2, 64, 33, (1, 5) * 150, (16, 1)),           # the same with a ragged prefix
+    (6, 1, 128, 1000, (1,) * 600, (16, 8)),          # many blocks that are nearly empty, over many keys
 ]
 
 
-@pytest.mark.parametrize("Hq,Hkv,D,P,lens", SHAPES)
-def test_f32_forward_and_backward_tiles(Hq, Hkv, D, P, lens):
+@pytest.mark.parametrize("Hq,Hkv,D,P,lens,blocks", SHAPES)
+def test_f32_forward_and_backward_tiles(Hq, Hkv, D, P, lens, blocks):
+    import paper_2507_07966_amd as pa
+    plan = pa.prefix_attn_plan(Hq, Hkv, D, P, lens, D ** -0.5, dtype="f32", device=-1)
+    assert blocks is None or tuple(plan.launch_items(3)[0, 3:5]) == blocks
+    plan.destroy()
     x = wl.make_custom("f32", Hq, Hkv, D, P, lens, seed=31)
     do, _ = wl.make_d_out(x)
     print(f"fp32 tiles Hq={Hq} Hkv={Hkv} D={D} P={P} lens={lens}", flush=True)
@@ -150,6 +156,7 @@ def test_f32_non_finite_values_reach_only_the_rows_that_see_them(Hq, Hkv, D, P, 
 
 @pytest.mark.parametrize("Hq,Hkv,D,P,lens", [
     (1, 1, 64, 3000, (200, 50)), (7, 1, 128, 0, (900,)), (2, 1, 64, 65, (700,)), (4, 2, 128, 1, (513, 1, 700)), (2, 1, 128, 3000, (257, 9)),
+    (4, 2, 128, 512, (300, 40)),   # rows and keys cut at D = 128
 ])
 def test_f32_backward_cut_into_ranges(Hq, Hkv, D, P, lens):
     """Launches of few blocks, whose blocks of rows or keys are cut into ranges with partial sums: ranges that end inside a
@@ -157,5 +164,5 @@ def test_f32_backward_cut_into_ranges(Hq, Hkv, D, P, lens):
     import paper_2507_07966_amd as pa
     plan = pa.prefix_attn_plan(Hq, Hkv, D, P, lens, D ** -0.5, dtype="f32", device=-1)
     assert len(plan.launch_sums(6)) + len(plan.launch_sums(7)) > 0
-    test_f32_forward_and_backward_tiles(Hq, Hkv, D, P, lens)
+    test_f32_forward_and_backward_tiles(Hq, Hkv, D, P, lens, None)
     test_f32_non_finite_values_reach_only_the_rows_that_see_them(Hq, Hkv, D, P, lens, float("inf"))
